@@ -98,24 +98,26 @@ __device__ __forceinline__ int popc_below(uint64_t mask)
 
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 
-// Lanes of the wave whose `key` has the same low `nbits` bits as this lane's,
-// restricted to lanes with `valid`.  nbits ballots, no LDS.
-__device__ __forceinline__ uint64_t match_bits(uint32_t key, int nbits, bool valid)
+// Table of lookup i: the largest t in [0, T) with offsets[t * B] <= i.  Every lane of the wave calls it with the
+// same arguments; 64 tables are probed at once, so up to 64 tables cost one load's latency (one thread bisecting
+// pays a load per halving: 5 us of every block's time with 16 tables).  Bad offsets cannot take it out of range.
+__device__ __forceinline__ int wave_table_of(const int64_t* __restrict__ offsets, int T, int64_t B, int64_t i)
 {
-    const uint64_t all = ballot(valid);
-    uint32_t m_lo = (uint32_t)all, m_hi = (uint32_t)(all >> 32);
-#pragma unroll 1
-    for (int b = 0; b < nbits; ++b) {
-        uint32_t x = (uint32_t)((int32_t)(key << (31 - b)) >> 31);   // 0 or ~0: the lane's bit b
-        asm volatile("" : "+v"(x));
-        const uint64_t v = ballot(x != 0u);
-        m_lo &= ~((uint32_t)v ^ x);                                  // lanes whose bit b agrees with this lane's
-        m_hi &= ~((uint32_t)(v >> 32) ^ x);
+    int lo = 0, hi = T - 1;
+    while (lo < hi) {
+        const int step = (hi - lo + kWave - 1) / kWave;
+        const int64_t t = (int64_t)lo + (int64_t)(lane_id() + 1) * step;
+        const bool starts = t <= hi && offsets[t * B] <= i;
+        const int before = __popcll(ballot(starts));
+        lo += before * step;                             // as many probes were in range, so lo stays <= hi
+        const int end = lo + step - 1;
+        hi = end < hi ? end : hi;
     }
-    return ((uint64_t)m_hi << 32) | m_lo;
+    return lo;
 }
 
-// The same with the bit count known at compile time: the loop unrolls, the shifts fold.  Written on
+// Lanes of the wave whose `key` has the same low NBITS bits as this lane's, restricted to lanes with `valid`:
+// NBITS ballots, no LDS.  Written on
 // 32-bit halves with the lane's bit spread to a whole word: per bit one bit-field extract, one compare
 // (the ballot), one exclusive-or per half, and the halves' mismatches are or-ed three at a time: a
 // third fewer vector instructions than selecting between the ballot and its complement, and the sort's

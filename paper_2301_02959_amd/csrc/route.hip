@@ -1,14 +1,15 @@
 // fs_route_bucketize: jagged ids -> (tier, owner) -> stable bucketize by owner.
 //
-// A stable counting sort of the n lookups by destination bucket, in four steps
+// A stable counting sort of the n lookups by destination bucket, in three steps
 // that touch each lookup twice:
 //   route_remap     one 2048-lookup tile per block: table of each lookup, global
 //                   row g, placement entry, destination; per-tile bucket
-//                   histogram (wave-aggregated LDS adds) plus the tile's three tier
+//                   histogram (the own bucket by ballots, the others by LDS adds) plus the tile's three tier
 //                   counts; dest (u16) and g (u32) go to the workspace; each block also
 //                   validates its share of the offsets
 //   route_scan      one block per bucket (and per tier): exclusive scan of its per-tile
-//                   counts over the tiles, and its total
+//                   counts over the tiles, and its total (skipped when the counts are few
+//                   enough for every scatter block to sum them itself)
 //   route_scatter   same tiles: each wave ranks its 512 consecutive lookups by
 //                   ballot matching against a wave-private running histogram in
 //                   LDS, adds the tile's and the bucket's base, writes
@@ -27,6 +28,11 @@ constexpr int kRouteItems = 8;                        // lookups per thread
 constexpr int kRouteTile = kBlock * kRouteItems;      // lookups per block
 constexpr int kRouteWaveSpan = kWave * kRouteItems;   // consecutive lookups per wave
 constexpr int kRouteStripe = 32;                      // tiles per XCD stripe in the scatter
+// Up to this many tile counts (tiles x (buckets + 3)) every scatter block sums them itself, the threads of a block
+// sharing a bucket's tiles, and route_scan is not launched: 8192 lookups over 8 buckets take 5.5 us of GPU time
+// after the remap instead of 9, 80 k over 64 (2747 counts) 6 instead of 8, and the host saves a launch (2.3 us).
+// At 6499 counts the two are even on the GPU, at 14 k the sums are 12 us slower.
+constexpr int64_t kRouteSumMax = 6144;
 
 __global__ __launch_bounds__(kBlock) void route_prepare_kernel(
     const int64_t* __restrict__ offsets, int64_t S, int64_t n, int32_t* status)
@@ -39,66 +45,67 @@ __global__ __launch_bounds__(kBlock) void route_prepare_kernel(
     if (ballot(bad) != 0 && lane_id() == 0) report(status, FS_DEV_BAD_OFFSETS);
 }
 
-// Table of lookup i: the largest t in [0, T) with offsets[t * B] <= i.  Clamped, so bad
-// offsets cannot take it out of range.
-__device__ __forceinline__ int table_of(const int64_t* __restrict__ offsets, int T, int64_t B, int64_t i)
-{
-    int lo = 0, hi = T - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (offsets[(int64_t)mid * B] <= i) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
+// A tile's tables and their rows, staged in LDS when there are at most this many of them.
+constexpr int kRouteTileTables = 64;
 
 __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     const int64_t* __restrict__ ids, const int64_t* __restrict__ offsets, int T, int64_t B,
     const int64_t* __restrict__ row_base, const uint32_t* __restrict__ placement,
-    int64_t n, int U, int W, int self, int dest_bits,
+    int64_t n, int U, int W, int self,
     uint16_t* __restrict__ dest_out, uint32_t* __restrict__ g_out, int32_t* __restrict__ slot_out /* or null */,
-    uint32_t* __restrict__ tile_hist /* [U + 3][tiles]: buckets, then the three tiers */, int64_t tiles,
-    int32_t* status)
+    uint32_t* __restrict__ tile_hist /* buckets, then the three tiers */, int64_t tiles,
+    int by_tile /* tile_hist is [tiles][U + 3], else [U + 3][tiles] */, int32_t* status)
 {
-    // this block's share of the offsets check (S = T * B segments over `tiles` blocks)
-    {
-        const int64_t S = (int64_t)T * B;
-        const int64_t per = (S + tiles - 1) / tiles;
-        const int64_t lo = (int64_t)blockIdx.x * per;
-        const int64_t hi = lo + per < S ? lo + per : S;
-        bool bad = false;
-        for (int64_t sg = lo + threadIdx.x; sg < hi; sg += kBlock) bad |= offsets[sg] > offsets[sg + 1];
-        if (blockIdx.x == 0 && threadIdx.x == 0) bad |= offsets[0] != 0 || offsets[S] != n;
-        if (ballot(bad) != 0 && lane_id() == 0) report(status, FS_DEV_BAD_OFFSETS);
-    }
     extern __shared__ uint32_t lds_hist[];            // [U]
     __shared__ int tile_tables[2];
-    __shared__ unsigned int wave_tiers[kWavesPerBlock][3];
+    __shared__ int64_t table_end[kRouteTileTables];   // tables t_lo .. t_hi of the tile: first lookup after table t,
+    __shared__ int64_t table_first[kRouteTileTables]; // its first row,
+    __shared__ int64_t table_rows[kRouteTileTables];  // and how many it has
+    __shared__ unsigned int wave_counts[kWavesPerBlock][4];   // the three tiers, lookups of the own bucket
     const int64_t tile = blockIdx.x;
     const int64_t base = tile * kRouteTile;
-    for (int b = threadIdx.x; b < U; b += kBlock) lds_hist[b] = 0;
-    if (threadIdx.x == 0) {
-        const int64_t last = (base + kRouteTile < n ? base + kRouteTile : n) - 1;
-        tile_tables[0] = table_of(offsets, T, B, base);
-        tile_tables[1] = table_of(offsets, T, B, last);
-    }
-    __syncthreads();
-    const int t_lo = __builtin_amdgcn_readfirstlane(tile_tables[0]);
-    const int t_hi = __builtin_amdgcn_readfirstlane(tile_tables[1]);
-    const int group_base = (self / W) * W;
-    const int64_t R_all = row_base[T];                // rows of all tables; g must stay below it (and below 2^32 - 1)
-    const bool rows_ok = R_all >= 1 && R_all < 4294967295LL;
-    int32_t faults = rows_ok ? 0 : FS_DEV_BAD_ID;
-    unsigned int tiers[3] = {0, 0, 0};
+    const int w = wave_id();
 
-    // Three rounds of loads for the thread's 8 lookups, each round's loads all in flight together: the
-    // ids, then (only in a tile that spans tables) the offsets and row_base of each lookup's table,
-    // then the placement entries.  Item by item the kernel's time was a chain of 8 x 3 dependent loads.
+    // Every load that waits for nothing goes out first: the ids, this block's share of the offsets (checked at
+    // the very end), the table bounds.
     int64_t id[kRouteItems];
 #pragma unroll
     for (int it = 0; it < kRouteItems; ++it) {
         const int64_t i = base + (int64_t)it * kBlock + threadIdx.x;
         id[it] = load_stream(ids + (i < n ? i : n - 1));             // past the end: the last id again, unused
     }
+    const int64_t S = (int64_t)T * B;                                // S segments over `tiles` blocks
+    const int64_t per = (S + tiles - 1) / tiles;
+    const int64_t s_lo = (int64_t)blockIdx.x * per;
+    const int64_t s_hi = s_lo + per < S ? s_lo + per : S;
+    const bool has_segment = s_lo + threadIdx.x < s_hi;
+    int64_t seg0 = 0, seg1 = 0;
+    if (has_segment) { seg0 = offsets[s_lo + threadIdx.x]; seg1 = offsets[s_lo + threadIdx.x + 1]; }
+
+    for (int b = threadIdx.x; b < U; b += kBlock) lds_hist[b] = 0;
+    if (w < 2) {                                                     // two waves find the tile's first and last table
+        const int64_t last = (base + kRouteTile < n ? base + kRouteTile : n) - 1;
+        const int t = wave_table_of(offsets, T, B, w == 0 ? base : last);
+        if (lane_id() == 0) tile_tables[w] = t;
+    }
+    __syncthreads();
+    const int t_lo = __builtin_amdgcn_readfirstlane(tile_tables[0]);
+    const int t_hi = __builtin_amdgcn_readfirstlane(tile_tables[1]);
+    const bool staged = t_hi - t_lo < kRouteTileTables;              // block-uniform
+    if (t_lo != t_hi && staged) {
+        const int k = threadIdx.x;
+        if (k <= t_hi - t_lo) {
+            table_end[k] = offsets[(int64_t)(t_lo + k + 1) * B];
+            table_first[k] = row_base[t_lo + k];
+            table_rows[k] = row_base[t_lo + k + 1] - row_base[t_lo + k];
+        }
+        __syncthreads();
+    }
+    const int group_base = (self / W) * W;
+    const int64_t R_all = row_base[T];                // rows of all tables; g must stay below it (and below 2^32 - 1)
+    const bool rows_ok = R_all >= 1 && R_all < 4294967295LL;
+    int32_t faults = rows_ok ? 0 : FS_DEV_BAD_ID;
+
     const int64_t first_lo = row_base[t_lo];
     const int64_t rows_lo = row_base[t_lo + 1] - first_lo;
     int64_t g[kRouteItems];
@@ -107,10 +114,17 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
         const int64_t i = base + (int64_t)it * kBlock + threadIdx.x;
         int64_t first = first_lo, rows_t = rows_lo;
         if (t_lo != t_hi) {                                          // block-uniform
-            int t = t_lo;
-            while (t < t_hi && offsets[(int64_t)(t + 1) * B] <= i) ++t;
-            first = row_base[t];
-            rows_t = row_base[t + 1] - first;
+            if (staged) {
+                int k = 0;
+                while (k < t_hi - t_lo && table_end[k] <= i) ++k;
+                first = table_first[k];
+                rows_t = table_rows[k];
+            } else {
+                int t = t_lo;
+                while (t < t_hi && offsets[(int64_t)(t + 1) * B] <= i) ++t;
+                first = row_base[t];
+                rows_t = row_base[t + 1] - first;
+            }
         }
         int64_t x = id[it];
         const bool valid = i < n;
@@ -122,54 +136,57 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     uint32_t e[kRouteItems];
 #pragma unroll
     for (int it = 0; it < kRouteItems; ++it) e[it] = rows_ok ? placement[g[it]] : 0u;
+    // Counts of the wave: the tiers and the own bucket (where most lookups of a power-law batch go) with one ballot
+    // each, the other buckets with plain LDS adds, which rarely meet.
+    uint32_t in_tier0 = 0, in_tier1 = 0, in_tier2 = 0, own = 0;
 #pragma unroll
     for (int it = 0; it < kRouteItems; ++it) {
         const int64_t i = base + (int64_t)it * kBlock + threadIdx.x;
         const bool valid = i < n;
-        uint32_t dest = 0;
+        const uint32_t tier = e[it] >> FS_TIER_SHIFT;
+        const uint32_t owner = e[it] & FS_OWNER_MASK;
+        uint32_t dest = (uint32_t)self;                              // tier 0, and every fault
+        if (tier == FS_TIER_GROUP) { if (owner < (uint32_t)W) dest = (uint32_t)group_base + owner; else if (valid) faults |= FS_DEV_BAD_PLACEMENT; }
+        if (tier == FS_TIER_SHARDED) { if (owner < (uint32_t)U) dest = owner; else if (valid) faults |= FS_DEV_BAD_PLACEMENT; }
+        if (tier > FS_TIER_SHARDED && valid) faults |= FS_DEV_BAD_PLACEMENT;
         if (valid) {
-            const uint32_t tier = e[it] >> FS_TIER_SHIFT;
-            const uint32_t owner = e[it] & FS_OWNER_MASK;
-            if (tier == FS_TIER_GLOBAL) {
-                dest = self; tiers[0]++;
-            } else if (tier == FS_TIER_GROUP) {
-                tiers[1]++;
-                if (owner < (uint32_t)W) dest = group_base + owner;
-                else { dest = self; faults |= FS_DEV_BAD_PLACEMENT; }
-            } else if (tier == FS_TIER_SHARDED) {
-                tiers[2]++;
-                if (owner < (uint32_t)U) dest = owner;
-                else { dest = self; faults |= FS_DEV_BAD_PLACEMENT; }
-            } else {
-                dest = self; tiers[0]++; faults |= FS_DEV_BAD_PLACEMENT;
-            }
             dest_out[i] = (uint16_t)dest;
             g_out[i] = (uint32_t)g[it];
             // a replicated row's entry names no owner: its owner bits carry the row's replica slot, if it has one
             if (slot_out != nullptr)
                 slot_out[i] = (tier == FS_TIER_GLOBAL && owner != FS_OWNER_MASK) ? (int32_t)owner : -1;
+            if (dest != (uint32_t)self) atomicAdd(&lds_hist[dest], 1u);
         }
-        // one LDS add per distinct bucket per wave
-        const uint64_t same = match_bits(dest, dest_bits, valid);
-        if (valid && popc_below(same) == 0) atomicAdd(&lds_hist[dest], (uint32_t)__popcll(same));
+        in_tier1 += (uint32_t)__popcll(ballot(valid && tier == FS_TIER_GROUP));
+        in_tier2 += (uint32_t)__popcll(ballot(valid && tier == FS_TIER_SHARDED));
+        in_tier0 += (uint32_t)__popcll(ballot(valid && tier != FS_TIER_GROUP && tier != FS_TIER_SHARDED));
+        own += (uint32_t)__popcll(ballot(valid && dest == (uint32_t)self));
     }
-    // tier counts travel as three more histogram rows (no global atomics: 3 hot addresses
-    // shared by every wave of the grid serialise in L2)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        unsigned int v = tiers[k];
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
-        if (lane_id() == 0) wave_tiers[wave_id()][k] = v;
+    if (lane_id() == 0) {
+        wave_counts[w][0] = in_tier0; wave_counts[w][1] = in_tier1; wave_counts[w][2] = in_tier2;
+        wave_counts[w][3] = own;
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < U; b += kBlock) tile_hist[(int64_t)b * tiles + tile] = lds_hist[b];
-    if (threadIdx.x < 3) {
-        unsigned int v = 0;
-        for (int k = 0; k < kWavesPerBlock; ++k) v += wave_tiers[k][threadIdx.x];
-        tile_hist[(int64_t)(U + threadIdx.x) * tiles + tile] = v;
+    auto waves_sum = [&](int k) {
+        uint32_t v = 0;
+        for (int q = 0; q < kWavesPerBlock; ++q) v += wave_counts[q][k];
+        return v;
+    };
+    uint32_t* my_hist = by_tile ? tile_hist + tile * (U + 3) : tile_hist + tile;
+    const int64_t step = by_tile ? 1 : tiles;
+    for (int b = threadIdx.x; b < U; b += kBlock) my_hist[b * step] = b == self ? waves_sum(3) : lds_hist[b];
+    // tier counts travel as three more histogram rows (no global atomics: 3 hot addresses
+    // shared by every wave of the grid serialise in L2)
+    if (threadIdx.x < 3) my_hist[(U + threadIdx.x) * step] = waves_sum(threadIdx.x);
+
+    bool bad = has_segment && seg0 > seg1;
+    for (int64_t sg = s_lo + threadIdx.x + kBlock; sg < s_hi; sg += kBlock) bad |= offsets[sg] > offsets[sg + 1];
+    if (blockIdx.x == 0 && threadIdx.x == 0) bad |= offsets[0] != 0 || offsets[S] != n;
+    if (bad) faults |= FS_DEV_BAD_OFFSETS;
+    if (ballot(faults != 0) != 0) {
+        for (int off = 32; off > 0; off >>= 1) faults |= __shfl_down(faults, off);
+        if (lane_id() == 0) report(status, faults);
     }
-    for (int off = 32; off > 0; off >>= 1) faults |= __shfl_down(faults, off);
-    if (lane_id() == 0) report(status, faults);
 }
 
 // One block per bucket b: tile_hist[b][0..tiles) -> exclusive prefix in place, total[b].
@@ -191,9 +208,11 @@ __global__ __launch_bounds__(kRouteScanBlock) void route_scan_kernel(uint32_t* _
     for (int64_t k = lo; k < hi; ++k) { const uint32_t v = h[k]; h[k] = run; run += v; }
 }
 
+// SUM: the counts are few, route_scan has not run: tile_hist holds plain counts and every block adds up what it needs.
+template <int NBITS, bool SUM>
 __global__ __launch_bounds__(kBlock) void route_scatter_kernel(
-    const uint16_t* __restrict__ dest_in, const uint32_t* __restrict__ g_in, int64_t n, int U, int dest_bits,
-    const uint32_t* __restrict__ tile_hist /* scanned */, int64_t tiles, const uint32_t* __restrict__ totals,
+    const uint16_t* __restrict__ dest_in, const uint32_t* __restrict__ g_in, int64_t n, int U,
+    const uint32_t* __restrict__ tile_hist /* scanned, unless SUM */, int64_t tiles, const uint32_t* __restrict__ totals,
     int64_t* __restrict__ out_rows, int32_t* __restrict__ out_pos,
     int64_t* __restrict__ bucket_offsets, int64_t* __restrict__ tier_counts,
     const int32_t* __restrict__ slot_in /* or null */, int32_t* __restrict__ out_slots)
@@ -201,46 +220,19 @@ __global__ __launch_bounds__(kBlock) void route_scatter_kernel(
     extern __shared__ uint32_t lds[];
     uint32_t* bucket_base = lds;                                        // [U] first output index of the tile in bucket b
     uint16_t* wave_hist = reinterpret_cast<uint16_t*>(lds + U);         // [waves][U]
-    __shared__ uint32_t scan_part[kBlock];
+    __shared__ uint32_t wave_sums[16];
+    constexpr int kBins = 1 << NBITS;                                   // U <= kBins
+    constexpr int kParts = SUM && kBins < kBlock ? kBlock / kBins : 1;
+    __shared__ uint32_t part_all[kParts > 1 ? kBlock : 1];
+    __shared__ uint32_t part_before[kParts > 1 ? kBlock : 1];
     // tiles in stripes per XCD: consecutive tiles write neighbouring pieces of every bucket's range,
     // which one XCD's L2 merges into whole lines (0.082 -> 0.073 ms on 15.7 M lookups)
-    const int64_t tile = xcd_striped_tile(blockIdx.x, kRouteStripe);
+    const int64_t tile = SUM ? (int64_t)blockIdx.x : xcd_striped_tile(blockIdx.x, kRouteStripe);
     if (tile >= tiles) return;                                          // block-uniform, before any barrier
     const int64_t base = tile * kRouteTile;
     const int w = wave_id();
     const int lane = lane_id();
 
-    // exclusive scan of the bucket totals (every block repeats it: U is small)
-    {
-        const int per = (U + kBlock - 1) / kBlock;
-        const int lo = threadIdx.x * per;
-        const int hi = lo + per < U ? lo + per : U;
-        uint32_t sum = 0;
-        for (int b = lo; b < hi; ++b) sum += totals[b];
-        scan_part[threadIdx.x] = sum;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t run = 0;
-            for (int k = 0; k < kBlock; ++k) { const uint32_t v = scan_part[k]; scan_part[k] = run; run += v; }
-        }
-        __syncthreads();
-        uint32_t run = scan_part[threadIdx.x];
-        const bool writes_offsets = blockIdx.x == 0;                    // tile 0 exists whenever this kernel runs
-        for (int b = lo; b < hi; ++b) {
-            bucket_base[b] = run + tile_hist[(int64_t)b * tiles + tile];
-            if (writes_offsets) bucket_offsets[b] = (int64_t)run;
-            run += totals[b];
-        }
-        if (writes_offsets && threadIdx.x == 0) {
-            bucket_offsets[U] = n;                                      // every lookup has a bucket
-            if (tier_counts != nullptr)
-                for (int k = 0; k < 3; ++k) tier_counts[k] = (int64_t)totals[U + k];
-        }
-    }
-    for (int b = threadIdx.x; b < kWavesPerBlock * U; b += kBlock) wave_hist[b] = 0;
-    __syncthreads();
-
-    uint16_t* my_hist = wave_hist + w * U;
     uint32_t dest[kRouteItems];
     uint32_t rank[kRouteItems];
     uint32_t g[kRouteItems];
@@ -253,11 +245,81 @@ __global__ __launch_bounds__(kBlock) void route_scatter_kernel(
         g[it] = valid ? g_in[i] : 0;
         slot[it] = (valid && slot_in != nullptr) ? slot_in[i] : -1;
     }
+
+    // the tile's first index in every bucket: exclusive scan of the bucket totals (every block repeats it: U is
+    // small) plus the lookups of the tiles before
+    {
+        const int stride = U + 3;                                       // SUM: tile_hist is [tiles][U + 3]
+        const int per = (U + kBlock - 1) / kBlock;
+        const int lo = threadIdx.x * per < U ? threadIdx.x * per : U;
+        const int hi = lo + per < U ? lo + per : U;
+        const bool writes_offsets = blockIdx.x == 0;                    // tile 0 exists whenever this kernel runs
+        if constexpr (kParts > 1) {
+            // fewer buckets than threads: kParts threads share a bucket, each sums every kParts-th tile
+            const int b = threadIdx.x & (kBins - 1);
+            const int part = threadIdx.x >> NBITS;
+            uint32_t all = 0, before = 0;
+            if (b < U) {
+#pragma unroll 8
+                for (int k = part; k < (int)tiles; k += kParts) {
+                    const uint32_t v = tile_hist[k * stride + b];
+                    all += v;
+                    before += k < (int)tile ? v : 0u;
+                }
+            }
+            part_all[threadIdx.x] = all;
+            part_before[threadIdx.x] = before;
+            __syncthreads();
+        }
+        uint32_t sum = 0;
+        for (int b = lo; b < hi; ++b) {
+            uint32_t all = 0, before = 0;
+            if constexpr (kParts > 1) {
+                for (int q = 0; q < kParts && q < (int)tiles; ++q) { all += part_all[q * kBins + b]; before += part_before[q * kBins + b]; }
+            } else if constexpr (SUM) {
+#pragma unroll 8
+                for (int k = 0; k < (int)tiles; ++k) {
+                    const uint32_t v = tile_hist[k * stride + b];
+                    all += v;
+                    before += k < (int)tile ? v : 0u;
+                }
+            } else {
+                all = totals[b];
+                before = tile_hist[(int64_t)b * tiles + tile];
+            }
+            bucket_base[b] = sum + before;
+            if (writes_offsets) bucket_offsets[b] = (int64_t)sum;       // both completed below
+            sum += all;
+        }
+        uint32_t unused;
+        const uint32_t run = block_exclusive_scan(sum, wave_sums, &unused);
+        for (int b = lo; b < hi; ++b) {
+            bucket_base[b] += run;
+            if (writes_offsets) bucket_offsets[b] += (int64_t)run;
+        }
+        if (writes_offsets) {
+            if (threadIdx.x == 0) bucket_offsets[U] = n;                // every lookup has a bucket
+            if (tier_counts != nullptr && w < 3) {                      // wave w adds up tier w
+                uint32_t v = 0;
+                if constexpr (SUM) {
+                    for (int k = lane; k < (int)tiles; k += kWave) v += tile_hist[k * stride + U + w];
+                    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
+                } else {
+                    v = totals[U + w];
+                }
+                if (lane == 0) tier_counts[w] = (int64_t)v;
+            }
+        }
+    }
+    for (int b = threadIdx.x; b < kWavesPerBlock * U; b += kBlock) wave_hist[b] = 0;
+    __syncthreads();
+
+    uint16_t* my_hist = wave_hist + w * U;
 #pragma unroll
     for (int it = 0; it < kRouteItems; ++it) {
         const int64_t i = base + (int64_t)w * kRouteWaveSpan + it * kWave + lane;
         const bool valid = i < n;
-        const uint64_t same = match_bits(dest[it], dest_bits, valid);
+        const uint64_t same = match_bits_n<NBITS>(dest[it], valid);
         const uint32_t before = popc_below(same);
         uint32_t seen = 0;
         if (valid) seen = my_hist[dest[it]];
@@ -341,16 +403,32 @@ static fs_status route_run(
         return FS_OK;
     }
     {
+        const bool sum = tiles * ((int64_t)U + 3) <= kRouteSumMax;
         FS_LAUNCH_SMEM("route_remap", route_remap_kernel, dim3((unsigned)tiles), dim3(kBlock),
                        (size_t)U * sizeof(uint32_t), s,
                        ids, offsets, (int)T, (int64_t)B, row_base, placement, n, (int)U, (int)W, (int)self,
-                       dest_bits, dest_tmp, g_tmp, slot_tmp, tile_hist, tiles, dev_status);
-        FS_LAUNCH("route_scan", route_scan_kernel, dim3((unsigned)U + 3), dim3(kRouteScanBlock), s, tile_hist, tiles, totals);
-        const unsigned scatter_grid = (unsigned)xcd_striped_grid(tiles, kRouteStripe);
-        FS_LAUNCH_SMEM("route_scatter", route_scatter_kernel, dim3(scatter_grid), dim3(kBlock),
-                       (size_t)U * sizeof(uint32_t) + (size_t)kWavesPerBlock * U * sizeof(uint16_t), s,
-                       dest_tmp, g_tmp, n, (int)U, dest_bits, tile_hist, tiles, totals, out_rows, out_pos,
-                       bucket_offsets, tier_counts, (const int32_t*)slot_tmp, out_slots);
+                       dest_tmp, g_tmp, slot_tmp, tile_hist, tiles, sum ? 1 : 0, dev_status);
+        if (!sum)
+            FS_LAUNCH("route_scan", route_scan_kernel, dim3((unsigned)U + 3), dim3(kRouteScanBlock), s, tile_hist, tiles, totals);
+        const unsigned scatter_grid = (unsigned)(sum ? tiles : xcd_striped_grid(tiles, kRouteStripe));
+        const size_t scatter_lds = (size_t)U * sizeof(uint32_t) + (size_t)kWavesPerBlock * U * sizeof(uint16_t);
+#define FS_SCATTER(NB)                                                                                             \
+    if (sum)                                                                                                       \
+        FS_LAUNCH_SMEM("route_scatter", (route_scatter_kernel<NB, true>), dim3(scatter_grid), dim3(kBlock), scatter_lds, s, \
+                       dest_tmp, g_tmp, n, (int)U, tile_hist, tiles, totals, out_rows, out_pos, bucket_offsets,    \
+                       tier_counts, (const int32_t*)slot_tmp, out_slots);                                          \
+    else                                                                                                           \
+        FS_LAUNCH_SMEM("route_scatter", (route_scatter_kernel<NB, false>), dim3(scatter_grid), dim3(kBlock), scatter_lds, s, \
+                       dest_tmp, g_tmp, n, (int)U, tile_hist, tiles, totals, out_rows, out_pos, bucket_offsets,    \
+                       tier_counts, (const int32_t*)slot_tmp, out_slots)
+        switch (dest_bits) {                            // U <= FS_MAX_BUCKETS = 2^12
+            case 1: FS_SCATTER(1); break;  case 2: FS_SCATTER(2); break;  case 3: FS_SCATTER(3); break;
+            case 4: FS_SCATTER(4); break;  case 5: FS_SCATTER(5); break;  case 6: FS_SCATTER(6); break;
+            case 7: FS_SCATTER(7); break;  case 8: FS_SCATTER(8); break;  case 9: FS_SCATTER(9); break;
+            case 10: FS_SCATTER(10); break;  case 11: FS_SCATTER(11); break;
+            default: FS_SCATTER(12); break;
+        }
+#undef FS_SCATTER
     }
     return FS_OK;
 }
