@@ -70,6 +70,48 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_P, _I, _L, _F, _Z = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.POINTER(ctypes.c_size_t)
+_ROUTE = [_P, _P, _I, _I, _P, _P, _L, _I, _I, _I, _P, _P, _P]
+_SIGNATURES = {
+    "fs_route_bucketize": _ROUTE + [_P, _P, _Z, _P, _P],
+    "fs_route_bucketize_noalloc": _ROUTE + [_P, _P, _P],
+    "fs_route_bucketize_slots": _ROUTE + [_P, _P, _P, _Z, _P, _P],
+    "fs_seq_gather_fwd": [_P, _L, _I, _I, _P, _P, _L, _L, _P, _L, _P, _P],
+    "fs_seq_gather_send": [_P, _L, _I, _I, _P, _L, _L, _P, _P, _P],
+    "fs_seq_unbucketize": [_P, _I, _I, _P, _L, _L, _P, _L, _P, _P],
+    "fs_replica_build": [_P, _L, _I, _I, _P, _L, _P, _P, _P, _P, _P],
+    "fs_seq_gather_fwd_replica": [_P, _L, _I, _I, _P, _L, _P, _P, _P, _L, _L, _P, _L, _P, _P],
+    "fs_replica_tag_slots": [_P, _L, _P, _P, _P],
+    "fs_seq_gather_fwd_slots": [_P, _L, _I, _I, _P, _L, _P, _P, _P, _L, _L, _P, _L, _P, _P],
+    "fs_seq_grad_bwd": [_P, _L, _I, _I, _P, _P, _L, _L, _L, _I, _P, _P, _L, _P, _P, _Z, _P, _P],
+    "fs_sort_lookups": [_P, _P, _L, _L, _L, _L, _P, _P, _P, _Z, _P, _P],
+    "fs_seq_grad_bwd_sorted": [_P, _L, _I, _I, _P, _P, _L, _L, _I, _P, _P, _L, _P, _P, _Z, _P, _P],
+    "fs_seq_gather_fwd_sorted": [_P, _L, _I, _I, _P, _P, _L, _P, _L, _P, _P],
+    "fs_plan_replication": [_P, _P, _I, _I, _P, _L, _L, _P, _I, _L, _L, _P, _P, _P, _P, _Z, _P, _P],
+    "fs_plan_tiers": [_P, _L, _P, _I, _P, _L, _P, _P, _P, _Z, _P, _P],
+    "fs_sparse_update": [_P, _L, _I, _I, _P, _P, _L, _P, _I, _F, _F, _P, _P, _P, _L, _P, _P],
+    "fs_seq_grad_bwd_update": [_P, _L, _I, _I, _P, _P, _L, _L, _P, _I, _F, _F, _P, _P, _P, _L, _P, _P, _L, _P, _P, _Z, _P, _P],
+    "fs_util_copy": [_P, _P, _L, _P],
+    "fs_util_read_write_mix": [_P, _L, _I, _P, _L, _P],
+}
+_typed_lib: Optional[ctypes.CDLL] = None
+
+
+def _typed() -> ctypes.CDLL:
+    """The library with declared argument types, for the calls below: plain integers go straight into the call,
+    where an untyped handle needs a ctypes object built for each (a third of a call's host time).  A handle of its
+    own, so that lib() stays as it was for callers that marshal for themselves."""
+    global _typed_lib
+    if _typed_lib is None:
+        lib()
+        typed = ctypes.CDLL(LIB_PATH)
+        for name, args in _SIGNATURES.items():
+            fn = getattr(typed, name)
+            fn.argtypes, fn.restype = args, ctypes.c_int
+        _typed_lib = typed
+    return _typed_lib
+
+
 _I64 = (torch.int64,)
 _I32 = (torch.int32,)
 _U32 = (torch.int32, torch.uint32)          # 32-bit words: torch code usually holds them as int32
@@ -77,21 +119,28 @@ _F32 = (torch.float32,)
 _ROWS = (torch.float32, torch.float16, torch.bfloat16)
 
 
-def _ptr(t: Optional[torch.Tensor], dtypes: Optional[tuple] = None) -> ctypes.c_void_p:
+def _ptr(t: Optional[torch.Tensor], dtypes: Optional[tuple] = None) -> Optional[int]:
     """Device pointer of a contiguous CUDA tensor (None -> NULL); `dtypes`: the element types the C side reads."""
     if t is None:
-        return ctypes.c_void_p(0)
+        return None
     if not t.is_cuda:
         raise TypeError("the library takes device memory: got a tensor on " + str(t.device))
     if not t.is_contiguous():
         raise TypeError("tensors must be contiguous")
     if dtypes is not None and t.dtype not in dtypes:
         raise TypeError(f"expected a tensor of {' or '.join(str(d) for d in dtypes)}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+# torch's current stream as a handle.  torch.cuda.current_stream() builds a Stream object for it (2.9 us of the
+# 6.7 us that a call of one launch took); the raw getter it is built on costs 0.2 us.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream() -> int:
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check(fn: str, code: int, raise_on_error: bool) -> int:
@@ -103,7 +152,7 @@ def _check(fn: str, code: int, raise_on_error: bool) -> int:
 def _workspace(query, device) -> Tuple[Optional[torch.Tensor], ctypes.c_size_t, int]:
     """Ask the entry point for its scratch size, then allocate it through torch."""
     size = ctypes.c_size_t(0)
-    code = query(ctypes.c_void_p(0), ctypes.byref(size))
+    code = query(None, ctypes.byref(size))
     if code != 0:
         return None, size, code
     ws = torch.empty(max(int(size.value), 256), dtype=torch.uint8, device=device)
@@ -113,14 +162,15 @@ def _workspace(query, device) -> Tuple[Optional[torch.Tensor], ctypes.c_size_t, 
 def fs_route_bucketize(ids, offsets, T: int, B: int, row_base, placement, n: int, U: int, W: int, self_: int,
                        bucket_offsets, out_rows, out_pos, tier_counts=None, dev_status=None,
                        workspace: Optional[torch.Tensor] = None, raise_on_error: bool = True) -> int:
-    L = lib()
+    L = _typed()
+
+    args = (_ptr(ids, _I64), _ptr(offsets, _I64), T, B, _ptr(row_base, _I64), _ptr(placement, _U32), n, U, W,
+            self_, _ptr(bucket_offsets, _I64), _ptr(out_rows, _I64), _ptr(out_pos, _I32),
+            _ptr(tier_counts, _I64))
+    tail = (_stream(), _ptr(dev_status, _I32))
 
     def call(ws_ptr, ws_size_ref):
-        return L.fs_route_bucketize(
-            _ptr(ids, _I64), _ptr(offsets, _I64), ctypes.c_int32(T), ctypes.c_int32(B), _ptr(row_base, _I64), _ptr(placement, _U32),
-            ctypes.c_int64(n), ctypes.c_int32(U), ctypes.c_int32(W), ctypes.c_int32(self_),
-            _ptr(bucket_offsets, _I64), _ptr(out_rows, _I64), _ptr(out_pos, _I32), _ptr(tier_counts, _I64),
-            ws_ptr, ws_size_ref, _stream(), _ptr(dev_status, _I32))
+        return L.fs_route_bucketize(*args, ws_ptr, ws_size_ref, *tail)
 
     if workspace is None:
         workspace, size, code = _workspace(call, offsets.device)
@@ -134,9 +184,9 @@ def fs_route_bucketize(ids, offsets, T: int, B: int, row_base, placement, n: int
 def fs_route_bucketize_noalloc(ids, offsets, T: int, B: int, row_base, placement, n: int, U: int, W: int, self_: int,
                                bucket_offsets, out_rows, out_pos, tier_counts=None, dev_status=None,
                                raise_on_error: bool = True) -> int:
-    code = lib().fs_route_bucketize_noalloc(
-        _ptr(ids, _I64), _ptr(offsets, _I64), ctypes.c_int32(T), ctypes.c_int32(B), _ptr(row_base, _I64), _ptr(placement, _U32),
-        ctypes.c_int64(n), ctypes.c_int32(U), ctypes.c_int32(W), ctypes.c_int32(self_),
+    code = _typed().fs_route_bucketize_noalloc(
+        _ptr(ids, _I64), _ptr(offsets, _I64), T, B, _ptr(row_base, _I64), _ptr(placement, _U32),
+        n, U, W, self_,
         _ptr(bucket_offsets, _I64), _ptr(out_rows, _I64), _ptr(out_pos, _I32), _ptr(tier_counts, _I64),
         _stream(), _ptr(dev_status, _I32))
     return _check("fs_route_bucketize_noalloc", code, raise_on_error)
@@ -144,10 +194,8 @@ def fs_route_bucketize_noalloc(ids, offsets, T: int, B: int, row_base, placement
 
 def route_workspace_bytes(T: int, B: int, n: int, U: int, W: int, self_: int) -> int:
     size = ctypes.c_size_t(0)
-    z = ctypes.c_void_p(0)
-    code = lib().fs_route_bucketize(z, z, ctypes.c_int32(T), ctypes.c_int32(B), z, z, ctypes.c_int64(n),
-                                    ctypes.c_int32(U), ctypes.c_int32(W), ctypes.c_int32(self_), z, z, z, z,
-                                    z, ctypes.byref(size), z, z)
+    code = _typed().fs_route_bucketize(None, None, T, B, None, None, n, U, W, self_, None, None, None, None,
+                                       None, ctypes.byref(size), None, None)
     _check("fs_route_bucketize", code, True)
     return int(size.value)
 
@@ -159,9 +207,9 @@ def fs_seq_gather_fwd(weights, rows, pos, j0: int, j1: int, out, dev_status=None
     D = weights.shape[1] if D is None else D
     n = out.shape[0] if n is None else n
     dtype = _DTYPES[weights.dtype] if dtype is None else dtype
-    code = lib().fs_seq_gather_fwd(
-        _ptr(weights, _ROWS), ctypes.c_int64(R), ctypes.c_int32(D), ctypes.c_int(dtype), _ptr(rows, _I64), _ptr(pos, _I32),
-        ctypes.c_int64(j0), ctypes.c_int64(j1), _ptr(out, _ROWS), ctypes.c_int64(n), _stream(), _ptr(dev_status, _I32))
+    code = _typed().fs_seq_gather_fwd(
+        _ptr(weights, _ROWS), R, D, dtype, _ptr(rows, _I64), _ptr(pos, _I32),
+        j0, j1, _ptr(out, _ROWS), n, _stream(), _ptr(dev_status, _I32))
     return _check("fs_seq_gather_fwd", code, raise_on_error)
 
 
@@ -170,9 +218,9 @@ def fs_seq_gather_send(weights, rows, j0: int, j1: int, send, dev_status=None, r
     R = weights.shape[0] if R is None else R
     D = weights.shape[1] if D is None else D
     dtype = _DTYPES[weights.dtype] if dtype is None else dtype
-    code = lib().fs_seq_gather_send(
-        _ptr(weights, _ROWS), ctypes.c_int64(R), ctypes.c_int32(D), ctypes.c_int(dtype), _ptr(rows, _I64),
-        ctypes.c_int64(j0), ctypes.c_int64(j1), _ptr(send, _ROWS), _stream(), _ptr(dev_status, _I32))
+    code = _typed().fs_seq_gather_send(
+        _ptr(weights, _ROWS), R, D, dtype, _ptr(rows, _I64),
+        j0, j1, _ptr(send, _ROWS), _stream(), _ptr(dev_status, _I32))
     return _check("fs_seq_gather_send", code, raise_on_error)
 
 
@@ -181,9 +229,9 @@ def fs_seq_unbucketize(recv, pos, j0: int, j1: int, out, dev_status=None, raise_
     D = recv.shape[1] if D is None else D
     n = out.shape[0] if n is None else n
     dtype = _DTYPES[recv.dtype] if dtype is None else dtype
-    code = lib().fs_seq_unbucketize(
-        _ptr(recv, _ROWS), ctypes.c_int32(D), ctypes.c_int(dtype), _ptr(pos, _I32), ctypes.c_int64(j0), ctypes.c_int64(j1),
-        _ptr(out, _ROWS), ctypes.c_int64(n), _stream(), _ptr(dev_status, _I32))
+    code = _typed().fs_seq_unbucketize(
+        _ptr(recv, _ROWS), D, dtype, _ptr(pos, _I32), j0, j1,
+        _ptr(out, _ROWS), n, _stream(), _ptr(dev_status, _I32))
     return _check("fs_seq_unbucketize", code, raise_on_error)
 
 
@@ -193,9 +241,9 @@ def fs_replica_build(weights, sel_rows, k: int, num_selected, store, slot_of_row
     R = weights.shape[0] if R is None else R
     D = weights.shape[1] if D is None else D
     dtype = _DTYPES[weights.dtype] if dtype is None else dtype
-    code = lib().fs_replica_build(
-        _ptr(weights, _ROWS), ctypes.c_int64(R), ctypes.c_int32(D), ctypes.c_int(dtype), _ptr(sel_rows, _I64),
-        ctypes.c_int64(k), _ptr(num_selected, _I64), _ptr(store, _ROWS), _ptr(slot_of_row, _I32), _stream(), _ptr(dev_status, _I32))
+    code = _typed().fs_replica_build(
+        _ptr(weights, _ROWS), R, D, dtype, _ptr(sel_rows, _I64),
+        k, _ptr(num_selected, _I64), _ptr(store, _ROWS), _ptr(slot_of_row, _I32), _stream(), _ptr(dev_status, _I32))
     return _check("fs_replica_build", code, raise_on_error)
 
 
@@ -207,17 +255,17 @@ def fs_seq_gather_fwd_replica(weights, store, k: int, slot_of_row, rows, pos, j0
     D = weights.shape[1] if D is None else D
     n = out.shape[0] if n is None else n
     dtype = _DTYPES[weights.dtype] if dtype is None else dtype
-    code = lib().fs_seq_gather_fwd_replica(
-        _ptr(weights, _ROWS), ctypes.c_int64(R), ctypes.c_int32(D), ctypes.c_int(dtype), _ptr(store, _ROWS), ctypes.c_int64(k),
-        _ptr(slot_of_row, _I32), _ptr(rows, _I64), _ptr(pos, _I32), ctypes.c_int64(j0), ctypes.c_int64(j1), _ptr(out, _ROWS),
-        ctypes.c_int64(n), _stream(), _ptr(dev_status, _I32))
+    code = _typed().fs_seq_gather_fwd_replica(
+        _ptr(weights, _ROWS), R, D, dtype, _ptr(store, _ROWS), k,
+        _ptr(slot_of_row, _I32), _ptr(rows, _I64), _ptr(pos, _I32), j0, j1, _ptr(out, _ROWS),
+        n, _stream(), _ptr(dev_status, _I32))
     return _check("fs_seq_gather_fwd_replica", code, raise_on_error)
 
 
 def fs_replica_tag_slots(placement, slot_of_row, dev_status=None, raise_on_error: bool = True,
                          R: Optional[int] = None) -> int:
     R = placement.shape[0] if R is None else R
-    code = lib().fs_replica_tag_slots(_ptr(placement, _U32), ctypes.c_int64(R), _ptr(slot_of_row, _I32), _stream(),
+    code = _typed().fs_replica_tag_slots(_ptr(placement, _U32), R, _ptr(slot_of_row, _I32), _stream(),
                                       _ptr(dev_status, _I32))
     return _check("fs_replica_tag_slots", code, raise_on_error)
 
@@ -225,14 +273,15 @@ def fs_replica_tag_slots(placement, slot_of_row, dev_status=None, raise_on_error
 def fs_route_bucketize_slots(ids, offsets, T: int, B: int, row_base, placement, n: int, U: int, W: int, self_: int,
                              bucket_offsets, out_rows, out_pos, out_slots, tier_counts=None, dev_status=None,
                              workspace: Optional[torch.Tensor] = None, raise_on_error: bool = True) -> int:
-    L = lib()
+    L = _typed()
+
+    args = (_ptr(ids, _I64), _ptr(offsets, _I64), T, B, _ptr(row_base, _I64), _ptr(placement, _U32), n, U, W,
+            self_, _ptr(bucket_offsets, _I64), _ptr(out_rows, _I64), _ptr(out_pos, _I32), _ptr(out_slots, _I32),
+            _ptr(tier_counts, _I64))
+    tail = (_stream(), _ptr(dev_status, _I32))
 
     def call(ws_ptr, ws_size_ref):
-        return L.fs_route_bucketize_slots(
-            _ptr(ids, _I64), _ptr(offsets, _I64), ctypes.c_int32(T), ctypes.c_int32(B), _ptr(row_base, _I64), _ptr(placement, _U32),
-            ctypes.c_int64(n), ctypes.c_int32(U), ctypes.c_int32(W), ctypes.c_int32(self_),
-            _ptr(bucket_offsets, _I64), _ptr(out_rows, _I64), _ptr(out_pos, _I32), _ptr(out_slots, _I32), _ptr(tier_counts, _I64),
-            ws_ptr, ws_size_ref, _stream(), _ptr(dev_status, _I32))
+        return L.fs_route_bucketize_slots(*args, ws_ptr, ws_size_ref, *tail)
 
     if workspace is None:
         workspace, size, code = _workspace(call, offsets.device)
@@ -250,10 +299,10 @@ def fs_seq_gather_fwd_slots(weights, store, k: int, rows, slots, pos, j0: int, j
     D = weights.shape[1] if D is None else D
     n = out.shape[0] if n is None else n
     dtype = _DTYPES[weights.dtype] if dtype is None else dtype
-    code = lib().fs_seq_gather_fwd_slots(
-        _ptr(weights, _ROWS), ctypes.c_int64(R), ctypes.c_int32(D), ctypes.c_int(dtype), _ptr(store, _ROWS), ctypes.c_int64(k),
-        _ptr(rows, _I64), _ptr(slots, _I32), _ptr(pos, _I32), ctypes.c_int64(j0), ctypes.c_int64(j1), _ptr(out, _ROWS),
-        ctypes.c_int64(n), _stream(), _ptr(dev_status, _I32))
+    code = _typed().fs_seq_gather_fwd_slots(
+        _ptr(weights, _ROWS), R, D, dtype, _ptr(store, _ROWS), k,
+        _ptr(rows, _I64), _ptr(slots, _I32), _ptr(pos, _I32), j0, j1, _ptr(out, _ROWS),
+        n, _stream(), _ptr(dev_status, _I32))
     return _check("fs_seq_gather_fwd_slots", code, raise_on_error)
 
 
@@ -261,17 +310,17 @@ def fs_seq_grad_bwd(grad_out, rows, pos, j0: int, j1: int, R: int, variant: int,
                     uniq_rows, row_grads, cap_unique: int, num_unique, dev_status=None,
                     workspace: Optional[torch.Tensor] = None, raise_on_error: bool = True,
                     n: Optional[int] = None, D: Optional[int] = None, dtype: Optional[int] = None) -> int:
-    L = lib()
+    L = _typed()
     n = grad_out.shape[0] if n is None else n
     D = grad_out.shape[1] if D is None else D
     dtype = _DTYPES[grad_out.dtype] if dtype is None else dtype
 
+    args = (_ptr(grad_out, _ROWS), n, D, dtype, _ptr(rows, _I64), _ptr(pos, _I32), j0, j1, R, variant,
+            _ptr(uniq_rows, _I64), _ptr(row_grads, _F32), cap_unique, _ptr(num_unique, _I64))
+    tail = (_stream(), _ptr(dev_status, _I32))
+
     def call(ws_ptr, ws_size_ref):
-        return L.fs_seq_grad_bwd(
-            _ptr(grad_out, _ROWS), ctypes.c_int64(n), ctypes.c_int32(D), ctypes.c_int(dtype), _ptr(rows, _I64), _ptr(pos, _I32),
-            ctypes.c_int64(j0), ctypes.c_int64(j1), ctypes.c_int64(R), ctypes.c_int32(variant),
-            _ptr(uniq_rows, _I64), _ptr(row_grads, _F32), ctypes.c_int64(cap_unique), _ptr(num_unique, _I64),
-            ws_ptr, ws_size_ref, _stream(), _ptr(dev_status, _I32))
+        return L.fs_seq_grad_bwd(*args, ws_ptr, ws_size_ref, *tail)
 
     if workspace is None:
         workspace, size, code = _workspace(call, grad_out.device)
@@ -284,12 +333,13 @@ def fs_seq_grad_bwd(grad_out, rows, pos, j0: int, j1: int, R: int, variant: int,
 
 def fs_sort_lookups(rows, pos, j0: int, j1: int, R: int, n: int, sorted_rows, sorted_pos, dev_status=None,
                     workspace: Optional[torch.Tensor] = None, raise_on_error: bool = True) -> int:
-    L = lib()
+    L = _typed()
+
+    args = (_ptr(rows, _I64), _ptr(pos, _I32), j0, j1, R, n, _ptr(sorted_rows, _U32), _ptr(sorted_pos, _U32))
+    tail = (_stream(), _ptr(dev_status, _I32))
 
     def call(ws_ptr, ws_size_ref):
-        return L.fs_sort_lookups(_ptr(rows, _I64), _ptr(pos, _I32), ctypes.c_int64(j0), ctypes.c_int64(j1), ctypes.c_int64(R),
-                                 ctypes.c_int64(n), _ptr(sorted_rows, _U32), _ptr(sorted_pos, _U32), ws_ptr, ws_size_ref,
-                                 _stream(), _ptr(dev_status, _I32))
+        return L.fs_sort_lookups(*args, ws_ptr, ws_size_ref, *tail)
 
     if workspace is None:
         device = next((t.device for t in (rows, sorted_rows, pos) if t is not None), "cuda")
@@ -305,17 +355,17 @@ def fs_seq_grad_bwd_sorted(grad_out, sorted_rows, sorted_pos, m: int, R: int, va
                            uniq_rows, row_grads, cap_unique: int, num_unique, dev_status=None,
                            workspace: Optional[torch.Tensor] = None, raise_on_error: bool = True,
                            n: Optional[int] = None, D: Optional[int] = None, dtype: Optional[int] = None) -> int:
-    L = lib()
+    L = _typed()
     n = grad_out.shape[0] if n is None else n
     D = grad_out.shape[1] if D is None else D
     dtype = _DTYPES[grad_out.dtype] if dtype is None else dtype
 
+    args = (_ptr(grad_out, _ROWS), n, D, dtype, _ptr(sorted_rows, _U32), _ptr(sorted_pos, _U32), m, R, variant,
+            _ptr(uniq_rows, _I64), _ptr(row_grads, _F32), cap_unique, _ptr(num_unique, _I64))
+    tail = (_stream(), _ptr(dev_status, _I32))
+
     def call(ws_ptr, ws_size_ref):
-        return L.fs_seq_grad_bwd_sorted(
-            _ptr(grad_out, _ROWS), ctypes.c_int64(n), ctypes.c_int32(D), ctypes.c_int(dtype), _ptr(sorted_rows, _U32),
-            _ptr(sorted_pos, _U32), ctypes.c_int64(m), ctypes.c_int64(R), ctypes.c_int32(variant),
-            _ptr(uniq_rows, _I64), _ptr(row_grads, _F32), ctypes.c_int64(cap_unique), _ptr(num_unique, _I64),
-            ws_ptr, ws_size_ref, _stream(), _ptr(dev_status, _I32))
+        return L.fs_seq_grad_bwd_sorted(*args, ws_ptr, ws_size_ref, *tail)
 
     if workspace is None:
         workspace, size, code = _workspace(call, grad_out.device)
@@ -333,9 +383,9 @@ def fs_seq_gather_fwd_sorted(weights, sorted_rows, sorted_pos, m: int, out, dev_
     D = weights.shape[1] if D is None else D
     n = out.shape[0] if n is None else n
     dtype = _DTYPES[weights.dtype] if dtype is None else dtype
-    code = lib().fs_seq_gather_fwd_sorted(
-        _ptr(weights, _ROWS), ctypes.c_int64(R), ctypes.c_int32(D), ctypes.c_int(dtype), _ptr(sorted_rows, _U32),
-        _ptr(sorted_pos, _U32), ctypes.c_int64(m), _ptr(out, _ROWS), ctypes.c_int64(n), _stream(), _ptr(dev_status, _I32))
+    code = _typed().fs_seq_gather_fwd_sorted(
+        _ptr(weights, _ROWS), R, D, dtype, _ptr(sorted_rows, _U32),
+        _ptr(sorted_pos, _U32), m, _ptr(out, _ROWS), n, _stream(), _ptr(dev_status, _I32))
     return _check("fs_seq_gather_fwd_sorted", code, raise_on_error)
 
 
@@ -343,14 +393,14 @@ def fs_plan_replication(ids, offsets, T: int, B: int, row_base, n: int, R: int, 
                         budget_bytes: int = 0, bytes_per_row: int = 1, sel_rows=None, num_selected=None,
                         placement=None, dev_status=None, workspace: Optional[torch.Tensor] = None,
                         raise_on_error: bool = True) -> int:
-    L = lib()
+    L = _typed()
+
+    args = (_ptr(ids, _I64), _ptr(offsets, _I64), T, B, _ptr(row_base, _I64), n, R, _ptr(counts, _U32), flags,
+            budget_bytes, bytes_per_row, _ptr(sel_rows, _I64), _ptr(num_selected, _I64), _ptr(placement, _U32))
+    tail = (_stream(), _ptr(dev_status, _I32))
 
     def call(ws_ptr, ws_size_ref):
-        return L.fs_plan_replication(
-            _ptr(ids, _I64), _ptr(offsets, _I64), ctypes.c_int32(T), ctypes.c_int32(B), _ptr(row_base, _I64), ctypes.c_int64(n),
-            ctypes.c_int64(R), _ptr(counts, _U32), ctypes.c_int32(flags), ctypes.c_int64(budget_bytes),
-            ctypes.c_int64(bytes_per_row), _ptr(sel_rows, _I64), _ptr(num_selected, _I64), _ptr(placement, _U32),
-            ws_ptr, ws_size_ref, _stream(), _ptr(dev_status, _I32))
+        return L.fs_plan_replication(*args, ws_ptr, ws_size_ref, *tail)
 
     if workspace is None:
         workspace, size, code = _workspace(call, counts.device)
@@ -370,13 +420,15 @@ class TierParams(ctypes.Structure):
 
 def fs_plan_tiers(counts, R: int, params: dict, tiers: int, sorted_rows, cap: int, cuts, placement=None,
                   dev_status=None, workspace: Optional[torch.Tensor] = None, raise_on_error: bool = True) -> int:
-    L = lib()
+    L = _typed()
     tp = TierParams(**params)
 
+    args = (_ptr(counts, _U32), R, ctypes.byref(tp), tiers, _ptr(sorted_rows, _I64), cap, _ptr(cuts, _I64),
+            _ptr(placement, _U32))
+    tail = (_stream(), _ptr(dev_status, _I32))
+
     def call(ws_ptr, ws_size_ref):
-        return L.fs_plan_tiers(_ptr(counts, _U32), ctypes.c_int64(R), ctypes.byref(tp), ctypes.c_int32(tiers),
-                               _ptr(sorted_rows, _I64), ctypes.c_int64(cap), _ptr(cuts, _I64), _ptr(placement, _U32),
-                               ws_ptr, ws_size_ref, _stream(), _ptr(dev_status, _I32))
+        return L.fs_plan_tiers(*args, ws_ptr, ws_size_ref, *tail)
 
     if workspace is None:
         device = next((t.device for t in (counts, cuts, sorted_rows) if t is not None), "cuda")
@@ -395,10 +447,10 @@ def fs_sparse_update(weights, uniq_rows, row_grads, cap_unique: int, num_unique,
     R = weights.shape[0] if R is None else R
     D = weights.shape[1] if D is None else D
     dtype = _DTYPES[weights.dtype] if dtype is None else dtype
-    code = lib().fs_sparse_update(
-        _ptr(weights, _ROWS), ctypes.c_int64(R), ctypes.c_int32(D), ctypes.c_int(dtype), _ptr(uniq_rows, _I64), _ptr(row_grads, _F32),
-        ctypes.c_int64(cap_unique), _ptr(num_unique, _I64), ctypes.c_int32(optimizer), ctypes.c_float(lr), ctypes.c_float(eps),
-        _ptr(state, _F32), _ptr(store, _ROWS), _ptr(slot_of_row, _I32), ctypes.c_int64(k), _stream(), _ptr(dev_status, _I32))
+    code = _typed().fs_sparse_update(
+        _ptr(weights, _ROWS), R, D, dtype, _ptr(uniq_rows, _I64), _ptr(row_grads, _F32),
+        cap_unique, _ptr(num_unique, _I64), optimizer, lr, eps,
+        _ptr(state, _F32), _ptr(store, _ROWS), _ptr(slot_of_row, _I32), k, _stream(), _ptr(dev_status, _I32))
     return _check("fs_sparse_update", code, raise_on_error)
 
 
@@ -407,18 +459,19 @@ def fs_seq_grad_bwd_update(grad_out, sorted_rows, sorted_pos, m: int, R: int, we
                            num_unique, dev_status=None, workspace: Optional[torch.Tensor] = None,
                            raise_on_error: bool = True, n: Optional[int] = None, D: Optional[int] = None,
                            dtype: Optional[int] = None) -> int:
-    L = lib()
+    L = _typed()
     n = grad_out.shape[0] if n is None else n
     D = grad_out.shape[1] if D is None else D
     dtype = _DTYPES[grad_out.dtype] if dtype is None else dtype
 
+    args = (_ptr(grad_out, _ROWS), n, D, dtype, _ptr(sorted_rows, _U32), _ptr(sorted_pos, _U32), m, R,
+            _ptr(weights, _ROWS), optimizer, lr, eps, _ptr(state, _F32), _ptr(store, _ROWS),
+            _ptr(slot_of_row, _I32), k, _ptr(uniq_rows, _I64), _ptr(row_grads, _F32), cap_unique,
+            _ptr(num_unique, _I64))
+    tail = (_stream(), _ptr(dev_status, _I32))
+
     def call(ws_ptr, ws_size_ref):
-        return L.fs_seq_grad_bwd_update(
-            _ptr(grad_out, _ROWS), ctypes.c_int64(n), ctypes.c_int32(D), ctypes.c_int(dtype), _ptr(sorted_rows, _U32),
-            _ptr(sorted_pos, _U32), ctypes.c_int64(m), ctypes.c_int64(R), _ptr(weights, _ROWS), ctypes.c_int32(optimizer),
-            ctypes.c_float(lr), ctypes.c_float(eps), _ptr(state, _F32), _ptr(store, _ROWS), _ptr(slot_of_row, _I32),
-            ctypes.c_int64(k), _ptr(uniq_rows, _I64), _ptr(row_grads, _F32), ctypes.c_int64(cap_unique),
-            _ptr(num_unique, _I64), ws_ptr, ws_size_ref, _stream(), _ptr(dev_status, _I32))
+        return L.fs_seq_grad_bwd_update(*args, ws_ptr, ws_size_ref, *tail)
 
     if workspace is None:
         workspace, size, code = _workspace(call, grad_out.device)
@@ -456,14 +509,13 @@ def fs_tier_traffic(tier_counts, D: int, dtype_bytes: int, raise_on_error: bool 
 
 def fs_util_copy(dst, src, nbytes: Optional[int] = None, raise_on_error: bool = True) -> int:
     nbytes = src.numel() * src.element_size() if nbytes is None else nbytes
-    code = lib().fs_util_copy(_ptr(dst), _ptr(src), ctypes.c_int64(nbytes), _stream())
+    code = _typed().fs_util_copy(_ptr(dst), _ptr(src), nbytes, _stream())
     return _check("fs_util_copy", code, raise_on_error)
 
 
 def fs_util_read_write_mix(src, pieces_per_write: int, dst=None, raise_on_error: bool = True) -> int:
-    code = lib().fs_util_read_write_mix(_ptr(src), ctypes.c_int64(src.numel() * src.element_size()),
-                                        ctypes.c_int32(pieces_per_write), _ptr(dst),
-                                        ctypes.c_int64(0 if dst is None else dst.numel() * dst.element_size()), _stream())
+    code = _typed().fs_util_read_write_mix(_ptr(src), src.numel() * src.element_size(), pieces_per_write, _ptr(dst),
+                                           0 if dst is None else dst.numel() * dst.element_size(), _stream())
     return _check("fs_util_read_write_mix", code, raise_on_error)
 
 
