@@ -7,13 +7,13 @@
 //                     start in it, with a block-local exclusive prefix
 //   bwd_scan_blocks   exclusive scan of the per-block sums -> index of every run,
 //                     *num_unique
-//   bwd_segreduce     a group of LG lanes (one 16-byte piece of the row per lane) walks
-//                     one chunk left to right with 8 gradient rows in flight; the chunk's
-//                     keys and positions are staged in LDS by coalesced loads and read back
-//                     as broadcasts; a run that starts in the chunk goes to row_grads, the
-//                     piece that continues a run from the previous chunk goes to carry[chunk]
+//   bwd_segreduce     a wave walks one chunk left to right, the rows' addresses in scalar registers and
+//                     8 rows in flight; a run that starts in the chunk goes to row_grads, the piece that
+//                     continues a run from the previous chunk goes to carry[chunk]
 //   bwd_singletons    runs of one lookup (most runs: the cold tail) are skipped by the walk and
 //                     converted here, fully parallel
+//   bwd_chunk_sums    in place of these two for few chunks: a block brings one chunk's rows to LDS, every
+//                     load in flight at once, and sums the run pieces out of LDS side by side
 //   bwd_fold          for every run that spills over a chunk end: row_grads += carry of
 //                     the following chunks, left to right
 // which is exactly the summation order stated in flexshard.h (chunk = FS_BWD_TILE).
@@ -29,10 +29,12 @@ namespace fs {
 constexpr int kChunk = FS_BWD_TILE;
 constexpr int kChunksPerBlock = 64;          // bwd_count_heads: chunks per block
 constexpr int kSinglesSplit = 4;             // bwd_singletons: waves per chunk (divides kChunk / 64)
-constexpr int kBwdUnroll = 8;               // rows a group keeps in flight
+constexpr int kWalkAhead = 8;                // rows per batch of a walking wave, the next batch in flight beside it
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;     // never a row: R < 2^32 - 1
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
 // Block b covers chunks [64 b, 64 b + 64): 16 waves, each walks 4 of them (with 4 waves of 16 chunks
 // each the kernel's time was the chain of 16 dependent rounds of loads per wave).  chunk_local[c] = runs
@@ -156,169 +158,327 @@ struct Vec<FS_BF16> {
     }
 };
 
-// A group of LG lanes (LG >= 16) walks one chunk of 256 sorted lookups left to right.  The
-// group first stages the chunk's keys and positions in LDS with coalesced loads (a per-step
-// index load in front of every gradient row would stall the row loads); bit 31 of a staged
-// position says "the run's piece ends here" (next key differs, or last lookup of the chunk).
-// They are read back as LDS broadcasts, 8 lookups per batch, the next batch's 8 gradient
-// rows already in flight while the current batch is summed.
-constexpr uint32_t kEndBit = 0x80000000u;        // positions are < 2^31
-constexpr uint32_t kSkip = 0xFFFFFFFFu;          // a run of one lookup: bwd_singletons writes it (not a position + flag:
-                                                 // positions stop at 2^31 - 2)
+constexpr uint32_t kEndBit = 0x80000000u;        // of a listed position (positions are < 2^31): the run's piece ends here
 
+// The segmented sum for few chunks, where a walk of the chunk leaves the chip idle and costs its serial chain of
+// loads whatever the batch (54 us for 8192 lookups of 256-byte rows).  One block takes one chunk, one slab of up
+// to 16 pieces of its rows: the lookups it sums are listed in LDS, their rows follow with every load in flight at
+// once (64 KB), and the chunk's run pieces are then summed out of LDS side by side, four columns to a lane, each
+// piece left to right as the walk does it.  Bound by two rounds of memory latency and the longest run's chain in
+// LDS: 9.0 us for those 8192 lookups, 14 us (was 63) for 50 k of 144-byte rows.  It sums runs of one
+// lookup too, unless the optimizer's kernel takes them.  512 and 1024 threads per block measure the same, slabs of
+// 8 and 4 pieces are no faster anywhere and 4 are slower from 1 M lookups on.
+constexpr int kSlabPieces = 16;                  // 16-byte pieces of a row per slab
+constexpr int kChunkLoads = 16;                  // loads a thread keeps in flight
+// Up to this many chunks.  5 k / 40 k / 300 k / 3 M lookups, the whole backward, this kernel against the walk:
+// 48-byte rows 70 : 81, 103 : 115, 134 : 139, 262 : 280 us; 208-byte 73 : 84, 104 : 116, 154 : 154, 431 : 385;
+// 1 KB 68 : 85, 107 : 121, 206 : 205, 966 : 819.
+constexpr int64_t kSumsMaxChunks = 1024;
 
-template <int LG, int DT, bool EXACT>            // EXACT: units == LG, the row stride is a compile-time constant
-__global__ __launch_bounds__(kBlock) void bwd_segreduce_kernel(
-    const u32x4* __restrict__ grad, int units, int D,
+template <int P_, int DT>                        // P_: pieces per slab, 0: `pieces`
+__global__ __launch_bounds__(kBlock) void bwd_chunk_sums_kernel(
+    const u32x4* __restrict__ grad, int units, int D, int pieces, int slabs,
     const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals, int64_t m, int64_t chunks, uint32_t n,
     const uint32_t* __restrict__ block_base, const uint32_t* __restrict__ chunk_local,
     int64_t* __restrict__ uniq_rows, float* __restrict__ row_grads, int64_t cap,
     float* __restrict__ carry, int atomic, uint8_t* __restrict__ applied)
 {
-    static_assert(LG >= 16 && LG <= kWave, "groups of 16..64 lanes (smaller groups would need > 64 KB of LDS)");
+    static_assert(kChunk == kBlock, "a thread per lookup of the chunk");
     constexpr int N = Vec<DT>::N;
-    constexpr int GPB = kBlock / LG;
-    constexpr int U8 = kBwdUnroll;
-    constexpr int kPad = 2 * U8;                 // batches issued past the end read position 0
-    __shared__ __attribute__((aligned(16))) uint32_t s_val[GPB][kChunk + kPad];
-    __shared__ uint32_t s_key[GPB][kChunk + 1];  // [kChunk]: the key that follows the chunk
-    __shared__ __attribute__((aligned(16))) float s_stage[N == 8 ? GPB : 1][N == 8 ? LG * 8 : 4];
-    const int lig = threadIdx.x % LG;
-    const int gi = threadIdx.x / LG;
-    int64_t chunk = (int64_t)blockIdx.x * GPB + gi;
-    const bool group_on = chunk < chunks;                        // idle groups walk the last chunk, writing nothing
-    if (!group_on) chunk = chunks - 1;
-    const int c = blockIdx.y * LG + lig;                         // 16-byte piece of the row
-    const bool lane_on = group_on && c < units;
-    const int cc = c < units ? c : 0;
+    const int P = P_ != 0 ? P_ : pieces;
+    extern __shared__ __attribute__((aligned(16))) u32x4 s_rows[];   // [kChunk][P]
+    __shared__ uint32_t s_pos[kChunk];
+    __shared__ uint32_t s_start[kChunk + 1];     // a run piece's first row in s_rows
+    __shared__ uint32_t s_run[kChunk];           // its run index
+    __shared__ uint32_t wave_n[kWavesPerBlock][3];
+    const int t = threadIdx.x;
+    const int w = wave_id();
+    const int64_t chunk = blockIdx.x / slabs;
+    const int slab = (int)(blockIdx.x - chunk * slabs);
     const int64_t k0 = chunk * kChunk;
     const int64_t k1 = k0 + kChunk < m ? k0 + kChunk : m;
-    const int cnt = (int)(k1 - k0);
-    const int col = cc * N;
-
-    {
-        constexpr int PER = kChunk / LG;
-        uint32_t key[PER], prev[PER], next[PER], val[PER];
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {                          // all loads first, then the LDS writes
-            const int64_t k = k0 + i * LG + lig;
-            key[i] = k < k1 ? keys[k] : kNoKey;
-            prev[i] = k > 0 ? keys[k - 1] : kNoKey;
-            next[i] = k + 1 < m ? keys[k + 1] : kNoKey;
-            val[i] = k < k1 ? vals[k] : 0u;                      // past the end: position 0, loaded but unused
-        }
-#pragma unroll
-        for (int i = 0; i < PER; ++i) val[i] = val[i] < n ? val[i] : 0u;   // a position outside the batch reads row 0
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int e = i * LG + lig;
-            const bool end = k0 + e + 1 >= k1 || next[i] != key[i];
-            const bool single = k0 + e < k1 && prev[i] != key[i] && next[i] != key[i];
-            s_key[gi][e] = key[i];
-            s_val[gi][e] = single ? kSkip : (val[i] | (end ? kEndBit : 0u));
-            if (e == kChunk - 1) s_key[gi][kChunk] = next[i];
-        }
-        if (lig < kPad) s_val[gi][kChunk + lig] = 0u;
+    const int64_t k = k0 + t;
+    const bool valid = k < k1;
+    const int64_t ks = valid ? k : k1 - 1;       // no load behind a predicate
+    const uint32_t key = keys[ks];
+    const uint32_t prev_key = keys[ks > 0 ? ks - 1 : 0];
+    const uint32_t next_key = keys[ks + 1 < m ? ks + 1 : ks];
+    uint32_t pos = vals[ks];
+    const uint32_t first_run = runs_before(block_base, chunk_local, chunk, chunks);
+    pos = pos < n ? pos : 0u;                    // a position outside the batch reads row 0
+    const bool head = valid && (k == 0 || key != prev_key);          // a run starts here
+    const bool last = k + 1 >= m || key != next_key;                 // it ends here
+    const bool keep = valid && !(applied != nullptr && head && last);// a row looked up once is the update kernel's
+    const bool start = keep && (head || t == 0);                     // a piece of a run starts here
+    const uint64_t hb = ballot(head), kb = ballot(keep), sb = ballot(start);
+    if (lane_id() == 0) {
+        wave_n[w][0] = (uint32_t)__popcll(hb); wave_n[w][1] = (uint32_t)__popcll(kb); wave_n[w][2] = (uint32_t)__popcll(sb);
     }
-    bool piece_cont = k0 > 0 && keys[k0 - 1] == keys[k0];    // first piece continues the previous chunk's run
-    int64_t u = (int64_t)runs_before(block_base, chunk_local, chunk, chunks) - 1;
-    bool fresh = true;
-    float acc[N];
+    __syncthreads();
+    uint32_t heads = (uint32_t)popc_below(hb) + (head ? 1u : 0u), at = (uint32_t)popc_below(kb), piece = (uint32_t)popc_below(sb);
+    uint32_t rows = 0, num_pieces = 0;
+#pragma unroll
+    for (int q = 0; q < kWavesPerBlock; ++q) {
+        if (q < w) { heads += wave_n[q][0]; at += wave_n[q][1]; piece += wave_n[q][2]; }
+        rows += wave_n[q][1];
+        num_pieces += wave_n[q][2];
+    }
+    if (rows == 0) return;                                           // block-uniform
+    const int64_t run = (int64_t)first_run + heads - 1;
+    if (keep) s_pos[at] = pos;
+    if (start) { s_start[piece] = at; s_run[piece] = (uint32_t)run; }
+    if (t == 0) s_start[num_pieces] = rows;
+    if (slab == 0 && keep && head && run < cap) {
+        uniq_rows[run] = (int64_t)key;
+        if (applied != nullptr) applied[run] = 0;                    // this row's gradient is in row_grads
+    }
+    const bool cont = k0 > 0 && keys[k0 - 1] == keys[k0];            // the first piece continues the previous chunk's run
+    const bool goes_on = k1 < m && keys[k1] == keys[k1 - 1];         // the last run goes on in the next chunk
     __syncthreads();
 
-    const uint32_t* my_val = s_val[gi];
-    const uint32_t* my_key = s_key[gi];
-    const u32x4* my_grad = grad + cc;
-
-    // 8 row loads, never predicated (a predicated load makes the compiler serialise the batch)
-#define FS_ISSUE(X, PV, E0)                                                                  \
-    _Pragma("unroll") for (int j = 0; j < U8; ++j) {                                         \
-        PV[j] = my_val[(E0) + j];                                                            \
-        X[j] = load_stream(my_grad + (int64_t)(PV[j] == kSkip ? 0u : PV[j] & ~kEndBit) * (EXACT ? LG : units)); \
-    }
-#define FS_CONSUME(X, PV, E0)                                                                \
-    _Pragma("unroll") for (int j = 0; j < U8; ++j) {                                         \
-        if ((E0) + j < cnt && PV[j] == kSkip) {                                              \
-            ++u;                       /* a run of one: counted here, written elsewhere */   \
-        } else if ((E0) + j < cnt) {                                                         \
-            float f[N];                                                                      \
-            Vec<DT>::load(X[j], f);                                                          \
-            if (fresh) {                                                                     \
-                if (!piece_cont) ++u;                                                        \
-                _Pragma("unroll") for (int q = 0; q < N; ++q) acc[q] = f[q];                 \
-            } else {                                                                         \
-                _Pragma("unroll") for (int q = 0; q < N; ++q) acc[q] = acc[q] + f[q];        \
-            }                                                                                \
-            fresh = false;                                                                   \
-            if (PV[j] & kEndBit) {                                                           \
-                flush((E0) + j);                                                             \
-                fresh = true;                                                                \
-                piece_cont = false;                                                          \
-            }                                                                                \
-        }                                                                                    \
-    }
-
-    // The piece that ends at chunk-local index e goes out.  A lane holds N consecutive floats;
-    // with N = 8 a direct store would be two instructions that each fill every other 16 bytes
-    // of the row, so the group first transposes through LDS: afterwards lane i owns floats
-    // [4i, 4i+4) of each half of the group's slab and both stores are fully coalesced.
-    // The stores are non-temporal: the rows are not read again by this kernel (1.99 -> 1.74 ms
-    // on 15.7M lookups of 512-byte rows).
-    auto store_row = [&](float* row) {           // row = first float of the destination row
-        if constexpr (N == 4) {
-            if (lane_on) store_stream(reinterpret_cast<f32x4*>(row + col), f32x4{acc[0], acc[1], acc[2], acc[3]});
-        } else {
-            float* stage = s_stage[gi];
-            *reinterpret_cast<f32x4*>(stage + lig * 8) = f32x4{acc[0], acc[1], acc[2], acc[3]};
-            *reinterpret_cast<f32x4*>(stage + lig * 8 + 4) = f32x4{acc[4], acc[5], acc[6], acc[7]};
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const f32x4 lo = *reinterpret_cast<const f32x4*>(stage + lig * 4);
-            const f32x4 hi = *reinterpret_cast<const f32x4*>(stage + LG * 4 + lig * 4);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const int slab = blockIdx.y * LG * 8;
-            const int col_lo = slab + lig * 4;
-            const int col_hi = slab + LG * 4 + lig * 4;
-            if (group_on && col_lo < D) store_stream(reinterpret_cast<f32x4*>(row + col_lo), lo);
-            if (group_on && col_hi < D) store_stream(reinterpret_cast<f32x4*>(row + col_hi), hi);
-        }
-    };
-    auto flush = [&](int e) {
-        if (piece_cont && !atomic) {
-            store_row(carry + chunk * D);
-        } else if (u < cap) {
-            float* dst = row_grads + u * D;
-            const uint32_t key = my_key[e];
-            const bool run_goes_on = my_key[e + 1] == key;       // also across the chunk end
-            if (atomic && (piece_cont || run_goes_on)) {
-                if (lane_on) {
+    const uint32_t total = rows * (uint32_t)P;
+    const uint32_t inv = (65536u + (uint32_t)P - 1u) / (uint32_t)P;  // e / P = e * inv >> 16 for e < 4096, P <= 16
+    const int piece0 = slab * P;
+    for (uint32_t e0 = 0; e0 < total; e0 += kBlock * kChunkLoads) {
+        u32x4 x[kChunkLoads];
 #pragma unroll
-                    for (int q = 0; q < N; ++q) unsafeAtomicAdd(dst + col + q, acc[q]);
-                }
+        for (int j = 0; j < kChunkLoads; ++j) {
+            uint32_t e = e0 + j * kBlock + t;
+            e = e < total ? e : total - 1;
+            const uint32_t r = P_ != 0 ? e / (uint32_t)P : (e * inv) >> 16;
+            const int c = piece0 + (int)(e - r * (uint32_t)P);
+            x[j] = load_stream(grad + (int64_t)s_pos[r] * units + (c < units ? c : units - 1));
+        }
+#pragma unroll
+        for (int j = 0; j < kChunkLoads; ++j) {
+            const uint32_t e = e0 + j * kBlock + t;
+            if (e < total) s_rows[e] = x[j];
+        }
+    }
+    __syncthreads();
+
+    // a lane sums four columns of a run's piece
+    const int quads = P * (N / 4);
+    const int slots = kBlock / quads;
+    const int slot = t / quads;
+    const int quad = t - slot * quads;
+    const int col = slab * P * N + quad * 4;
+    if (slot >= slots || col >= D) return;                           // no barrier below
+    auto load_quad = [&](uint32_t r) -> f32x4 {
+        if constexpr (N == 4) {
+            const u32x4 v = s_rows[r * P + quad];
+            return f32x4{__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3])};
+        } else {
+            const u32x2 v = reinterpret_cast<const u32x2*>(s_rows)[r * (2 * P) + quad];
+            if constexpr (DT == FS_F16) {
+                const f16x4 h = __builtin_bit_cast(f16x4, v);
+                return f32x4{(float)h[0], (float)h[1], (float)h[2], (float)h[3]};
             } else {
-                store_row(dst);
-            }
-            if (lane_on && !piece_cont && c == 0) {
-                uniq_rows[u] = (int64_t)key;
-                if (applied != nullptr) applied[u] = 0;          // this row's gradient is in row_grads
+                return f32x4{__uint_as_float(v[0] << 16), __uint_as_float(v[0] & 0xFFFF0000u),
+                             __uint_as_float(v[1] << 16), __uint_as_float(v[1] & 0xFFFF0000u)};
             }
         }
     };
-
-    u32x4 xa[U8], xb[U8];
-    uint32_t pa[U8], pb[U8];
-    FS_ISSUE(xa, pa, 0)
-#pragma unroll 1
-    for (int e0 = 0; e0 < cnt; e0 += 2 * U8) {
-        FS_ISSUE(xb, pb, e0 + U8)
-        FS_CONSUME(xa, pa, e0)
-        FS_ISSUE(xa, pa, e0 + 2 * U8)
-        FS_CONSUME(xb, pb, e0 + U8)
+    for (uint32_t p = slot; p < num_pieces; p += slots) {
+        uint32_t r = s_start[p];
+        const uint32_t end = s_start[p + 1];
+        const int64_t u = s_run[p];
+        f32x4 acc = load_quad(r++);
+        for (; r + 8 <= end; r += 8) {
+            f32x4 f[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = load_quad(r + j);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc = acc + f[j];
+        }
+        for (; r < end; ++r) acc = acc + load_quad(r);
+        const bool continues = cont && p == 0;
+        float* dst;
+        if (continues && !atomic) dst = carry + chunk * D + col;
+        else if (u < cap) dst = row_grads + u * D + col;
+        else continue;
+        if (atomic && (continues || (goes_on && p == num_pieces - 1))) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) unsafeAtomicAdd(dst + q, acc[q]);
+        } else {
+            store_stream(reinterpret_cast<f32x4*>(dst), acc);
+        }
     }
-#undef FS_ISSUE
-#undef FS_CONSUME
+}
+
+// VB bytes of a row as a lane holds them, and their elements as floats.
+template <int VB>
+struct Bytes;
+template <>
+struct Bytes<4> {
+    typedef uint32_t type;
+    template <int DT>
+    static __device__ __forceinline__ void load(uint32_t x, float* f)
+    {
+        if constexpr (DT == FS_F32) {
+            f[0] = __uint_as_float(x);
+        } else if constexpr (DT == FS_F16) {
+            const f16x2 h = __builtin_bit_cast(f16x2, x);
+            f[0] = (float)h[0]; f[1] = (float)h[1];
+        } else {
+            f[0] = __uint_as_float(x << 16); f[1] = __uint_as_float(x & 0xFFFF0000u);
+        }
+    }
+};
+template <>
+struct Bytes<8> {
+    typedef u32x2 type;
+    template <int DT>
+    static __device__ __forceinline__ void load(const u32x2& x, float* f)
+    {
+        constexpr int H = DT == FS_F32 ? 1 : 2;
+        Bytes<4>::load<DT>(x[0], f);
+        Bytes<4>::load<DT>(x[1], f + H);
+    }
+};
+// The segmented sum.  A wave walks one chunk left to right (one slab of 64 * VB bytes of its rows, VB bytes to a
+// lane).  The lookups of repeated rows are listed in LDS, position and run index; the walk reads a batch of 8 of
+// them with one LDS load, hands the positions to scalar registers, and has the next batch's rows in flight while it
+// sums this one's.  A run's end is a bit of a scalar mask, so nothing in the walk diverges and a finished piece
+// leaves as one coalesced store.  Bound by the mix of the gradient stream with the stores' (the whole chip's reads
+// and writes, 5.2 TB/s on 512-byte rows), below some 8 k chunks by the walk's serial chain.
+// 4 bytes to a lane for rows of up to 256 bytes: a chunk per wave instead of four of them in 16-lane groups with 16
+// bytes to a lane gives four times the waves and no divergent flushes: 1.05 M lookups of 256-byte rows 74 -> 58 us,
+// 4.2 M 244 -> 206, 8.4 M (a table's head row is a quarter of them) 438 -> 408.  8 bytes for longer rows (15.7 M
+// lookups of 512-byte rows 1552 -> 1531 us, 72 M 7.08 -> 7.03 ms): the
+// same as 4 on 15.7 M lookups of 512-byte rows, 1 % faster on 72 M, and on 256-byte rows it would leave half the
+// lanes idle (937 us).  16 rows to a batch instead of 8 measure the same.
+template <int VB, int DT>
+__global__ __launch_bounds__(kBlock) void bwd_segreduce_kernel(
+    const unsigned char* __restrict__ grad, int row_bytes, int D,
+    const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals, int64_t m, int64_t chunks, uint32_t n,
+    const uint32_t* __restrict__ block_base, const uint32_t* __restrict__ chunk_local,
+    int64_t* __restrict__ uniq_rows, float* __restrict__ row_grads, int64_t cap,
+    float* __restrict__ carry, int atomic, uint8_t* __restrict__ applied)
+{
+    constexpr int U = kWalkAhead;
+    constexpr int ES = DT == FS_F32 ? 4 : 2;
+    constexpr int N = VB / ES;                                       // elements per lane
+    typedef typename Bytes<VB>::type part_t;
+    __shared__ uint32_t s_pos[kWavesPerBlock][kChunk + kWave];
+    __shared__ uint32_t s_run[kWavesPerBlock][kChunk + kWave];
+    const int w = wave_id();
+    const int lane = lane_id();
+    const int64_t chunk = (int64_t)blockIdx.x * kWavesPerBlock + w;
+    if (chunk >= chunks) return;                                     // wave-uniform; no block barrier below
+    const int64_t k0 = chunk * kChunk;
+    const int64_t k1 = k0 + kChunk < m ? k0 + kChunk : m;
+    uint32_t* pos_of = s_pos[w];
+    uint32_t* run_of = s_run[w];
+    constexpr int Q = kChunk / kWave;
+    uint32_t key[Q], prev[Q], next[Q], pos[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {                                    // all loads in one round, none behind a predicate
+        const int64_t k = k0 + q * kWave + lane;
+        const int64_t ks = k < k1 ? k : k1 - 1;
+        key[q] = keys[ks];
+        prev[q] = keys[ks > 0 ? ks - 1 : 0];
+        next[q] = keys[ks + 1 < m ? ks + 1 : ks];
+        pos[q] = vals[ks];
+    }
+    uint32_t runs = runs_before(block_base, chunk_local, chunk, chunks);
+    uint32_t listed = 0;
+    bool cont = false;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int64_t k = k0 + q * kWave + lane;
+        const bool valid = k < k1;
+        const bool head = valid && (k == 0 || key[q] != prev[q]);
+        const bool last = k + 1 >= m || key[q] != next[q];
+        const bool keep = valid && !(head && last);                  // runs of one lookup are another kernel's
+        const bool end = last || k + 1 == k1;
+        const uint64_t hb = ballot(head), kb = ballot(keep);
+        const uint32_t at = listed + (uint32_t)popc_below(kb);
+        const uint32_t run = runs + (uint32_t)popc_below(hb) + (head ? 1u : 0u) - 1u;
+        if (keep) {
+            pos_of[at] = (pos[q] < n ? pos[q] : 0u) | (end ? kEndBit : 0u);   // a position outside the batch reads row 0
+            run_of[at] = run;
+        }
+        if (keep && head && blockIdx.y == 0 && (int64_t)run < cap) {
+            uniq_rows[run] = (int64_t)key[q];
+            if (applied != nullptr) applied[run] = 0;                // this row's gradient is in row_grads
+        }
+        if (q == 0) cont = k0 > 0 && (hb & 1) == 0;                  // the first piece continues the previous chunk's run
+        runs += (uint32_t)__popcll(hb);
+        listed += (uint32_t)__popcll(kb);
+    }
+    const int cnt = (int)listed;
+    if (cnt == 0) return;
+    static_assert(3 * U <= kWave);
+    pos_of[cnt + lane] = 0u;                                         // batches issued past the end (up to 3 U - 1 lookups) read row 0, unused
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const bool goes_on = k1 < m && keys[k1] == keys[k1 - 1];         // the chunk's last run goes on in the next
+    const int byte = (blockIdx.y * kWave + lane) * VB;
+    const bool lane_on = byte < row_bytes;
+    const unsigned char* my_grad = grad + (lane_on ? byte : 0);
+    const int col = byte / ES;
+    float acc[N];
+    bool fresh = true;
+
+    auto issue = [&](part_t* x, uint32_t* ends, uint32_t& run, int e0) {
+        const uint32_t p = pos_of[e0 + lane % U];
+        run = run_of[e0 + lane % U];
+        *ends = (uint32_t)ballot((p & kEndBit) != 0);
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const uint32_t pj = (uint32_t)__builtin_amdgcn_readlane((int)p, j) & ~kEndBit;
+            x[j] = load_stream(reinterpret_cast<const part_t*>(my_grad + (int64_t)pj * row_bytes));
+        }
+    };
+    auto consume = [&](const part_t* x, uint32_t ends, uint32_t run, int e0) {
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            if (e0 + j < cnt) {
+                float f[N];
+                Bytes<VB>::template load<DT>(x[j], f);
+                if (fresh) {
+#pragma unroll
+                    for (int q = 0; q < N; ++q) acc[q] = f[q];
+                } else {
+#pragma unroll
+                    for (int q = 0; q < N; ++q) acc[q] = acc[q] + f[q];
+                }
+                fresh = false;
+                if ((ends >> j) & 1u) {
+                    const int64_t u = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)run, j);
+                    float* dst = nullptr;
+                    if (cont && !atomic) dst = carry + chunk * D;
+                    else if (u < cap) dst = row_grads + u * D;
+                    if (dst != nullptr && lane_on) {
+                        if (atomic && (cont || (goes_on && e0 + j == cnt - 1))) {
+#pragma unroll
+                            for (int q = 0; q < N; ++q) unsafeAtomicAdd(dst + col + q, acc[q]);
+                        } else {
+                            typedef float out_t __attribute__((ext_vector_type(N)));
+                            out_t o;
+#pragma unroll
+                            for (int q = 0; q < N; ++q) o[q] = acc[q];
+                            store_stream(reinterpret_cast<out_t*>(dst + col), o);
+                        }
+                    }
+                    fresh = true;
+                    cont = false;
+                }
+            }
+        }
+    };
+    part_t xa[U], xb[U];
+    uint32_t ea, eb, ra, rb;
+    issue(xa, &ea, ra, 0);
+#pragma unroll 1
+    for (int e0 = 0; e0 < cnt; e0 += 2 * U) {
+        issue(xb, &eb, rb, e0 + U);
+        consume(xa, ea, ra, e0);
+        issue(xa, &ea, ra, e0 + 2 * U);
+        consume(xb, eb, rb, e0 + U);
+    }
 }
 
 // Moves CNT * 64/LG listed singletons: the rows' loads first, then conversion and stores.  An index
@@ -672,26 +832,6 @@ __global__ __launch_bounds__(kBlock) void bwd_zero_spilled_kernel(
 __global__ void bwd_empty_kernel(int64_t* num_unique) { *num_unique = 0; }
 
 template <int LG>
-static fs_status launch_segreduce(fs_dtype dtype, const void* grad, int units, int D, const uint32_t* keys,
-                                  const uint32_t* vals, int64_t m, int64_t chunks, uint32_t n, const uint32_t* block_base,
-                                  const uint32_t* chunk_local, int64_t* uniq_rows, float* row_grads, int64_t cap,
-                                  float* carry, int atomic, uint8_t* applied, hipStream_t stream)
-{
-    constexpr int GPB = kBlock / LG;
-    const dim3 grid((unsigned)((chunks + GPB - 1) / GPB), (unsigned)((units + LG - 1) / LG));
-    const u32x4* g = static_cast<const u32x4*>(grad);
-#define FS_SEG_LAUNCH(DT, EX)                                                                                      \
-    FS_LAUNCH("bwd_segreduce", (bwd_segreduce_kernel<LG, DT, EX>), grid, dim3(kBlock), stream, g, units, D, keys, vals, \
-              m, chunks, n, block_base, chunk_local, uniq_rows, row_grads, cap, carry, atomic, applied)
-    const bool exact = units == LG;
-    if (dtype == FS_F32) { if (exact) FS_SEG_LAUNCH(FS_F32, true); else FS_SEG_LAUNCH(FS_F32, false); }
-    else if (dtype == FS_F16) { if (exact) FS_SEG_LAUNCH(FS_F16, true); else FS_SEG_LAUNCH(FS_F16, false); }
-    else { if (exact) FS_SEG_LAUNCH(FS_BF16, true); else FS_SEG_LAUNCH(FS_BF16, false); }
-#undef FS_SEG_LAUNCH
-    return FS_OK;
-}
-
-template <int LG>
 static fs_status launch_singletons(fs_dtype dtype, const void* grad, int units, int D, const uint32_t* keys,
                                    const uint32_t* vals, int64_t m, int64_t chunks, uint32_t n, const uint32_t* block_base,
                                    const uint32_t* chunk_local, int64_t* uniq_rows, float* row_grads, int64_t cap,
@@ -709,6 +849,49 @@ static fs_status launch_singletons(fs_dtype dtype, const void* grad, int units, 
     else if (dtype == FS_F16) { if (exact) FS_SINGLE_LAUNCH(FS_F16, (LG >= 16)); else FS_SINGLE_LAUNCH(FS_F16, false); }
     else { if (exact) FS_SINGLE_LAUNCH(FS_BF16, (LG >= 16)); else FS_SINGLE_LAUNCH(FS_BF16, false); }
 #undef FS_SINGLE_LAUNCH
+    return FS_OK;
+}
+
+static fs_status launch_chunk_sums(fs_dtype dtype, const void* grad, int units, int D, const uint32_t* keys,
+                                   const uint32_t* vals, int64_t m, int64_t chunks, uint32_t n, const uint32_t* block_base,
+                                   const uint32_t* chunk_local, int64_t* uniq_rows, float* row_grads, int64_t cap,
+                                   float* carry, int atomic, uint8_t* applied, hipStream_t stream)
+{
+    const int slabs = (units + kSlabPieces - 1) / kSlabPieces;
+    const int pieces = (units + slabs - 1) / slabs;
+    if (chunks * slabs > 0x7FFFFFFF) return FS_ERR_SIZE;
+    const dim3 grid((unsigned)(chunks * slabs));
+    const size_t lds = (size_t)kChunk * pieces * 16;
+    const u32x4* g = static_cast<const u32x4*>(grad);
+#define FS_SUMS_LAUNCH(P, DT)                                                                                      \
+    FS_LAUNCH_SMEM("bwd_chunk_sums", (bwd_chunk_sums_kernel<P, DT>), grid, dim3(kBlock), lds, stream, g, units, D, pieces, \
+                   slabs, keys, vals, m, chunks, n, block_base, chunk_local, uniq_rows, row_grads, cap, carry, atomic, applied)
+#define FS_SUMS(DT)                                                                                                \
+    if (pieces == kSlabPieces) FS_SUMS_LAUNCH(kSlabPieces, DT);                                                    \
+    else FS_SUMS_LAUNCH(0, DT)
+    if (dtype == FS_F32) { FS_SUMS(FS_F32); }
+    else if (dtype == FS_F16) { FS_SUMS(FS_F16); }
+    else { FS_SUMS(FS_BF16); }
+#undef FS_SUMS
+#undef FS_SUMS_LAUNCH
+    return FS_OK;
+}
+
+template <int VB>
+static fs_status launch_segreduce(fs_dtype dtype, const void* grad, int units, int D, const uint32_t* keys,
+                             const uint32_t* vals, int64_t m, int64_t chunks, uint32_t n, const uint32_t* block_base,
+                             const uint32_t* chunk_local, int64_t* uniq_rows, float* row_grads, int64_t cap,
+                             float* carry, int atomic, uint8_t* applied, hipStream_t stream)
+{
+    const dim3 grid((unsigned)((chunks + kWavesPerBlock - 1) / kWavesPerBlock), (unsigned)((units * 16 + kWave * VB - 1) / (kWave * VB)));
+    const unsigned char* g = static_cast<const unsigned char*>(grad);
+#define FS_SEG_LAUNCH(DT)                                                                                         \
+    FS_LAUNCH("bwd_segreduce", (bwd_segreduce_kernel<VB, DT>), grid, dim3(kBlock), stream, g, units * 16, D, keys, vals, m,    \
+              chunks, n, block_base, chunk_local, uniq_rows, row_grads, cap, carry, atomic, applied)
+    if (dtype == FS_F32) FS_SEG_LAUNCH(FS_F32);
+    else if (dtype == FS_F16) FS_SEG_LAUNCH(FS_F16);
+    else FS_SEG_LAUNCH(FS_BF16);
+#undef FS_SEG_LAUNCH
     return FS_OK;
 }
 
@@ -774,13 +957,16 @@ static fs_status bwd_after_sort(const void* grad_out, int64_t n, int D, fs_dtype
         FS_LAUNCH("bwd_zero_spilled", bwd_zero_spilled_kernel, dim3(wave_grid), dim3(kBlock), s,
                   keys, m, chunks, w.block_base, w.chunk_local, row_grads, D, cap_unique);
     fs_status rc;
-#define FS_SEG(LG)                                                                                              \
-    rc = launch_segreduce<LG>(dtype, grad_out, units, D, keys, vals, m, chunks, (uint32_t)n, w.block_base,        \
-                              w.chunk_local, uniq_rows, row_grads, cap_unique, w.carry, variant, applied, s)
-    if (units <= 16) FS_SEG(16);            // rows under 256 bytes leave lanes of the group idle
-    else if (units <= 32) FS_SEG(32);
-    else FS_SEG(64);
-#undef FS_SEG
+    const bool few = chunks <= kSumsMaxChunks;
+    if (few)
+        rc = launch_chunk_sums(dtype, grad_out, units, D, keys, vals, m, chunks, (uint32_t)n, w.block_base, w.chunk_local,
+                               uniq_rows, row_grads, cap_unique, w.carry, variant, applied, s);
+    else if (units <= 16)
+        rc = launch_segreduce<4>(dtype, grad_out, units, D, keys, vals, m, chunks, (uint32_t)n, w.block_base, w.chunk_local,
+                            uniq_rows, row_grads, cap_unique, w.carry, variant, applied, s);
+    else
+        rc = launch_segreduce<8>(dtype, grad_out, units, D, keys, vals, m, chunks, (uint32_t)n, w.block_base, w.chunk_local,
+                            uniq_rows, row_grads, cap_unique, w.carry, variant, applied, s);
     if (rc != FS_OK) return rc;
     if (update != nullptr) {                     // rows looked up once are updated in place, the others flagged for the step below
 #define FS_SINGLE_UPDATE(LG)                                                                                    \
@@ -802,18 +988,20 @@ static fs_status bwd_after_sort(const void* grad_out, int64_t n, int D, fs_dtype
         rest.skip = applied;
         return sparse_update_launch(rest, dtype, optimizer, s);
     }
+    if (!few) {
 #define FS_SINGLE(LG)                                                                                           \
     rc = launch_singletons<LG>(dtype, grad_out, units, D, keys, vals, m, chunks, (uint32_t)n, w.block_base,       \
                                w.chunk_local, uniq_rows, row_grads, cap_unique, s)
-    if (units <= 1) FS_SINGLE(1);
-    else if (units <= 2) FS_SINGLE(2);
-    else if (units <= 4) FS_SINGLE(4);
-    else if (units <= 8) FS_SINGLE(8);
-    else if (units <= 16) FS_SINGLE(16);
-    else if (units <= 32) FS_SINGLE(32);
-    else FS_SINGLE(64);
+        if (units <= 1) FS_SINGLE(1);
+        else if (units <= 2) FS_SINGLE(2);
+        else if (units <= 4) FS_SINGLE(4);
+        else if (units <= 8) FS_SINGLE(8);
+        else if (units <= 16) FS_SINGLE(16);
+        else if (units <= 32) FS_SINGLE(32);
+        else FS_SINGLE(64);
 #undef FS_SINGLE
-    if (rc != FS_OK) return rc;
+        if (rc != FS_OK) return rc;
+    }
     if (variant == 0)
         FS_LAUNCH("bwd_fold", bwd_fold_kernel, dim3(wave_grid), dim3(kBlock), s,
                   keys, m, chunks, w.block_base, w.chunk_local, row_grads, D, cap_unique, w.carry);

@@ -1,0 +1,111 @@
+"""The backward where its segmented sum changes shape, bit for bit against the oracle: up to 1024 chunks of 256
+lookups are summed a block at a time out of LDS in slabs of up to 16 row pieces, more are walked by a wave each with
+4 bytes to a lane (rows of up to 256 bytes) or 8."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from test_gpu_bwd import _check, _np_grad
+
+pytestmark = pytest.mark.gpu
+
+CHUNK = 256
+
+
+@pytest.fixture(scope="module")
+def G():
+    import gpu_common
+    assert torch.cuda.is_available()
+    return gpu_common
+
+
+def lookups(rng, n, R):
+    """Sorted-friendly rows: a head that spans chunks, a stretch of pairs, a cold tail; positions a permutation."""
+    head = np.minimum(rng.pareto(0.9, n // 2).astype(np.int64), R - 1)
+    rows_i = rng.permutation(np.concatenate([head, rng.integers(0, R, n - n // 2)]))
+    order = np.argsort(rows_i % 3, kind="stable")
+    return rows_i[order], order.astype(np.int32)
+
+
+def check_atomic(G, grad_np, grad_t, rows, pos, R, dt):
+    """Variant 1 where a gradient row is looked up many times over.  The terms of a row are then not independent, and
+    the 2-norm that the other tests take does not bound an fp32 sum of them in another order; what does is
+    k u sum |term|, k the additions that one result passes through: up to 256 in its chunk, one per chunk of its run."""
+    m = len(rows)
+    _, _, ou, _, og64, _ = oracle.seq_grad_bwd(grad_np, rows, pos, 0, m, R, dtype=G.oracle_dtype(dt))
+    rc, st, u, g, _ = G.hip_bwd(grad_t.to(G.DEV), G.to_dev(rows, torch.int64), G.to_dev(pos), 0, m, R, 1)
+    assert (rc, st) == (0, 0) and np.array_equal(u.cpu().numpy(), ou)
+    inv = torch.from_numpy(np.searchsorted(ou, rows))
+    total = torch.zeros(len(ou), grad_t.shape[1], dtype=torch.float64)
+    total.index_add_(0, inv, grad_t.double().abs()[torch.from_numpy(pos).long()])
+    k = CHUNK + np.ceil(np.bincount(inv.numpy(), minlength=len(ou)) / CHUNK) + 1
+    assert np.all(np.abs(g.double().cpu().numpy() - og64) <= k[:, None] * 2.0 ** -24 * total.numpy())
+
+
+@pytest.mark.parametrize("dt,D", [("f16", 8), ("f32", 20), ("bf16", 128), ("f16", 136), ("f32", 100), ("bf16", 520)])
+@pytest.mark.parametrize("m", [1, CHUNK - 1, CHUNK, CHUNK + 1, 5 * CHUNK + 3])
+def test_few_chunks(G, dt, D, m):
+    rng = np.random.default_rng(D + m)
+    R = 700
+    rows, pos = lookups(rng, m, R)
+    gnp, gt = _np_grad(rng.standard_normal((m, D)).astype(np.float32), dt)
+    _check(G, gnp, gt, rows, pos, 0, m, R, dt)
+
+
+@pytest.mark.parametrize("dt,D", [("f32", 4), ("bf16", 72), ("f16", 128), ("f32", 68), ("f16", 264)])
+@pytest.mark.parametrize("m", [1024 * CHUNK, 1024 * CHUNK + 1])
+def test_around_the_rule(G, dt, D, m):
+    rng = np.random.default_rng(D + m)
+    R, n = 90_000, 3_000                             # few gradient rows, each used by many lookups
+    rows, order = lookups(rng, m, R)
+    pos = (np.arange(m) // (m // n + 1)).astype(np.int32)          # ascending
+    gnp, gt = _np_grad(rng.standard_normal((n, D)).astype(np.float32), dt)
+    _check(G, gnp, gt, rows, pos, 0, m, R, dt, atomic_too=False)
+    check_atomic(G, gnp, gt, rows, pos, R, dt)
+
+
+@pytest.mark.parametrize("R", [1, 2, 3])
+@pytest.mark.parametrize("m", [1025 * CHUNK, 1025 * CHUNK + 77])
+def test_walks_of_whole_chunks(G, R, m):
+    """Every chunk one run that goes on into the next, the last chunk whole or ragged."""
+    rng = np.random.default_rng(m + R)
+    rows = np.sort(rng.integers(0, R, m))
+    pos = (np.arange(m) % 911).astype(np.int32)
+    pos = pos[np.lexsort((pos, rows))]
+    gnp, gt = _np_grad(rng.standard_normal((911, 24)).astype(np.float32), "f16")
+    _check(G, gnp, gt, rows, pos, 0, m, R, "f16", atomic_too=False)
+    check_atomic(G, gnp, gt, rows, pos, R, "f16")
+
+
+@pytest.mark.parametrize("dt,D", [("bf16", 72), ("f32", 132)])
+def test_update_leaves_the_walk_only_repeated_rows(G, dt, D):
+    """The backward with the optimizer step over more than 1024 chunks, against the two calls it stands for."""
+    import paper_2301_02959_amd as fs
+    rng = np.random.default_rng(D)
+    R, n, m = 400_000, 2_000, 1024 * CHUNK + 300
+    rows, _ = lookups(rng, m, R)
+    pos = (np.arange(m) // (m // n + 1)).astype(np.int32)
+    tdt = {"bf16": torch.bfloat16, "f32": torch.float32}[dt]
+    grad = torch.randn(n, D, generator=torch.Generator().manual_seed(1)).to(tdt).to(G.DEV)
+    table = torch.randn(R, D, generator=torch.Generator().manual_seed(2)).to(tdt).to(G.DEV)
+    srows, spos = (torch.zeros(m, dtype=torch.int32, device=G.DEV) for _ in range(2))
+    st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    fs.fs_sort_lookups(G.to_dev(rows, torch.int64), G.to_dev(pos), 0, m, R, n, srows, spos, st)
+    got = []
+    for fused in (True, False):
+        w, state = table.clone(), torch.zeros(R, device=G.DEV)
+        uniq = torch.zeros(m, dtype=torch.int64, device=G.DEV)
+        rg = torch.zeros(m, D, device=G.DEV)
+        nu = torch.zeros(1, dtype=torch.int64, device=G.DEV)
+        if fused:
+            fs.fs_seq_grad_bwd_update(grad, srows, spos, m, R, w, fs.FS_OPT_ADAGRAD_ROWWISE, 0.05, 1e-6, state, None, None, 0,
+                                      uniq, rg, m, nu, st)
+        else:
+            fs.fs_seq_grad_bwd_sorted(grad, srows, spos, m, R, 0, uniq, rg, m, nu, st)
+            fs.fs_sparse_update(w, uniq, rg, m, nu, fs.FS_OPT_ADAGRAD_ROWWISE, 0.05, 1e-6, state, dev_status=st)
+        torch.cuda.synchronize()
+        got.append((w, state, uniq[:int(nu.item())]))
+    assert int(st.item()) == 0 and len(got[0][2]) == len(np.unique(rows))
+    for a, b in zip(*got):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
