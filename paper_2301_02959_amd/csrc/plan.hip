@@ -265,9 +265,10 @@ static int64_t hist_span(int64_t n)
 template <bool VEC>
 __global__ __launch_bounds__(kBlock) void plan_mark_kernel(
     const uint32_t* __restrict__ counts, int64_t R, int allow_zero, uint32_t* __restrict__ tile_count,
-    uint32_t* __restrict__ stage_keys, uint32_t* __restrict__ stage_vals)
+    uint32_t* __restrict__ tile_bits, uint32_t* __restrict__ stage_keys, uint32_t* __restrict__ stage_vals)
 {
     __shared__ uint32_t wave_sum[kWavesPerBlock];
+    __shared__ uint32_t wave_bits[kWavesPerBlock];
     constexpr int kItems = kSelTile / kBlock;
     constexpr int kSpan = kWave * kItems;                 // consecutive rows per wave
     constexpr int kStep = VEC ? 4 : 1;                    // consecutive rows per lane and load
@@ -323,14 +324,20 @@ __global__ __launch_bounds__(kBlock) void plan_mark_kernel(
         for (int e = 0; e < kStep; ++e) before[it0 + e] += total + lower;
         total += all;
     }
-    if (lane == 0) wave_sum[w] = total;
+    uint32_t bits = 0;                                    // the counts or-ed together: how many bits the sort has to look at
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) bits |= cnt[it];
+    for (int o = 32; o > 0; o >>= 1) bits |= __shfl_xor(bits, o);
+    if (lane == 0) { wave_sum[w] = total; wave_bits[w] = bits; }
     __syncthreads();
     uint32_t off = 0, all = 0;
+    bits = 0;
     for (int k = 0; k < kWavesPerBlock; ++k) {
         if (k < w) off += wave_sum[k];
         all += wave_sum[k];
+        bits |= wave_bits[k];
     }
-    if (threadIdx.x == 0) tile_count[blockIdx.x] = all;
+    if (threadIdx.x == 0) { tile_count[blockIdx.x] = all; tile_bits[blockIdx.x] = bits; }
 #pragma unroll
     for (int it = 0; it < kItems; ++it) {
         if (cand[it]) {
@@ -342,22 +349,36 @@ __global__ __launch_bounds__(kBlock) void plan_mark_kernel(
 }
 
 static fs_status launch_mark(const uint32_t* counts, int64_t R, int allow_zero, int64_t sel_tiles, uint32_t* tile_count,
-                             uint32_t* stage_keys, uint32_t* stage_vals, hipStream_t s)
+                             uint32_t* tile_bits, uint32_t* stage_keys, uint32_t* stage_vals, hipStream_t s)
 {
     if ((reinterpret_cast<uintptr_t>(counts) & 15) == 0)
         FS_LAUNCH("plan_mark", plan_mark_kernel<true>, dim3((unsigned)sel_tiles), dim3(kBlock), s,
-                  counts, R, allow_zero, tile_count, stage_keys, stage_vals);
+                  counts, R, allow_zero, tile_count, tile_bits, stage_keys, stage_vals);
     else
         FS_LAUNCH("plan_mark", plan_mark_kernel<false>, dim3((unsigned)sel_tiles), dim3(kBlock), s,
-                  counts, R, allow_zero, tile_count, stage_keys, stage_vals);
+                  counts, R, allow_zero, tile_count, tile_bits, stage_keys, stage_vals);
     return FS_OK;
 }
 
 constexpr int kScanBlock = 1024;
 
-__global__ __launch_bounds__(kScanBlock) void plan_scan_kernel(uint32_t* __restrict__ tile_count, int64_t tiles,
-                                                               int64_t* __restrict__ num_candidates)
+// `v` or-ed over the threads of the block, in every thread.  `waves` is LDS scratch of 16 words.
+__device__ __forceinline__ uint32_t block_or(uint32_t v, uint32_t* waves)
 {
+    for (int off = 32; off > 0; off >>= 1) v |= __shfl_xor(v, off);
+    if (lane_id() == 0) waves[wave_id()] = v;
+    __syncthreads();
+    v = 0;
+    for (int k = 0; k < (int)(blockDim.x >> 6); ++k) v |= waves[k];
+    return v;
+}
+
+__global__ __launch_bounds__(kScanBlock) void plan_scan_kernel(uint32_t* __restrict__ tile_count, int64_t tiles,
+                                                               const uint32_t* __restrict__ tile_bits,
+                                                               int64_t* __restrict__ num_candidates,
+                                                               uint32_t* __restrict__ count_bits)
+{
+    __shared__ uint32_t wave_bits[16];
     __shared__ uint32_t wave_sums[16];
     const int64_t per = (tiles + kScanBlock - 1) / kScanBlock;
     if (per <= 16) {
@@ -366,14 +387,16 @@ __global__ __launch_bounds__(kScanBlock) void plan_scan_kernel(uint32_t* __restr
         // runs the strided accesses cost more than the scans they save)
         const int64_t lo = (int64_t)threadIdx.x * per < tiles ? (int64_t)threadIdx.x * per : tiles;
         const int64_t hi = lo + per < tiles ? lo + per : tiles;
-        uint32_t sum = 0;
-        for (int64_t k = lo; k < hi; ++k) sum += tile_count[k];
+        uint32_t sum = 0, bits = 0;
+        for (int64_t k = lo; k < hi; ++k) { sum += tile_count[k]; bits |= tile_bits[k]; }
         uint32_t total;
         uint32_t run = block_exclusive_scan(sum, wave_sums, &total);
         for (int64_t k = lo; k < hi; ++k) { const uint32_t v = tile_count[k]; tile_count[k] = run; run += v; }
-        if (threadIdx.x == 0) *num_candidates = (int64_t)total;
+        bits = block_or(bits, wave_bits);
+        if (threadIdx.x == 0) { *num_candidates = (int64_t)total; *count_bits = bits; }
         return;
     }
+    uint32_t bits = 0;
     uint32_t carry = 0;                                          // coalesced rounds of 1024 tiles, 8 rounds of loads in flight
     for (int64_t base = 0; base < tiles; base += 8 * kScanBlock) {
         uint32_t v[8];
@@ -381,6 +404,7 @@ __global__ __launch_bounds__(kScanBlock) void plan_scan_kernel(uint32_t* __restr
         for (int q = 0; q < 8; ++q) {
             const int64_t k = base + (int64_t)q * kScanBlock + threadIdx.x;
             v[q] = k < tiles ? tile_count[k] : 0u;
+            bits |= k < tiles ? tile_bits[k] : 0u;
         }
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
@@ -391,29 +415,106 @@ __global__ __launch_bounds__(kScanBlock) void plan_scan_kernel(uint32_t* __restr
             carry += total;
         }
     }
-    if (threadIdx.x == 0) *num_candidates = (int64_t)carry;
+    bits = block_or(bits, wave_bits);
+    if (threadIdx.x == 0) { *num_candidates = (int64_t)carry; *count_bits = bits; }
 }
 
 // Moves each tile's packed candidates to their final place (tile_base = scanned tile counts).
+// SUM: few tiles, plan_scan has not run: tile_base holds plain counts, every block sums those before its own, and the
+// first one writes the number of candidates and the bits of their counts.
+template <bool SUM>
 __global__ __launch_bounds__(kBlock) void plan_move_kernel(
-    const uint32_t* __restrict__ tile_base, int64_t tiles, const int64_t* __restrict__ num_candidates,
+    const uint32_t* __restrict__ tile_base, int64_t tiles, const uint32_t* __restrict__ tile_bits,
+    int64_t* __restrict__ num_candidates, uint32_t* __restrict__ count_bits,
     const uint32_t* __restrict__ stage_keys, const uint32_t* __restrict__ stage_vals,
     uint32_t* __restrict__ keys, uint32_t* __restrict__ vals)
 {
     const int64_t tile = blockIdx.x;
-    const uint32_t first = tile_base[tile];
-    const uint32_t next = tile + 1 < tiles ? tile_base[tile + 1] : (uint32_t)*num_candidates;
     const int64_t from = tile * kSelTile;
+    uint32_t first, next;
+    if constexpr (SUM) {
+        __shared__ uint32_t wave_sums[16];
+        __shared__ uint32_t wave_bits[16];
+        uint32_t before = 0, bits = 0;
+        const int64_t last = tile == 0 ? tiles : tile;           // the first block adds up all of them
+        for (int64_t k = threadIdx.x; k < last; k += kBlock) {
+            before += tile_base[k];
+            if (tile == 0) bits |= tile_bits[k];
+        }
+        uint32_t sum;
+        block_exclusive_scan(before, wave_sums, &sum);
+        first = tile == 0 ? 0u : sum;
+        next = first + tile_base[tile];
+        if (tile == 0) {                                         // block-uniform
+            bits = block_or(bits, wave_bits);
+            if (threadIdx.x == 0) { *num_candidates = (int64_t)sum; *count_bits = bits; }
+        }
+    } else {
+        first = tile_base[tile];
+        next = tile + 1 < tiles ? tile_base[tile + 1] : (uint32_t)*num_candidates;
+    }
     for (uint32_t i = threadIdx.x; i < next - first; i += kBlock) {
         keys[first + i] = stage_keys[from + i];
         vals[first + i] = stage_vals[from + i];
     }
 }
 
+// Compaction and sort of the candidates, shared by the two planners: rows in (count desc, row asc) order, in vals_a
+// or vals_b as sort_result_in_b(*count_bits) says, with their keys ~count beside them.
+// Up to 1024 tiles (8 M rows) the moving blocks sum the tile counts themselves, at most four loads to a thread, and
+// the scan is no launch of its own; beyond, what each of the blocks would read again is more than the scan costs.
+constexpr int64_t kMoveSumTiles = 1024;
+
+struct PlanScratch {
+    int64_t* num_cand;
+    uint32_t* count_bits;
+    uint32_t* tile_count;
+    uint32_t* tile_bits;
+    uint32_t* keys_a;
+    uint32_t* vals_a;
+    uint32_t* keys_b;
+    uint32_t* vals_b;
+    char* sort_scratch;
+};
+
+static PlanScratch take_plan_scratch(Carver& ws, int64_t R)
+{
+    PlanScratch p;
+    const size_t tiles = (size_t)((R + kSelTile - 1) / kSelTile);
+    p.num_cand = ws.take<int64_t>(1);
+    p.count_bits = ws.take<uint32_t>(1);
+    p.tile_count = ws.take<uint32_t>(tiles);
+    p.tile_bits = ws.take<uint32_t>(tiles);
+    p.keys_a = ws.take<uint32_t>((size_t)R);
+    p.vals_a = ws.take<uint32_t>((size_t)R);
+    p.keys_b = ws.take<uint32_t>((size_t)R);
+    p.vals_b = ws.take<uint32_t>((size_t)R);
+    p.sort_scratch = ws.take<char>(R > 0 ? radix_sort_scratch_bytes(R) : 0);
+    return p;
+}
+
+static fs_status sort_candidates(const uint32_t* counts, int64_t R, int allow_zero, const PlanScratch& p, hipStream_t s)
+{
+    const int64_t tiles = (R + kSelTile - 1) / kSelTile;
+    if (fs_status rc = launch_mark(counts, R, allow_zero, tiles, p.tile_count, p.tile_bits, p.keys_b, p.vals_b, s); rc != FS_OK) return rc;
+    if (tiles <= kMoveSumTiles) {
+        FS_LAUNCH("plan_move", plan_move_kernel<true>, dim3((unsigned)tiles), dim3(kBlock), s, p.tile_count, tiles,
+                  p.tile_bits, p.num_cand, p.count_bits, p.keys_b, p.vals_b, p.keys_a, p.vals_a);
+    } else {
+        FS_LAUNCH("plan_scan", plan_scan_kernel, dim3(1), dim3(kScanBlock), s, p.tile_count, tiles, p.tile_bits, p.num_cand, p.count_bits);
+        FS_LAUNCH("plan_move", plan_move_kernel<false>, dim3((unsigned)tiles), dim3(kBlock), s, p.tile_count, tiles,
+                  p.tile_bits, p.num_cand, p.count_bits, p.keys_b, p.vals_b, p.keys_a, p.vals_a);
+    }
+    uint32_t *keys = nullptr, *vals = nullptr;                   // where the last pass would leave them
+    return radix_sort_pairs(p.keys_a, p.vals_a, p.keys_b, p.vals_b, R, p.num_cand, 32, p.sort_scratch, s, &keys, &vals,
+                            SortSource(), p.count_bits);
+}
+
 __global__ __launch_bounds__(kBlock) void plan_emit_kernel(
-    const uint32_t* __restrict__ vals, const int64_t* __restrict__ num_candidates, int64_t cap,
+    const uint32_t* __restrict__ vals_a, const uint32_t* __restrict__ vals_b, const uint32_t* __restrict__ count_bits, const int64_t* __restrict__ num_candidates, int64_t cap,
     int64_t* __restrict__ sel_rows, int64_t* __restrict__ num_selected, uint32_t* __restrict__ placement)
 {
+    const uint32_t* vals = sort_result_in_b(*count_bits) ? vals_b : vals_a;
     const int64_t nc = *num_candidates;
     const int64_t k = cap < nc ? cap : nc;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -466,8 +567,10 @@ struct TierConsts {
 };
 
 __global__ __launch_bounds__(kBlock) void tiers_tile_sums_kernel(
-    const uint32_t* __restrict__ keys, const int64_t* __restrict__ num_candidates, uint64_t* __restrict__ tile_sum)
+    const uint32_t* __restrict__ keys_a, const uint32_t* __restrict__ keys_b, const uint32_t* __restrict__ count_bits,
+    const int64_t* __restrict__ num_candidates, uint64_t* __restrict__ tile_sum)
 {
+    const uint32_t* keys = sort_result_in_b(*count_bits) ? keys_b : keys_a;
     __shared__ uint64_t part[kWavesPerBlock];
     const int64_t K = *num_candidates;
     const int64_t base = (int64_t)blockIdx.x * kSumTile;
@@ -555,9 +658,11 @@ __device__ __forceinline__ i128 cum_memory(const TierConsts& c, int64_t k, uint6
 }
 
 __global__ __launch_bounds__(kWave) void tiers_cuts_kernel(
-    const uint32_t* __restrict__ keys, const int64_t* __restrict__ num_candidates,
+    const uint32_t* __restrict__ keys_a, const uint32_t* __restrict__ keys_b, const uint32_t* __restrict__ count_bits,
+    const int64_t* __restrict__ num_candidates,
     const uint64_t* __restrict__ tile_sum, const TierConsts c, int64_t* __restrict__ cuts)
 {
+    const uint32_t* keys = sort_result_in_b(*count_bits) ? keys_b : keys_a;
     const int lane = lane_id();
     const int64_t K = *num_candidates;
     const int64_t tiles = (K + kSumTile - 1) / kSumTile;
@@ -637,9 +742,11 @@ __global__ __launch_bounds__(kWave) void tiers_cuts_kernel(
 }
 
 __global__ __launch_bounds__(kBlock) void tiers_emit_kernel(
-    const uint32_t* __restrict__ vals, const int64_t* __restrict__ cuts, int64_t cap, int W,
+    const uint32_t* __restrict__ vals_a, const uint32_t* __restrict__ vals_b, const uint32_t* __restrict__ count_bits,
+    const int64_t* __restrict__ cuts, int64_t cap, int W,
     int64_t* __restrict__ sorted_rows, uint32_t* __restrict__ placement)
 {
+    const uint32_t* vals = sort_result_in_b(*count_bits) ? vals_b : vals_a;
     const int64_t n_dp = cuts[5];
     const int64_t n_both = n_dp + cuts[6];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -674,17 +781,9 @@ extern "C" fs_status fs_plan_replication(
     if (acc && (n < 0 || n >= (1LL << 31) || T < 1 || B < 1 || (int64_t)T * B >= (1LL << 31))) return FS_ERR_SIZE;
     if (sel && (budget_bytes < 0 || bytes_per_row < 1)) return FS_ERR_SIZE;
 
-    const int64_t sel_tiles = sel ? (R + kSelTile - 1) / kSelTile : 0;
-    const int64_t m_max = sel ? R : 0;
     Carver ws(workspace);
     int32_t* ok_flag = ws.take<int32_t>(1);
-    int64_t* num_cand = ws.take<int64_t>(1);
-    uint32_t* tile_count = ws.take<uint32_t>((size_t)sel_tiles);
-    uint32_t* keys_a = ws.take<uint32_t>((size_t)m_max);
-    uint32_t* vals_a = ws.take<uint32_t>((size_t)m_max);
-    uint32_t* keys_b = ws.take<uint32_t>((size_t)m_max);
-    uint32_t* vals_b = ws.take<uint32_t>((size_t)m_max);
-    char* sort_scratch = ws.take<char>(sel ? radix_sort_scratch_bytes(m_max) : 0);
+    const PlanScratch p = take_plan_scratch(ws, sel ? R : 0);
     if (!workspace) { *workspace_bytes = ws.used; return FS_OK; }
     if (*workspace_bytes < ws.used || (reinterpret_cast<uintptr_t>(workspace) & 255)) return FS_ERR_WORKSPACE;
     if (!counts) return FS_ERR_NULL;
@@ -716,17 +815,9 @@ extern "C" fs_status fs_plan_replication(
     }
     if (sel) {
         const int allow_zero = (flags & FS_PLAN_ALLOW_ZERO) ? 1 : 0;
-        if (fs_status rc = launch_mark(counts, R, allow_zero, sel_tiles, tile_count, keys_b, vals_b, s); rc != FS_OK) return rc;
-        FS_LAUNCH("plan_scan", plan_scan_kernel, dim3(1), dim3(kScanBlock), s, tile_count, sel_tiles, num_cand);
-        FS_LAUNCH("plan_move", plan_move_kernel, dim3((unsigned)sel_tiles), dim3(kBlock), s,
-                  tile_count, sel_tiles, num_cand, keys_b, vals_b, keys_a, vals_a);
-        uint32_t* keys = nullptr;
-        uint32_t* vals = nullptr;
-        fs_status rc = radix_sort_pairs(keys_a, vals_a, keys_b, vals_b, m_max, num_cand, 32, sort_scratch, s,
-                                        &keys, &vals);
-        if (rc != FS_OK) return rc;
+        if (fs_status rc = sort_candidates(counts, R, allow_zero, p, s); rc != FS_OK) return rc;
         FS_LAUNCH("plan_emit", plan_emit_kernel, dim3(1024), dim3(kBlock), s,
-                  vals, num_cand, cap, sel_rows, num_selected, (flags & FS_PLAN_TAG) ? placement : nullptr);
+                  p.vals_a, p.vals_b, p.count_bits, p.num_cand, cap, sel_rows, num_selected, (flags & FS_PLAN_TAG) ? placement : nullptr);
     }
     return FS_OK;
 }
@@ -750,17 +841,10 @@ extern "C" fs_status fs_plan_tiers(
         p.ar_global < 1 || p.ar_global >= bw_max || p.ar_cross < 1 || p.ar_cross >= bw_max)
         return FS_ERR_CONFIG;
 
-    const int64_t sel_tiles = (R + kSelTile - 1) / kSelTile;
     const int64_t sum_tiles = (R + kSumTile - 1) / kSumTile;
     Carver ws(workspace);
-    int64_t* num_cand = ws.take<int64_t>(1);
-    uint32_t* tile_count = ws.take<uint32_t>((size_t)sel_tiles);
     uint64_t* tile_sum = ws.take<uint64_t>((size_t)sum_tiles + 1);
-    uint32_t* keys_a = ws.take<uint32_t>((size_t)R);
-    uint32_t* vals_a = ws.take<uint32_t>((size_t)R);
-    uint32_t* keys_b = ws.take<uint32_t>((size_t)R);
-    uint32_t* vals_b = ws.take<uint32_t>((size_t)R);
-    char* sort_scratch = ws.take<char>(radix_sort_scratch_bytes(R));
+    const PlanScratch q = take_plan_scratch(ws, R);
     if (!workspace) { *workspace_bytes = ws.used; return FS_OK; }
     if (*workspace_bytes < ws.used || (reinterpret_cast<uintptr_t>(workspace) & 255)) return FS_ERR_WORKSPACE;
     if (!counts || !cuts) return FS_ERR_NULL;
@@ -789,19 +873,13 @@ extern "C" fs_status fs_plan_tiers(
                   : (uint64_t)1 << 62;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (fs_status rc = launch_mark(counts, R, 0, sel_tiles, tile_count, keys_b, vals_b, s); rc != FS_OK) return rc;
-    FS_LAUNCH("plan_scan", plan_scan_kernel, dim3(1), dim3(kScanBlock), s, tile_count, sel_tiles, num_cand);
-    FS_LAUNCH("plan_move", plan_move_kernel, dim3((unsigned)sel_tiles), dim3(kBlock), s,
-              tile_count, sel_tiles, num_cand, keys_b, vals_b, keys_a, vals_a);
-    uint32_t* keys = nullptr;
-    uint32_t* vals = nullptr;
-    fs_status rc = radix_sort_pairs(keys_a, vals_a, keys_b, vals_b, R, num_cand, 32, sort_scratch, s, &keys, &vals);
-    if (rc != FS_OK) return rc;
+    if (fs_status rc = sort_candidates(counts, R, 0, q, s); rc != FS_OK) return rc;
     FS_LAUNCH("tiers_tile_sums", tiers_tile_sums_kernel, dim3((unsigned)sum_tiles), dim3(kBlock), s,
-              keys, num_cand, tile_sum);
+              q.keys_a, q.keys_b, q.count_bits, q.num_cand, tile_sum);
     FS_LAUNCH("tiers_scan_sums", tiers_scan_sums_kernel, dim3(1), dim3(kScanBlock), s, tile_sum, sum_tiles);
-    FS_LAUNCH("tiers_cuts", tiers_cuts_kernel, dim3(1), dim3(kWave), s, keys, num_cand, tile_sum, c, cuts);
-    FS_LAUNCH("tiers_emit", tiers_emit_kernel, dim3(1024), dim3(kBlock), s, vals, cuts, cap, (int)p.W,
+    FS_LAUNCH("tiers_cuts", tiers_cuts_kernel, dim3(1), dim3(kWave), s, q.keys_a, q.keys_b, q.count_bits, q.num_cand,
+              tile_sum, c, cuts);
+    FS_LAUNCH("tiers_emit", tiers_emit_kernel, dim3(1024), dim3(kBlock), s, q.vals_a, q.vals_b, q.count_bits, cuts, cap, (int)p.W,
               sorted_rows, placement);
     return FS_OK;
 }

@@ -39,9 +39,21 @@ size_t radix_sort_scratch_bytes(int64_t m_max);
 // `src`; (keys_b, vals_b) is the other buffer.  The number of pairs is *m_dev if m_dev != nullptr
 // (device memory, read by the kernels; must be <= m_max) else m_max.  On return *keys_out /
 // *vals_out name the buffer that holds the result.
+//   varying (or null): a device word with every bit set in which two keys differ.  Passes above its highest set bit
+//   copy nothing and return at once; the result is then where the last pass that ran left it, which only the device
+//   knows: sort_result_in_b below, for pairs that came in A (and not in `src`).
 fs_status radix_sort_pairs(uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b, uint32_t* vals_b,
                            int64_t m_max, const int64_t* m_dev, int key_bits, void* scratch,
                            hipStream_t stream, uint32_t** keys_out, uint32_t** vals_out,
-                           const SortSource& src = SortSource());
+                           const SortSource& src = SortSource(), const uint32_t* varying = nullptr);
+
+#ifdef __HIPCC__
+// Whether a sort by 32 bits with `varying` left its result in the B buffers.
+__device__ __forceinline__ bool sort_result_in_b(uint32_t varying)
+{
+    const int bits = varying == 0 ? 1 : 32 - __builtin_clz(varying);
+    return ((bits + kSortMaxDigitBits - 1) / kSortMaxDigitBits) & 1;
+}
+#endif
 
 }  // namespace fs

@@ -1,6 +1,7 @@
 // Stable LSD radix sort of (key, value) pairs, up to 10 bits per pass (27-bit row ids: 3 passes).
 //
-// Per pass, four launches over 4096-pair tiles (blocks walk the tiles with a grid stride):
+// Per pass, three or four launches over 4096-pair tiles (blocks walk the tiles with a grid stride; sorts of few pairs
+// take smaller tiles and two launches, see sort_shape):
 //   sort_count    per-tile digit histogram (one LDS add per distinct digit per wave, found by
 //                 ballot matching), stored tile-major
 //   sort_scan     exclusive scan of every digit's per-tile counts over the tiles (two levels,
@@ -17,7 +18,6 @@
 
 namespace fs {
 
-constexpr int kSortWaveSpan = kWave * kSortItems;
 constexpr int kSortMaxBins = 1 << kSortMaxDigitBits;
 constexpr int kSortStripe = 16;              // tiles per XCD stripe in the scatter
 constexpr int64_t kSortMaxGrid = 8192;       // 32 blocks per CU: fills the chip, cheap when most are idle
@@ -62,6 +62,14 @@ struct RowPosReader {                         // pairs are (rows[i], pos[i]), va
     }
 };
 
+// A pass whose digit is the same in all keys would copy the pairs: every kernel of it returns at once.  `varying`
+// (or null) has, at least, every bit set in which two keys differ.  The first pass always runs (it moves the pairs
+// out of their source).
+__device__ __forceinline__ bool sort_pass_idle(const uint32_t* varying, int shift)
+{
+    return varying != nullptr && shift > 0 && (*varying >> shift) == 0;
+}
+
 // One LDS add per distinct digit per wave: the lanes that hold the same digit are found with one
 // ballot per bit (plain per-lane LDS adds serialise on the popular rows' digits and were slower).
 template <int NBITS>
@@ -71,29 +79,31 @@ __device__ __forceinline__ void count_digit(uint32_t* hist, uint32_t digit, bool
     if (valid && popc_below(same) == 0) atomicAdd(&hist[digit], (uint32_t)__popcll(same));
 }
 
-template <typename Reader, int NBITS>
+template <typename Reader, int NBITS, int ITEMS>
 __global__ __launch_bounds__(kBlock) void sort_count_kernel(
-    Reader in, int64_t m_max, const int64_t* __restrict__ m_dev,
+    Reader in, int64_t m_max, const int64_t* __restrict__ m_dev, const uint32_t* __restrict__ varying,
     int shift, uint32_t* __restrict__ tile_hist /* [tiles][bins] */, uint32_t* __restrict__ scan_done)
 {
     constexpr int bins = 1 << NBITS;
+    constexpr int kTile = kBlock * ITEMS;
     __shared__ uint32_t hist[bins];
+    if (sort_pass_idle(varying, shift)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) *scan_done = 0;    // the scan kernel that follows counts its finished blocks here
     const int64_t m = sort_count_of(m_dev, m_max);
-    const int64_t used = (m + kSortTile - 1) / kSortTile;      // tiles that hold pairs (m may live on the device)
+    const int64_t used = (m + kTile - 1) / kTile;      // tiles that hold pairs (m may live on the device)
     constexpr uint32_t mask = (uint32_t)bins - 1u;
     for (int64_t tile = blockIdx.x; tile < used; tile += gridDim.x) {
-        const int64_t base = tile * kSortTile;
+        const int64_t base = tile * kTile;
         for (int b = threadIdx.x; b < bins; b += kBlock) hist[b] = 0;
         __syncthreads();
-        if (base + kSortTile <= m) {                            // whole tile: unpredicated loads, all in flight
-            uint32_t key[kSortItems];
+        if (base + kTile <= m) {                            // whole tile: unpredicated loads, all in flight
+            uint32_t key[ITEMS];
 #pragma unroll
-            for (int it = 0; it < kSortItems; ++it) key[it] = in.key(base + (int64_t)it * kBlock + threadIdx.x);
+            for (int it = 0; it < ITEMS; ++it) key[it] = in.key(base + (int64_t)it * kBlock + threadIdx.x);
 #pragma unroll
-            for (int it = 0; it < kSortItems; ++it) count_digit<NBITS>(hist, (key[it] >> shift) & mask, true);
+            for (int it = 0; it < ITEMS; ++it) count_digit<NBITS>(hist, (key[it] >> shift) & mask, true);
         } else {
-            for (int it = 0; it < kSortItems; ++it) {
+            for (int it = 0; it < ITEMS; ++it) {
                 const int64_t i = base + (int64_t)it * kBlock + threadIdx.x;
                 const bool valid = i < m;
                 count_digit<NBITS>(hist, valid ? ((in.key(i) >> shift) & mask) : 0u, valid);
@@ -117,9 +127,11 @@ constexpr int kScanAhead = 8;                // loads a scan thread keeps in fli
 
 __global__ __launch_bounds__(1024) void sort_scan_kernel(
     uint32_t* __restrict__ tile_hist, int bins, int64_t m_max, const int64_t* __restrict__ m_dev,
+    const uint32_t* __restrict__ varying, int shift,
     uint32_t* __restrict__ chunk_sums, uint32_t* __restrict__ totals, uint32_t* __restrict__ scan_done, int fused)
 {
     __shared__ bool is_last;
+    if (sort_pass_idle(varying, shift)) return;
     const int64_t m = sort_count_of(m_dev, m_max);
     const int64_t used = (m + kSortTile - 1) / kSortTile;
     const int64_t chunks = (used + kSortChunkTiles - 1) / kSortChunkTiles;
@@ -168,8 +180,9 @@ __global__ __launch_bounds__(1024) void sort_scan_kernel(
 // longer than a launch costs (72 M pairs, 275 chunks: 230 µs against 11 µs).
 __global__ __launch_bounds__(kBlock) void sort_scan_chunks_kernel(
     uint32_t* __restrict__ chunk_sums, int bins, int64_t m_max, const int64_t* __restrict__ m_dev,
-    uint32_t* __restrict__ totals)
+    const uint32_t* __restrict__ varying, int shift, uint32_t* __restrict__ totals)
 {
+    if (sort_pass_idle(varying, shift)) return;
     const int64_t m = sort_count_of(m_dev, m_max);
     const int64_t used = (m + kSortTile - 1) / kSortTile;
     const int64_t chunks = (used + kSortChunkTiles - 1) / kSortChunkTiles;
@@ -188,21 +201,26 @@ __global__ __launch_bounds__(kBlock) void sort_scan_chunks_kernel(
     totals[b] = run;
 }
 
-template <typename Reader, int NBITS>
+// SUM: few tiles, no scan has run: tile_hist holds plain counts and every block adds up the digits' totals and the
+// tiles before its own itself, one vector load per tile and thread.
+template <typename Reader, int NBITS, int ITEMS, bool SUM>
 __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
-    Reader in, int64_t m_max, const int64_t* __restrict__ m_dev, int shift,
-    const uint32_t* __restrict__ tile_hist /* scanned */, const uint32_t* __restrict__ chunk_sums /* scanned */,
+    Reader in, int64_t m_max, const int64_t* __restrict__ m_dev, const uint32_t* __restrict__ varying, int shift,
+    const uint32_t* __restrict__ tile_hist /* scanned, unless SUM */, const uint32_t* __restrict__ chunk_sums /* scanned */,
     const uint32_t* __restrict__ totals, uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int32_t* status)
 {
     constexpr int bins = 1 << NBITS;
+    constexpr int kTile = kBlock * ITEMS;
+    constexpr int kWaveSpan = kWave * ITEMS;
     __shared__ uint32_t out_base[bins];                         // global index of the tile's first pair of a digit,
                                                                 // minus the digit's first index inside the tile
     __shared__ uint16_t wave_hist[kWavesPerBlock][bins];
-    __shared__ uint32_t s_key[kSortTile];
-    __shared__ uint32_t s_val[kSortTile];
+    __shared__ uint32_t s_key[kTile];
+    __shared__ uint32_t s_val[kTile];
     __shared__ uint32_t wave_sums[16];
+    if (sort_pass_idle(varying, shift)) return;
     const int64_t m = sort_count_of(m_dev, m_max);
-    const int64_t used = (m + kSortTile - 1) / kSortTile;
+    const int64_t used = (m + kTile - 1) / kTile;
     constexpr uint32_t mask = (uint32_t)bins - 1u;
     const int w = wave_id();
     const int lane = lane_id();
@@ -213,35 +231,51 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
     // grid stride): consecutive tiles write neighbouring runs of every digit's region, a few tens of
     // bytes each, and one XCD's L2 then merges what four XCDs would write into one 128-byte line
     // piece by piece (scatter 0.343 -> 0.327 ms per step on 15.7 M pairs).
-    const int64_t padded = xcd_striped_grid_dev(used, kSortStripe);
+    const int64_t padded = SUM ? used : xcd_striped_grid_dev(used, kSortStripe);
     for (int64_t v = blockIdx.x; v < padded; v += gridDim.x) {
-        const int64_t tile = xcd_striped_tile((unsigned)v, kSortStripe);
+        const int64_t tile = SUM ? v : xcd_striped_tile((unsigned)v, kSortStripe);
         if (tile >= used) continue;                              // block-uniform
-        const int64_t base = tile * kSortTile;
-        const int64_t wbase = base + (int64_t)w * kSortWaveSpan;
+        const int64_t base = tile * kTile;
+        const int64_t wbase = base + (int64_t)w * kWaveSpan;
         for (int b = lane; b < bins; b += kWave) wave_hist[w][b] = 0;
 
-        uint32_t key[kSortItems];
-        uint32_t val[kSortItems];
-        uint32_t rank[kSortItems];
-        const bool whole = base + kSortTile <= m;
+        uint32_t key[ITEMS];
+        uint32_t val[ITEMS];
+        uint32_t rank[ITEMS];
+        const bool whole = base + kTile <= m;
         if (whole) {
 #pragma unroll
-            for (int it = 0; it < kSortItems; ++it) in.pair(wbase + it * kWave + lane, &key[it], &val[it], &faults);
+            for (int it = 0; it < ITEMS; ++it) in.pair(wbase + it * kWave + lane, &key[it], &val[it], &faults);
         } else {
 #pragma unroll
-            for (int it = 0; it < kSortItems; ++it) {
+            for (int it = 0; it < ITEMS; ++it) {
                 const int64_t i = wbase + it * kWave + lane;
                 key[it] = 0u;
                 val[it] = 0u;
                 if (i < m) in.pair(i, &key[it], &val[it], &faults);
             }
         }
+        uint32_t tot[kBinsPerThread];                            // the digits' totals
+        uint32_t before_tile[kBinsPerThread];                    // and their pairs in the tiles before this one
+#pragma unroll
+        for (int q = 0; q < kBinsPerThread; ++q) { tot[q] = 0; before_tile[q] = 0; }
+        if constexpr (SUM) {
+            typedef uint32_t Bins __attribute__((ext_vector_type(kBinsPerThread)));    // 1, 2 or 4: aligned (256-byte tables)
+            if (threadIdx.x * kBinsPerThread < bins) {
+                const Bins* mine = reinterpret_cast<const Bins*>(tile_hist) + threadIdx.x;
+#pragma unroll 8
+                for (int t = 0; t < (int)used; ++t) {
+                    const Bins v = mine[t * (bins / kBinsPerThread)];
+#pragma unroll
+                    for (int q = 0; q < kBinsPerThread; ++q) { tot[q] += v[q]; before_tile[q] += t < (int)tile ? v[q] : 0u; }
+                }
+            }
+        }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // the zeroing above, seen by the wave's other lanes
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-        for (int it = 0; it < kSortItems; ++it) {
+        for (int it = 0; it < ITEMS; ++it) {
             const bool valid = whole || wbase + it * kWave + lane < m;
             const uint32_t digit = (key[it] >> shift) & mask;
             const uint64_t same = match_bits_n<NBITS>(digit, valid);
@@ -257,7 +291,6 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
 
         // per digit: waves' counts -> waves' offsets inside the digit; the tile's count of the digit
         uint32_t count[kBinsPerThread];
-        uint32_t tot[kBinsPerThread];
         uint32_t sum = 0, tsum = 0;
 #pragma unroll
         for (int q = 0; q < kBinsPerThread; ++q) {
@@ -273,7 +306,7 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
             }
             count[q] = run;
             sum += run;
-            tot[q] = b < bins ? totals[b] : 0u;
+            if constexpr (!SUM) tot[q] = b < bins ? totals[b] : 0u;
             tsum += tot[q];
         }
         // exclusive scans over the digits: inside the tile (sum) and over the whole input (totals)
@@ -284,7 +317,8 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
         for (int q = 0; q < kBinsPerThread; ++q) {
             const int b = threadIdx.x * kBinsPerThread + q;
             if (b < bins) {
-                out_base[b] = in_all + chunk_sums[(tile / kSortChunkTiles) * bins + b] + tile_hist[tile * bins + b] - in_tile;
+                if constexpr (!SUM) before_tile[q] = chunk_sums[(tile / kSortChunkTiles) * bins + b] + tile_hist[tile * bins + b];
+                out_base[b] = in_all + before_tile[q] - in_tile;
 #pragma unroll
                 for (int k = 0; k < kWavesPerBlock; ++k) wave_hist[k][b] = (uint16_t)(wave_hist[k][b] + in_tile);
             }
@@ -294,7 +328,7 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
         __syncthreads();
         // the tile in digit order, in LDS
 #pragma unroll
-        for (int it = 0; it < kSortItems; ++it) {
+        for (int it = 0; it < ITEMS; ++it) {
             const bool valid = whole || wbase + it * kWave + lane < m;
             if (valid) {
                 const uint32_t digit = (key[it] >> shift) & mask;
@@ -304,9 +338,9 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
             }
         }
         __syncthreads();
-        const int valid_in_tile = (int)(m - base < kSortTile ? m - base : kSortTile);
+        const int valid_in_tile = (int)(m - base < kTile ? m - base : kTile);
 #pragma unroll
-        for (int it = 0; it < kSortItems; ++it) {
+        for (int it = 0; it < ITEMS; ++it) {
             const int at = it * kBlock + threadIdx.x;
             if (at < valid_in_tile) {
                 const uint32_t k = s_key[at];
@@ -323,40 +357,105 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
     }
 }
 
-static int64_t sort_tiles(int64_t m_max) { return (m_max + kSortTile - 1) / kSortTile; }
+// Sorts of few pairs: tiles of 1024 pairs instead of 4096 (a block's time is a chain of ranking rounds, one per item
+// of a thread, and 8192 pairs had two blocks) and no scan launch (the scatter sums up to 64 tiles' counts itself, one
+// load each, while its pairs are on the way).  With the count on the device (the plan's candidates, usually a few
+// per cent of the rows that the buffers are sized for) the small tiles go up to 128 of them.  A whole step of 8192
+// lookups over 100 k rows (two such sorts) 170 -> 115 us, a training iteration of 50 k lookups 151 -> 125 us.
+constexpr int kSortSmallItems = 4;
+constexpr int64_t kSortSumTiles = 64;
+
+struct SortShape {
+    bool small;                              // kSortSmallItems pairs per thread, else kSortItems
+    bool sum;                                // no scan launch
+    int64_t tiles;
+};
+
+static SortShape sort_shape(int64_t m_max, bool device_count)
+{
+    const int64_t small_tile = kBlock * kSortSmallItems;
+    const int64_t small_tiles = (m_max + small_tile - 1) / small_tile;
+    if (small_tiles <= (device_count ? 2 : 1) * kSortSumTiles) return {true, true, small_tiles};
+    const int64_t tiles = (m_max + kSortTile - 1) / kSortTile;
+    return {false, tiles <= kSortSumTiles, tiles};
+}
 
 size_t radix_sort_scratch_bytes(int64_t m_max)
 {
+    // for either way of knowing the count, and never less than a smaller m_max asks for: a workspace sized for a
+    // caller's largest batch serves the smaller ones
+    const int64_t small_max = 2 * kSortSumTiles;
+    int64_t tiles = (m_max + kBlock * kSortSmallItems - 1) / (kBlock * kSortSmallItems);
+    if (tiles > small_max) {
+        const int64_t large = (m_max + kSortTile - 1) / kSortTile;
+        tiles = large > small_max ? large : small_max;
+    }
     Carver c(nullptr);
     c.take<uint32_t>((size_t)kSortMaxBins);
     c.take<uint32_t>(1);
-    c.take<uint32_t>((size_t)kSortMaxBins * (size_t)sort_tiles(m_max));
-    c.take<uint32_t>((size_t)kSortMaxBins * (size_t)((sort_tiles(m_max) + kSortChunkTiles - 1) / kSortChunkTiles));
+    c.take<uint32_t>((size_t)kSortMaxBins * (size_t)tiles);
+    c.take<uint32_t>((size_t)kSortMaxBins * (size_t)((tiles + kSortChunkTiles - 1) / kSortChunkTiles));
     return c.used;
+}
+
+template <int NBITS, typename Reader>
+static fs_status launch_sort_pass(const Reader& in, const SortShape& shape, int64_t m_max, const int64_t* m_dev,
+                                  const uint32_t* varying, int shift, unsigned max_grid, bool fused_scan, uint32_t* tile_hist,
+                                  uint32_t* chunk_sums, uint32_t* totals, uint32_t* scan_done, uint32_t* keys_out,
+                                  uint32_t* vals_out, int32_t* status, hipStream_t stream)
+{
+    constexpr int bins = 1 << NBITS;
+    if (shape.sum) {
+        const dim3 grid((unsigned)shape.tiles);
+        if (shape.small) {
+            FS_LAUNCH("sort_count", (sort_count_kernel<Reader, NBITS, kSortSmallItems>), grid, dim3(kBlock), stream,
+                      in, m_max, m_dev, varying, shift, tile_hist, scan_done);
+            FS_LAUNCH("sort_scatter", (sort_scatter_kernel<Reader, NBITS, kSortSmallItems, true>), grid, dim3(kBlock), stream,
+                      in, m_max, m_dev, varying, shift, tile_hist, chunk_sums, totals, keys_out, vals_out, status);
+        } else {
+            FS_LAUNCH("sort_count", (sort_count_kernel<Reader, NBITS, kSortItems>), grid, dim3(kBlock), stream,
+                      in, m_max, m_dev, varying, shift, tile_hist, scan_done);
+            FS_LAUNCH("sort_scatter", (sort_scatter_kernel<Reader, NBITS, kSortItems, true>), grid, dim3(kBlock), stream,
+                      in, m_max, m_dev, varying, shift, tile_hist, chunk_sums, totals, keys_out, vals_out, status);
+        }
+        return FS_OK;
+    }
+    // blocks walk the tiles with a grid stride: when the pair count lives on the device the grid
+    // is sized for m_max, and idle blocks would otherwise dominate a small sort
+    const int64_t padded_tiles = xcd_striped_grid(shape.tiles, kSortStripe);       // a multiple of 8, as max_grid is
+    const dim3 grid(padded_tiles < (int64_t)max_grid ? (unsigned)padded_tiles : max_grid);
+    const int64_t chunks = (shape.tiles + kSortChunkTiles - 1) / kSortChunkTiles;
+    FS_LAUNCH("sort_count", (sort_count_kernel<Reader, NBITS, kSortItems>), grid, dim3(kBlock), stream,
+              in, m_max, m_dev, varying, shift, tile_hist, scan_done);
+    FS_LAUNCH("sort_scan", sort_scan_kernel, dim3((unsigned)chunks), dim3(bins < kWave ? kWave : bins), stream,
+              tile_hist, bins, m_max, m_dev, varying, shift, chunk_sums, totals, scan_done, fused_scan ? 1 : 0);
+    if (!fused_scan)
+        FS_LAUNCH("sort_scan_chunks", sort_scan_chunks_kernel, dim3((bins + kBlock - 1) / kBlock),
+                  dim3(kBlock), stream, chunk_sums, bins, m_max, m_dev, varying, shift, totals);
+    FS_LAUNCH("sort_scatter", (sort_scatter_kernel<Reader, NBITS, kSortItems, false>), grid, dim3(kBlock), stream,
+              in, m_max, m_dev, varying, shift, tile_hist, chunk_sums, totals, keys_out, vals_out, status);
+    return FS_OK;
 }
 
 fs_status radix_sort_pairs(uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b, uint32_t* vals_b,
                            int64_t m_max, const int64_t* m_dev, int key_bits, void* scratch,
-                           hipStream_t stream, uint32_t** keys_out, uint32_t** vals_out, const SortSource& src)
+                           hipStream_t stream, uint32_t** keys_out, uint32_t** vals_out, const SortSource& src,
+                           const uint32_t* varying)
 {
     *keys_out = keys_a;
     *vals_out = vals_a;
     if (m_max <= 0) return FS_OK;
     if (key_bits < 1) key_bits = 1;
     if (key_bits > 32) key_bits = 32;
-    const int64_t tiles = sort_tiles(m_max);
-    if (tiles > 0x7FFFFFFF) return FS_ERR_SIZE;
+    const SortShape shape = sort_shape(m_max, m_dev != nullptr);
+    if (shape.tiles > 0x7FFFFFFF) return FS_ERR_SIZE;
     Carver c(scratch);
     uint32_t* totals = c.take<uint32_t>((size_t)kSortMaxBins);
     uint32_t* scan_done = c.take<uint32_t>(1);
-    uint32_t* tile_hist = c.take<uint32_t>((size_t)kSortMaxBins * (size_t)tiles);
-    const int64_t chunks = (tiles + kSortChunkTiles - 1) / kSortChunkTiles;
+    uint32_t* tile_hist = c.take<uint32_t>((size_t)kSortMaxBins * (size_t)shape.tiles);
+    const int64_t chunks = (shape.tiles + kSortChunkTiles - 1) / kSortChunkTiles;
     uint32_t* chunk_sums = c.take<uint32_t>((size_t)kSortMaxBins * (size_t)chunks);
 
-    // blocks walk the tiles with a grid stride: when the pair count lives on the device the grid
-    // is sized for m_max, and idle blocks would otherwise dominate a small sort
-    const int64_t padded_tiles = xcd_striped_grid(tiles, kSortStripe);       // a multiple of 8
-    const unsigned grid = (unsigned)(padded_tiles < kSortMaxGrid ? padded_tiles : kSortMaxGrid);
     const int passes = radix_sort_passes(key_bits);
     // The second scan level runs inside the first level's launch for small sorts.  When the pair count lives on
     // the device (the plan's candidates: a few per cent of the rows the buffers are sized for), "small" cannot be
@@ -369,45 +468,30 @@ fs_status radix_sort_pairs(uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
     uint32_t* dst_k = from_rows ? keys_a : keys_b;
     uint32_t* dst_v = from_rows ? vals_a : vals_b;
     for (int p = 0; p < passes; ++p) {
-        // spread the bits evenly over the passes: 27 bits -> 9, 9, 9; 32 bits -> 8, 8, 8, 8
+        // spread the bits evenly over the passes: 27 bits -> 9, 9, 9; where passes can turn out idle the digits are
+        // as wide as they can be: 32 bits -> 10, 10, 10, 2, and the last pass, which only counts of 2^30 and more
+        // need, has a grid that costs little when it is idle (new tiers for 40 M rows 402 -> 393 us)
         const int left = key_bits - shift;
-        const int nbits = (left + (passes - p) - 1) / (passes - p);
-        const unsigned scan_threads = (1u << nbits) < (unsigned)kWave ? (unsigned)kWave : (1u << nbits);   // <= 1024
+        const int even = (left + (passes - p) - 1) / (passes - p);
+        const int nbits = varying == nullptr ? even : (left < kSortMaxDigitBits ? left : kSortMaxDigitBits);
+        const unsigned max_grid = varying != nullptr && p == passes - 1 ? 1024u : (unsigned)kSortMaxGrid;
+        fs_status rc = FS_OK;
         if (p == 0 && from_rows) {
             const RowPosReader in{src.rows, src.pos, src.R, src.n};
-#define FS_COUNT_ROWS(NB)                                                                                     \
-    FS_LAUNCH("sort_count", (sort_count_kernel<RowPosReader, NB>), dim3(grid), dim3(kBlock), stream, in, m_max,     \
-              m_dev, shift, tile_hist, scan_done)
-            FS_DISPATCH_BITS(nbits, FS_COUNT_ROWS)
-#undef FS_COUNT_ROWS
-            FS_LAUNCH("sort_scan", sort_scan_kernel, dim3((unsigned)chunks), dim3(scan_threads), stream,
-                      tile_hist, 1 << nbits, m_max, m_dev, chunk_sums, totals, scan_done, fused_scan ? 1 : 0);
-            if (!fused_scan)
-                FS_LAUNCH("sort_scan_chunks", sort_scan_chunks_kernel, dim3(((1u << nbits) + kBlock - 1) / kBlock),
-                          dim3(kBlock), stream, chunk_sums, 1 << nbits, m_max, m_dev, totals);
-#define FS_SCATTER_ROWS(NB)                                                                                   \
-    FS_LAUNCH("sort_scatter", (sort_scatter_kernel<RowPosReader, NB>), dim3(grid), dim3(kBlock), stream, in, m_max, \
-              m_dev, shift, tile_hist, chunk_sums, totals, dst_k, dst_v, src.status)
-            FS_DISPATCH_BITS(nbits, FS_SCATTER_ROWS)
-#undef FS_SCATTER_ROWS
+#define FS_SORT_ROWS(NB)                                                                                      \
+    rc = launch_sort_pass<NB>(in, shape, m_max, m_dev, varying, shift, max_grid, fused_scan, tile_hist, chunk_sums,   \
+                              totals, scan_done, dst_k, dst_v, src.status, stream)
+            FS_DISPATCH_BITS(nbits, FS_SORT_ROWS)
+#undef FS_SORT_ROWS
         } else {
             const PairReader in{src_k, src_v};
-#define FS_COUNT_PAIRS(NB)                                                                                    \
-    FS_LAUNCH("sort_count", (sort_count_kernel<PairReader, NB>), dim3(grid), dim3(kBlock), stream, in, m_max,       \
-              m_dev, shift, tile_hist, scan_done)
-            FS_DISPATCH_BITS(nbits, FS_COUNT_PAIRS)
-#undef FS_COUNT_PAIRS
-            FS_LAUNCH("sort_scan", sort_scan_kernel, dim3((unsigned)chunks), dim3(scan_threads), stream,
-                      tile_hist, 1 << nbits, m_max, m_dev, chunk_sums, totals, scan_done, fused_scan ? 1 : 0);
-            if (!fused_scan)
-                FS_LAUNCH("sort_scan_chunks", sort_scan_chunks_kernel, dim3(((1u << nbits) + kBlock - 1) / kBlock),
-                          dim3(kBlock), stream, chunk_sums, 1 << nbits, m_max, m_dev, totals);
-#define FS_SCATTER_PAIRS(NB)                                                                                  \
-    FS_LAUNCH("sort_scatter", (sort_scatter_kernel<PairReader, NB>), dim3(grid), dim3(kBlock), stream, in, m_max,   \
-              m_dev, shift, tile_hist, chunk_sums, totals, dst_k, dst_v, (int32_t*)nullptr)
-            FS_DISPATCH_BITS(nbits, FS_SCATTER_PAIRS)
-#undef FS_SCATTER_PAIRS
+#define FS_SORT_PAIRS(NB)                                                                                     \
+    rc = launch_sort_pass<NB>(in, shape, m_max, m_dev, varying, shift, max_grid, fused_scan, tile_hist, chunk_sums,   \
+                              totals, scan_done, dst_k, dst_v, nullptr, stream)
+            FS_DISPATCH_BITS(nbits, FS_SORT_PAIRS)
+#undef FS_SORT_PAIRS
         }
+        if (rc != FS_OK) return rc;
         shift += nbits;
         src_k = dst_k; src_v = dst_v;
         dst_k = (src_k == keys_a) ? keys_b : keys_a;

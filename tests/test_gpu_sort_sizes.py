@@ -1,0 +1,88 @@
+"""The sort and the planner's selection at the sizes where their kernels change shape, against the oracle: 1024-pair
+and 4096-pair tiles, the largest numbers of tiles whose counts the scatter sums itself, the passes of the selection's
+sort that are left out where the counts are small, and the compaction with and without a scan of its own."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import entry
+
+pytestmark = pytest.mark.gpu
+
+S, TAG, Z = oracle.PLAN_SELECT, oracle.PLAN_TAG, oracle.PLAN_ALLOW_ZERO
+TILE = 8192                                          # rows of one compaction tile
+
+
+@pytest.fixture(scope="module")
+def G():
+    import gpu_common
+    assert torch.cuda.is_available()
+    return gpu_common
+
+
+@pytest.mark.parametrize("m", [1, 1023, 1024, 1025, 65536, 65537, 262144, 262145])
+@pytest.mark.parametrize("R", [3, 200, 1 << 10, (1 << 17) + 1, 1 << 20, 3_000_000])
+def test_sort_sizes(G, m, R):
+    import paper_2301_02959_amd as fs
+    rng = np.random.default_rng(m + R)
+    rows = np.where(rng.random(m) < 0.5, rng.integers(0, min(R, 7), m), rng.integers(0, R, m)).astype(np.int64)
+    rows[0] = R - 1
+    pos = np.arange(m, dtype=np.int32)
+    srows = torch.full((m,), -7, dtype=torch.int32, device=G.DEV)
+    spos = torch.full((m,), -7, dtype=torch.int32, device=G.DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    fs.fs_sort_lookups(G.to_dev(rows), G.to_dev(pos), 0, m, R, m, srows, spos, st)
+    orc, ost, osr, osp = oracle.sort_lookups(rows, pos, 0, m, R, m)
+    assert orc == 0 and int(st.item()) == ost == 0
+    assert np.array_equal(srows.cpu().numpy().view(np.uint32), osr)
+    assert np.array_equal(spos.cpu().numpy().view(np.uint32), osp)
+
+
+@pytest.mark.parametrize("R", [1, 1024, 128 * 1024, 128 * 1024 + 1, 64 * 4096, 64 * 4096 + 1, 1024 * TILE, 1024 * TILE + 1])
+@pytest.mark.parametrize("bits,share", [(1, 0.9), (10, 0.01), (11, 0.3), (20, 0.05), (21, 0.3), (30, 0.1), (31, 0.3), (32, 0.02)])
+def test_selection_sizes(G, R, bits, share):
+    """Counts of up to `bits` bits on `share` of the rows: passes are left out at 10, 20 and 30 bits."""
+    import paper_2301_02959_amd as fs
+    rng = np.random.default_rng(R + bits)
+    counts = np.where(rng.random(R) < share, 1 + rng.geometric(0.4, R), 0).astype(np.uint64)
+    some = rng.integers(0, R, 50)
+    counts[some] = rng.integers(1, 1 << bits, 50)
+    counts = np.minimum(counts, (1 << bits) - 1)
+    counts[some[0]] = 1 << (bits - 1)
+    counts = counts.astype(np.uint32)
+    for flags, budget in [(S | TAG, max(1, R // 50)), (S | Z, R)]:
+        if R > 1_000_000 and flags & Z:
+            continue
+        placement = np.full(R, entry(2, 3), np.uint32)
+        oc, opl = counts.copy(), placement.copy()
+        orc, ost, osel = oracle.plan_replication(None, None, 1, 1, None, R, oc, flags, budget, 1, opl, n=0)
+        dev = torch.from_numpy(counts.view(np.int32).copy()).to(G.DEV)
+        pl = G.placement_dev(placement)
+        sel = torch.full((budget,), -7, dtype=torch.int64, device=G.DEV)
+        num = torch.full((1,), -7, dtype=torch.int64, device=G.DEV)
+        fs.fs_plan_replication(None, None, 1, 1, None, 0, R, dev, flags, budget, 1, sel, num, pl)
+        assert orc == ost == 0 and int(num.item()) == len(osel)
+        assert np.array_equal(sel[:len(osel)].cpu().numpy(), osel)
+        assert np.array_equal(pl.cpu().numpy().view(np.uint32), opl if flags & TAG else placement)
+    # the tier planner reads the same sorted counts, keys included
+    params = dict(num_samples=1000, B=64, U=8, W=4, dp_multiplier=6, granule=8, a2a_global=1, a2a_intra=6, ar_global=3, ar_cross=2)
+    cuts = torch.zeros(fs.FS_TIER_CUTS, dtype=torch.int64, device=G.DEV)
+    rows = torch.full((R,), -7, dtype=torch.int64, device=G.DEV)
+    fs.fs_plan_tiers(torch.from_numpy(counts.view(np.int32).copy()).to(G.DEV), R, params, 3, rows, R, cuts)
+    orc, ocuts, orows = oracle.plan_tiers(counts, params, 3)
+    assert orc == 0 and cuts.cpu().numpy().tolist() == ocuts.tolist()
+    assert np.array_equal(rows[:len(orows)].cpu().numpy(), orows)
+
+
+def test_a_workspace_for_more_rows_serves_fewer():
+    """The scratch size does not shrink as the rows grow, also where the sort goes over to larger tiles."""
+    import ctypes
+    import paper_2301_02959_amd as fs
+    sizes = []
+    for R in [1, 1024, 65536, 65537, 100_000, 131_072, 131_073, 150_000, 262_144, 262_145, 600_000, 1024 * TILE, 1024 * TILE + 1]:
+        size = ctypes.c_size_t(0)
+        assert fs.lib().fs_plan_replication(None, None, 1, 1, None, ctypes.c_int64(0), ctypes.c_int64(R), None, S, ctypes.c_int64(8),
+                                            ctypes.c_int64(1), None, None, None, None, ctypes.byref(size), None, None) == 0
+        sizes.append(size.value)
+    assert sizes == sorted(sizes)
