@@ -5,9 +5,10 @@
 //   sort_count    per-tile digit histogram (one LDS add per distinct digit per wave, found by
 //                 ballot matching), stored tile-major
 //   sort_scan     exclusive scan of every digit's per-tile counts over the tiles (two levels,
-//                 coalesced across digits), and the digits' totals; for small sorts the block that
-//                 finishes its chunk of tiles last (a counter, no waiting) runs the second level,
-//                 for large ones the second level is a launch of its own (sort_scan_chunks)
+//                 coalesced across digits), and the digits' totals; the second level is the scatter's for
+//                 small sorts, a launch of its own for large ones (sort_scan_chunks), and where the number of
+//                 pairs is only known on the device and is large, the work of the block that finishes its
+//                 chunk of tiles last (a counter, no waiting)
 //   sort_scatter  each wave ranks its 1024 consecutive pairs against a wave-private running
 //                 histogram in LDS (ballot matching keeps equal digits in order); the tile is put
 //                 in digit order in LDS, then written out so that consecutive lanes write
@@ -116,13 +117,28 @@ __global__ __launch_bounds__(kBlock) void sort_count_kernel(
 }
 
 // Column-wise exclusive scan of tile_hist[tile][digit] over the tiles, in two levels so that every
-// access is coalesced across digits.  Level 1: a block takes a chunk of 64 tiles; thread b walks
+// access is coalesced across digits.  Level 1: a block takes a chunk of tiles; thread b walks
 // the chunk's tiles for digit b, leaves the running prefix in place and the chunk's sum in
-// chunk_sums[chunk][b].  Level 2 (one block): thread b walks the chunks for digit b: chunk_sums ->
-// exclusive prefix, totals[b].
+// chunk_sums[chunk][b].  Level 2: up to 16 chunks (4 M pairs) every block of the scatter adds up the chunks' sums
+// itself, one vector load each, while its pairs are on the way: no hand-over between blocks.  Beyond, one block:
+// thread b walks the chunks for digit b: chunk_sums -> exclusive prefix, totals[b].
+// Chunks are 64 tiles, and 32 where 16 of them are enough: level 1's time is its chain of rounds of loads.  With level 2
+// in the block that finished last a pass over 1 to 2 M pairs spent 9.8 us here, now 5.2 and 2.6 in the scatter.
 constexpr int kSortChunkTiles = 64;
-constexpr int kSortFusedScanChunks = 16;     // up to this many chunks (4 M pairs) the scan's second level runs inside its first launch
+constexpr int kSortSumChunks = 16;
 constexpr int kSortFusedScanChunksDev = 1024;
+
+__host__ __device__ __forceinline__ int64_t sort_chunk_tiles(int64_t used)
+{
+    return used <= kSortSumChunks * kSortChunkTiles / 2 ? kSortChunkTiles / 2 : kSortChunkTiles;
+}
+
+__host__ __device__ __forceinline__ int64_t sort_chunks(int64_t used)
+{
+    const int64_t per = sort_chunk_tiles(used);
+    return (used + per - 1) / per;
+}
+
 constexpr int kScanAhead = 8;                // loads a scan thread keeps in flight (16 and 32 are slower)
 
 __global__ __launch_bounds__(1024) void sort_scan_kernel(
@@ -134,10 +150,11 @@ __global__ __launch_bounds__(1024) void sort_scan_kernel(
     if (sort_pass_idle(varying, shift)) return;
     const int64_t m = sort_count_of(m_dev, m_max);
     const int64_t used = (m + kSortTile - 1) / kSortTile;
-    const int64_t chunks = (used + kSortChunkTiles - 1) / kSortChunkTiles;
-    const int64_t t0 = (int64_t)blockIdx.x * kSortChunkTiles;
+    const int64_t per = sort_chunk_tiles(used);
+    const int64_t chunks = sort_chunks(used);
+    const int64_t t0 = (int64_t)blockIdx.x * per;
     if (t0 >= used) return;                                      // block-uniform: this block has no tiles
-    const int64_t t1 = t0 + kSortChunkTiles < used ? t0 + kSortChunkTiles : used;
+    const int64_t t1 = t0 + per < used ? t0 + per : used;
     for (int b = threadIdx.x; b < bins; b += blockDim.x) {       // launched with one thread per digit (up to 1024)
         uint32_t run = 0;
         int64_t t = t0;
@@ -151,7 +168,7 @@ __global__ __launch_bounds__(1024) void sort_scan_kernel(
         for (; t < t1; ++t) { const uint32_t v = tile_hist[t * bins + b]; tile_hist[t * bins + b] = run; run += v; }
         chunk_sums[(int64_t)blockIdx.x * bins + b] = run;
     }
-    if (!fused) return;                                          // block-uniform: level 2 is a launch of its own
+    if (!fused || chunks <= kSortSumChunks) return;              // block-uniform: level 2 is a launch of its own, or the scatter's
     // Level 2 needs every block's chunk sums.  Each block publishes its own (fence), then takes a ticket;
     // the block that draws the last ticket sees all of them (fence) and runs the second level.  Nobody waits.
     __threadfence();
@@ -185,9 +202,9 @@ __global__ __launch_bounds__(kBlock) void sort_scan_chunks_kernel(
     if (sort_pass_idle(varying, shift)) return;
     const int64_t m = sort_count_of(m_dev, m_max);
     const int64_t used = (m + kSortTile - 1) / kSortTile;
-    const int64_t chunks = (used + kSortChunkTiles - 1) / kSortChunkTiles;
+    const int64_t chunks = sort_chunks(used);
     const int b = blockIdx.x * kBlock + threadIdx.x;
-    if (b >= bins) return;
+    if (b >= bins || chunks <= kSortSumChunks) return;           // few chunks: the scatter's
     uint32_t run = 0;
     int64_t c = 0;
     for (; c + kScanAhead <= chunks; c += kScanAhead) {
@@ -231,6 +248,9 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
     // grid stride): consecutive tiles write neighbouring runs of every digit's region, a few tens of
     // bytes each, and one XCD's L2 then merges what four XCDs would write into one 128-byte line
     // piece by piece (scatter 0.343 -> 0.327 ms per step on 15.7 M pairs).
+    const int64_t chunk_tiles = sort_chunk_tiles(used);
+    const int64_t chunks = sort_chunks(used);
+    const bool sums_chunks = !SUM && chunks <= kSortSumChunks;
     const int64_t padded = SUM ? used : xcd_striped_grid_dev(used, kSortStripe);
     for (int64_t v = blockIdx.x; v < padded; v += gridDim.x) {
         const int64_t tile = SUM ? v : xcd_striped_tile((unsigned)v, kSortStripe);
@@ -259,15 +279,19 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
         uint32_t before_tile[kBinsPerThread];                    // and their pairs in the tiles before this one
 #pragma unroll
         for (int q = 0; q < kBinsPerThread; ++q) { tot[q] = 0; before_tile[q] = 0; }
-        if constexpr (SUM) {
+        // SUM: of all tiles' counts.  Else, where they are few, of the chunks' sums; the tiles before in its own chunk follow.
+        const int64_t my_chunk = tile / chunk_tiles;
+        if (SUM || sums_chunks) {
             typedef uint32_t Bins __attribute__((ext_vector_type(kBinsPerThread)));    // 1, 2 or 4: aligned (256-byte tables)
             if (threadIdx.x * kBinsPerThread < bins) {
-                const Bins* mine = reinterpret_cast<const Bins*>(tile_hist) + threadIdx.x;
+                const Bins* mine = reinterpret_cast<const Bins*>(SUM ? tile_hist : chunk_sums) + threadIdx.x;
+                const int parts = (int)(SUM ? used : chunks);
+                const int me = (int)(SUM ? tile : my_chunk);
 #pragma unroll 8
-                for (int t = 0; t < (int)used; ++t) {
+                for (int t = 0; t < parts; ++t) {
                     const Bins v = mine[t * (bins / kBinsPerThread)];
 #pragma unroll
-                    for (int q = 0; q < kBinsPerThread; ++q) { tot[q] += v[q]; before_tile[q] += t < (int)tile ? v[q] : 0u; }
+                    for (int q = 0; q < kBinsPerThread; ++q) { tot[q] += v[q]; before_tile[q] += t < me ? v[q] : 0u; }
                 }
             }
         }
@@ -306,7 +330,7 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
             }
             count[q] = run;
             sum += run;
-            if constexpr (!SUM) tot[q] = b < bins ? totals[b] : 0u;
+            if (!SUM && !sums_chunks) tot[q] = b < bins ? totals[b] : 0u;
             tsum += tot[q];
         }
         // exclusive scans over the digits: inside the tile (sum) and over the whole input (totals)
@@ -317,7 +341,8 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
         for (int q = 0; q < kBinsPerThread; ++q) {
             const int b = threadIdx.x * kBinsPerThread + q;
             if (b < bins) {
-                if constexpr (!SUM) before_tile[q] = chunk_sums[(tile / kSortChunkTiles) * bins + b] + tile_hist[tile * bins + b];
+                if constexpr (!SUM)
+                    before_tile[q] += (sums_chunks ? 0u : chunk_sums[my_chunk * bins + b]) + tile_hist[tile * bins + b];
                 out_base[b] = in_all + before_tile[q] - in_tile;
 #pragma unroll
                 for (int k = 0; k < kWavesPerBlock; ++k) wave_hist[k][b] = (uint16_t)(wave_hist[k][b] + in_tile);
@@ -380,6 +405,13 @@ static SortShape sort_shape(int64_t m_max, bool device_count)
     return {false, tiles <= kSortSumTiles, tiles};
 }
 
+// Chunks of any number of tiles up to `tiles` (fewer tiles can have more chunks: shorter ones).
+static int64_t sort_chunks_max(int64_t tiles)
+{
+    const int64_t chunks = (tiles + kSortChunkTiles - 1) / kSortChunkTiles;
+    return chunks > kSortSumChunks ? chunks : kSortSumChunks;
+}
+
 size_t radix_sort_scratch_bytes(int64_t m_max)
 {
     // for either way of knowing the count, and never less than a smaller m_max asks for: a workspace sized for a
@@ -394,7 +426,7 @@ size_t radix_sort_scratch_bytes(int64_t m_max)
     c.take<uint32_t>((size_t)kSortMaxBins);
     c.take<uint32_t>(1);
     c.take<uint32_t>((size_t)kSortMaxBins * (size_t)tiles);
-    c.take<uint32_t>((size_t)kSortMaxBins * (size_t)((tiles + kSortChunkTiles - 1) / kSortChunkTiles));
+    c.take<uint32_t>((size_t)kSortMaxBins * (size_t)sort_chunks_max(tiles));
     return c.used;
 }
 
@@ -424,7 +456,7 @@ static fs_status launch_sort_pass(const Reader& in, const SortShape& shape, int6
     // is sized for m_max, and idle blocks would otherwise dominate a small sort
     const int64_t padded_tiles = xcd_striped_grid(shape.tiles, kSortStripe);       // a multiple of 8, as max_grid is
     const dim3 grid(padded_tiles < (int64_t)max_grid ? (unsigned)padded_tiles : max_grid);
-    const int64_t chunks = (shape.tiles + kSortChunkTiles - 1) / kSortChunkTiles;
+    const int64_t chunks = m_dev == nullptr ? sort_chunks(shape.tiles) : sort_chunks_max(shape.tiles);
     FS_LAUNCH("sort_count", (sort_count_kernel<Reader, NBITS, kSortItems>), grid, dim3(kBlock), stream,
               in, m_max, m_dev, varying, shift, tile_hist, scan_done);
     FS_LAUNCH("sort_scan", sort_scan_kernel, dim3((unsigned)chunks), dim3(bins < kWave ? kWave : bins), stream,
@@ -453,14 +485,15 @@ fs_status radix_sort_pairs(uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
     uint32_t* totals = c.take<uint32_t>((size_t)kSortMaxBins);
     uint32_t* scan_done = c.take<uint32_t>(1);
     uint32_t* tile_hist = c.take<uint32_t>((size_t)kSortMaxBins * (size_t)shape.tiles);
-    const int64_t chunks = (shape.tiles + kSortChunkTiles - 1) / kSortChunkTiles;
+    const int64_t chunks = sort_chunks_max(shape.tiles);
     uint32_t* chunk_sums = c.take<uint32_t>((size_t)kSortMaxBins * (size_t)chunks);
 
     const int passes = radix_sort_passes(key_bits);
-    // The second scan level runs inside the first level's launch for small sorts.  When the pair count lives on
+    // The second scan level is the scatter's for up to kSortSumChunks chunks.  When the pair count lives on
     // the device (the plan's candidates: a few per cent of the rows the buffers are sized for), "small" cannot be
-    // known here; the launch is then fused up to a size at which the lone workgroup costs at most a tenth of a pass.
-    const bool fused_scan = chunks <= kSortFusedScanChunks || (m_dev != nullptr && chunks <= kSortFusedScanChunksDev);
+    // known here; the second level then runs inside the first one's launch if it turns out larger, up to a size at
+    // which the lone workgroup costs at most a tenth of a pass.
+    const bool fused_scan = chunks <= kSortSumChunks || (m_dev != nullptr && chunks <= kSortFusedScanChunksDev);
     int shift = 0;
     const bool from_rows = src.rows != nullptr;
     // from_rows: source -> A -> B -> A ...; else A -> B -> A ...
