@@ -29,25 +29,27 @@ __device__ __forceinline__ void add_saturating(uint32_t* p, uint32_t v, int32_t*
     }
 }
 
-__device__ __forceinline__ int plan_table_of(const int64_t* __restrict__ offsets, int T, int64_t B, int64_t i)
-{
-    int lo = 0, hi = T - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (offsets[(int64_t)mid * B] <= i) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
+// Bad offsets count nothing, so all of them are checked before the first count.  Few segments and blocks: every
+// block of the histogram checks them all itself (SELF).  Otherwise the blocks of this kernel check a share each and leave
+// their verdicts, which every block of the histogram reads: no flag to set beforehand.
+constexpr int kCheckBlocksMax = 256;          // one verdict per thread of a histogram block at most
+constexpr int kCheckPerThread = 4;
+constexpr int64_t kCheckSelfSegments = 8192;  // 8 segments to a thread of a histogram block
+constexpr int64_t kCheckSelfBlocks = 256;     // at most 16 MB read out of the L2s in all; a launch costs 4 to 5 us
 
 __global__ __launch_bounds__(kBlock) void plan_check_offsets_kernel(
-    const int64_t* __restrict__ offsets, int64_t S, int64_t n, int32_t* ok_flag, int32_t* status)
+    const int64_t* __restrict__ offsets, int64_t S, int64_t n, int32_t* __restrict__ verdicts, int32_t* status)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool bad = false;
     for (int64_t s = tid; s < S; s += stride) bad |= offsets[s] > offsets[s + 1];
     if (tid == 0) bad |= offsets[0] != 0 || offsets[S] != n;
-    if (ballot(bad) != 0 && lane_id() == 0) { report(status, FS_DEV_BAD_OFFSETS); atomicExch(ok_flag, 0); }
+    const int any = __syncthreads_or(bad);
+    if (threadIdx.x == 0) {
+        verdicts[blockIdx.x] = any ? 1 : 0;
+        if (any) report(status, FS_DEV_BAD_OFFSETS);
+    }
 }
 
 constexpr int kHistSlotBits = 14;
@@ -73,10 +75,11 @@ constexpr int kHistBlock = 1024;          // 16 waves per span: a span per 256 t
 // those 67 M ids; counting the most popular rows in registers changed nothing (the LDS is not the limit).
 typedef int64_t Id2 __attribute__((ext_vector_type(2)));
 
+template <bool SELF>
 __global__ __launch_bounds__(kHistBlock) void plan_histogram_kernel(
     const int64_t* __restrict__ ids, const int64_t* __restrict__ offsets, int T, int64_t B,
     const int64_t* __restrict__ row_base, int64_t n, int64_t R, int64_t span, uint32_t* __restrict__ counts,
-    const int32_t* __restrict__ ok_flag, int32_t* status)
+    const int32_t* __restrict__ verdicts, int num_verdicts, int32_t* status)
 {
     constexpr int kSlots = 1 << kHistSlotBits;
     constexpr int kRestBits = 32 - kHistSlotBits;                   // bits of a row's hash that its slot does not give
@@ -85,16 +88,26 @@ __global__ __launch_bounds__(kHistBlock) void plan_histogram_kernel(
     constexpr uint32_t kCountMax = (1u << (32 - kCountShift)) - 1u;
     __shared__ uint32_t table[kSlots];         // 0 = free
     __shared__ int span_tables[2];
-    if (*ok_flag == 0) return;                 // bad offsets: count nothing
+    bool bad = false;
+    if constexpr (SELF) {
+        const int S = (int)(T * B);            // at most kCheckSelfSegments
+        for (int sg = threadIdx.x; sg < S; sg += kHistBlock) bad |= offsets[sg] > offsets[sg + 1];
+        if (threadIdx.x == 0) bad |= offsets[0] != 0 || offsets[S] != n;
+    } else {
+        bad = (int)threadIdx.x < num_verdicts && verdicts[threadIdx.x] != 0;
+    }
     const int64_t base = (int64_t)blockIdx.x * span;
     const int64_t end = base + span < n ? base + span : n;
     if (base >= end) return;
     for (int s = threadIdx.x; s < kSlots; s += kHistBlock) table[s] = 0;
-    if (threadIdx.x == 0) {
-        span_tables[0] = plan_table_of(offsets, T, B, base);
-        span_tables[1] = plan_table_of(offsets, T, B, end - 1);
+    if (threadIdx.x < 2 * kWave) {              // a wave each for the first and the last id's table
+        const int t = wave_table_of(offsets, T, B, threadIdx.x < kWave ? base : end - 1);
+        if (lane_id() == 0) span_tables[wave_id()] = t;
     }
-    __syncthreads();
+    if (__syncthreads_or(bad)) {               // bad offsets (they keep the search above in range): count nothing
+        if (SELF && blockIdx.x == 0 && threadIdx.x == 0) report(status, FS_DEV_BAD_OFFSETS);
+        return;
+    }
     const int t_lo = __builtin_amdgcn_readfirstlane(span_tables[0]);
     const int t_hi = __builtin_amdgcn_readfirstlane(span_tables[1]);
     int32_t faults = 0;
@@ -233,7 +246,9 @@ __global__ __launch_bounds__(kHistBlock) void plan_histogram_kernel(
     }
 }
 
-// Span length for n ids: batches keep 32 k spans (many blocks).  From one 64 k span for each of the two
+// Span length for n ids: a span for every CU up to 32 k ids each (one block of 8192 ids spends its time on its 16 k
+// slots and a chain of rounds: 14.9 us, four blocks of 2048 with the offsets checked inside 8.6; 4.2 M ids 105 us at
+// 16 k as at 32 k), then 32 k spans.  From one 64 k span for each of the two
 // blocks a CU holds, spans of up to 128 k ids, shortened so that their number is a multiple of the CU count
 // where that is possible.  A popular row is flushed once per span, so a planning pass over very many ids
 // (from 2^27) takes spans of up to 512 k ids, all of one length and a whole number of rounds over the chip's
@@ -249,7 +264,10 @@ constexpr int64_t kHistCus = 256;
 
 static int64_t hist_span(int64_t n)
 {
-    if (n < 2 * kHistCus * (kHistSpanLarge / 2)) return kHistSpanSmall;   // under one 64 k span for every CU, twice over
+    if (n < 2 * kHistCus * (kHistSpanLarge / 2)) {                // under one 64 k span for every CU, twice over
+        const int64_t share = (n / kHistCus + 2047) / 2048 * 2048;
+        return share < kHistSpanSmall ? (share > 2048 ? share : 2048) : kHistSpanSmall;
+    }
     const int64_t longest = n >= kHistHugeFrom ? kHistSpanHuge : kHistSpanLarge;
     const int64_t per_round = n >= kHistHugeFrom ? 2 * kHistCus : kHistCus;
     const int64_t rounds = (n + per_round * longest - 1) / (per_round * longest);
@@ -526,27 +544,6 @@ __global__ __launch_bounds__(kBlock) void plan_emit_kernel(
     if (blockIdx.x == 0 && threadIdx.x == 0) *num_selected = k;
 }
 
-__global__ void plan_set_flag_kernel(int32_t* flag) { *flag = 1; }
-
-// The same check by one block that also sets the flag itself (few segments: one launch instead of two).
-constexpr int64_t kCheckOneBlockMax = 8192;
-__global__ __launch_bounds__(kHistBlock) void plan_check_offsets_one_kernel(
-    const int64_t* __restrict__ offsets, int64_t S, int64_t n, int32_t* ok_flag, int32_t* status)
-{
-    __shared__ int any_bad;
-    if (threadIdx.x == 0) any_bad = 0;
-    __syncthreads();
-    bool bad = false;
-    for (int64_t s = threadIdx.x; s < S; s += kHistBlock) bad |= offsets[s] > offsets[s + 1];
-    if (threadIdx.x == 0) bad |= offsets[0] != 0 || offsets[S] != n;
-    if (ballot(bad) != 0 && lane_id() == 0) any_bad = 1;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        *ok_flag = any_bad ? 0 : 1;
-        if (any_bad) report(status, FS_DEV_BAD_OFFSETS);
-    }
-}
-
 // ---- tier planner -----------------------------------------------------------
 // After the same compaction and sort, rows stand in descending frequency order with
 // key = ~count.  The breakpoints are thresholds on the count (found on the host from the
@@ -782,7 +779,7 @@ extern "C" fs_status fs_plan_replication(
     if (sel && (budget_bytes < 0 || bytes_per_row < 1)) return FS_ERR_SIZE;
 
     Carver ws(workspace);
-    int32_t* ok_flag = ws.take<int32_t>(1);
+    int32_t* verdicts = ws.take<int32_t>(kCheckBlocksMax);
     const PlanScratch p = take_plan_scratch(ws, sel ? R : 0);
     if (!workspace) { *workspace_bytes = ws.used; return FS_OK; }
     if (*workspace_bytes < ws.used || (reinterpret_cast<uintptr_t>(workspace) & 255)) return FS_ERR_WORKSPACE;
@@ -797,20 +794,19 @@ extern "C" fs_status fs_plan_replication(
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (acc) {
         const int64_t S = (int64_t)T * B;
-        if (S <= kCheckOneBlockMax) {
-            FS_LAUNCH("plan_check_offsets", plan_check_offsets_one_kernel, dim3(1), dim3(kHistBlock), s,
-                      offsets, S, n, ok_flag, dev_status);
+        const int64_t span = hist_span(n);
+        const int64_t blocks = (n + span - 1) / span;
+        if (n > 0 && S <= kCheckSelfSegments && blocks <= kCheckSelfBlocks) {
+            FS_LAUNCH("plan_histogram", plan_histogram_kernel<true>, dim3((unsigned)blocks), dim3(kHistBlock), s,
+                      ids, offsets, (int)T, (int64_t)B, row_base, n, R, span, counts, verdicts, 0, dev_status);
         } else {
-            FS_LAUNCH("plan_set_flag", plan_set_flag_kernel, dim3(1), dim3(1), s, ok_flag);
-            const unsigned grid = (unsigned)((S + kBlock - 1) / kBlock < 1024 ? (S + kBlock - 1) / kBlock : 1024);
-            FS_LAUNCH("plan_check_offsets", plan_check_offsets_kernel, dim3(grid), dim3(kBlock), s,
-                      offsets, S, n, ok_flag, dev_status);
-        }
-        if (n > 0) {
-            const int64_t span = hist_span(n);
-            const int64_t blocks = (n + span - 1) / span;
-            FS_LAUNCH("plan_histogram", plan_histogram_kernel, dim3((unsigned)blocks), dim3(kHistBlock), s,
-                      ids, offsets, (int)T, (int64_t)B, row_base, n, R, span, counts, ok_flag, dev_status);
+            const int64_t wanted = (S + kBlock * kCheckPerThread - 1) / (kBlock * kCheckPerThread);
+            const int grid = (int)(wanted < kCheckBlocksMax ? wanted : kCheckBlocksMax);
+            FS_LAUNCH("plan_check_offsets", plan_check_offsets_kernel, dim3((unsigned)grid), dim3(kBlock), s,
+                      offsets, S, n, verdicts, dev_status);
+            if (n > 0)
+                FS_LAUNCH("plan_histogram", plan_histogram_kernel<false>, dim3((unsigned)blocks), dim3(kHistBlock), s,
+                          ids, offsets, (int)T, (int64_t)B, row_base, n, R, span, counts, verdicts, grid, dev_status);
         }
     }
     if (sel) {

@@ -86,3 +86,29 @@ def test_a_workspace_for_more_rows_serves_fewer():
                                             ctypes.c_int64(1), None, None, None, None, ctypes.byref(size), None, None) == 0
         sizes.append(size.value)
     assert sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("T,B,n", [(1, 1, 1), (1, 8, 2048), (3, 5, 2049), (2, 4096, 100_000), (8193, 1, 100_000), (70, 200, 524_289),
+                                   (5, 3, 256 * 32768), (5, 3, 256 * 32768 + 1), (5, 300_000, 3_000_001)])
+@pytest.mark.parametrize("bad", [False, True])
+def test_histogram_sizes(G, T, B, n, bad):
+    """The offsets checked by the counting blocks themselves or by blocks of their own, spans of every length below
+    the longest; bad offsets (the last pair of them) count nothing either way."""
+    import paper_2301_02959_amd as fs
+    rng = np.random.default_rng(T + n)
+    E = 4001
+    offsets = np.concatenate([[0], np.sort(rng.integers(0, n + 1, T * B - 1)), [n]]).astype(np.int64)
+    if bad:
+        offsets[-2] = n + 1
+        if T * B == 1:
+            offsets[-1] = n + 1
+    ids = np.where(rng.random(n) < 0.5, 7, rng.integers(0, E, n)).astype(np.int64)
+    row_base = (np.arange(T + 1) * E).astype(np.int64)
+    counts = rng.integers(0, 3, T * E).astype(np.uint32)
+    dev = torch.from_numpy(counts.view(np.int32).copy()).to(G.DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    fs.fs_plan_replication(G.to_dev(ids), G.to_dev(offsets), T, B, G.to_dev(row_base), n, T * E, dev, fs.FS_PLAN_ACCUMULATE, dev_status=st)
+    oc = counts.copy()
+    orc, ost, _ = oracle.plan_replication(ids, offsets, T, B, row_base, T * E, oc, oracle.PLAN_ACCUMULATE, n=n)
+    assert orc == 0 and int(st.item()) == ost and (ost != 0) == bad
+    assert np.array_equal(dev.cpu().numpy().view(np.uint32), oc)
