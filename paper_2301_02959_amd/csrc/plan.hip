@@ -570,21 +570,29 @@ __global__ __launch_bounds__(kBlock) void tiers_tile_sums_kernel(
     const uint32_t* keys = sort_result_in_b(*count_bits) ? keys_b : keys_a;
     __shared__ uint64_t part[kWavesPerBlock];
     const int64_t K = *num_candidates;
-    const int64_t base = (int64_t)blockIdx.x * kSumTile;
-    uint64_t sum = 0;
-    for (int i = threadIdx.x; i < kSumTile; i += kBlock) {
-        const int64_t k = base + i;
-        if (k < K) sum += (uint32_t)~keys[k];
+    // candidates are usually a few per cent of the rows: the blocks walk the tiles that hold any (a block for every
+    // 4096 rows: 13 us for 40 M rows, now 6.5, and the scan of the sums 16, now 4.4)
+    for (int64_t tile = blockIdx.x; tile * kSumTile < K; tile += gridDim.x) {
+        const int64_t base = tile * kSumTile;
+        uint64_t sum = 0;
+#pragma unroll
+        for (int i = 0; i < kSumTile / kBlock; ++i) {
+            const int64_t k = base + i * kBlock + threadIdx.x;
+            sum += k < K ? (uint32_t)~keys[k] : 0u;
+        }
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off);
+        if (lane_id() == 0) part[wave_id()] = sum;
+        __syncthreads();
+        if (threadIdx.x == 0) tile_sum[tile] = part[0] + part[1] + part[2] + part[3];
+        __syncthreads();
     }
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off);
-    if (lane_id() == 0) part[wave_id()] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) tile_sum[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
 }
 
-// tile_sum[t] -> sum of the tiles before t, tile_sum[tiles] = the grand total.  One block.
-__global__ __launch_bounds__(kScanBlock) void tiers_scan_sums_kernel(uint64_t* __restrict__ tile_sum, int64_t tiles)
+// tile_sum[t] -> sum of the tiles before t, for the tiles that hold candidates, and the grand total behind them.  One block.
+__global__ __launch_bounds__(kScanBlock) void tiers_scan_sums_kernel(uint64_t* __restrict__ tile_sum,
+                                                                     const int64_t* __restrict__ num_candidates)
 {
+    const int64_t tiles = (*num_candidates + kSumTile - 1) / kSumTile;
     __shared__ uint64_t wave_tot[kScanBlock / kWave];
     const int lane = lane_id();
     const int w = wave_id();
@@ -643,7 +651,11 @@ __device__ __forceinline__ uint64_t prefix_count(const uint32_t* __restrict__ ke
 {
     const int64_t t = k / kSumTile;
     uint64_t part = 0;
-    for (int64_t i = t * kSumTile + lane_id(); i < k; i += kWave) part += (uint32_t)~keys[i];
+#pragma unroll 16
+    for (int j = 0; j < kSumTile / kWave; ++j) {
+        const int64_t i = t * kSumTile + j * kWave + lane_id();
+        part += i < k ? (uint32_t)~keys[i] : 0u;
+    }
     for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
     return tile_sum[t] + part;
 }
@@ -654,7 +666,10 @@ __device__ __forceinline__ i128 cum_memory(const TierConsts& c, int64_t k, uint6
     return (i128)k * (i128)c.static_term - (i128)c.dyn_factor * (i128)prefix;
 }
 
-__global__ __launch_bounds__(kWave) void tiers_cuts_kernel(
+// The searches are chains of dependent loads, so each has a wave of its own: breakpoints A, C and FLEX and point B.
+// The budget and the sums of the two tiers follow in the first wave, the sums' partial tiles with 16 loads in flight:
+// 39 -> 27 us with 1.5 M candidates (one wave doing all of it, and every row of point B's tile tested on its own).
+__global__ __launch_bounds__(kBlock) void tiers_cuts_kernel(
     const uint32_t* __restrict__ keys_a, const uint32_t* __restrict__ keys_b, const uint32_t* __restrict__ count_bits,
     const int64_t* __restrict__ num_candidates,
     const uint64_t* __restrict__ tile_sum, const TierConsts c, int64_t* __restrict__ cuts)
@@ -666,48 +681,52 @@ __global__ __launch_bounds__(kWave) void tiers_cuts_kernel(
     auto at_least = [&](uint64_t thr) {
         return wave_partition_point(0, K, [&](int64_t i) { return (uint64_t)(uint32_t)~keys[i] >= thr; });
     };
-    const int64_t kA = at_least(c.thr_a);
-    const int64_t kC = at_least(c.thr_c);
-    const int64_t kF = at_least(c.thr_f);
-
-    // point B: the summed terms are <= 0 on a prefix of k = 0 .. K.  Tile boundaries first
-    // (k_t = min(t * tile, K), P(k_t) = tile_sum[t]), then the rows of the one tile that holds it.
-    const int64_t t_false = wave_partition_point(0, tiles + 1, [&](int64_t t) {
-        const int64_t k = t * kSumTile < K ? t * kSumTile : K;
-        return cum_memory(c, k, tile_sum[t]) <= 0;
-    });
-    int64_t kB;
-    if (t_false > tiles) {
-        kB = K;
-    } else {
-        const int64_t t0 = t_false - 1;                                  // boundary t0 holds, t0 + 1 does not
-        const int64_t first = t0 * kSumTile;
-        constexpr int kPer = kSumTile / kWave;                           // consecutive rows per lane
-        uint64_t mine = 0;
-        for (int q = 0; q < kPer; ++q) {
-            const int64_t i = first + (int64_t)lane * kPer + q;
-            if (i < K) mine += (uint32_t)~keys[i];
-        }
-        uint64_t incl = mine;
-        for (int off = 1; off < kWave; off <<= 1) {
-            const uint64_t up = __shfl_up(incl, off);
-            if (lane >= off) incl += up;
-        }
-        uint64_t run = tile_sum[t0] + incl - mine;
-        int64_t best = first;                                            // cum(first) <= 0 is known
-        for (int q = 0; q < kPer; ++q) {
-            const int64_t i = first + (int64_t)lane * kPer + q;
-            if (i < K) {
-                run += (uint32_t)~keys[i];
-                if (cum_memory(c, i + 1, run) <= 0) best = i + 1;
-            }
-        }
-        for (int off = 32; off > 0; off >>= 1) {
-            const int64_t other = __shfl_xor(best, off);
-            best = other > best ? other : best;
-        }
-        kB = best;
+    __shared__ int64_t found[kWavesPerBlock];
+    const int w = __builtin_amdgcn_readfirstlane(wave_id());
+    if (w < 3) {
+        const int64_t at = at_least(w == 0 ? c.thr_a : w == 1 ? c.thr_c : c.thr_f);
+        if (lane == 0) found[w] = at;
     }
+    if (w == 3) {
+        // point B: the summed terms are <= 0 on a prefix of k = 0 .. K.  Tile boundaries first
+        // (k_t = min(t * tile, K), P(k_t) = tile_sum[t]), then pieces of 64 rows of the one tile that holds it,
+        // then the rows of the one piece.
+        const int64_t t_false = wave_partition_point(0, tiles + 1, [&](int64_t t) {
+            const int64_t k = t * kSumTile < K ? t * kSumTile : K;
+            return cum_memory(c, k, tile_sum[t]) <= 0;
+        });
+        int64_t kB = K;
+        if (t_false <= tiles) {
+            const int64_t t0 = t_false - 1;                              // boundary t0 holds, t0 + 1 does not
+            const int64_t first = t0 * kSumTile;
+            constexpr int kPer = kSumTile / kWave;                       // consecutive rows per lane: a piece
+            static_assert(kPer == kWave, "a piece has a row for every lane");
+            auto wave_inclusive = [&](uint64_t v) {
+                for (int off = 1; off < kWave; off <<= 1) {
+                    const uint64_t up = __shfl_up(v, off);
+                    if (lane >= off) v += up;
+                }
+                return v;
+            };
+            uint64_t mine = 0;
+#pragma unroll 16
+            for (int q = 0; q < kPer; ++q) {
+                const int64_t i = first + (int64_t)lane * kPer + q;
+                mine += i < K ? (uint32_t)~keys[i] : 0u;
+            }
+            const uint64_t upto = tile_sum[t0] + wave_inclusive(mine);
+            const int64_t piece_end = first + (int64_t)(lane + 1) * kPer;
+            const int whole = __popcll(ballot(cum_memory(c, piece_end < K ? piece_end : K, upto) <= 0));   // < 64
+            const uint64_t before = whole == 0 ? tile_sum[t0] : __shfl(upto, whole - 1);
+            const int64_t i = first + (int64_t)whole * kPer + lane;
+            const uint64_t run = before + wave_inclusive(i < K ? (uint32_t)~keys[i] : 0u);
+            kB = first + (int64_t)whole * kPer + __popcll(ballot(i < K && cum_memory(c, i + 1, run) <= 0));
+        }
+        if (lane == 0) found[3] = kB;
+    }
+    __syncthreads();
+    if (w != 0) return;
+    const int64_t kA = found[0], kC = found[1], kF = found[2], kB = found[3];
 
     const int64_t gran = c.granule;
     int64_t n_dp, n_flex = 0;
@@ -747,12 +766,25 @@ __global__ __launch_bounds__(kBlock) void tiers_emit_kernel(
     const int64_t n_dp = cuts[5];
     const int64_t n_both = n_dp + cuts[6];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_both; i += stride) {
-        const uint32_t g = vals[i];
-        if (i < cap) sorted_rows[i] = (int64_t)g;
+    // four rows to a thread in flight: each is a load of the row and, for a replicated one, a load of its entry
+    constexpr int kAhead = 4;
+    for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i0 < n_both; i0 += kAhead * stride) {
+        uint32_t g[kAhead], tag[kAhead];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) g[q] = i0 + q * stride < n_both ? vals[i0 + q * stride] : 0u;
         if (placement != nullptr) {
-            if (i < n_dp) placement[g] &= FS_OWNER_MASK;
-            else placement[g] = (1u << FS_TIER_SHIFT) | (uint32_t)((i - n_dp) % W);
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) {
+                const int64_t i = i0 + q * stride;
+                tag[q] = i < n_dp ? placement[g[q]] & FS_OWNER_MASK : (1u << FS_TIER_SHIFT) | ((uint32_t)(i - n_dp) % (uint32_t)W);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const int64_t i = i0 + q * stride;
+            if (i >= n_both) break;
+            if (i < cap) sorted_rows[i] = (int64_t)g[q];
+            if (placement != nullptr) placement[g[q]] = tag[q];
         }
     }
 }
@@ -870,10 +902,11 @@ extern "C" fs_status fs_plan_tiers(
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (fs_status rc = sort_candidates(counts, R, 0, q, s); rc != FS_OK) return rc;
-    FS_LAUNCH("tiers_tile_sums", tiers_tile_sums_kernel, dim3((unsigned)sum_tiles), dim3(kBlock), s,
+    const unsigned sum_grid = sum_tiles < 2048 ? (unsigned)sum_tiles : 2048u;        // 8 blocks per CU
+    FS_LAUNCH("tiers_tile_sums", tiers_tile_sums_kernel, dim3(sum_grid), dim3(kBlock), s,
               q.keys_a, q.keys_b, q.count_bits, q.num_cand, tile_sum);
-    FS_LAUNCH("tiers_scan_sums", tiers_scan_sums_kernel, dim3(1), dim3(kScanBlock), s, tile_sum, sum_tiles);
-    FS_LAUNCH("tiers_cuts", tiers_cuts_kernel, dim3(1), dim3(kWave), s, q.keys_a, q.keys_b, q.count_bits, q.num_cand,
+    FS_LAUNCH("tiers_scan_sums", tiers_scan_sums_kernel, dim3(1), dim3(kScanBlock), s, tile_sum, q.num_cand);
+    FS_LAUNCH("tiers_cuts", tiers_cuts_kernel, dim3(1), dim3(kBlock), s, q.keys_a, q.keys_b, q.count_bits, q.num_cand,
               tile_sum, c, cuts);
     FS_LAUNCH("tiers_emit", tiers_emit_kernel, dim3(1024), dim3(kBlock), s, q.vals_a, q.vals_b, q.count_bits, cuts, cap, (int)p.W,
               sorted_rows, placement);
