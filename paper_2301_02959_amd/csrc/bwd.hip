@@ -792,6 +792,10 @@ __global__ __launch_bounds__(kBlock) void bwd_singletons_kernel(
 
 // One wave per chunk; a wave whose chunk starts a spilling run (one that goes on into the next
 // chunk) adds the carries of the chunks the run goes on into, left to right.
+// VL: consecutive columns per lane.  Rows of up to 64 or 128 columns take 1 or 2, so that all lanes of the wave carry a
+// share and the same registers hold four times or twice as many carries in flight: the longest run's chain of rounds of
+// loads is the kernel's time.
+template <int VL>
 __global__ __launch_bounds__(kBlock) void bwd_fold_kernel(
     const uint32_t* __restrict__ keys, int64_t m, int64_t chunks,
     const uint32_t* __restrict__ block_base, const uint32_t* __restrict__ chunk_local,
@@ -829,20 +833,33 @@ __global__ __launch_bounds__(kBlock) void bwd_fold_kernel(
         if (keys[mid * kChunk] == key) lo = mid; else hi = mid;
     }
     const int64_t last_chunk = lo;
-    constexpr int kAhead = 32;                   // carries in flight: the longest run's chain is latency-bound
-    for (int col = lane_id() * 4; col < D; col += kWave * 4) {
-        f32x4 acc = *reinterpret_cast<const f32x4*>(row_grads + u * D + col);
+    typedef float Cols __attribute__((ext_vector_type(VL)));
+    constexpr int kAhead = 128 / VL;             // carries in flight: the longest run's chain is latency-bound
+    constexpr int kRest = 8;
+    for (int col = lane_id() * VL; col < D; col += kWave * VL) {
+        Cols acc = *reinterpret_cast<const Cols*>(row_grads + u * D + col);
         int64_t cc = chunk + 1;
         for (; cc + kAhead <= last_chunk + 1; cc += kAhead) {
-            f32x4 part[kAhead];
+            Cols part[kAhead];
 #pragma unroll
             for (int j = 0; j < kAhead; ++j)
-                part[j] = *reinterpret_cast<const f32x4*>(carry + (cc + j) * D + col);
+                part[j] = *reinterpret_cast<const Cols*>(carry + (cc + j) * D + col);
 #pragma unroll
             for (int j = 0; j < kAhead; ++j) acc = acc + part[j];
         }
-        for (; cc <= last_chunk; ++cc) acc = acc + *reinterpret_cast<const f32x4*>(carry + cc * D + col);
-        *reinterpret_cast<f32x4*>(row_grads + u * D + col) = acc;
+        for (; cc + 1 <= last_chunk; cc += kRest) {              // the rest, eight at a time, the last of them repeated
+            Cols part[kRest];
+#pragma unroll
+            for (int j = 0; j < kRest; ++j) {
+                const int64_t at = cc + j < last_chunk ? cc + j : last_chunk;
+                part[j] = *reinterpret_cast<const Cols*>(carry + at * D + col);
+            }
+#pragma unroll
+            for (int j = 0; j < kRest; ++j)
+                if (cc + j <= last_chunk) acc = acc + part[j];
+        }
+        if (cc == last_chunk) acc = acc + *reinterpret_cast<const Cols*>(carry + cc * D + col);   // most runs: one carry
+        *reinterpret_cast<Cols*>(row_grads + u * D + col) = acc;
     }
 }
 
@@ -966,6 +983,19 @@ static fs_status launch_singletons_update(fs_dtype dtype, int optimizer, const v
                                                      uniq_rows, cap, applied, stream);
 }
 
+static fs_status launch_fold(const uint32_t* keys, int64_t m, int64_t chunks, const uint32_t* block_base,
+                             const uint32_t* chunk_local, float* row_grads, int D, int64_t cap, const float* carry, hipStream_t s)
+{
+    const dim3 grid((unsigned)((chunks + kWavesPerBlock - 1) / kWavesPerBlock));
+#define FS_FOLD(VL) \
+    FS_LAUNCH("bwd_fold", bwd_fold_kernel<VL>, grid, dim3(kBlock), s, keys, m, chunks, block_base, chunk_local, row_grads, D, cap, carry)
+    if (D <= kWave) FS_FOLD(1);
+    else if (D <= 2 * kWave) FS_FOLD(2);                  // D is a multiple of 4: rows are whole 16-byte pieces
+    else FS_FOLD(4);
+#undef FS_FOLD
+    return FS_OK;
+}
+
 // Everything after the sort: (keys, vals) are the lookups in (row, position) order.
 struct BwdScratch {
     uint32_t* chunk_local;
@@ -1019,8 +1049,8 @@ static fs_status bwd_after_sort(const void* grad_out, int64_t n, int D, fs_dtype
         else FS_SINGLE_UPDATE(64);
 #undef FS_SINGLE_UPDATE
         if (rc != FS_OK) return rc;
-        FS_LAUNCH("bwd_fold", bwd_fold_kernel, dim3(wave_grid), dim3(kBlock), s,
-                  keys, m, chunks, w.block_base, w.chunk_local, row_grads, D, cap_unique, w.carry);
+        rc = launch_fold(keys, m, chunks, w.block_base, w.chunk_local, row_grads, D, cap_unique, w.carry, s);
+        if (rc != FS_OK) return rc;
         UpdateArgs rest = *update;               // the optimizer step on the rows whose gradient is in row_grads
         rest.uniq_rows = uniq_rows; rest.row_grads = row_grads; rest.cap = cap_unique; rest.num_unique = num_unique;
         rest.skip = applied;
@@ -1040,9 +1070,7 @@ static fs_status bwd_after_sort(const void* grad_out, int64_t n, int D, fs_dtype
 #undef FS_SINGLE
         if (rc != FS_OK) return rc;
     }
-    if (variant == 0)
-        FS_LAUNCH("bwd_fold", bwd_fold_kernel, dim3(wave_grid), dim3(kBlock), s,
-                  keys, m, chunks, w.block_base, w.chunk_local, row_grads, D, cap_unique, w.carry);
+    if (variant == 0) return launch_fold(keys, m, chunks, w.block_base, w.chunk_local, row_grads, D, cap_unique, w.carry, s);
     return FS_OK;
 }
 

@@ -109,3 +109,19 @@ def test_update_leaves_the_walk_only_repeated_rows(G, dt, D):
     assert int(st.item()) == 0 and len(got[0][2]) == len(np.unique(rows))
     for a, b in zip(*got):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.parametrize("D", [4, 64, 72, 128, 132, 256, 260])
+@pytest.mark.parametrize("first", [0, 100])
+def test_runs_over_many_chunks(G, D, first):
+    """Runs that go on into 1, 2, 8, 9, 31 .. 130 further chunks: every length at which the fold's rounds change, for
+    rows of one, two and four columns to a lane."""
+    rng = np.random.default_rng(D + first)
+    more = [1, 2, 7, 8, 9, 10, 16, 17, 31, 32, 33, 40, 63, 64, 65, 96, 127, 128, 129, 130, 300]
+    rows = np.repeat(np.arange(len(more) + 1), [first] + [k * CHUNK for k in more])
+    rows = rows[rows > 0] if first == 0 else rows
+    m = len(rows)
+    pos = (np.arange(m) % 1021).astype(np.int32)
+    pos = pos[np.lexsort((pos, rows))]
+    gnp, gt = _np_grad(rng.standard_normal((1021, D)).astype(np.float32), "f32")
+    _check(G, gnp, gt, rows, pos, 0, m, len(more) + 2, "f32", atomic_too=False)
