@@ -249,18 +249,44 @@ __global__ __launch_bounds__(kBlock) void replica_clear_kernel(int32_t* __restri
     for (int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x; r < R; r += step) slot_of_row[r] = -1;
 }
 
-// The owner bits of every tier-0 placement entry = the row's slot, FS_OWNER_MASK if it has none.
+// The owner bits of every tier-0 placement entry = the row's slot, FS_OWNER_MASK if it has none.  The placement is read
+// four entries to a lane and kTagAhead loads in flight (one entry at a time, each behind the last one's slot: 68 us for
+// 40 M rows, 160 MB); tier-0 entries are few, their slots and the new entries are accesses of their own.
+constexpr int kTagAhead = 4;
 __global__ __launch_bounds__(kBlock) void replica_tag_slots_kernel(
     uint32_t* __restrict__ placement, int64_t R, const int32_t* __restrict__ slot_of_row, int32_t* status)
 {
-    const int64_t step = (int64_t)gridDim.x * kBlock;
     int32_t faults = 0;
-    for (int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x; r < R; r += step) {
-        if ((placement[r] >> FS_TIER_SHIFT) != FS_TIER_GLOBAL) continue;
+    auto tag = [&](int64_t r, uint32_t entry) {
+        if ((entry >> FS_TIER_SHIFT) != FS_TIER_GLOBAL) return;
         int32_t slot = slot_of_row[r];
         if (slot >= 0 && (uint32_t)slot >= FS_OWNER_MASK) { faults |= FS_DEV_BAD_ID; slot = -1; }   // no such slot number
         placement[r] = slot >= 0 ? (uint32_t)slot : FS_OWNER_MASK;
+    };
+    const int64_t step = (int64_t)gridDim.x * kBlock;
+    const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t to_aligned = (int64_t)((16 - (reinterpret_cast<uintptr_t>(placement) & 15)) & 15) / 4;
+    const int64_t head = to_aligned < R ? to_aligned : R;            // entries before the first 16-byte boundary
+    const int64_t quads = (R - head) / 4;
+    const u32x4* body = reinterpret_cast<const u32x4*>(placement + head);
+    for (int64_t q0 = tid; q0 < quads; q0 += kTagAhead * step) {
+        u32x4 e[kTagAhead];
+#pragma unroll
+        for (int a = 0; a < kTagAhead; ++a) {
+            const int64_t q = q0 + a * step;
+            e[a] = body[q < quads ? q : q0];
+        }
+#pragma unroll
+        for (int a = 0; a < kTagAhead; ++a) {
+            const int64_t q = q0 + a * step;
+            if (q >= quads) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) tag(head + 4 * q + i, e[a][i]);
+        }
     }
+    if (tid < head) tag(tid, placement[tid]);
+    const int64_t tail = head + 4 * quads + tid;
+    if (tail < R) tag(tail, placement[tail]);                        // at most three
     if (ballot(faults != 0) != 0 && lane_id() == 0) report(status, FS_DEV_BAD_ID);
 }
 
@@ -413,7 +439,8 @@ extern "C" fs_status fs_replica_tag_slots(
     if (!placement || !slot_of_row) return FS_ERR_NULL;
     if (R < 1) return FS_ERR_SIZE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t grid = (R + kBlock - 1) / kBlock;
+    const int64_t per_block = kBlock * 4 * kTagAhead;
+    const int64_t grid = (R + per_block - 1) / per_block;
     FS_LAUNCH("replica_tag_slots", replica_tag_slots_kernel, dim3((unsigned)(grid < 16384 ? grid : 16384)), dim3(kBlock), s,
               placement, R, slot_of_row, dev_status);
     return FS_OK;

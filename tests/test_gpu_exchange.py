@@ -315,3 +315,23 @@ def test_slot_faults(G):
     assert fs.fs_route_bucketize_slots(None, off0, 1, 1, rb, pl, 0, 1, 1, 0, bo, None, None, None, None, st) == 0
     torch.cuda.synchronize()
     assert bo.tolist() == [0, 0]
+
+
+@pytest.mark.parametrize("skip", [0, 1, 2, 3])
+@pytest.mark.parametrize("R", [1, 2, 3, 4, 5, 7, 4095, 4096, 4099, 300_007])
+def test_tag_slots_at_every_alignment(G, R, skip):
+    """The placement is read 16 bytes at a time: any first entry, any number of entries, neighbours untouched."""
+    import paper_2301_02959_amd as fs
+    rng = np.random.default_rng(R + skip)
+    full = rng.integers(0, 1 << 32, R + 8, dtype=np.uint64).astype(np.uint32)
+    full[rng.random(R + 8) < 0.4] &= np.uint32(0x3FFFFFFF)                       # tier 0
+    slots = np.where(rng.random(R) < 0.5, -1, rng.integers(0, 0x3FFFFFFF, R)).astype(np.int32)
+    slots[0] = 0x3FFFFFFF                                                        # no such slot number
+    dev = torch.from_numpy(full.view(np.int32).copy()).to(G.DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    fs.fs_replica_tag_slots(dev[skip:skip + R], torch.from_numpy(slots).to(G.DEV), st)
+    part = np.ascontiguousarray(full[skip:skip + R])
+    orc, ost = oracle.replica_tag_slots(part, slots)
+    expected = np.concatenate([full[:skip], part, full[skip + R:]])
+    assert orc == 0 and int(st.item()) == ost
+    assert np.array_equal(dev.cpu().numpy().view(np.uint32), expected)
