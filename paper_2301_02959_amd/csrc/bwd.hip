@@ -794,7 +794,7 @@ __global__ __launch_bounds__(kBlock) void bwd_singletons_kernel(
 // chunk) adds the carries of the chunks the run goes on into, left to right.
 // VL: consecutive columns per lane.  Rows of up to 64 or 128 columns take 1 or 2, so that all lanes of the wave carry a
 // share and the same registers hold four times or twice as many carries in flight: the longest run's chain of rounds of
-// loads is the kernel's time.
+// loads is the kernel's time (a run over 2100 chunks of 128 columns, 32 carries in flight 100 us, 64 in flight 64 us).
 template <int VL>
 __global__ __launch_bounds__(kBlock) void bwd_fold_kernel(
     const uint32_t* __restrict__ keys, int64_t m, int64_t chunks,
