@@ -30,7 +30,6 @@ constexpr int kChunk = FS_BWD_TILE;
 constexpr int kChunksPerBlock = 64;          // bwd_count_heads: chunks per block
 constexpr int kSinglesSplit = 4;             // bwd_singletons: waves per chunk (divides kChunk / 64)
 constexpr int kWalkAhead = 8;                // rows per batch of a walking wave, the next batch in flight beside it
-constexpr uint32_t kNoKey = 0xFFFFFFFFu;     // never a row: R < 2^32 - 1
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
@@ -595,11 +594,12 @@ __device__ __forceinline__ bool list_singletons(
     for (int q = 0; q < kChunk / kWave; ++q) {
         const int64_t k = k0 + q * kWave + lane;
         const bool valid = k < k1;
-        const uint32_t key = valid ? keys[k] : kNoKey;
-        const uint32_t prev = (valid && k > 0) ? keys[k - 1] : kNoKey;
-        const uint32_t next = (valid && k + 1 < m) ? keys[k + 1] : kNoKey;
-        const bool head = valid && key != prev;
-        const bool single = head && key != next && q * kSinglesSplit / (kChunk / kWave) == part;
+        const uint32_t key = valid ? keys[k] : 0u;
+        const uint32_t prev = (valid && k > 0) ? keys[k - 1] : 0u;
+        const uint32_t next = (valid && k + 1 < m) ? keys[k + 1] : 0u;
+        // the ends of the list by index: no key can stand for "none", a caller's list may hold any 32-bit word
+        const bool head = valid && (k == 0 || key != prev);
+        const bool single = head && (k + 1 >= m || key != next) && q * kSinglesSplit / (kChunk / kWave) == part;
         const uint64_t hb = ballot(head);
         const uint64_t sb = ballot(single);
         if (single) {
@@ -810,12 +810,12 @@ __global__ __launch_bounds__(kBlock) void bwd_fold_kernel(
     const uint32_t key = keys[k1 - 1];
     const uint32_t next = keys[k1];
     const uint32_t head = keys[k0];
-    const uint32_t before = k0 > 0 ? keys[k0 - 1] : kNoKey;
+    const uint32_t before = keys[k0 > 0 ? k0 - 1 : 0];
     const bool has_far = chunk + 2 < chunks;                         // then (chunk + 2) * kChunk < m
     const uint32_t far = keys[has_far ? k1 + kChunk : k1];
     const int64_t u = (int64_t)runs_before(block_base, chunk_local, chunk + 1, chunks) - 1;
     if (next != key) return;                                         // the chunk's last run ends with it
-    if (head == key && before == key) return;                        // the run started in an earlier chunk
+    if (k0 > 0 && head == key && before == key) return;              // the run started in an earlier chunk
     if (u >= cap) return;
     // The last chunk whose first lookup still belongs to the run.  Most spilling runs end in the
     // very next chunk, so the search gallops from there (1, 2, 4 .. chunks ahead) and then bisects:

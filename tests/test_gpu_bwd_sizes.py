@@ -125,3 +125,42 @@ def test_runs_over_many_chunks(G, D, first):
     pos = pos[np.lexsort((pos, rows))]
     gnp, gt = _np_grad(rng.standard_normal((1021, D)).astype(np.float32), "f32")
     _check(G, gnp, gt, rows, pos, 0, m, len(more) + 2, "f32", atomic_too=False)
+
+
+@pytest.mark.parametrize("tail", [1, 2, 700])
+@pytest.mark.parametrize("m", [1, 2, 300, 700, 1024 * CHUNK, 1024 * CHUNK + 1, 1024 * CHUNK + 300])
+def test_last_row_of_all_ones(G, m, tail):
+    """A caller's sorted list that ends with rows of 0xFFFFFFFF (-1, a padding value): outside the table, reported, and a
+    row like any other for the sums.  The oracle sums it under the first number past the table."""
+    import paper_2301_02959_amd as fs
+    tail = min(tail, m)
+    rng = np.random.default_rng(m + tail)
+    R, n, D = 100_000, 1_500, 24
+    rows = np.sort(np.concatenate([rng.integers(0, R, m - tail), np.full(tail, R)]))
+    pos = (np.arange(m) // (m // n + 1)).astype(np.int32)
+    gnp, gt = _np_grad(rng.standard_normal((n, D)).astype(np.float32), "f16")
+    orc, ost, ou, og, _, onu = oracle.seq_grad_bwd(gnp, rows, pos, 0, m, R + 1, dtype=G.oracle_dtype("f16"))
+    assert (orc, ost) == (0, 0)
+    ou = np.where(ou == R, 0xFFFFFFFF, ou)
+    srows = G.to_dev(np.where(rows == R, -1, rows), torch.int32)
+    spos, grad = G.to_dev(pos), gt.to(G.DEV)
+
+    def outputs():
+        return (torch.full((onu,), 5, dtype=torch.int64, device=G.DEV), torch.full((onu, D), 7.0, device=G.DEV),
+                torch.zeros(1, dtype=torch.int64, device=G.DEV), torch.zeros(1, dtype=torch.int32, device=G.DEV))
+
+    uniq, rg, nu, st = outputs()
+    fs.fs_seq_grad_bwd_sorted(grad, srows, spos, m, R, 0, uniq, rg, onu, nu, st)
+    assert int(nu.item()) == onu and int(st.item()) == oracle.BAD_ID
+    assert np.array_equal(uniq.cpu().numpy(), ou) and np.array_equal(G.bits(rg), og.view(np.uint8).reshape(-1))
+    # the backward with the optimizer step skips that row and leaves every other one as the two calls do
+    table = torch.randn(R, D, generator=torch.Generator().manual_seed(m)).to(torch.float16).to(G.DEV)
+    two, w, state = table.clone(), table.clone(), [torch.zeros(R, device=G.DEV) for _ in range(2)]
+    fs.fs_sparse_update(two, uniq, rg, onu, nu, fs.FS_OPT_ADAGRAD_ROWWISE, 0.05, 1e-6, state[0])
+    uniq, rg, nu, st = outputs()
+    scratch = torch.zeros(64 << 20, dtype=torch.uint8, device=G.DEV)
+    fs.fs_seq_grad_bwd_update(grad, srows, spos, m, R, w, fs.FS_OPT_ADAGRAD_ROWWISE, 0.05, 1e-6, state[1], None, None, 0,
+                              uniq, rg, onu, nu, st, workspace=scratch)
+    assert int(nu.item()) == onu and int(st.item()) & oracle.BAD_ID
+    assert np.array_equal(uniq.cpu().numpy(), ou)
+    assert torch.equal(w.view(torch.int16), two.view(torch.int16)) and torch.equal(state[0], state[1])
