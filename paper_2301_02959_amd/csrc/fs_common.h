@@ -71,6 +71,19 @@ inline int64_t xcd_striped_grid(int64_t tiles, int stripe)
     return (tiles + round - 1) / round * round;
 }
 
+// One round of wave_table_of: the distance between its 64 probes over tables lo .. hi (the first at lo + the distance),
+// and the range that is left when `before` of them lie at or before the lookup.  Unsigned, as hi - lo + 63 may pass 2^31 - 1.
+__host__ __device__ inline int table_step(int lo, int hi)
+{
+    return (int)(((unsigned)hi - (unsigned)lo + (unsigned)(kWave - 1)) / (unsigned)kWave);
+}
+
+__host__ __device__ inline void table_narrow(int* lo, int* hi, int step, int before)
+{
+    *lo += before * step;                                // as many probes were in range, so lo stays <= hi
+    if (*hi - *lo >= step) *hi = *lo + step - 1;
+}
+
 #ifdef __HIPCC__
 // ---- device helpers ---------------------------------------------------------
 __device__ __forceinline__ int64_t xcd_striped_grid_dev(int64_t tiles, int stripe)
@@ -105,13 +118,10 @@ __device__ __forceinline__ int wave_table_of(const int64_t* __restrict__ offsets
 {
     int lo = 0, hi = T - 1;
     while (lo < hi) {
-        const int step = (hi - lo + kWave - 1) / kWave;
+        const int step = table_step(lo, hi);
         const int64_t t = (int64_t)lo + (int64_t)(lane_id() + 1) * step;
         const bool starts = t <= hi && offsets[t * B] <= i;
-        const int before = __popcll(ballot(starts));
-        lo += before * step;                             // as many probes were in range, so lo stays <= hi
-        const int end = lo + step - 1;
-        hi = end < hi ? end : hi;
+        table_narrow(&lo, &hi, step, __popcll(ballot(starts)));
     }
     return lo;
 }
