@@ -4,7 +4,7 @@
 // that touch each lookup twice:
 //   route_remap     one 2048-lookup tile per block: table of each lookup, global
 //                   row g, placement entry, destination; per-tile bucket
-//                   histogram (the own bucket by ballots, the others by LDS adds) plus the tile's three tier
+//                   histogram (the own bucket and one other by ballots, the rest by LDS adds) plus the tile's three tier
 //                   counts; dest (u16) and g (u32) go to the workspace; each block also
 //                   validates its share of the offsets
 //   route_scan      one block per bucket (and per tier): exclusive scan of its per-tile
@@ -33,6 +33,11 @@ constexpr int kRouteStripe = 32;                      // tiles per XCD stripe in
 // after the remap instead of 9, 80 k over 64 (2747 counts) 6 instead of 8, and the host saves a launch (2.3 us).
 // At 6499 counts the two are even on the GPU, at 14 k the sums are 12 us slower.
 constexpr int64_t kRouteSumMax = 6144;
+// Beyond one tile for every CU the remap counts the first foreign bucket by ballots too (LEAD).  16 M lookups, every row
+// on one other GPU: 76 us with a full match of the buckets, 83 with plain adds, 73 so; rows dealt over 8 buckets 82, 73.5,
+// 73.5.  2.4 M: plain 20.7 and 16.4, so 16.9 and 16.8.  Up to one tile the waves' own chains are the time, and the ballots
+// cost 0.4 us of 8.6 where the adds that meet cost 0.2.
+constexpr int64_t kRouteLeadTiles = 256;
 
 __global__ __launch_bounds__(kBlock) void route_prepare_kernel(
     const int64_t* __restrict__ offsets, int64_t S, int64_t n, int32_t* status)
@@ -48,6 +53,7 @@ __global__ __launch_bounds__(kBlock) void route_prepare_kernel(
 // A tile's tables and their rows, staged in LDS when there are at most this many of them.
 constexpr int kRouteTileTables = 64;
 
+template <bool LEAD>
 __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     const int64_t* __restrict__ ids, const int64_t* __restrict__ offsets, int T, int64_t B,
     const int64_t* __restrict__ row_base, const uint32_t* __restrict__ placement,
@@ -136,9 +142,11 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     uint32_t e[kRouteItems];
 #pragma unroll
     for (int it = 0; it < kRouteItems; ++it) e[it] = rows_ok ? placement[g[it]] : 0u;
-    // Counts of the wave: the tiers and the own bucket (where most lookups of a power-law batch go) with one ballot
-    // each, the other buckets with plain LDS adds, which rarely meet.
+    // Counts of the wave: the tiers and the own bucket with one ballot each, and (LEAD) one more for the bucket of the
+    // wave's first lookup that goes elsewhere: a bucket that most of the rest go to (few buckets, whole tables or a hot row
+    // on one other GPU) is nearly always that one.  What is left are plain LDS adds, of which few meet in one word.
     uint32_t in_tier0 = 0, in_tier1 = 0, in_tier2 = 0, own = 0;
+    uint32_t led = 0, in_led = 0;                                    // led: any bucket if the first item has none
 #pragma unroll
     for (int it = 0; it < kRouteItems; ++it) {
         const int64_t i = base + (int64_t)it * kBlock + threadIdx.x;
@@ -155,7 +163,15 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
             // a replicated row's entry names no owner: its owner bits carry the row's replica slot, if it has one
             if (slot_out != nullptr)
                 slot_out[i] = (tier == FS_TIER_GLOBAL && owner != FS_OWNER_MASK) ? (int32_t)owner : -1;
-            if (dest != (uint32_t)self) atomicAdd(&lds_hist[dest], 1u);
+        }
+        const bool foreign = valid && dest != (uint32_t)self;
+        if constexpr (LEAD) {
+            if (it == 0) led = (uint32_t)__builtin_amdgcn_readlane((int)dest, __builtin_ctzll(ballot(foreign) | (1ull << 63)));
+            const bool same = foreign && dest == led;
+            in_led += (uint32_t)__popcll(ballot(same));
+            if (foreign && !same) atomicAdd(&lds_hist[dest], 1u);
+        } else if (foreign) {
+            atomicAdd(&lds_hist[dest], 1u);
         }
         in_tier1 += (uint32_t)__popcll(ballot(valid && tier == FS_TIER_GROUP));
         in_tier2 += (uint32_t)__popcll(ballot(valid && tier == FS_TIER_SHARDED));
@@ -165,6 +181,7 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     if (lane_id() == 0) {
         wave_counts[w][0] = in_tier0; wave_counts[w][1] = in_tier1; wave_counts[w][2] = in_tier2;
         wave_counts[w][3] = own;
+        if (LEAD && in_led != 0) atomicAdd(&lds_hist[led], in_led);
     }
     __syncthreads();
     auto waves_sum = [&](int k) {
@@ -404,10 +421,13 @@ static fs_status route_run(
     }
     {
         const bool sum = tiles * ((int64_t)U + 3) <= kRouteSumMax;
-        FS_LAUNCH_SMEM("route_remap", route_remap_kernel, dim3((unsigned)tiles), dim3(kBlock),
-                       (size_t)U * sizeof(uint32_t), s,
-                       ids, offsets, (int)T, (int64_t)B, row_base, placement, n, (int)U, (int)W, (int)self,
-                       dest_tmp, g_tmp, slot_tmp, tile_hist, tiles, sum ? 1 : 0, dev_status);
+#define FS_REMAP(LEAD)                                                                                             \
+    FS_LAUNCH_SMEM("route_remap", route_remap_kernel<LEAD>, dim3((unsigned)tiles), dim3(kBlock), (size_t)U * sizeof(uint32_t), s, \
+                   ids, offsets, (int)T, (int64_t)B, row_base, placement, n, (int)U, (int)W, (int)self,             \
+                   dest_tmp, g_tmp, slot_tmp, tile_hist, tiles, sum ? 1 : 0, dev_status)
+        if (tiles > kRouteLeadTiles) FS_REMAP(true);
+        else FS_REMAP(false);
+#undef FS_REMAP
         if (!sum)
             FS_LAUNCH("route_scan", route_scan_kernel, dim3((unsigned)U + 3), dim3(kRouteScanBlock), s, tile_hist, tiles, totals);
         const unsigned scatter_grid = (unsigned)(sum ? tiles : xcd_striped_grid(tiles, kRouteStripe));

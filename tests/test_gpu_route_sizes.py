@@ -43,3 +43,25 @@ def test_route_shapes(G, T, B, n, U, W):
     assert (rc, st) == (orc, ost) == (0, 0)
     assert np.array_equal(bo.cpu().numpy(), obo) and np.array_equal(tc.cpu().numpy(), otc)
     assert np.array_equal(rows.cpu().numpy(), orows) and np.array_equal(pos.cpu().numpy(), opos)
+
+
+@pytest.mark.parametrize("n", [256 * TILE, 256 * TILE + 1, 256 * TILE + 777])
+@pytest.mark.parametrize("U,self_", [(1, 0), (2, 0), (2, 1), (3, 1), (64, 5)])
+@pytest.mark.parametrize("owners", ["one", "tables", "hot"])
+def test_where_most_lookups_go_to_one_other_bucket(G, n, U, self_, owners):
+    """Every row on one other GPU, whole tables on one owner each, one hot row: the counts that the ballots take and
+    those that are left to LDS adds, on either side of one tile for every CU."""
+    rng = np.random.default_rng(n + U + len(owners))
+    T, E = 3, 50
+    offsets = np.array([0, n // 3, n // 2, n], np.int64)
+    ids = np.where(rng.random(n) < (0.6 if owners == "hot" else 0.0), 7, rng.integers(0, E, n)).astype(np.int64)
+    row_base = (np.arange(T + 1) * E).astype(np.int64)
+    row = np.arange(T * E)
+    owner = {"one": np.full(T * E, (self_ + 1) % U), "tables": (row // E + self_) % U, "hot": row % U}[owners]
+    placement = ((2 << 30) | owner).astype(np.uint32)
+    rc, st, bo, rows, pos, tc = G.hip_route(G.to_dev(ids), G.to_dev(offsets), T, 1, G.to_dev(row_base),
+                                            G.placement_dev(placement), U, 1, self_, n=n)
+    orc, ost, obo, orows, opos, otc = oracle.route_bucketize(ids, offsets, T, 1, row_base, placement, U, 1, self_, n=n)
+    assert (rc, st) == (orc, ost) == (0, 0)
+    assert np.array_equal(bo.cpu().numpy(), obo) and np.array_equal(tc.cpu().numpy(), otc)
+    assert np.array_equal(rows.cpu().numpy(), orows) and np.array_equal(pos.cpu().numpy(), opos)
