@@ -120,7 +120,8 @@ __global__ __launch_bounds__(kBlock) void sort_count_kernel(
 // access is coalesced across digits.  Level 1: a block takes a chunk of tiles; thread b walks
 // the chunk's tiles for digit b, leaves the running prefix in place and the chunk's sum in
 // chunk_sums[chunk][b].  Level 2: up to 16 chunks (4 M pairs) every block of the scatter adds up the chunks' sums
-// itself, one vector load each, while its pairs are on the way: no hand-over between blocks.  Beyond, one block:
+// itself, one vector load each (while its pairs are on the way, where the host knows their number): no hand-over
+// between blocks.  Beyond, one block:
 // thread b walks the chunks for digit b: chunk_sums -> exclusive prefix, totals[b].
 // Chunks are 64 tiles, and 32 where 16 of them are enough: level 1's time is its chain of rounds of loads.  With level 2
 // in the block that finished last a pass over 1 to 2 M pairs spent 9.8 us here, now 5.2 and 2.6 in the scatter.
@@ -128,15 +129,18 @@ constexpr int kSortChunkTiles = 64;
 constexpr int kSortSumChunks = 16;
 constexpr int kSortFusedScanChunksDev = 1024;
 
-__host__ __device__ __forceinline__ int64_t sort_chunk_tiles(int64_t used)
+constexpr int kSortChunkShift = 6;           // log2(kSortChunkTiles): no 64-bit division on the device
+static_assert(kSortChunkTiles == 1 << kSortChunkShift);
+
+__host__ __device__ __forceinline__ int sort_chunk_shift(int64_t used)     // log2 of a chunk's tiles
 {
-    return used <= kSortSumChunks * kSortChunkTiles / 2 ? kSortChunkTiles / 2 : kSortChunkTiles;
+    return used <= kSortSumChunks * kSortChunkTiles / 2 ? kSortChunkShift - 1 : kSortChunkShift;
 }
 
 __host__ __device__ __forceinline__ int64_t sort_chunks(int64_t used)
 {
-    const int64_t per = sort_chunk_tiles(used);
-    return (used + per - 1) / per;
+    const int shift = sort_chunk_shift(used);
+    return (used + (1 << shift) - 1) >> shift;
 }
 
 constexpr int kScanAhead = 8;                // loads a scan thread keeps in flight (16 and 32 are slower)
@@ -150,7 +154,7 @@ __global__ __launch_bounds__(1024) void sort_scan_kernel(
     if (sort_pass_idle(varying, shift)) return;
     const int64_t m = sort_count_of(m_dev, m_max);
     const int64_t used = (m + kSortTile - 1) / kSortTile;
-    const int64_t per = sort_chunk_tiles(used);
+    const int64_t per = 1 << sort_chunk_shift(used);
     const int64_t chunks = sort_chunks(used);
     const int64_t t0 = (int64_t)blockIdx.x * per;
     if (t0 >= used) return;                                      // block-uniform: this block has no tiles
@@ -218,13 +222,17 @@ __global__ __launch_bounds__(kBlock) void sort_scan_chunks_kernel(
     totals[b] = run;
 }
 
-// SUM: few tiles, no scan has run: tile_hist holds plain counts and every block adds up the digits' totals and the
-// tiles before its own itself, one vector load per tile and thread.
+// SUM: every block adds up the digits' totals and what stands before its tile itself, one vector load per part and
+// thread, while its pairs are on the way.  The parts are the tiles (few of them; no scan has run, tile_hist holds plain
+// counts) or, `by_chunk`, the scan's chunks.  Without SUM the sums are ready, or, where the number of pairs is only
+// known on the device and turned out small, added up after the ranking: kept in registers through it they are what
+// takes the 10-bit scatter past 168 registers, to two waves per SIMD (72 M pairs 1057 -> 1274 us over three passes).
 template <typename Reader, int NBITS, int ITEMS, bool SUM>
 __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
     Reader in, int64_t m_max, const int64_t* __restrict__ m_dev, const uint32_t* __restrict__ varying, int shift,
     const uint32_t* __restrict__ tile_hist /* scanned, unless SUM */, const uint32_t* __restrict__ chunk_sums /* scanned */,
-    const uint32_t* __restrict__ totals, uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int32_t* status)
+    const uint32_t* __restrict__ totals, int by_chunk, uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
+    int32_t* status)
 {
     constexpr int bins = 1 << NBITS;
     constexpr int kTile = kBlock * ITEMS;
@@ -248,12 +256,13 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
     // grid stride): consecutive tiles write neighbouring runs of every digit's region, a few tens of
     // bytes each, and one XCD's L2 then merges what four XCDs would write into one 128-byte line
     // piece by piece (scatter 0.343 -> 0.327 ms per step on 15.7 M pairs).
-    const int64_t chunk_tiles = sort_chunk_tiles(used);
+    const int chunk_shift = sort_chunk_shift(used);
     const int64_t chunks = sort_chunks(used);
-    const bool sums_chunks = !SUM && chunks <= kSortSumChunks;
-    const int64_t padded = SUM ? used : xcd_striped_grid_dev(used, kSortStripe);
+    const bool sums_chunks = SUM ? ITEMS == kSortItems && by_chunk != 0 : chunks <= kSortSumChunks;
+    const bool sums_tiles = SUM && !sums_chunks;
+    const int64_t padded = sums_tiles ? used : xcd_striped_grid_dev(used, kSortStripe);
     for (int64_t v = blockIdx.x; v < padded; v += gridDim.x) {
-        const int64_t tile = SUM ? v : xcd_striped_tile((unsigned)v, kSortStripe);
+        const int64_t tile = sums_tiles ? v : xcd_striped_tile((unsigned)v, kSortStripe);
         if (tile >= used) continue;                              // block-uniform
         const int64_t base = tile * kTile;
         const int64_t wbase = base + (int64_t)w * kWaveSpan;
@@ -279,14 +288,11 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
         uint32_t before_tile[kBinsPerThread];                    // and their pairs in the tiles before this one
 #pragma unroll
         for (int q = 0; q < kBinsPerThread; ++q) { tot[q] = 0; before_tile[q] = 0; }
-        // SUM: of all tiles' counts.  Else, where they are few, of the chunks' sums; the tiles before in its own chunk follow.
-        const int64_t my_chunk = tile / chunk_tiles;
-        if (SUM || sums_chunks) {
+        const int64_t my_chunk = tile >> chunk_shift;
+        auto add_up = [&](const uint32_t* table, int parts, int me) {          // [parts][bins], parts before `me` apart
             typedef uint32_t Bins __attribute__((ext_vector_type(kBinsPerThread)));    // 1, 2 or 4: aligned (256-byte tables)
             if (threadIdx.x * kBinsPerThread < bins) {
-                const Bins* mine = reinterpret_cast<const Bins*>(SUM ? tile_hist : chunk_sums) + threadIdx.x;
-                const int parts = (int)(SUM ? used : chunks);
-                const int me = (int)(SUM ? tile : my_chunk);
+                const Bins* mine = reinterpret_cast<const Bins*>(table) + threadIdx.x;
 #pragma unroll 8
                 for (int t = 0; t < parts; ++t) {
                     const Bins v = mine[t * (bins / kBinsPerThread)];
@@ -294,7 +300,9 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
                     for (int q = 0; q < kBinsPerThread; ++q) { tot[q] += v[q]; before_tile[q] += t < me ? v[q] : 0u; }
                 }
             }
-        }
+        };
+        if constexpr (SUM)
+            add_up(sums_tiles ? tile_hist : chunk_sums, (int)(sums_tiles ? used : chunks), (int)(sums_tiles ? tile : my_chunk));
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // the zeroing above, seen by the wave's other lanes
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -330,9 +338,20 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
             }
             count[q] = run;
             sum += run;
-            if (!SUM && !sums_chunks) tot[q] = b < bins ? totals[b] : 0u;
-            tsum += tot[q];
         }
+        if constexpr (!SUM) {
+            if (sums_chunks) {                                   // block-uniform
+                add_up(chunk_sums, (int)chunks, (int)my_chunk);
+            } else {
+#pragma unroll
+                for (int q = 0; q < kBinsPerThread; ++q) {
+                    const int b = threadIdx.x * kBinsPerThread + q;
+                    if (b < bins) { tot[q] = totals[b]; before_tile[q] = chunk_sums[my_chunk * bins + b]; }
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kBinsPerThread; ++q) tsum += tot[q];
         // exclusive scans over the digits: inside the tile (sum) and over the whole input (totals)
         uint32_t unused;
         uint32_t in_tile = block_exclusive_scan(sum, wave_sums, &unused);
@@ -341,8 +360,7 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(
         for (int q = 0; q < kBinsPerThread; ++q) {
             const int b = threadIdx.x * kBinsPerThread + q;
             if (b < bins) {
-                if constexpr (!SUM)
-                    before_tile[q] += (sums_chunks ? 0u : chunk_sums[my_chunk * bins + b]) + tile_hist[tile * bins + b];
+                if (!sums_tiles) before_tile[q] += tile_hist[tile * bins + b];
                 out_base[b] = in_all + before_tile[q] - in_tile;
 #pragma unroll
                 for (int k = 0; k < kWavesPerBlock; ++k) wave_hist[k][b] = (uint16_t)(wave_hist[k][b] + in_tile);
@@ -443,12 +461,12 @@ static fs_status launch_sort_pass(const Reader& in, const SortShape& shape, int6
             FS_LAUNCH("sort_count", (sort_count_kernel<Reader, NBITS, kSortSmallItems>), grid, dim3(kBlock), stream,
                       in, m_max, m_dev, varying, shift, tile_hist, scan_done);
             FS_LAUNCH("sort_scatter", (sort_scatter_kernel<Reader, NBITS, kSortSmallItems, true>), grid, dim3(kBlock), stream,
-                      in, m_max, m_dev, varying, shift, tile_hist, chunk_sums, totals, keys_out, vals_out, status);
+                      in, m_max, m_dev, varying, shift, tile_hist, chunk_sums, totals, 0, keys_out, vals_out, status);
         } else {
             FS_LAUNCH("sort_count", (sort_count_kernel<Reader, NBITS, kSortItems>), grid, dim3(kBlock), stream,
                       in, m_max, m_dev, varying, shift, tile_hist, scan_done);
             FS_LAUNCH("sort_scatter", (sort_scatter_kernel<Reader, NBITS, kSortItems, true>), grid, dim3(kBlock), stream,
-                      in, m_max, m_dev, varying, shift, tile_hist, chunk_sums, totals, keys_out, vals_out, status);
+                      in, m_max, m_dev, varying, shift, tile_hist, chunk_sums, totals, 0, keys_out, vals_out, status);
         }
         return FS_OK;
     }
@@ -464,8 +482,12 @@ static fs_status launch_sort_pass(const Reader& in, const SortShape& shape, int6
     if (!fused_scan)
         FS_LAUNCH("sort_scan_chunks", sort_scan_chunks_kernel, dim3((bins + kBlock - 1) / kBlock),
                   dim3(kBlock), stream, chunk_sums, bins, m_max, m_dev, varying, shift, totals);
-    FS_LAUNCH("sort_scatter", (sort_scatter_kernel<Reader, NBITS, kSortItems, false>), grid, dim3(kBlock), stream,
-              in, m_max, m_dev, varying, shift, tile_hist, chunk_sums, totals, keys_out, vals_out, status);
+    if (m_dev == nullptr && chunks <= kSortSumChunks)
+        FS_LAUNCH("sort_scatter", (sort_scatter_kernel<Reader, NBITS, kSortItems, true>), grid, dim3(kBlock), stream,
+                  in, m_max, m_dev, varying, shift, tile_hist, chunk_sums, totals, 1, keys_out, vals_out, status);
+    else
+        FS_LAUNCH("sort_scatter", (sort_scatter_kernel<Reader, NBITS, kSortItems, false>), grid, dim3(kBlock), stream,
+                  in, m_max, m_dev, varying, shift, tile_hist, chunk_sums, totals, 0, keys_out, vals_out, status);
     return FS_OK;
 }
 

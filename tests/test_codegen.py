@@ -104,3 +104,18 @@ def test_no_kernel_selects_on_a_stale_condition(tmp_path):
         assert p.returncode == 0, err[-2000:]
         hits = stale_condition_selects(out.read_text())
         assert not hits, f"{os.path.basename(src)}: s_cselect on a stale condition code at assembly lines {hits[:4]}"
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None and not os.path.exists(HIPCC), reason="hipcc not found")
+def test_the_sorts_scatter_keeps_three_waves_per_simd(tmp_path):
+    """512 vector registers per SIMD lane in groups of 8: three waves need at most 168 each.  Past that the large sorts
+    run on two (72 M pairs with 10-bit digits: 1274 us of scatter instead of 1057)."""
+    from paper_2301_02959_amd.build import FLAGS
+    out = tmp_path / "radix_sort.s"
+    flags = [f for f in FLAGS if f not in ("-shared", "-fPIC")]
+    subprocess.run([HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(CSRC, "radix_sort.hip"), "-I", os.path.join(ROOT, "include"),
+                    "-I", CSRC, "-o", str(out)], check=True, stderr=subprocess.DEVNULL)
+    kernels = re.findall(r"\.name:\s+(\S*sort_scatter_kernel\S*).*?\.vgpr_count:\s+(\d+)", out.read_text(), re.S)
+    large = {name: int(count) for name, count in kernels if "ELi16E" in name}          # 16 pairs to a thread
+    assert len(large) >= 20
+    assert not {name: count for name, count in large.items() if count > 168}

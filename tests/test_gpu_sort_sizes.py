@@ -24,6 +24,18 @@ def G():
 @pytest.mark.parametrize("m", [1, 1023, 1024, 1025, 65536, 65537, 262144, 262145])
 @pytest.mark.parametrize("R", [3, 200, 1 << 10, (1 << 17) + 1, 1 << 20, 3_000_000])
 def test_sort_sizes(G, m, R):
+    check_sort(G, m, R)
+
+
+@pytest.mark.parametrize("m", [512 * 4096, 512 * 4096 + 1, 1024 * 4096, 1024 * 4096 + 1])
+@pytest.mark.parametrize("R", [200, 3_000_000, 1 << 30])
+def test_sort_sizes_with_a_scan(G, m, R):
+    """Up to 512 tiles the scan's chunks are of 32 tiles, then of 64; up to 16 chunks, 1024 tiles, the scatter adds up
+    their sums, beyond them a launch of its own does."""
+    check_sort(G, m, R)
+
+
+def check_sort(G, m, R):
     import paper_2301_02959_amd as fs
     rng = np.random.default_rng(m + R)
     rows = np.where(rng.random(m) < 0.5, rng.integers(0, min(R, 7), m), rng.integers(0, R, m)).astype(np.int64)
