@@ -478,7 +478,7 @@ __global__ __launch_bounds__(kBlock) void plan_move_kernel(
 }
 
 // Compaction and sort of the candidates, shared by the two planners: rows in (count desc, row asc) order, in vals_a
-// or vals_b as sort_result_in_b(*count_bits) says, with their keys ~count beside them.
+// or vals_b as sort_result_in_b(*count_bits, first_bits) says, with their keys ~count beside them.
 // Up to 1024 tiles (8 M rows) the moving blocks sum the tile counts themselves, at most four loads to a thread, and
 // the scan is no launch of its own; beyond, what each of the blocks would read again is more than the scan costs.
 constexpr int64_t kMoveSumTiles = 1024;
@@ -493,7 +493,19 @@ struct PlanScratch {
     uint32_t* keys_b;
     uint32_t* vals_b;
     char* sort_scratch;
+    int first_bits;
 };
+
+// Digits of the selection's sort: 10, 10, 6, 6 bits up to 2^26 rows, 8, 8, 8, 8 beyond; as many passes run as the
+// largest count needs.  Over few candidates a pass costs its launches, and counts below 1024 (small batches) or of 17 to 20
+// bits (profiles) take a pass less with the wide digits; a wide pass over many candidates costs up to two narrow ones, and
+// the more rows, the more of them a profile touches.  Sort in us, wide : narrow, for largest counts of 9 / 15 / 20 / 23 / 27
+// bits: 4 M rows, 160 k candidates 81 : 85, 91 : 86, 92 : 93, 99 : 93, 105 : 100; 32 M, 1.3 M 87 : 94, 103 : 94, 104 : 106,
+// 116 : 108, 127 : 117; 80 M, 16 M 195 : 225, 317 : 225, 319 : 300, 386 : 303, 464 : 378.  Digits of
+// 10, 10, 10, 2 bits cost 124 on 32 M rows and 23 bits, and 1221 : 1010 on 200 M rows, 50 M candidates and 27 bits.
+constexpr int64_t kSelectionWideRows = (int64_t)1 << 26;
+
+static int selection_first_bits(int64_t R) { return R <= kSelectionWideRows ? 10 : 8; }
 
 static PlanScratch take_plan_scratch(Carver& ws, int64_t R)
 {
@@ -508,6 +520,7 @@ static PlanScratch take_plan_scratch(Carver& ws, int64_t R)
     p.keys_b = ws.take<uint32_t>((size_t)R);
     p.vals_b = ws.take<uint32_t>((size_t)R);
     p.sort_scratch = ws.take<char>(R > 0 ? radix_sort_scratch_bytes(R) : 0);
+    p.first_bits = selection_first_bits(R);
     return p;
 }
 
@@ -525,14 +538,14 @@ static fs_status sort_candidates(const uint32_t* counts, int64_t R, int allow_ze
     }
     uint32_t *keys = nullptr, *vals = nullptr;                   // where the last pass would leave them
     return radix_sort_pairs(p.keys_a, p.vals_a, p.keys_b, p.vals_b, R, p.num_cand, 32, p.sort_scratch, s, &keys, &vals,
-                            SortSource(), p.count_bits);
+                            SortSource(), p.count_bits, p.first_bits);
 }
 
 __global__ __launch_bounds__(kBlock) void plan_emit_kernel(
-    const uint32_t* __restrict__ vals_a, const uint32_t* __restrict__ vals_b, const uint32_t* __restrict__ count_bits, const int64_t* __restrict__ num_candidates, int64_t cap,
+    const uint32_t* __restrict__ vals_a, const uint32_t* __restrict__ vals_b, const uint32_t* __restrict__ count_bits, int first_bits, const int64_t* __restrict__ num_candidates, int64_t cap,
     int64_t* __restrict__ sel_rows, int64_t* __restrict__ num_selected, uint32_t* __restrict__ placement)
 {
-    const uint32_t* vals = sort_result_in_b(*count_bits) ? vals_b : vals_a;
+    const uint32_t* vals = sort_result_in_b(*count_bits, first_bits) ? vals_b : vals_a;
     const int64_t nc = *num_candidates;
     const int64_t k = cap < nc ? cap : nc;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -564,10 +577,10 @@ struct TierConsts {
 };
 
 __global__ __launch_bounds__(kBlock) void tiers_tile_sums_kernel(
-    const uint32_t* __restrict__ keys_a, const uint32_t* __restrict__ keys_b, const uint32_t* __restrict__ count_bits,
+    const uint32_t* __restrict__ keys_a, const uint32_t* __restrict__ keys_b, const uint32_t* __restrict__ count_bits, int first_bits,
     const int64_t* __restrict__ num_candidates, uint64_t* __restrict__ tile_sum)
 {
-    const uint32_t* keys = sort_result_in_b(*count_bits) ? keys_b : keys_a;
+    const uint32_t* keys = sort_result_in_b(*count_bits, first_bits) ? keys_b : keys_a;
     __shared__ uint64_t part[kWavesPerBlock];
     const int64_t K = *num_candidates;
     // candidates are usually a few per cent of the rows: the blocks walk the tiles that hold any (a block for every
@@ -670,11 +683,11 @@ __device__ __forceinline__ i128 cum_memory(const TierConsts& c, int64_t k, uint6
 // The budget and the sums of the two tiers follow in the first wave, the sums' partial tiles with 16 loads in flight:
 // 39 -> 27 us with 1.5 M candidates (one wave doing all of it, and every row of point B's tile tested on its own).
 __global__ __launch_bounds__(kBlock) void tiers_cuts_kernel(
-    const uint32_t* __restrict__ keys_a, const uint32_t* __restrict__ keys_b, const uint32_t* __restrict__ count_bits,
+    const uint32_t* __restrict__ keys_a, const uint32_t* __restrict__ keys_b, const uint32_t* __restrict__ count_bits, int first_bits,
     const int64_t* __restrict__ num_candidates,
     const uint64_t* __restrict__ tile_sum, const TierConsts c, int64_t* __restrict__ cuts)
 {
-    const uint32_t* keys = sort_result_in_b(*count_bits) ? keys_b : keys_a;
+    const uint32_t* keys = sort_result_in_b(*count_bits, first_bits) ? keys_b : keys_a;
     const int lane = lane_id();
     const int64_t K = *num_candidates;
     const int64_t tiles = (K + kSumTile - 1) / kSumTile;
@@ -758,11 +771,11 @@ __global__ __launch_bounds__(kBlock) void tiers_cuts_kernel(
 }
 
 __global__ __launch_bounds__(kBlock) void tiers_emit_kernel(
-    const uint32_t* __restrict__ vals_a, const uint32_t* __restrict__ vals_b, const uint32_t* __restrict__ count_bits,
+    const uint32_t* __restrict__ vals_a, const uint32_t* __restrict__ vals_b, const uint32_t* __restrict__ count_bits, int first_bits,
     const int64_t* __restrict__ cuts, int64_t cap, int W,
     int64_t* __restrict__ sorted_rows, uint32_t* __restrict__ placement)
 {
-    const uint32_t* vals = sort_result_in_b(*count_bits) ? vals_b : vals_a;
+    const uint32_t* vals = sort_result_in_b(*count_bits, first_bits) ? vals_b : vals_a;
     const int64_t n_dp = cuts[5];
     const int64_t n_both = n_dp + cuts[6];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -845,7 +858,7 @@ extern "C" fs_status fs_plan_replication(
         const int allow_zero = (flags & FS_PLAN_ALLOW_ZERO) ? 1 : 0;
         if (fs_status rc = sort_candidates(counts, R, allow_zero, p, s); rc != FS_OK) return rc;
         FS_LAUNCH("plan_emit", plan_emit_kernel, dim3(1024), dim3(kBlock), s,
-                  p.vals_a, p.vals_b, p.count_bits, p.num_cand, cap, sel_rows, num_selected, (flags & FS_PLAN_TAG) ? placement : nullptr);
+                  p.vals_a, p.vals_b, p.count_bits, p.first_bits, p.num_cand, cap, sel_rows, num_selected, (flags & FS_PLAN_TAG) ? placement : nullptr);
     }
     return FS_OK;
 }
@@ -904,11 +917,11 @@ extern "C" fs_status fs_plan_tiers(
     if (fs_status rc = sort_candidates(counts, R, 0, q, s); rc != FS_OK) return rc;
     const unsigned sum_grid = sum_tiles < 2048 ? (unsigned)sum_tiles : 2048u;        // 8 blocks per CU
     FS_LAUNCH("tiers_tile_sums", tiers_tile_sums_kernel, dim3(sum_grid), dim3(kBlock), s,
-              q.keys_a, q.keys_b, q.count_bits, q.num_cand, tile_sum);
+              q.keys_a, q.keys_b, q.count_bits, q.first_bits, q.num_cand, tile_sum);
     FS_LAUNCH("tiers_scan_sums", tiers_scan_sums_kernel, dim3(1), dim3(kScanBlock), s, tile_sum, q.num_cand);
-    FS_LAUNCH("tiers_cuts", tiers_cuts_kernel, dim3(1), dim3(kBlock), s, q.keys_a, q.keys_b, q.count_bits, q.num_cand,
+    FS_LAUNCH("tiers_cuts", tiers_cuts_kernel, dim3(1), dim3(kBlock), s, q.keys_a, q.keys_b, q.count_bits, q.first_bits, q.num_cand,
               tile_sum, c, cuts);
-    FS_LAUNCH("tiers_emit", tiers_emit_kernel, dim3(1024), dim3(kBlock), s, q.vals_a, q.vals_b, q.count_bits, cuts, cap, (int)p.W,
+    FS_LAUNCH("tiers_emit", tiers_emit_kernel, dim3(1024), dim3(kBlock), s, q.vals_a, q.vals_b, q.count_bits, q.first_bits, cuts, cap, (int)p.W,
               sorted_rows, placement);
     return FS_OK;
 }

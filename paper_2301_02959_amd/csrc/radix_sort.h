@@ -42,17 +42,21 @@ size_t radix_sort_scratch_bytes(int64_t m_max);
 //   varying (or null): a device word with every bit set in which two keys differ.  Passes above its highest set bit
 //   copy nothing and return at once; the result is then where the last pass that ran left it, which only the device
 //   knows: sort_result_in_b below, for pairs that came in A (and not in `src`).
+//   first_bits: with `varying` (and 32 key bits), the bits of the first two passes; two more share the rest.  Without it
+//   the bits are spread evenly over as few passes as possible.
 fs_status radix_sort_pairs(uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b, uint32_t* vals_b,
                            int64_t m_max, const int64_t* m_dev, int key_bits, void* scratch,
                            hipStream_t stream, uint32_t** keys_out, uint32_t** vals_out,
-                           const SortSource& src = SortSource(), const uint32_t* varying = nullptr);
+                           const SortSource& src = SortSource(), const uint32_t* varying = nullptr,
+                           int first_bits = kSortMaxDigitBits);
 
 #ifdef __HIPCC__
-// Whether a sort by 32 bits with `varying` left its result in the B buffers.
-__device__ __forceinline__ bool sort_result_in_b(uint32_t varying)
+// Whether a sort by 32 bits with `varying` and `first_bits` left its result in the B buffers.
+__device__ __forceinline__ bool sort_result_in_b(uint32_t varying, int first_bits)
 {
     const int bits = varying == 0 ? 1 : 32 - __builtin_clz(varying);
-    return ((bits + kSortMaxDigitBits - 1) / kSortMaxDigitBits) & 1;
+    const int passes = bits <= first_bits ? 1 : bits <= 2 * first_bits ? 2 : bits <= 16 + first_bits ? 3 : 4;
+    return passes & 1;
 }
 #endif
 

@@ -494,7 +494,7 @@ static fs_status launch_sort_pass(const Reader& in, const SortShape& shape, int6
 fs_status radix_sort_pairs(uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b, uint32_t* vals_b,
                            int64_t m_max, const int64_t* m_dev, int key_bits, void* scratch,
                            hipStream_t stream, uint32_t** keys_out, uint32_t** vals_out, const SortSource& src,
-                           const uint32_t* varying)
+                           const uint32_t* varying, int first_bits)
 {
     *keys_out = keys_a;
     *vals_out = vals_a;
@@ -510,7 +510,7 @@ fs_status radix_sort_pairs(uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
     const int64_t chunks = sort_chunks_max(shape.tiles);
     uint32_t* chunk_sums = c.take<uint32_t>((size_t)kSortMaxBins * (size_t)chunks);
 
-    const int passes = radix_sort_passes(key_bits);
+    const int passes = varying == nullptr ? radix_sort_passes(key_bits) : 4;          // with `varying`: 32 bits
     // The second scan level is the scatter's for up to kSortSumChunks chunks.  When the pair count lives on
     // the device (the plan's candidates: a few per cent of the rows the buffers are sized for), "small" cannot be
     // known here; the second level then runs inside the first one's launch if it turns out larger, up to a size at
@@ -523,13 +523,13 @@ fs_status radix_sort_pairs(uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
     uint32_t* dst_k = from_rows ? keys_a : keys_b;
     uint32_t* dst_v = from_rows ? vals_a : vals_b;
     for (int p = 0; p < passes; ++p) {
-        // spread the bits evenly over the passes: 27 bits -> 9, 9, 9; where passes can turn out idle the digits are
-        // as wide as they can be: 32 bits -> 10, 10, 10, 2, and the last pass, which only counts of 2^30 and more
-        // need, has a grid that costs little when it is idle (new tiers for 40 M rows 402 -> 393 us)
+        // spread the bits evenly over the passes: 27 bits -> 9, 9, 9; where passes can turn out idle the digits are fixed:
+        // 32 bits -> 10, 10, 6, 6 or 8, 8, 8, 8.  The short digits are mostly idle: their grid costs little then, and is
+        // two whole rounds of the 3 blocks that a CU holds when they are not.
         const int left = key_bits - shift;
         const int even = (left + (passes - p) - 1) / (passes - p);
-        const int nbits = varying == nullptr ? even : (left < kSortMaxDigitBits ? left : kSortMaxDigitBits);
-        const unsigned max_grid = varying != nullptr && p == passes - 1 ? 1024u : (unsigned)kSortMaxGrid;
+        const int nbits = varying != nullptr && p < 2 ? first_bits : even;
+        const unsigned max_grid = varying != nullptr && nbits < 8 ? 1536u : (unsigned)kSortMaxGrid;
         fs_status rc = FS_OK;
         if (p == 0 && from_rows) {
             const RowPosReader in{src.rows, src.pos, src.R, src.n};

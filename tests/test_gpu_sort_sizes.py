@@ -54,7 +54,7 @@ def check_sort(G, m, R):
 @pytest.mark.parametrize("R", [1, 1024, 128 * 1024, 128 * 1024 + 1, 64 * 4096, 64 * 4096 + 1, 1024 * TILE, 1024 * TILE + 1])
 @pytest.mark.parametrize("bits,share", [(1, 0.9), (10, 0.01), (11, 0.3), (20, 0.05), (21, 0.3), (30, 0.1), (31, 0.3), (32, 0.02)])
 def test_selection_sizes(G, R, bits, share):
-    """Counts of up to `bits` bits on `share` of the rows: passes are left out at 10, 20 and 30 bits."""
+    """Counts of up to `bits` bits on `share` of the rows: passes are left out at 10, 20 and 26 bits."""
     import paper_2301_02959_amd as fs
     rng = np.random.default_rng(R + bits)
     counts = np.where(rng.random(R) < share, 1 + rng.geometric(0.4, R), 0).astype(np.uint64)
@@ -85,6 +85,35 @@ def test_selection_sizes(G, R, bits, share):
     orc, ocuts, orows = oracle.plan_tiers(counts, params, 3)
     assert orc == 0 and cuts.cpu().numpy().tolist() == ocuts.tolist()
     assert np.array_equal(rows[:len(orows)].cpu().numpy(), orows)
+
+
+@pytest.mark.parametrize("R", [1000, 100_000, 300_000, 1 << 26, (1 << 26) + 1])
+def test_selection_at_every_number_of_passes(G, R):
+    """Largest counts on both sides of every digit's end: 10, 20 and 26 bits up to 2^26 rows, 8, 16 and 24 beyond.  The order
+    is that of numpy's stable sort of the candidates."""
+    import paper_2301_02959_amd as fs
+    rng = np.random.default_rng(R)
+    K = min(R // 3, 60_000)
+    rows = np.sort(rng.choice(R, K, replace=False))
+    dev = torch.zeros(R, dtype=torch.int32, device=G.DEV)
+    sel = torch.zeros(K, dtype=torch.int64, device=G.DEV)
+    num = torch.zeros(1, dtype=torch.int64, device=G.DEV)
+    cuts = torch.zeros(fs.FS_TIER_CUTS, dtype=torch.int64, device=G.DEV)
+    params = dict(num_samples=1000, B=64, U=8, W=4, dp_multiplier=6, granule=8, a2a_global=1, a2a_intra=6, ar_global=3, ar_cross=2)
+    at = G.to_dev(rows)
+    for bits in [1, 8, 9, 10, 11, 16, 17, 20, 21, 24, 25, 26, 27, 32]:
+        counts = 1 + rng.integers(0, 1 << rng.integers(0, bits, K), K).astype(np.uint64)     # every length up to `bits`
+        counts = np.minimum(counts, (1 << bits) - 1)
+        counts[rng.integers(0, K)] = 1 << (bits - 1)
+        dev[at] = G.to_dev(counts.astype(np.uint32).view(np.int32))
+        order = rows[np.argsort(-counts.astype(np.int64), kind="stable")]
+        fs.fs_plan_replication(None, None, 1, 1, None, 0, R, dev, S, K, 1, sel, num)
+        assert int(num.item()) == K and np.array_equal(sel.cpu().numpy(), order), bits
+        sel.fill_(-7)
+        fs.fs_plan_tiers(dev, R, params, 3, sel, K, cuts)
+        n = int(cuts[fs.FS_CUT_N_DP] + cuts[fs.FS_CUT_N_FLEX])
+        assert int(cuts[fs.FS_CUT_CANDIDATES]) == K and int(cuts[fs.FS_CUT_SUM_ALL]) == int(counts.sum()), bits
+        assert np.array_equal(sel[:n].cpu().numpy(), order[:n]), bits
 
 
 def test_a_workspace_for_more_rows_serves_fewer():
