@@ -246,9 +246,11 @@ __global__ __launch_bounds__(kHistBlock) void plan_histogram_kernel(
     }
 }
 
-// Span length for n ids: a span for every CU up to 32 k ids each (one block of 8192 ids spends its time on its 16 k
-// slots and a chain of rounds: 14.9 us, four blocks of 2048 with the offsets checked inside 8.6; 4.2 M ids 105 us at
-// 16 k as at 32 k), then 32 k spans.  From one 64 k span for each of the two
+// Span length for n ids: 2048 ids up to 256 spans, then 129 to 256 spans of whole rounds of 2048 ids, up to 32 k each (one
+// block of 8192 ids spends its time on its 16 k slots and a chain of rounds: 14.9 us, four blocks of 2048 with the offsets
+// checked inside 8.6; 4.2 M ids 105 us at 16 k as at 32 k), then 32 k spans.  Shorter spans are never more than 256, so that
+// the blocks check the offsets themselves (257 and a launch for the check: 7 us more); rounds broken up for a span on every
+// CU gain nothing (540 k ids in 235 spans of 2304 23.6 us, in 132 of 4096 22.5).  From one 64 k span for each of the two
 // blocks a CU holds, spans of up to 128 k ids, shortened so that their number is a multiple of the CU count
 // where that is possible.  A popular row is flushed once per span, so a planning pass over very many ids
 // (from 2^27) takes spans of up to 512 k ids, all of one length and a whole number of rounds over the chip's
@@ -265,7 +267,7 @@ constexpr int64_t kHistCus = 256;
 static int64_t hist_span(int64_t n)
 {
     if (n < 2 * kHistCus * (kHistSpanLarge / 2)) {                // under one 64 k span for every CU, twice over
-        const int64_t share = (n / kHistCus + 2047) / 2048 * 2048;
+        const int64_t share = ((n + kHistCus - 1) / kHistCus + 2047) / 2048 * 2048;
         return share < kHistSpanSmall ? (share > 2048 ? share : 2048) : kHistSpanSmall;
     }
     const int64_t longest = n >= kHistHugeFrom ? kHistSpanHuge : kHistSpanLarge;

@@ -153,3 +153,16 @@ def test_histogram_sizes(G, T, B, n, bad):
     orc, ost, _ = oracle.plan_replication(ids, offsets, T, B, row_base, T * E, oc, oracle.PLAN_ACCUMULATE, n=n)
     assert orc == 0 and int(st.item()) == ost and (ost != 0) == bad
     assert np.array_equal(dev.cpu().numpy().view(np.uint32), oc)
+
+
+@pytest.mark.parametrize("n", [2048, 256 * 2048, 256 * 2048 + 1, 256 * 2048 + 255, 256 * 2048 + 256, 700_001, 256 * 30_720 + 1, 256 * 32_768])
+def test_batches_are_counted_in_one_launch(G, n):
+    """Up to 256 spans the counting blocks check the offsets themselves, and shorter spans never make more of them."""
+    import paper_2301_02959_amd as fs
+    ids = torch.randint(0, 999, (n,), device=G.DEV)
+    offsets, row_base = (torch.tensor([0, end], device=G.DEV) for end in (n, 999))
+    counts = torch.zeros(999, dtype=torch.int32, device=G.DEV)
+    fs.fs_prof_begin(16)
+    fs.fs_plan_replication(ids, offsets, 1, 1, row_base, n, 999, counts, fs.FS_PLAN_ACCUMULATE)
+    assert [name for name, _ in fs.fs_prof_end(16)] == ["plan_histogram"]
+    assert torch.equal(counts.long(), torch.bincount(ids, minlength=999))
