@@ -53,6 +53,22 @@ def test_few_chunks(G, dt, D, m):
     _check(G, gnp, gt, rows, pos, 0, m, R, dt)
 
 
+@pytest.mark.parametrize("dt,D", [("f32", 4), ("f32", 60), ("f32", 64), ("f32", 100), ("f16", 8), ("bf16", 24), ("bf16", 128), ("f16", 136),
+                                  ("f16", 264)])
+@pytest.mark.parametrize("R", [1, 2, 3, 5, 31, 32, 33, 64, 65])
+def test_few_rows_in_a_chunk(G, dt, D, R):
+    """Chunks of at most as many run pieces as fit side by side with one column to a lane (64 rows of one piece of f32
+    down to two of 128 16-bit columns), and of one more."""
+    rng = np.random.default_rng(D + R)
+    m = 4 * CHUNK + 77
+    rows = np.sort(np.concatenate([np.arange(R), rng.integers(0, R, CHUNK - R), np.full(m - CHUNK, R - 1)]))   # all in the first chunk
+    pos = (np.arange(m) % 611).astype(np.int32)
+    pos = pos[np.lexsort((pos, rows))]
+    gnp, gt = _np_grad(rng.standard_normal((611, D)).astype(np.float32), dt)
+    _check(G, gnp, gt, rows, pos, 0, m, R, dt, atomic_too=False)
+    check_atomic(G, gnp, gt, rows, pos, R, dt)
+
+
 @pytest.mark.parametrize("dt,D", [("f32", 4), ("bf16", 72), ("f16", 128), ("f32", 68), ("f16", 264)])
 @pytest.mark.parametrize("m", [1024 * CHUNK, 1024 * CHUNK + 1])
 def test_around_the_rule(G, dt, D, m):
