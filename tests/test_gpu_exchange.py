@@ -335,3 +335,22 @@ def test_tag_slots_at_every_alignment(G, R, skip):
     expected = np.concatenate([full[:skip], part, full[skip + R:]])
     assert orc == 0 and int(st.item()) == ost
     assert np.array_equal(dev.cpu().numpy().view(np.uint32), expected)
+
+
+@pytest.mark.parametrize("skip", [0, 1, 2, 3])
+@pytest.mark.parametrize("R", [1, 4, 7, 4096, 4099, 300_007])
+@pytest.mark.parametrize("share", [0.02, 0.5, 1.0])
+def test_tag_slots_with_slots_at_the_same_alignment(G, R, skip, share):
+    """Slots that lie as the placement does are read four at a time: few, half or all of the rows replicated."""
+    import paper_2301_02959_amd as fs
+    rng = np.random.default_rng(R + skip)
+    full = (rng.integers(0, 1 << 30, R + 8, dtype=np.uint64) | (rng.integers(1, 4, R + 8, dtype=np.uint64) << 30)).astype(np.uint32)
+    full[rng.random(R + 8) < share] &= np.uint32(0x3FFFFFFF)                     # tier 0
+    slots = np.where(rng.random(R + 8) < 0.5, -1, rng.integers(0, 0x3FFFFFFF, R + 8)).astype(np.int32)
+    dev = torch.from_numpy(full.view(np.int32).copy()).to(G.DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    fs.fs_replica_tag_slots(dev[skip:skip + R], torch.from_numpy(slots).to(G.DEV)[skip:skip + R], st)
+    part = np.ascontiguousarray(full[skip:skip + R])
+    orc, ost = oracle.replica_tag_slots(part, slots[skip:skip + R])
+    assert orc == 0 and int(st.item()) == ost
+    assert np.array_equal(dev.cpu().numpy().view(np.uint32), np.concatenate([full[:skip], part, full[skip + R:]]))
