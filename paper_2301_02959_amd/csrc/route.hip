@@ -67,7 +67,7 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     __shared__ int64_t table_end[kRouteTileTables];   // tables t_lo .. t_hi of the tile: first lookup after table t,
     __shared__ int64_t table_first[kRouteTileTables]; // its first row,
     __shared__ int64_t table_rows[kRouteTileTables];  // and how many it has
-    __shared__ unsigned int wave_counts[kWavesPerBlock][4];   // the three tiers, lookups of the own bucket
+    __shared__ unsigned int wave_counts[kWavesPerBlock][3];   // tiers 1 and 2, lookups of the own bucket
     const int64_t tile = blockIdx.x;
     const int64_t base = tile * kRouteTile;
     const int w = wave_id();
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     // Counts of the wave: the tiers and the own bucket with one ballot each, and (LEAD) one more for the bucket of the
     // wave's first lookup that goes elsewhere: a bucket that most of the rest go to (few buckets, whole tables or a hot row
     // on one other GPU) is nearly always that one.  What is left are plain LDS adds, of which few meet in one word.
-    uint32_t in_tier0 = 0, in_tier1 = 0, in_tier2 = 0, own = 0;
+    uint32_t in_tier1 = 0, in_tier2 = 0, own = 0;                    // tier 0: the tile's other lookups
     uint32_t led = 0, in_led = 0;                                    // led: any bucket if the first item has none
 #pragma unroll
     for (int it = 0; it < kRouteItems; ++it) {
@@ -175,12 +175,10 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
         }
         in_tier1 += (uint32_t)__popcll(ballot(valid && tier == FS_TIER_GROUP));
         in_tier2 += (uint32_t)__popcll(ballot(valid && tier == FS_TIER_SHARDED));
-        in_tier0 += (uint32_t)__popcll(ballot(valid && tier != FS_TIER_GROUP && tier != FS_TIER_SHARDED));
         own += (uint32_t)__popcll(ballot(valid && dest == (uint32_t)self));
     }
     if (lane_id() == 0) {
-        wave_counts[w][0] = in_tier0; wave_counts[w][1] = in_tier1; wave_counts[w][2] = in_tier2;
-        wave_counts[w][3] = own;
+        wave_counts[w][0] = in_tier1; wave_counts[w][1] = in_tier2; wave_counts[w][2] = own;
         if (LEAD && in_led != 0) atomicAdd(&lds_hist[led], in_led);
     }
     __syncthreads();
@@ -191,10 +189,14 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     };
     uint32_t* my_hist = by_tile ? tile_hist + tile * (U + 3) : tile_hist + tile;
     const int64_t step = by_tile ? 1 : tiles;
-    for (int b = threadIdx.x; b < U; b += kBlock) my_hist[b * step] = b == self ? waves_sum(3) : lds_hist[b];
+    for (int b = threadIdx.x; b < U; b += kBlock) my_hist[b * step] = b == self ? waves_sum(2) : lds_hist[b];
     // tier counts travel as three more histogram rows (no global atomics: 3 hot addresses
     // shared by every wave of the grid serialise in L2)
-    if (threadIdx.x < 3) my_hist[(U + threadIdx.x) * step] = waves_sum(threadIdx.x);
+    if (threadIdx.x < 3) {
+        const uint32_t in_tile = (uint32_t)(n - base < kRouteTile ? n - base : kRouteTile);
+        const uint32_t in_tier = threadIdx.x == 0 ? in_tile - waves_sum(0) - waves_sum(1) : waves_sum(threadIdx.x - 1);
+        my_hist[(U + threadIdx.x) * step] = in_tier;
+    }
 
     bool bad = has_segment && seg0 > seg1;
     for (int64_t sg = s_lo + threadIdx.x + kBlock; sg < s_hi; sg += kBlock) bad |= offsets[sg] > offsets[sg + 1];
@@ -425,7 +427,7 @@ static fs_status route_run(
     FS_LAUNCH_SMEM("route_remap", route_remap_kernel<LEAD>, dim3((unsigned)tiles), dim3(kBlock), (size_t)U * sizeof(uint32_t), s, \
                    ids, offsets, (int)T, (int64_t)B, row_base, placement, n, (int)U, (int)W, (int)self,             \
                    dest_tmp, g_tmp, slot_tmp, tile_hist, tiles, sum ? 1 : 0, dev_status)
-        if (tiles > kRouteLeadTiles) FS_REMAP(true);
+        if (tiles > kRouteLeadTiles && U > 1) FS_REMAP(true);
         else FS_REMAP(false);
 #undef FS_REMAP
         if (!sum)
