@@ -1,11 +1,12 @@
 // fs_plan_replication: row-frequency histogram and top-k rows under a byte budget.
 //
-// ACCUMULATE  plan_histogram: each block walks a span of 32768 sampled ids.  Zipf samples hit
-//             a few rows most of the time, so a block keeps a 4096-entry direct-mapped cache of
-//             (row, count) in LDS (first row to claim a slot keeps it); only misses and the final
-//             flush reach the global counters, as saturating 32-bit atomic adds.
-// SELECT      plan_mark / plan_scan / plan_move: stable compaction of the candidate rows (count > 0,
-//             or all) in ascending row order into (key = ~count, value = row), reading counts once;
+// ACCUMULATE  plan_histogram: each block counts a span of the sampled ids (2048 to 512 k of them, see hist_span).  Zipf
+//             samples hit a few rows most of the time, so a block counts in a table of 2^14 entries in LDS, two slots
+//             to choose from for a row (the first row to claim a slot keeps it); only rows that find both taken and
+//             the final flush reach the global counters, as saturating 32-bit atomic adds.  The offsets are checked by
+//             the same blocks, or by plan_check_offsets before them where there are many.
+// SELECT      plan_mark / plan_move: stable compaction of the candidate rows (count > 0, or all) in ascending row order into
+//             (key = ~count, value = row), reading counts once (plan_scan between them where the tiles are many);
 //             a stable radix sort by key then yields (count desc, row asc); plan_emit writes the
 //             first k = min(budget / bytes_per_row, #candidates) rows, k, and the tier-0 tags.
 // The candidate count lives in device memory; the sort kernels read it there.
@@ -564,7 +565,7 @@ __global__ __launch_bounds__(kBlock) void plan_emit_kernel(
 // key = ~count.  The breakpoints are thresholds on the count (found on the host from the
 // parameters), so points A, C and the Flex breakpoint are partition points of the sorted keys;
 // point B and the Flex budget need sums of counts over prefixes, which come from one pass of
-// per-tile sums plus a scan of those.  One wave then finds every cut with 64-way searches.
+// per-tile sums plus a scan of those.  One block then finds every cut, a wave to each 64-way search.
 constexpr int kSumTile = 4096;                // sorted counts per tile sum
 
 typedef unsigned __int128 u128;

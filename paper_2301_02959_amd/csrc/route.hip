@@ -384,7 +384,7 @@ __global__ __launch_bounds__(kBlock) void route_finalize_kernel(
     }
 }
 
-// Both entry points: host checks, workspace carving, the five launches.
+// All three entry points: host checks, workspace carving, and the launches (remap, scan unless the counts are few, scatter).
 static fs_status route_run(
     const int64_t* ids, const int64_t* offsets, int32_t T, int32_t B,
     const int64_t* row_base, const uint32_t* placement,

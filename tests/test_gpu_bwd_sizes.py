@@ -81,6 +81,15 @@ def test_around_the_rule(G, dt, D, m):
     check_atomic(G, gnp, gt, rows, pos, R, dt)
 
 
+@pytest.mark.parametrize("m", [64 * CHUNK - 1, 64 * CHUNK, 64 * CHUNK + 1, 128 * CHUNK, 128 * CHUNK + 1])
+def test_around_the_blocks_of_the_run_counts(G, m):
+    """64 chunks are one block of the run counts, which then writes the totals itself; 65 are two and a scan."""
+    rng = np.random.default_rng(m)
+    rows, pos = lookups(rng, m, 9_000)
+    gnp, gt = _np_grad(rng.standard_normal((m, 16)).astype(np.float32), "bf16")
+    _check(G, gnp, gt, rows, pos, 0, m, 9_000, "bf16")
+
+
 @pytest.mark.parametrize("R", [1, 2, 3])
 @pytest.mark.parametrize("m", [1025 * CHUNK, 1025 * CHUNK + 77])
 def test_walks_of_whole_chunks(G, R, m):
