@@ -290,31 +290,55 @@ __global__ __launch_bounds__(kBlock) void route_scatter_kernel(
             part_before[threadIdx.x] = before;
             __syncthreads();
         }
-        uint32_t sum = 0;
-        for (int b = lo; b < hi; ++b) {
-            uint32_t all = 0, before = 0;
-            if constexpr (kParts > 1) {
-                for (int q = 0; q < kParts && q < (int)tiles; ++q) { all += part_all[q * kBins + b]; before += part_before[q * kBins + b]; }
-            } else if constexpr (SUM) {
-#pragma unroll 8
-                for (int k = 0; k < (int)tiles; ++k) {
-                    const uint32_t v = tile_hist[k * stride + b];
-                    all += v;
-                    before += k < (int)tile ? v : 0u;
-                }
-            } else {
-                all = totals[b];
-                before = tile_hist[(int64_t)b * tiles + tile];
-            }
-            bucket_base[b] = sum + before;
-            if (writes_offsets) bucket_offsets[b] = (int64_t)sum;       // both completed below
-            sum += all;
-        }
         uint32_t unused;
-        const uint32_t run = block_exclusive_scan(sum, wave_sums, &unused);
-        for (int b = lo; b < hi; ++b) {
-            bucket_base[b] += run;
-            if (writes_offsets) bucket_offsets[b] += (int64_t)run;
+        if constexpr (SUM) {
+            uint32_t sum = 0;
+            for (int b = lo; b < hi; ++b) {
+                uint32_t all = 0, before = 0;
+                if constexpr (kParts > 1) {
+                    for (int q = 0; q < kParts && q < (int)tiles; ++q) { all += part_all[q * kBins + b]; before += part_before[q * kBins + b]; }
+                } else {
+#pragma unroll 8
+                    for (int k = 0; k < (int)tiles; ++k) {
+                        const uint32_t v = tile_hist[k * stride + b];
+                        all += v;
+                        before += k < (int)tile ? v : 0u;
+                    }
+                }
+                bucket_base[b] = sum + before;
+                if (writes_offsets) bucket_offsets[b] = (int64_t)sum;   // both completed below
+                sum += all;
+            }
+            const uint32_t run = block_exclusive_scan(sum, wave_sums, &unused);
+            for (int b = lo; b < hi; ++b) {
+                bucket_base[b] += run;
+                if (writes_offsets) bucket_offsets[b] += (int64_t)run;
+            }
+        } else {
+            // per <= kPer; a thread's loads all in flight (20 M lookups over 4096 buckets 523 us bucket by bucket, 412 so)
+            constexpr int kPer = kBins > kBlock ? kBins / kBlock : 1;
+            uint32_t all[kPer], before[kPer];
+            uint32_t sum = 0;
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                const int b = lo + q < hi ? lo + q : U - 1;             // past its buckets: the last one again, unused
+                all[q] = totals[b];
+                before[q] = tile_hist[(int64_t)b * tiles + tile];
+            }
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                if (lo + q >= hi) all[q] = 0;
+                sum += all[q];
+            }
+            uint32_t run = block_exclusive_scan(sum, wave_sums, &unused);
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                if (lo + q < hi) {
+                    bucket_base[lo + q] = run + before[q];
+                    if (writes_offsets) bucket_offsets[lo + q] = (int64_t)run;
+                    run += all[q];
+                }
+            }
         }
         if (writes_offsets) {
             if (threadIdx.x == 0) bucket_offsets[U] = n;                // every lookup has a bucket

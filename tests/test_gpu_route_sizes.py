@@ -65,3 +65,23 @@ def test_where_most_lookups_go_to_one_other_bucket(G, n, U, self_, owners):
     assert (rc, st) == (orc, ost) == (0, 0)
     assert np.array_equal(bo.cpu().numpy(), obo) and np.array_equal(tc.cpu().numpy(), otc)
     assert np.array_equal(rows.cpu().numpy(), orows) and np.array_equal(pos.cpu().numpy(), opos)
+
+
+@pytest.mark.parametrize("U", [255, 256, 257, 300, 511, 512, 513, 1500, 2049, 4095, 4096])
+def test_buckets_a_thread_holds_in_registers(G, U):
+    """Buckets that do not share out evenly over a scatter block's 256 threads, with one tile more than the blocks sum
+    themselves."""
+    rng = np.random.default_rng(U)
+    n = (6144 // (U + 3) + 1) * TILE - 11
+    T, B, E = 2, 9, 3 * U
+    offsets = np.concatenate([[0], np.sort(rng.integers(0, n + 1, T * B - 1)), [n]]).astype(np.int64)
+    ids = rng.integers(0, E, n).astype(np.int64)
+    row_base = (np.arange(T + 1) * E).astype(np.int64)
+    placement = random_placement(rng, T * E, U, 1)
+    self_ = U - 1
+    rc, st, bo, rows, pos, tc = G.hip_route(G.to_dev(ids), G.to_dev(offsets), T, B, G.to_dev(row_base),
+                                            G.placement_dev(placement), U, 1, self_, n=n)
+    orc, ost, obo, orows, opos, otc = oracle.route_bucketize(ids, offsets, T, B, row_base, placement, U, 1, self_, n=n)
+    assert (rc, st) == (orc, ost) == (0, 0)
+    assert np.array_equal(bo.cpu().numpy(), obo) and np.array_equal(tc.cpu().numpy(), otc)
+    assert np.array_equal(rows.cpu().numpy(), orows) and np.array_equal(pos.cpu().numpy(), opos)
