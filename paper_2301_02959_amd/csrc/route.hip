@@ -38,6 +38,11 @@ constexpr int64_t kRouteSumMax = 6144;
 // 73.5.  2.4 M: plain 20.7 and 16.4, so 16.9 and 16.8.  Up to one tile the waves' own chains are the time, and the ballots
 // cost 0.4 us of 8.6 where the adds that meet cost 0.2.
 constexpr int64_t kRouteLeadTiles = 256;
+// From this many bits of the bucket number (more than 2048 buckets) a scatter thread owns up to 16 buckets, and has the
+// loads of all of them in flight: 20 M lookups over 4096 buckets 523 us bucket by bucket, 412 so, 72 M over 16 tables 1457,
+// 1379.  With fewer the blocks then come to their stores at other times and write 3 % more: 72 M over 2048 buckets 923,
+// 953, over 128 359, 380.
+constexpr int kRouteBasesBits = 12;
 
 __global__ __launch_bounds__(kBlock) void route_prepare_kernel(
     const int64_t* __restrict__ offsets, int64_t S, int64_t n, int32_t* status)
@@ -291,19 +296,22 @@ __global__ __launch_bounds__(kBlock) void route_scatter_kernel(
             __syncthreads();
         }
         uint32_t unused;
-        if constexpr (SUM) {
+        if constexpr (SUM || NBITS < kRouteBasesBits) {
             uint32_t sum = 0;
             for (int b = lo; b < hi; ++b) {
                 uint32_t all = 0, before = 0;
                 if constexpr (kParts > 1) {
                     for (int q = 0; q < kParts && q < (int)tiles; ++q) { all += part_all[q * kBins + b]; before += part_before[q * kBins + b]; }
-                } else {
+                } else if constexpr (SUM) {
 #pragma unroll 8
                     for (int k = 0; k < (int)tiles; ++k) {
                         const uint32_t v = tile_hist[k * stride + b];
                         all += v;
                         before += k < (int)tile ? v : 0u;
                     }
+                } else {
+                    all = totals[b];
+                    before = tile_hist[(int64_t)b * tiles + tile];
                 }
                 bucket_base[b] = sum + before;
                 if (writes_offsets) bucket_offsets[b] = (int64_t)sum;   // both completed below
@@ -315,8 +323,7 @@ __global__ __launch_bounds__(kBlock) void route_scatter_kernel(
                 if (writes_offsets) bucket_offsets[b] += (int64_t)run;
             }
         } else {
-            // per <= kPer; a thread's loads all in flight (20 M lookups over 4096 buckets 523 us bucket by bucket, 412 so)
-            constexpr int kPer = kBins > kBlock ? kBins / kBlock : 1;
+            constexpr int kPer = kBins / kBlock;                        // per <= kPer: a thread's loads all in flight
             uint32_t all[kPer], before[kPer];
             uint32_t sum = 0;
 #pragma unroll

@@ -67,7 +67,7 @@ def test_where_most_lookups_go_to_one_other_bucket(G, n, U, self_, owners):
     assert np.array_equal(rows.cpu().numpy(), orows) and np.array_equal(pos.cpu().numpy(), opos)
 
 
-@pytest.mark.parametrize("U", [255, 256, 257, 300, 511, 512, 513, 1500, 2049, 4095, 4096])
+@pytest.mark.parametrize("U", [255, 256, 257, 300, 513, 1023, 1024, 1025, 1500, 2047, 2048, 2049, 4095, 4096])
 def test_buckets_a_thread_holds_in_registers(G, U):
     """Buckets that do not share out evenly over a scatter block's 256 threads, with one tile more than the blocks sum
     themselves."""
