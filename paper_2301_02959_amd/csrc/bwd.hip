@@ -412,8 +412,9 @@ struct Bytes<8> {
 // 4 bytes to a lane for rows of up to 256 bytes: a chunk per wave instead of four of them in 16-lane groups with 16
 // bytes to a lane gives four times the waves and no divergent flushes: 1.05 M lookups of 256-byte rows 74 -> 58 us,
 // 4.2 M 244 -> 206, 8.4 M (a table's head row is a quarter of them) 438 -> 408.  8 bytes for longer rows, where both
-// measure the same within the runs' spread (15.7 M lookups of 512-byte rows 1528 us, 72 M 5.9 to 7.0 ms where the bare stream
-// of the same mix takes 6.4 to 7.6; 4 bytes on 72 M 1 % more): the chip's rate is what bounds them.  On 256-byte rows 8 would leave half the lanes idle (937 us).  16 rows to a batch instead of 8 measure the same.
+// measure the same within the runs' spread (15.7 M lookups of 512-byte rows 1528 us, 72 M 5.9 to 7.0 ms where the bare
+// stream of the same mix takes 6.4 to 7.6; 4 bytes on 72 M 1 % more): the chip's rate is what bounds them.  On 256-byte
+// rows 8 would leave half the lanes idle (937 us).  16 rows to a batch instead of 8 measure the same.
 template <int VB, int DT>
 __global__ __launch_bounds__(kBlock) void bwd_segreduce_kernel(
     const unsigned char* __restrict__ grad, int row_bytes, int D,
