@@ -1143,10 +1143,8 @@ extern "C" fs_status fs_seq_grad_bwd(
     const int units = (int)(row_bytes / 16);
 
     Carver ws(workspace);
-    uint32_t* keys_a = ws.take<uint32_t>((size_t)m);
-    uint32_t* vals_a = ws.take<uint32_t>((size_t)m);
-    uint32_t* keys_b = ws.take<uint32_t>((size_t)m);
-    uint32_t* vals_b = ws.take<uint32_t>((size_t)m);
+    SortPair* pairs_a = ws.take<SortPair>((size_t)m);
+    SortPair* pairs_b = ws.take<SortPair>((size_t)m);
     char* sort_scratch = ws.take<char>(radix_sort_scratch_bytes(m));
     const BwdScratch scratch = take_bwd_scratch(ws, m, (int)D, (int)variant);
     if (!workspace) { *workspace_bytes = ws.used; return FS_OK; }
@@ -1162,16 +1160,16 @@ extern "C" fs_status fs_seq_grad_bwd(
     if (cap_unique > 0 && (!uniq_rows || !row_grads)) return FS_ERR_NULL;
     if ((reinterpret_cast<uintptr_t>(grad_out) | reinterpret_cast<uintptr_t>(row_grads)) & 15) return FS_ERR_ALIGN;
 
-    uint32_t* keys = nullptr;
-    uint32_t* vals = nullptr;
-    SortSource source;                           // the sort's first pass reads (row, pos) itself
-    source.rows = rows + j0;
-    source.pos = pos + j0;
-    source.R = R;
-    source.n = n;
-    source.status = dev_status;
-    fs_status rc = radix_sort_pairs(keys_a, vals_a, keys_b, vals_b, m, nullptr, bits_for((uint64_t)(R - 1)),
-                                    sort_scratch, s, &keys, &vals, source);
+    SortJob job;                                 // the sort's first pass reads (row, pos) itself
+    job.rows = rows + j0; job.pos = pos + j0; job.R = R; job.n = n; job.status = dev_status;
+    job.pairs_a = pairs_a; job.pairs_b = pairs_b;
+    job.m_max = m; job.key_bits = bits_for((uint64_t)(R - 1));
+    job.scratch = sort_scratch; job.stream = s;
+    // rows and positions apart in the buffer that the last pass does not read
+    uint32_t* keys = reinterpret_cast<uint32_t*>((radix_sort_passes(job.key_bits) & 1) ? pairs_a : pairs_b);
+    uint32_t* vals = keys + m;
+    job.keys_out = keys; job.vals_out = vals;
+    fs_status rc = radix_sort(job);
     if (rc != FS_OK) return rc;
     return bwd_after_sort(grad_out, n, (int)D, dtype, units, keys, vals, m, R, (int)variant, uniq_rows, row_grads,
                           cap_unique, num_unique, scratch, s, dev_status);
@@ -1187,35 +1185,23 @@ extern "C" fs_status fs_sort_lookups(
     if (R < 1 || R >= 4294967295LL || n < 0 || n >= (1LL << 31) || j0 < 0 || j0 > j1) return FS_ERR_SIZE;
     const int64_t m = j1 - j0;
     if (m >= (1LL << 31)) return FS_ERR_SIZE;
+    const int key_bits = bits_for((uint64_t)(R - 1));
+    const int passes = radix_sort_passes(key_bits);
     Carver ws(workspace);
-    uint32_t* keys_w = ws.take<uint32_t>((size_t)m);
-    uint32_t* vals_w = ws.take<uint32_t>((size_t)m);
+    SortPair* pairs_a = ws.take<SortPair>((size_t)m);
+    SortPair* pairs_b = ws.take<SortPair>(passes > 2 ? (size_t)m : 0);
     char* sort_scratch = ws.take<char>(radix_sort_scratch_bytes(m));
     if (!workspace) { *workspace_bytes = ws.used; return FS_OK; }
     if (*workspace_bytes < ws.used || (reinterpret_cast<uintptr_t>(workspace) & 255)) return FS_ERR_WORKSPACE;
     if (m == 0) return FS_OK;
     if (!rows || !pos || !sorted_rows || !sorted_pos) return FS_ERR_NULL;
-    // The first pass reads (rows, pos) and writes buffer A, later passes alternate A -> B -> A: with an odd
-    // number of passes the result lands in A, with an even number in B.  The caller's arrays take that role.
-    const int key_bits = bits_for((uint64_t)(R - 1));
-    const int passes = radix_sort_passes(key_bits);
-    uint32_t* keys_a = (passes & 1) ? sorted_rows : keys_w;
-    uint32_t* vals_a = (passes & 1) ? sorted_pos : vals_w;
-    uint32_t* keys_b = (passes & 1) ? keys_w : sorted_rows;
-    uint32_t* vals_b = (passes & 1) ? vals_w : sorted_pos;
-    SortSource source;
-    source.rows = rows + j0;
-    source.pos = pos + j0;
-    source.R = R;
-    source.n = n;
-    source.status = dev_status;
-    uint32_t* keys = nullptr;
-    uint32_t* vals = nullptr;
-    const fs_status rc = radix_sort_pairs(keys_a, vals_a, keys_b, vals_b, m, nullptr, key_bits, sort_scratch,
-                                          static_cast<hipStream_t>(stream), &keys, &vals, source);
-    if (rc != FS_OK) return rc;
-    if (keys != sorted_rows || vals != sorted_pos) return FS_ERR_DEVICE;     // cannot happen: see above
-    return FS_OK;
+    SortJob job;
+    job.rows = rows + j0; job.pos = pos + j0; job.R = R; job.n = n; job.status = dev_status;
+    job.pairs_a = pairs_a; job.pairs_b = pairs_b;
+    job.keys_out = sorted_rows; job.vals_out = sorted_pos;
+    job.m_max = m; job.key_bits = key_bits;
+    job.scratch = sort_scratch; job.stream = static_cast<hipStream_t>(stream);
+    return radix_sort(job);
 }
 
 extern "C" fs_status fs_seq_grad_bwd_sorted(

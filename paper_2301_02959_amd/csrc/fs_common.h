@@ -127,11 +127,11 @@ __device__ __forceinline__ int wave_table_of(const int64_t* __restrict__ offsets
 }
 
 // Lanes of the wave whose `key` has the same low NBITS bits as this lane's, restricted to lanes with `valid`:
-// NBITS ballots, no LDS.  Written on
-// 32-bit halves with the lane's bit spread to a whole word: per bit one bit-field extract, one compare
-// (the ballot), one exclusive-or per half, and the halves' mismatches are or-ed three at a time: a
-// third fewer vector instructions than selecting between the ballot and its complement, and the sort's
-// count and scatter kernels are bound by exactly these instructions.
+// NBITS ballots, no LDS.  Written on 32-bit halves with the lane's bit spread to a whole word: per bit one bit-field
+// extract, one compare (the ballot) and one three-input operation per half, as the router's and the sort's kernels are
+// bound by these instructions before anything else.
+constexpr uint32_t kAndXnor = 0x90;                     // a & ~(b ^ c): set for a = 1 and b = c
+
 template <int NBITS>
 __device__ __forceinline__ uint64_t match_bits_n(uint32_t key, bool valid)
 {
@@ -143,8 +143,8 @@ __device__ __forceinline__ uint64_t match_bits_n(uint32_t key, bool valid)
         uint32_t x = (uint32_t)((int32_t)(key << (31 - b)) >> 31);
         asm volatile("" : "+v"(x));          // one bit-field extract, and the ballot compares x itself (no second shift)
         const uint64_t v = ballot(x != 0u);
-        m_lo &= ~((uint32_t)v ^ x);
-        m_hi &= ~((uint32_t)(v >> 32) ^ x);
+        m_lo = __builtin_amdgcn_bitop3_b32(m_lo, (uint32_t)v, x, kAndXnor);
+        m_hi = __builtin_amdgcn_bitop3_b32(m_hi, (uint32_t)(v >> 32), x, kAndXnor);
     }
     return ((uint64_t)m_hi << 32) | m_lo;
 }

@@ -286,7 +286,7 @@ static int64_t hist_span(int64_t n)
 template <bool VEC>
 __global__ __launch_bounds__(kBlock) void plan_mark_kernel(
     const uint32_t* __restrict__ counts, int64_t R, int allow_zero, uint32_t* __restrict__ tile_count,
-    uint32_t* __restrict__ tile_bits, uint32_t* __restrict__ stage_keys, uint32_t* __restrict__ stage_vals)
+    uint32_t* __restrict__ tile_bits, SortPair* __restrict__ stage)
 {
     __shared__ uint32_t wave_sum[kWavesPerBlock];
     __shared__ uint32_t wave_bits[kWavesPerBlock];
@@ -363,21 +363,20 @@ __global__ __launch_bounds__(kBlock) void plan_mark_kernel(
     for (int it = 0; it < kItems; ++it) {
         if (cand[it]) {
             const int64_t g = base + row_of(it);
-            stage_keys[tile_base + off + before[it]] = ~cnt[it];
-            stage_vals[tile_base + off + before[it]] = (uint32_t)g;
+            stage[tile_base + off + before[it]] = SortPair{~cnt[it], (uint32_t)g};
         }
     }
 }
 
 static fs_status launch_mark(const uint32_t* counts, int64_t R, int allow_zero, int64_t sel_tiles, uint32_t* tile_count,
-                             uint32_t* tile_bits, uint32_t* stage_keys, uint32_t* stage_vals, hipStream_t s)
+                             uint32_t* tile_bits, SortPair* stage, hipStream_t s)
 {
     if ((reinterpret_cast<uintptr_t>(counts) & 15) == 0)
         FS_LAUNCH("plan_mark", plan_mark_kernel<true>, dim3((unsigned)sel_tiles), dim3(kBlock), s,
-                  counts, R, allow_zero, tile_count, tile_bits, stage_keys, stage_vals);
+                  counts, R, allow_zero, tile_count, tile_bits, stage);
     else
         FS_LAUNCH("plan_mark", plan_mark_kernel<false>, dim3((unsigned)sel_tiles), dim3(kBlock), s,
-                  counts, R, allow_zero, tile_count, tile_bits, stage_keys, stage_vals);
+                  counts, R, allow_zero, tile_count, tile_bits, stage);
     return FS_OK;
 }
 
@@ -447,8 +446,7 @@ template <bool SUM>
 __global__ __launch_bounds__(kBlock) void plan_move_kernel(
     const uint32_t* __restrict__ tile_base, int64_t tiles, const uint32_t* __restrict__ tile_bits,
     int64_t* __restrict__ num_candidates, uint32_t* __restrict__ count_bits,
-    const uint32_t* __restrict__ stage_keys, const uint32_t* __restrict__ stage_vals,
-    uint32_t* __restrict__ keys, uint32_t* __restrict__ vals)
+    const SortPair* __restrict__ stage, SortPair* __restrict__ pairs)
 {
     const int64_t tile = blockIdx.x;
     const int64_t from = tile * kSelTile;
@@ -474,14 +472,11 @@ __global__ __launch_bounds__(kBlock) void plan_move_kernel(
         first = tile_base[tile];
         next = tile + 1 < tiles ? tile_base[tile + 1] : (uint32_t)*num_candidates;
     }
-    for (uint32_t i = threadIdx.x; i < next - first; i += kBlock) {
-        keys[first + i] = stage_keys[from + i];
-        vals[first + i] = stage_vals[from + i];
-    }
+    for (uint32_t i = threadIdx.x; i < next - first; i += kBlock) pairs[first + i] = stage[from + i];
 }
 
-// Compaction and sort of the candidates, shared by the two planners: rows in (count desc, row asc) order, in vals_a
-// or vals_b as sort_result_in_b(*count_bits, first_bits) says, with their keys ~count beside them.
+// Compaction and sort of the candidates, shared by the two planners: rows in (count desc, row asc) order behind their
+// keys ~count, in pairs_a or pairs_b as sort_result_in_b(*count_bits, first_bits) says.
 // Up to 1024 tiles (8 M rows) the moving blocks sum the tile counts themselves, at most four loads to a thread, and
 // the scan is no launch of its own; beyond, what each of the blocks would read again is more than the scan costs.
 constexpr int64_t kMoveSumTiles = 1024;
@@ -491,10 +486,8 @@ struct PlanScratch {
     uint32_t* count_bits;
     uint32_t* tile_count;
     uint32_t* tile_bits;
-    uint32_t* keys_a;
-    uint32_t* vals_a;
-    uint32_t* keys_b;
-    uint32_t* vals_b;
+    SortPair* pairs_a;
+    SortPair* pairs_b;
     char* sort_scratch;
     int first_bits;
 };
@@ -518,10 +511,8 @@ static PlanScratch take_plan_scratch(Carver& ws, int64_t R)
     p.count_bits = ws.take<uint32_t>(1);
     p.tile_count = ws.take<uint32_t>(tiles);
     p.tile_bits = ws.take<uint32_t>(tiles);
-    p.keys_a = ws.take<uint32_t>((size_t)R);
-    p.vals_a = ws.take<uint32_t>((size_t)R);
-    p.keys_b = ws.take<uint32_t>((size_t)R);
-    p.vals_b = ws.take<uint32_t>((size_t)R);
+    p.pairs_a = ws.take<SortPair>((size_t)R);
+    p.pairs_b = ws.take<SortPair>((size_t)R);
     p.sort_scratch = ws.take<char>(R > 0 ? radix_sort_scratch_bytes(R) : 0);
     p.first_bits = selection_first_bits(R);
     return p;
@@ -530,30 +521,33 @@ static PlanScratch take_plan_scratch(Carver& ws, int64_t R)
 static fs_status sort_candidates(const uint32_t* counts, int64_t R, int allow_zero, const PlanScratch& p, hipStream_t s)
 {
     const int64_t tiles = (R + kSelTile - 1) / kSelTile;
-    if (fs_status rc = launch_mark(counts, R, allow_zero, tiles, p.tile_count, p.tile_bits, p.keys_b, p.vals_b, s); rc != FS_OK) return rc;
+    if (fs_status rc = launch_mark(counts, R, allow_zero, tiles, p.tile_count, p.tile_bits, p.pairs_b, s); rc != FS_OK) return rc;
     if (tiles <= kMoveSumTiles) {
         FS_LAUNCH("plan_move", plan_move_kernel<true>, dim3((unsigned)tiles), dim3(kBlock), s, p.tile_count, tiles,
-                  p.tile_bits, p.num_cand, p.count_bits, p.keys_b, p.vals_b, p.keys_a, p.vals_a);
+                  p.tile_bits, p.num_cand, p.count_bits, p.pairs_b, p.pairs_a);
     } else {
         FS_LAUNCH("plan_scan", plan_scan_kernel, dim3(1), dim3(kScanBlock), s, p.tile_count, tiles, p.tile_bits, p.num_cand, p.count_bits);
         FS_LAUNCH("plan_move", plan_move_kernel<false>, dim3((unsigned)tiles), dim3(kBlock), s, p.tile_count, tiles,
-                  p.tile_bits, p.num_cand, p.count_bits, p.keys_b, p.vals_b, p.keys_a, p.vals_a);
+                  p.tile_bits, p.num_cand, p.count_bits, p.pairs_b, p.pairs_a);
     }
-    uint32_t *keys = nullptr, *vals = nullptr;                   // where the last pass would leave them
-    return radix_sort_pairs(p.keys_a, p.vals_a, p.keys_b, p.vals_b, R, p.num_cand, 32, p.sort_scratch, s, &keys, &vals,
-                            SortSource(), p.count_bits, p.first_bits);
+    SortJob job;
+    job.pairs_a = p.pairs_a; job.pairs_b = p.pairs_b;
+    job.m_max = R; job.m_dev = p.num_cand;
+    job.varying = p.count_bits; job.first_bits = p.first_bits;
+    job.scratch = p.sort_scratch; job.stream = s;
+    return radix_sort(job);
 }
 
 __global__ __launch_bounds__(kBlock) void plan_emit_kernel(
-    const uint32_t* __restrict__ vals_a, const uint32_t* __restrict__ vals_b, const uint32_t* __restrict__ count_bits, int first_bits, const int64_t* __restrict__ num_candidates, int64_t cap,
+    const SortPair* __restrict__ pairs_a, const SortPair* __restrict__ pairs_b, const uint32_t* __restrict__ count_bits, int first_bits, const int64_t* __restrict__ num_candidates, int64_t cap,
     int64_t* __restrict__ sel_rows, int64_t* __restrict__ num_selected, uint32_t* __restrict__ placement)
 {
-    const uint32_t* vals = sort_result_in_b(*count_bits, first_bits) ? vals_b : vals_a;
+    const SortPair* pairs = sort_result_in_b(*count_bits, first_bits) ? pairs_b : pairs_a;
     const int64_t nc = *num_candidates;
     const int64_t k = cap < nc ? cap : nc;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k; i += stride) {
-        const uint32_t g = vals[i];
+        const uint32_t g = pairs[i][1];
         sel_rows[i] = (int64_t)g;
         if (placement != nullptr) placement[g] &= FS_OWNER_MASK;
     }
@@ -580,10 +574,10 @@ struct TierConsts {
 };
 
 __global__ __launch_bounds__(kBlock) void tiers_tile_sums_kernel(
-    const uint32_t* __restrict__ keys_a, const uint32_t* __restrict__ keys_b, const uint32_t* __restrict__ count_bits, int first_bits,
+    const SortPair* __restrict__ pairs_a, const SortPair* __restrict__ pairs_b, const uint32_t* __restrict__ count_bits, int first_bits,
     const int64_t* __restrict__ num_candidates, uint64_t* __restrict__ tile_sum)
 {
-    const uint32_t* keys = sort_result_in_b(*count_bits, first_bits) ? keys_b : keys_a;
+    const SortPair* pairs = sort_result_in_b(*count_bits, first_bits) ? pairs_b : pairs_a;
     __shared__ uint64_t part[kWavesPerBlock];
     const int64_t K = *num_candidates;
     // candidates are usually a few per cent of the rows: the blocks walk the tiles that hold any (a block for every
@@ -594,7 +588,7 @@ __global__ __launch_bounds__(kBlock) void tiers_tile_sums_kernel(
 #pragma unroll
         for (int i = 0; i < kSumTile / kBlock; ++i) {
             const int64_t k = base + i * kBlock + threadIdx.x;
-            sum += k < K ? (uint32_t)~keys[k] : 0u;
+            sum += k < K ? (uint32_t)~pairs[k][0] : 0u;
         }
         for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off);
         if (lane_id() == 0) part[wave_id()] = sum;
@@ -662,7 +656,7 @@ __device__ __forceinline__ int64_t wave_partition_point(int64_t lo, int64_t hi, 
 }
 
 // Sum of the first k sorted counts: the scanned tile sums plus a partial tile, summed by the wave.
-__device__ __forceinline__ uint64_t prefix_count(const uint32_t* __restrict__ keys,
+__device__ __forceinline__ uint64_t prefix_count(const SortPair* __restrict__ pairs,
                                                  const uint64_t* __restrict__ tile_sum, int64_t k)
 {
     const int64_t t = k / kSumTile;
@@ -670,7 +664,7 @@ __device__ __forceinline__ uint64_t prefix_count(const uint32_t* __restrict__ ke
 #pragma unroll 16
     for (int j = 0; j < kSumTile / kWave; ++j) {
         const int64_t i = t * kSumTile + j * kWave + lane_id();
-        part += i < k ? (uint32_t)~keys[i] : 0u;
+        part += i < k ? (uint32_t)~pairs[i][0] : 0u;
     }
     for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
     return tile_sum[t] + part;
@@ -686,16 +680,16 @@ __device__ __forceinline__ i128 cum_memory(const TierConsts& c, int64_t k, uint6
 // The budget and the sums of the two tiers follow in the first wave, the sums' partial tiles with 16 loads in flight:
 // 39 -> 27 us with 1.5 M candidates (one wave doing all of it, and every row of point B's tile tested on its own).
 __global__ __launch_bounds__(kBlock) void tiers_cuts_kernel(
-    const uint32_t* __restrict__ keys_a, const uint32_t* __restrict__ keys_b, const uint32_t* __restrict__ count_bits, int first_bits,
+    const SortPair* __restrict__ pairs_a, const SortPair* __restrict__ pairs_b, const uint32_t* __restrict__ count_bits, int first_bits,
     const int64_t* __restrict__ num_candidates,
     const uint64_t* __restrict__ tile_sum, const TierConsts c, int64_t* __restrict__ cuts)
 {
-    const uint32_t* keys = sort_result_in_b(*count_bits, first_bits) ? keys_b : keys_a;
+    const SortPair* pairs = sort_result_in_b(*count_bits, first_bits) ? pairs_b : pairs_a;
     const int lane = lane_id();
     const int64_t K = *num_candidates;
     const int64_t tiles = (K + kSumTile - 1) / kSumTile;
     auto at_least = [&](uint64_t thr) {
-        return wave_partition_point(0, K, [&](int64_t i) { return (uint64_t)(uint32_t)~keys[i] >= thr; });
+        return wave_partition_point(0, K, [&](int64_t i) { return (uint64_t)(uint32_t)~pairs[i][0] >= thr; });
     };
     __shared__ int64_t found[kWavesPerBlock];
     const int w = __builtin_amdgcn_readfirstlane(wave_id());
@@ -728,14 +722,14 @@ __global__ __launch_bounds__(kBlock) void tiers_cuts_kernel(
 #pragma unroll 16
             for (int q = 0; q < kPer; ++q) {
                 const int64_t i = first + (int64_t)lane * kPer + q;
-                mine += i < K ? (uint32_t)~keys[i] : 0u;
+                mine += i < K ? (uint32_t)~pairs[i][0] : 0u;
             }
             const uint64_t upto = tile_sum[t0] + wave_inclusive(mine);
             const int64_t piece_end = first + (int64_t)(lane + 1) * kPer;
             const int whole = __popcll(ballot(cum_memory(c, piece_end < K ? piece_end : K, upto) <= 0));   // < 64
             const uint64_t before = whole == 0 ? tile_sum[t0] : __shfl(upto, whole - 1);
             const int64_t i = first + (int64_t)whole * kPer + lane;
-            const uint64_t run = before + wave_inclusive(i < K ? (uint32_t)~keys[i] : 0u);
+            const uint64_t run = before + wave_inclusive(i < K ? (uint32_t)~pairs[i][0] : 0u);
             kB = first + (int64_t)whole * kPer + __popcll(ballot(i < K && cum_memory(c, i + 1, run) <= 0));
         }
         if (lane == 0) found[3] = kB;
@@ -750,7 +744,7 @@ __global__ __launch_bounds__(kBlock) void tiers_cuts_kernel(
         n_dp = kB / gran * gran;
     } else {
         n_dp = kA / gran * gran;
-        const i128 saved = -cum_memory(c, n_dp, prefix_count(keys, tile_sum, n_dp));     // >= 0
+        const i128 saved = -cum_memory(c, n_dp, prefix_count(pairs, tile_sum, n_dp));     // >= 0
         int64_t room = K - n_dp;
         if (kF - n_dp < room) room = kF > n_dp ? kF - n_dp : 0;
         int64_t lo = 0, hi = room;                                       // most rows j with j * flex_cost <= saved
@@ -764,8 +758,8 @@ __global__ __launch_bounds__(kBlock) void tiers_cuts_kernel(
         }
         n_flex = lo / gran * gran;
     }
-    const uint64_t sum_dp = prefix_count(keys, tile_sum, n_dp);
-    const uint64_t sum_both = prefix_count(keys, tile_sum, n_dp + n_flex);
+    const uint64_t sum_dp = prefix_count(pairs, tile_sum, n_dp);
+    const uint64_t sum_both = prefix_count(pairs, tile_sum, n_dp + n_flex);
     if (lane == 0) {
         cuts[0] = K; cuts[1] = kA; cuts[2] = kB; cuts[3] = kC; cuts[4] = kF;
         cuts[5] = n_dp; cuts[6] = n_flex;
@@ -774,11 +768,11 @@ __global__ __launch_bounds__(kBlock) void tiers_cuts_kernel(
 }
 
 __global__ __launch_bounds__(kBlock) void tiers_emit_kernel(
-    const uint32_t* __restrict__ vals_a, const uint32_t* __restrict__ vals_b, const uint32_t* __restrict__ count_bits, int first_bits,
+    const SortPair* __restrict__ pairs_a, const SortPair* __restrict__ pairs_b, const uint32_t* __restrict__ count_bits, int first_bits,
     const int64_t* __restrict__ cuts, int64_t cap, int W,
     int64_t* __restrict__ sorted_rows, uint32_t* __restrict__ placement)
 {
-    const uint32_t* vals = sort_result_in_b(*count_bits, first_bits) ? vals_b : vals_a;
+    const SortPair* pairs = sort_result_in_b(*count_bits, first_bits) ? pairs_b : pairs_a;
     const int64_t n_dp = cuts[5];
     const int64_t n_both = n_dp + cuts[6];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -787,7 +781,7 @@ __global__ __launch_bounds__(kBlock) void tiers_emit_kernel(
     for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i0 < n_both; i0 += kAhead * stride) {
         uint32_t g[kAhead], tag[kAhead];
 #pragma unroll
-        for (int q = 0; q < kAhead; ++q) g[q] = i0 + q * stride < n_both ? vals[i0 + q * stride] : 0u;
+        for (int q = 0; q < kAhead; ++q) g[q] = i0 + q * stride < n_both ? pairs[i0 + q * stride][1] : 0u;
         if (placement != nullptr) {
 #pragma unroll
             for (int q = 0; q < kAhead; ++q) {
@@ -861,7 +855,7 @@ extern "C" fs_status fs_plan_replication(
         const int allow_zero = (flags & FS_PLAN_ALLOW_ZERO) ? 1 : 0;
         if (fs_status rc = sort_candidates(counts, R, allow_zero, p, s); rc != FS_OK) return rc;
         FS_LAUNCH("plan_emit", plan_emit_kernel, dim3(1024), dim3(kBlock), s,
-                  p.vals_a, p.vals_b, p.count_bits, p.first_bits, p.num_cand, cap, sel_rows, num_selected, (flags & FS_PLAN_TAG) ? placement : nullptr);
+                  p.pairs_a, p.pairs_b, p.count_bits, p.first_bits, p.num_cand, cap, sel_rows, num_selected, (flags & FS_PLAN_TAG) ? placement : nullptr);
     }
     return FS_OK;
 }
@@ -920,11 +914,11 @@ extern "C" fs_status fs_plan_tiers(
     if (fs_status rc = sort_candidates(counts, R, 0, q, s); rc != FS_OK) return rc;
     const unsigned sum_grid = sum_tiles < 2048 ? (unsigned)sum_tiles : 2048u;        // 8 blocks per CU
     FS_LAUNCH("tiers_tile_sums", tiers_tile_sums_kernel, dim3(sum_grid), dim3(kBlock), s,
-              q.keys_a, q.keys_b, q.count_bits, q.first_bits, q.num_cand, tile_sum);
+              q.pairs_a, q.pairs_b, q.count_bits, q.first_bits, q.num_cand, tile_sum);
     FS_LAUNCH("tiers_scan_sums", tiers_scan_sums_kernel, dim3(1), dim3(kScanBlock), s, tile_sum, q.num_cand);
-    FS_LAUNCH("tiers_cuts", tiers_cuts_kernel, dim3(1), dim3(kBlock), s, q.keys_a, q.keys_b, q.count_bits, q.first_bits, q.num_cand,
+    FS_LAUNCH("tiers_cuts", tiers_cuts_kernel, dim3(1), dim3(kBlock), s, q.pairs_a, q.pairs_b, q.count_bits, q.first_bits, q.num_cand,
               tile_sum, c, cuts);
-    FS_LAUNCH("tiers_emit", tiers_emit_kernel, dim3(1024), dim3(kBlock), s, q.vals_a, q.vals_b, q.count_bits, q.first_bits, cuts, cap, (int)p.W,
+    FS_LAUNCH("tiers_emit", tiers_emit_kernel, dim3(1024), dim3(kBlock), s, q.pairs_a, q.pairs_b, q.count_bits, q.first_bits, cuts, cap, (int)p.W,
               sorted_rows, placement);
     return FS_OK;
 }

@@ -7,24 +7,46 @@
 
 namespace fs {
 
-constexpr int kSortItems = 16;                       // keys per thread
-constexpr int kSortTile = kBlock * kSortItems;       // keys per block and tile
 constexpr int kSortMaxDigitBits = 10;
 
-// Where the first pass reads its pairs from.
-//   rows == nullptr: (keys_a, vals_a) hold the pairs.
-//   rows != nullptr: pair q is (uint32) rows[q], (uint32) pos[q], validated on the fly
-//                    (row outside [0, R) -> 0, pos outside [0, n) -> 0, FS_DEV_BAD_ID into *status);
-//                    keys_a / vals_a are then only used as the second buffer.
-struct SortSource {
+// A pair between two passes: [0] the key, [1] the value.  Side by side they leave the scatter as one store and a
+// digit's run is twice as long as in an array of its own (very large sorts from `rows` keep them apart, in the same buffers).
+typedef u32x2 SortPair;
+
+struct SortJob {
+    // Where the first pass reads its pairs.
+    //   rows == nullptr: pairs_a holds them.
+    //   rows != nullptr: pair q is (uint32) rows[q], (uint32) pos[q], validated on the fly
+    //                    (row outside [0, R) -> 0, pos outside [0, n) -> 0, FS_DEV_BAD_ID into *status).
     const int64_t* rows = nullptr;
     const int32_t* pos = nullptr;
     int64_t R = 0;
     int64_t n = 0;
     int32_t* status = nullptr;
+    // Buffers of m_max pairs; the passes go from one to the other, the first pass of `rows` into pairs_a (pairs_b is
+    // not touched by sorts of up to two passes from `rows`).
+    SortPair* pairs_a = nullptr;
+    SortPair* pairs_b = nullptr;
+    // Where the last pass writes keys and values apart; null: as pairs, into the buffer whose turn it is.  They may
+    // lie in the buffer that the last pass does not read: pairs_a after an odd number of passes from `rows`, else pairs_b.
+    uint32_t* keys_out = nullptr;
+    uint32_t* vals_out = nullptr;
+    // Number of pairs: *m_dev if m_dev != nullptr (device memory, read by the kernels; at most m_max) else m_max.
+    int64_t m_max = 0;
+    const int64_t* m_dev = nullptr;
+    int key_bits = 32;               // the sort is by the low key_bits bits of the key
+    // A device word with every bit set in which two keys differ (or null).  Passes above its highest set bit copy
+    // nothing and return at once; the result is then where the last pass that ran left it, which only the device knows:
+    // sort_result_in_b below.  For 32-bit keys that came in pairs_a; keys_out must be null.
+    const uint32_t* varying = nullptr;
+    // With `varying`, the bits of the first two passes; two more share the rest.  Without it the bits are spread evenly
+    // over as few passes as possible.
+    int first_bits = kSortMaxDigitBits;
+    void* scratch = nullptr;         // radix_sort_scratch_bytes(m_max) bytes
+    hipStream_t stream = nullptr;
 };
 
-// Number of passes radix_sort_pairs makes over keys of key_bits bits.
+// Number of passes over keys of key_bits bits.
 inline int radix_sort_passes(int key_bits)
 {
     if (key_bits < 1) key_bits = 1;
@@ -32,26 +54,13 @@ inline int radix_sort_passes(int key_bits)
     return (key_bits + kSortMaxDigitBits - 1) / kSortMaxDigitBits;
 }
 
-// Scratch the sort needs for up to m_max pairs (beyond the two key/value buffers).
+// Scratch the sort needs for up to m_max pairs (beyond the two buffers).
 size_t radix_sort_scratch_bytes(int64_t m_max);
 
-// Sorts pairs by the low `key_bits` bits of the key, stable.  Input in (keys_a, vals_a) or in
-// `src`; (keys_b, vals_b) is the other buffer.  The number of pairs is *m_dev if m_dev != nullptr
-// (device memory, read by the kernels; must be <= m_max) else m_max.  On return *keys_out /
-// *vals_out name the buffer that holds the result.
-//   varying (or null): a device word with every bit set in which two keys differ.  Passes above its highest set bit
-//   copy nothing and return at once; the result is then where the last pass that ran left it, which only the device
-//   knows: sort_result_in_b below, for pairs that came in A (and not in `src`).
-//   first_bits: with `varying` (and 32 key bits), the bits of the first two passes; two more share the rest.  Without it
-//   the bits are spread evenly over as few passes as possible.
-fs_status radix_sort_pairs(uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b, uint32_t* vals_b,
-                           int64_t m_max, const int64_t* m_dev, int key_bits, void* scratch,
-                           hipStream_t stream, uint32_t** keys_out, uint32_t** vals_out,
-                           const SortSource& src = SortSource(), const uint32_t* varying = nullptr,
-                           int first_bits = kSortMaxDigitBits);
+fs_status radix_sort(const SortJob& job);
 
 #ifdef __HIPCC__
-// Whether a sort by 32 bits with `varying` and `first_bits` left its result in the B buffers.
+// Whether a sort with `varying` and `first_bits` left its result in pairs_b.
 __device__ __forceinline__ bool sort_result_in_b(uint32_t varying, int first_bits)
 {
     const int bits = varying == 0 ? 1 : 32 - __builtin_clz(varying);

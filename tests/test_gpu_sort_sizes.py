@@ -51,6 +51,26 @@ def check_sort(G, m, R):
     assert np.array_equal(spos.cpu().numpy().view(np.uint32), osp)
 
 
+@pytest.mark.parametrize("m", [128 * 4096 + 1, 384 * 4096, 384 * 4096 + 1, 2048 * 4096 + 4095, (1 << 25) - 1, 1 << 25])
+@pytest.mark.parametrize("R", [200, 700_000, (1 << 32) - 2])
+def test_sort_group_sizes(G, m, R):
+    """A scan thread takes up to 4, 12 or 32 groups of tiles, a group one tile, two or three (more than 1024, 2048 tiles),
+    and from 2^25 pairs on keys and values lie apart between passes; one to four passes.  Against torch's stable sort."""
+    import paper_2301_02959_amd as fs
+    torch.manual_seed(m % 1000)
+    rows = torch.randint(0, R, (m,), device=G.DEV)
+    rows[torch.rand(m, device=G.DEV) < 0.3] = R - 1                            # a popular row
+    pos = torch.arange(m, dtype=torch.int32, device=G.DEV)
+    srows = torch.full((m,), -7, dtype=torch.int32, device=G.DEV)
+    spos = torch.full((m,), -7, dtype=torch.int32, device=G.DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    fs.fs_sort_lookups(rows, pos, 0, m, R, m, srows, spos, st)
+    want, order = torch.sort(rows, stable=True)
+    assert int(st.item()) == 0
+    assert torch.equal(srows.long() & 0xFFFFFFFF, want)
+    assert torch.equal(spos.long(), order)
+
+
 @pytest.mark.parametrize("R", [1, 1024, 128 * 1024, 128 * 1024 + 1, 64 * 4096, 64 * 4096 + 1, 1024 * TILE, 1024 * TILE + 1])
 @pytest.mark.parametrize("bits,share", [(1, 0.9), (10, 0.01), (11, 0.3), (20, 0.05), (21, 0.3), (30, 0.1), (31, 0.3), (32, 0.02)])
 def test_selection_sizes(G, R, bits, share):
