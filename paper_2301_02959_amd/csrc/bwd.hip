@@ -54,11 +54,12 @@ __global__ __launch_bounds__(kHeadsBlock) void bwd_count_heads_kernel(
     const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals, int64_t m, int64_t chunks,
     uint32_t n, uint32_t R,
     uint32_t* __restrict__ chunk_local, uint32_t* __restrict__ block_sum, int64_t cap,
-    int64_t* __restrict__ num_unique, int32_t* status)
+    int64_t* __restrict__ num_unique, uint32_t* __restrict__ num_long /* or null */, int32_t* status)
 {
     __shared__ uint32_t heads[kChunksPerBlock];
     const int w = wave_id();
     const int lane = lane_id();
+    if (num_long != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *num_long = 0;       // bwd_fold counts here
     constexpr int kPerWave = kChunksPerBlock / (kHeadsBlock / kWave);
     bool disorder = false, bad = false, unsorted = false;
     // The wave's chunks follow one another, so its rounds of 64 lookups do: all rounds are loaded before the first is
@@ -825,16 +826,28 @@ __global__ __launch_bounds__(kBlock) void bwd_singletons_kernel(
     }
 }
 
+// A run that goes on over many chunks, left to bwd_fold_long: row_grads[run] += carry[first .. last], left to right.
+struct LongRun {
+    uint32_t run;
+    uint32_t first, last;                        // chunks
+};
+// Runs with more carries than this are left to it, where the batch is large enough (chunks times columns) for the launch
+// to be worth its 2 us.  The backward without and with it, Zipf(1.3) and Zipf(1.05) over 50 M rows: 300 k lookups (1172 chunks)
+// of 128 columns 52 : 54 and 62 : 66 us, of 256 80 : 75 and 93 : 96, 1 M (4102) of 64 93 : 97 and 107 : 107, of 128 111 : 105
+// and 125 : 125, of 256 197 : 167 and 224 : 219, 4.2 M of 64 293 : 287 and 313 : 314, of 256 657 : 519 and 729 : 691.
+constexpr int64_t kFoldLong = 64;
+constexpr int64_t kFoldLongWork = 500000;
+
 // One wave per chunk; a wave whose chunk starts a spilling run (one that goes on into the next
 // chunk) adds the carries of the chunks the run goes on into, left to right.
 // VL: consecutive columns per lane.  Rows of up to 64 or 128 columns take 1 or 2, so that all lanes of the wave carry a
-// share and the same registers hold four times or twice as many carries in flight: the longest run's chain of rounds of
-// loads is the kernel's time (a run over 2100 chunks of 128 columns, 32 carries in flight 100 us, 64 in flight 64 us).
+// share and the same registers hold four times or twice as many carries in flight.
 template <int VL>
 __global__ __launch_bounds__(kBlock) void bwd_fold_kernel(
     const uint32_t* __restrict__ keys, int64_t m, int64_t chunks,
     const uint32_t* __restrict__ block_base, const uint32_t* __restrict__ chunk_local,
-    float* __restrict__ row_grads, int D, int64_t cap, const float* __restrict__ carry)
+    float* __restrict__ row_grads, int D, int64_t cap, const float* __restrict__ carry,
+    LongRun* __restrict__ long_runs /* or null */, uint32_t* __restrict__ num_long)
 {
     const int64_t chunk = (int64_t)blockIdx.x * kWavesPerBlock + wave_id();
     const int64_t k0 = chunk * kChunk;
@@ -868,6 +881,10 @@ __global__ __launch_bounds__(kBlock) void bwd_fold_kernel(
         if (keys[mid * kChunk] == key) lo = mid; else hi = mid;
     }
     const int64_t last_chunk = lo;
+    if (long_runs != nullptr && last_chunk - chunk > kFoldLong) {
+        if (lane_id() == 0) long_runs[atomicAdd(num_long, 1u)] = {(uint32_t)u, (uint32_t)(chunk + 1), (uint32_t)last_chunk};
+        return;
+    }
     typedef float Cols __attribute__((ext_vector_type(VL)));
     constexpr int kAhead = 128 / VL;             // carries in flight: the longest run's chain is latency-bound
     constexpr int kRest = 8;
@@ -895,6 +912,102 @@ __global__ __launch_bounds__(kBlock) void bwd_fold_kernel(
         }
         if (cc == last_chunk) acc = acc + *reinterpret_cast<const Cols*>(carry + cc * D + col);   // most runs: one carry
         *reinterpret_cast<Cols*>(row_grads + u * D + col) = acc;
+    }
+}
+
+// The long runs, a block to 32 columns of one.  Four waves bring the carries to LDS, 256 at a time in two buffers, the
+// next 256 in flight; the first wave adds them up, a column to a lane.  In LDS a column's carries lie one after the other,
+// so that one read brings a lane four of them.  Bound by that chain of reads and adds, 15
+// clocks a carry: 8.4 M lookups of 128 columns over one table, whose head row spans 8900 chunks, 55 us (all waves loading and
+// then waiting for the adds 80 to 110); over four tables, 2100 chunks, both folds 35, the wave per chunk alone 65.
+constexpr int kLongCols = 32;
+constexpr int kLongLoads = 8;                                        // 16-byte loads a thread has in flight
+constexpr int kLongRows = kLongLoads * kBlock * 4 / kLongCols;       // carries in a buffer
+constexpr int kLongBlock = kWave + kBlock;
+constexpr unsigned kLongGrid = 512;                                  // two blocks a CU, by their LDS
+
+__global__ __launch_bounds__(kLongBlock) void bwd_fold_long_kernel(
+    float* __restrict__ row_grads, int D, const float* __restrict__ carry, const LongRun* __restrict__ long_runs,
+    const uint32_t* __restrict__ num_long)
+{
+    __shared__ __attribute__((aligned(16))) float cols[2][kLongCols][kLongRows + 4];      // 4 apart: the columns' banks, in reads and in writes
+    const int slabs = (D + kLongCols - 1) / kLongCols;
+    const int64_t items = (int64_t)*num_long * slabs;
+    constexpr int kQuads = kLongCols / 4;                            // threads to a row
+    constexpr int kPerLoad = kBlock / kQuads;                        // rows to a load of the four waves
+    const bool loads = threadIdx.x >= kWave;                         // wave-uniform
+    const int quad = threadIdx.x % kQuads;
+    const int row0 = ((int)threadIdx.x - kWave) / kQuads;
+    for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+        const LongRun r = long_runs[item / slabs];
+        const int col0 = (int)(item % slabs) * kLongCols;
+        const int count = (int)(r.last - r.first) + 1;
+        const int my_col = col0 + quad * 4 < D ? col0 + quad * 4 : D - 4;        // D is a multiple of 4
+        const float* const first = carry + (int64_t)r.first * D + my_col;
+        f32x4 x[kLongLoads];
+        auto load = [&](int from) {
+#pragma unroll
+            for (int j = 0; j < kLongLoads; ++j) {
+                const int c = from + j * kPerLoad + row0;
+                x[j] = load_stream(reinterpret_cast<const f32x4*>(first + (int64_t)(c < count ? c : count - 1) * D));
+            }
+        };
+        auto store = [&](int buffer) {
+#pragma unroll
+            for (int j = 0; j < kLongLoads; ++j) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) cols[buffer][quad * 4 + i][j * kPerLoad + row0] = x[j][i];
+            }
+        };
+        const int col = col0 + (int)threadIdx.x;
+        const bool adds = threadIdx.x < kLongCols && col < D;
+        float* const dst = row_grads + (int64_t)r.run * D + (adds ? col : 0);
+        float acc = adds ? *dst : 0.0f;
+        if (loads) {
+            load(0);
+            store(0);
+            if (kLongRows < count) load(kLongRows);
+        }
+        __syncthreads();
+        int buffer = 0;
+        for (int from = 0; from < count; from += kLongRows, buffer ^= 1) {
+            if (loads) {
+                if (from + kLongRows < count) store(buffer ^ 1);
+                if (from + 2 * kLongRows < count) load(from + 2 * kLongRows);
+            } else if (adds) {
+                // 32 at a time, the next 32 on their way while these are added (the scheduler would put the reads off)
+                constexpr int kBatch = 32;
+                static_assert(kLongRows % (2 * kBatch) == 0);
+                const int n = count - from < kLongRows ? count - from : kLongRows;
+                const f32x4* mine = reinterpret_cast<const f32x4*>(cols[buffer][threadIdx.x]);
+                f32x4 f[2][kBatch / 4];
+                auto read = [&](f32x4* to, int k) {
+#pragma unroll
+                    for (int j = 0; j < kBatch / 4; ++j) to[j] = mine[(k < kLongRows ? k : 0) / 4 + j];
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                auto add = [&](const f32x4* these, int k) {
+                    if (k + kBatch <= n) {                           // uniform
+#pragma unroll
+                        for (int j = 0; j < kBatch; ++j) acc = acc + these[j / 4][j % 4];
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < kBatch; ++j)
+                            if (k + j < n) acc = acc + these[j / 4][j % 4];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                read(f[0], 0);
+                for (int k = 0; k < n; k += 2 * kBatch) {
+                    read(f[1], k + kBatch);
+                    add(f[0], k);
+                    read(f[0], k + 2 * kBatch);
+                    add(f[1], k + kBatch);
+                }
+            }
+            __syncthreads();
+        }
+        if (adds) *dst = acc;
     }
 }
 
@@ -1018,25 +1131,30 @@ static fs_status launch_singletons_update(fs_dtype dtype, int optimizer, const v
                                                      uniq_rows, cap, applied, stream);
 }
 
-static fs_status launch_fold(const uint32_t* keys, int64_t m, int64_t chunks, const uint32_t* block_base,
-                             const uint32_t* chunk_local, float* row_grads, int D, int64_t cap, const float* carry, hipStream_t s)
-{
-    const dim3 grid((unsigned)((chunks + kWavesPerBlock - 1) / kWavesPerBlock));
-#define FS_FOLD(VL) \
-    FS_LAUNCH("bwd_fold", bwd_fold_kernel<VL>, grid, dim3(kBlock), s, keys, m, chunks, block_base, chunk_local, row_grads, D, cap, carry)
-    if (D <= kWave) FS_FOLD(1);
-    else if (D <= 2 * kWave) FS_FOLD(2);                  // D is a multiple of 4: rows are whole 16-byte pieces
-    else FS_FOLD(4);
-#undef FS_FOLD
-    return FS_OK;
-}
-
 // Everything after the sort: (keys, vals) are the lookups in (row, position) order.
 struct BwdScratch {
     uint32_t* chunk_local;
     uint32_t* block_base;
     float* carry;
+    LongRun* long_runs;                          // null: no run can be long enough
+    uint32_t* num_long;
 };
+
+static fs_status launch_fold(const uint32_t* keys, int64_t m, int64_t chunks, const BwdScratch& w, float* row_grads, int D,
+                             int64_t cap, hipStream_t s)
+{
+    const dim3 grid((unsigned)((chunks + kWavesPerBlock - 1) / kWavesPerBlock));
+#define FS_FOLD(VL)                                                                                                      \
+    FS_LAUNCH("bwd_fold", bwd_fold_kernel<VL>, grid, dim3(kBlock), s, keys, m, chunks, w.block_base, w.chunk_local, row_grads, \
+              D, cap, w.carry, w.long_runs, w.num_long)
+    if (D <= kWave) FS_FOLD(1);
+    else if (D <= 2 * kWave) FS_FOLD(2);                  // D is a multiple of 4: rows are whole 16-byte pieces
+    else FS_FOLD(4);
+#undef FS_FOLD
+    if (w.long_runs != nullptr)
+        FS_LAUNCH("bwd_fold_long", bwd_fold_long_kernel, dim3(kLongGrid), dim3(kLongBlock), s, row_grads, D, w.carry, w.long_runs, w.num_long);
+    return FS_OK;
+}
 
 static fs_status bwd_after_sort(const void* grad_out, int64_t n, int D, fs_dtype dtype, int units,
                                 const uint32_t* keys, const uint32_t* vals, int64_t m, int64_t R, int variant,
@@ -1048,10 +1166,10 @@ static fs_status bwd_after_sort(const void* grad_out, int64_t n, int D, fs_dtype
     const int64_t blocks = (chunks + kChunksPerBlock - 1) / kChunksPerBlock;
     if (blocks == 1) {
         FS_LAUNCH("bwd_count_heads", bwd_count_heads_kernel<true>, dim3(1), dim3(kHeadsBlock), s, keys, vals, m, chunks,
-                  (uint32_t)n, (uint32_t)R, w.chunk_local, w.block_base, cap_unique, num_unique, dev_status);
+                  (uint32_t)n, (uint32_t)R, w.chunk_local, w.block_base, cap_unique, num_unique, w.num_long, dev_status);
     } else {
         FS_LAUNCH("bwd_count_heads", bwd_count_heads_kernel<false>, dim3((unsigned)blocks), dim3(kHeadsBlock), s, keys, vals, m,
-                  chunks, (uint32_t)n, (uint32_t)R, w.chunk_local, w.block_base, cap_unique, num_unique, dev_status);
+                  chunks, (uint32_t)n, (uint32_t)R, w.chunk_local, w.block_base, cap_unique, num_unique, w.num_long, dev_status);
         FS_LAUNCH("bwd_scan_blocks", bwd_scan_blocks_kernel, dim3(1), dim3(kScanBlock), s,
                   w.block_base, blocks, cap_unique, num_unique, dev_status);
     }
@@ -1084,7 +1202,7 @@ static fs_status bwd_after_sort(const void* grad_out, int64_t n, int D, fs_dtype
         else FS_SINGLE_UPDATE(64);
 #undef FS_SINGLE_UPDATE
         if (rc != FS_OK) return rc;
-        rc = launch_fold(keys, m, chunks, w.block_base, w.chunk_local, row_grads, D, cap_unique, w.carry, s);
+        rc = launch_fold(keys, m, chunks, w, row_grads, D, cap_unique, s);
         if (rc != FS_OK) return rc;
         UpdateArgs rest = *update;               // the optimizer step on the rows whose gradient is in row_grads
         rest.uniq_rows = uniq_rows; rest.row_grads = row_grads; rest.cap = cap_unique; rest.num_unique = num_unique;
@@ -1105,7 +1223,7 @@ static fs_status bwd_after_sort(const void* grad_out, int64_t n, int D, fs_dtype
 #undef FS_SINGLE
         if (rc != FS_OK) return rc;
     }
-    if (variant == 0) return launch_fold(keys, m, chunks, w.block_base, w.chunk_local, row_grads, D, cap_unique, w.carry, s);
+    if (variant == 0) return launch_fold(keys, m, chunks, w, row_grads, D, cap_unique, s);
     return FS_OK;
 }
 
@@ -1117,6 +1235,10 @@ static BwdScratch take_bwd_scratch(Carver& ws, int64_t m, int D, int variant)
     w.chunk_local = ws.take<uint32_t>((size_t)chunks);
     w.block_base = ws.take<uint32_t>((size_t)blocks + 1);
     w.carry = ws.take<float>(variant == 0 ? (size_t)chunks * (size_t)D : 0);
+    const bool may_long = variant == 0 && chunks * D > kFoldLongWork;
+    w.long_runs = ws.take<LongRun>(may_long ? (size_t)(chunks / kFoldLong) + 1 : 0);      // each has more than kFoldLong chunks of its own
+    w.num_long = ws.take<uint32_t>(may_long ? 1 : 0);
+    if (!may_long) { w.long_runs = nullptr; w.num_long = nullptr; }
     return w;
 }
 
