@@ -280,103 +280,105 @@ static int64_t hist_span(int64_t n)
 }
 
 // ---- selection --------------------------------------------------------------
-// Reads counts once: the candidates of a 8192-row tile are packed, in row order, at the tile's
-// own place in a staging buffer (keys/vals at [tile * 8192 + i]) and counted.
+// Reads counts once: each wave packs the candidates of its 2048 rows, in row order, at their own place in a staging
+// buffer, four waves to a tile of 8192 rows, whose candidates are counted.
 // VEC: a lane loads four consecutive counters at once (counts 16-byte aligned); the packed order is the same.
-template <bool VEC>
+// Bound by the stream of the counters: 80 M of them, 1.6 M
+// candidates, 62 us (5.1 TB/s), 200 M 181.  With the positions of all 32 rows of a lane held until the block's waves had met,
+// 66 and 195 (three times the registers, twice the vector instructions).
+constexpr int kMarkSpan = kSelTile / kWavesPerBlock;      // consecutive rows per wave
+
+// The number of candidates of each wave's share, 16 bits each, first wave lowest.
+typedef uint64_t WaveCounts;
+
+template <bool VEC, bool ZERO>
 __global__ __launch_bounds__(kBlock) void plan_mark_kernel(
-    const uint32_t* __restrict__ counts, int64_t R, int allow_zero, uint32_t* __restrict__ tile_count,
+    const uint32_t* __restrict__ counts, int64_t R, uint32_t* __restrict__ tile_count, WaveCounts* __restrict__ tile_waves,
     uint32_t* __restrict__ tile_bits, SortPair* __restrict__ stage)
 {
     __shared__ uint32_t wave_sum[kWavesPerBlock];
     __shared__ uint32_t wave_bits[kWavesPerBlock];
-    constexpr int kItems = kSelTile / kBlock;
-    constexpr int kSpan = kWave * kItems;                 // consecutive rows per wave
+    constexpr int kItems = kMarkSpan / kWave;
     constexpr int kStep = VEC ? 4 : 1;                    // consecutive rows per lane and load
     const int w = wave_id();
     const int lane = lane_id();
-    const int64_t tile_base = (int64_t)blockIdx.x * kSelTile;
-    const int64_t base = tile_base + (int64_t)w * kSpan;
+    const int64_t base = (int64_t)blockIdx.x * kSelTile + (int64_t)w * kMarkSpan;
+    const uint32_t rows = (uint32_t)(R - base < kMarkSpan ? (R - base < 0 ? 0 : R - base) : kMarkSpan);      // the wave's
+    const bool whole = rows == kMarkSpan;
     // item `it` of a lane is row base + row_of(it): with VEC, load it / 4 brings rows 4 * lane .. 4 * lane + 3 of a
     // stretch of 256
-    auto row_of = [&](int it) { return VEC ? (it / 4) * (kWave * 4) + lane * 4 + (it & 3) : it * kWave + lane; };
+    auto row_of = [&](int it) -> uint32_t { return VEC ? (it / 4) * (kWave * 4) + lane * 4 + (it & 3) : it * kWave + lane; };
     uint32_t cnt[kItems];
-    uint32_t before[kItems];
-    bool cand[kItems];
-    uint32_t total = 0;
-    if constexpr (VEC) {
+    const uint32_t* mine = counts + base;
+    if (whole) {
+        if constexpr (VEC) {
 #pragma unroll
-        for (int v = 0; v < kItems / 4; ++v) {
-            const int64_t g = base + row_of(4 * v);
-            u32x4 c = {0u, 0u, 0u, 0u};
-            if (g + 3 < R) {
-                c = *reinterpret_cast<const u32x4*>(counts + g);
-            } else {
-                if (g < R) c[0] = counts[g];
-                if (g + 1 < R) c[1] = counts[g + 1];
-                if (g + 2 < R) c[2] = counts[g + 2];
+            for (int v = 0; v < kItems / 4; ++v) {
+                const u32x4 c = reinterpret_cast<const u32x4*>(mine)[v * kWave + lane];
+                cnt[4 * v] = c[0]; cnt[4 * v + 1] = c[1]; cnt[4 * v + 2] = c[2]; cnt[4 * v + 3] = c[3];
             }
-            cnt[4 * v] = c[0]; cnt[4 * v + 1] = c[1]; cnt[4 * v + 2] = c[2]; cnt[4 * v + 3] = c[3];
+        } else {
+#pragma unroll
+            for (int it = 0; it < kItems; ++it) cnt[it] = mine[row_of(it)];
         }
     } else {
 #pragma unroll
-        for (int it = 0; it < kItems; ++it) {
-            const int64_t g = base + row_of(it);
-            cnt[it] = g < R ? counts[g] : 0u;
-        }
+        for (int it = 0; it < kItems; ++it) cnt[it] = row_of(it) < rows ? mine[row_of(it)] : 0u;
     }
+    SortPair* const to = stage + base;
+    const uint32_t first = (uint32_t)base;                // rows are below 2^32
+    uint32_t total = 0, bits = 0;                         // bits: the counts or-ed together: how many bits the sort has to look at
     // Position of a candidate among the wave's: those of earlier stretches, those of lower lanes in its stretch
     // (one ballot per item position), and the lane's own earlier items of the stretch.
 #pragma unroll
     for (int it0 = 0; it0 < kItems; it0 += kStep) {
-        uint32_t lower = 0, mine = 0, all = 0;
+        uint64_t cand[kStep];
+        uint32_t at = total;
 #pragma unroll
         for (int e = 0; e < kStep; ++e) {
-            const int it = it0 + e;
-            const int64_t g = base + row_of(it);
-            cand[it] = g < R && (allow_zero || cnt[it] != 0);
-            const uint64_t bal = ballot(cand[it]);
-            before[it] = mine;
-            lower += (uint32_t)popc_below(bal);
-            mine += cand[it] ? 1u : 0u;
-            all += (uint32_t)__popcll(bal);
+            cand[e] = ballot(ZERO ? (whole || row_of(it0 + e) < rows) : cnt[it0 + e] != 0u);
+            at = __builtin_amdgcn_mbcnt_hi((uint32_t)(cand[e] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)cand[e], at));
+            total += (uint32_t)__popcll(cand[e]);
+            bits |= cnt[it0 + e];
         }
 #pragma unroll
-        for (int e = 0; e < kStep; ++e) before[it0 + e] += total + lower;
-        total += all;
+        for (int e = 0; e < kStep; ++e) {
+            if (ZERO ? (whole || row_of(it0 + e) < rows) : cnt[it0 + e] != 0u) {
+                to[at] = SortPair{~cnt[it0 + e], first + row_of(it0 + e)};
+                ++at;
+            }
+        }
     }
-    uint32_t bits = 0;                                    // the counts or-ed together: how many bits the sort has to look at
-#pragma unroll
-    for (int it = 0; it < kItems; ++it) bits |= cnt[it];
     for (int o = 32; o > 0; o >>= 1) bits |= __shfl_xor(bits, o);
     if (lane == 0) { wave_sum[w] = total; wave_bits[w] = bits; }
     __syncthreads();
-    uint32_t off = 0, all = 0;
-    bits = 0;
-    for (int k = 0; k < kWavesPerBlock; ++k) {
-        if (k < w) off += wave_sum[k];
-        all += wave_sum[k];
-        bits |= wave_bits[k];
-    }
-    if (threadIdx.x == 0) { tile_count[blockIdx.x] = all; tile_bits[blockIdx.x] = bits; }
-#pragma unroll
-    for (int it = 0; it < kItems; ++it) {
-        if (cand[it]) {
-            const int64_t g = base + row_of(it);
-            stage[tile_base + off + before[it]] = SortPair{~cnt[it], (uint32_t)g};
+    if (threadIdx.x == 0) {
+        uint32_t all = 0;
+        WaveCounts each = 0;
+        bits = 0;
+        for (int k = 0; k < kWavesPerBlock; ++k) {
+            all += wave_sum[k];
+            each |= (WaveCounts)wave_sum[k] << (16 * k);
+            bits |= wave_bits[k];
         }
+        tile_count[blockIdx.x] = all;
+        tile_waves[blockIdx.x] = each;
+        tile_bits[blockIdx.x] = bits;
     }
 }
 
 static fs_status launch_mark(const uint32_t* counts, int64_t R, int allow_zero, int64_t sel_tiles, uint32_t* tile_count,
-                             uint32_t* tile_bits, SortPair* stage, hipStream_t s)
+                             WaveCounts* tile_waves, uint32_t* tile_bits, SortPair* stage, hipStream_t s)
 {
-    if ((reinterpret_cast<uintptr_t>(counts) & 15) == 0)
-        FS_LAUNCH("plan_mark", plan_mark_kernel<true>, dim3((unsigned)sel_tiles), dim3(kBlock), s,
-                  counts, R, allow_zero, tile_count, tile_bits, stage);
-    else
-        FS_LAUNCH("plan_mark", plan_mark_kernel<false>, dim3((unsigned)sel_tiles), dim3(kBlock), s,
-                  counts, R, allow_zero, tile_count, tile_bits, stage);
+#define FS_MARK(VEC, ZERO)                                                                                          \
+    FS_LAUNCH("plan_mark", (plan_mark_kernel<VEC, ZERO>), dim3((unsigned)sel_tiles), dim3(kBlock), s,                \
+              counts, R, tile_count, tile_waves, tile_bits, stage)
+    const bool vec = (reinterpret_cast<uintptr_t>(counts) & 15) == 0;
+    if (vec && !allow_zero) FS_MARK(true, false);
+    else if (vec) FS_MARK(true, true);
+    else if (!allow_zero) FS_MARK(false, false);
+    else FS_MARK(false, true);
+#undef FS_MARK
     return FS_OK;
 }
 
@@ -393,6 +395,10 @@ __device__ __forceinline__ uint32_t block_or(uint32_t v, uint32_t* waves)
     return v;
 }
 
+constexpr int64_t kScanLdsTiles = 15 * kScanBlock;               // 126 M rows: 60 KB of LDS
+
+__host__ __device__ inline int scan_run(int64_t tiles) { return (int)((tiles + kScanBlock - 1) / kScanBlock) | 1; }
+
 __global__ __launch_bounds__(kScanBlock) void plan_scan_kernel(uint32_t* __restrict__ tile_count, int64_t tiles,
                                                                const uint32_t* __restrict__ tile_bits,
                                                                int64_t* __restrict__ num_candidates,
@@ -400,18 +406,38 @@ __global__ __launch_bounds__(kScanBlock) void plan_scan_kernel(uint32_t* __restr
 {
     __shared__ uint32_t wave_bits[16];
     __shared__ uint32_t wave_sums[16];
-    const int64_t per = (tiles + kScanBlock - 1) / kScanBlock;
-    if (per <= 16) {
-        // up to 16 k tiles: a thread sums a short run of consecutive tiles, ONE scan over the block's 1024
-        // sums, the thread then writes its run's prefixes (0.019 -> 0.012 ms for 10 k tiles; for longer
-        // runs the strided accesses cost more than the scans they save)
-        const int64_t lo = (int64_t)threadIdx.x * per < tiles ? (int64_t)threadIdx.x * per : tiles;
-        const int64_t hi = lo + per < tiles ? lo + per : tiles;
-        uint32_t sum = 0, bits = 0;
-        for (int64_t k = lo; k < hi; ++k) { sum += tile_count[k]; bits |= tile_bits[k]; }
+    extern __shared__ uint32_t s_count[];                        // [kScanBlock * per] where the tiles fit
+    if (tiles <= kScanLdsTiles) {
+        // The counts to LDS, every load in flight at once; a thread sums a run of consecutive tiles there (an odd number
+        // of them: no two lanes' runs start in one bank), ONE scan over the block's 1024 sums, the thread then leaves its
+        // run's prefixes in place.  9.8 k tiles 6.8 us; each thread summing its run from memory 12.
+        const int per = scan_run(tiles);
+        const int lo = threadIdx.x * per;
+        uint32_t bits = 0;
+        constexpr int kRound = 16;
+        for (int q0 = 0; q0 < per; q0 += kRound) {
+            uint32_t v[kRound], b[kRound];
+#pragma unroll
+            for (int q = 0; q < kRound; ++q) {
+                const int k = (q0 + q) * kScanBlock + (int)threadIdx.x;
+                v[q] = tile_count[k < tiles ? k : tiles - 1];
+                b[q] = tile_bits[k < tiles ? k : tiles - 1];
+            }
+#pragma unroll
+            for (int q = 0; q < kRound; ++q) {
+                const int k = (q0 + q) * kScanBlock + (int)threadIdx.x;
+                if (q0 + q < per) s_count[k] = k < tiles ? v[q] : 0u;
+                bits |= b[q];                                    // past the end: the last tile's again
+            }
+        }
+        __syncthreads();
+        uint32_t sum = 0;
+        for (int k = lo; k < lo + per; ++k) sum += s_count[k];
         uint32_t total;
         uint32_t run = block_exclusive_scan(sum, wave_sums, &total);
-        for (int64_t k = lo; k < hi; ++k) { const uint32_t v = tile_count[k]; tile_count[k] = run; run += v; }
+        for (int k = lo; k < lo + per; ++k) { const uint32_t v = s_count[k]; s_count[k] = run; run += v; }
+        __syncthreads();
+        for (int k = threadIdx.x; k < tiles; k += kScanBlock) tile_count[k] = s_count[k];
         bits = block_or(bits, wave_bits);
         if (threadIdx.x == 0) { *num_candidates = (int64_t)total; *count_bits = bits; }
         return;
@@ -444,13 +470,13 @@ __global__ __launch_bounds__(kScanBlock) void plan_scan_kernel(uint32_t* __restr
 // first one writes the number of candidates and the bits of their counts.
 template <bool SUM>
 __global__ __launch_bounds__(kBlock) void plan_move_kernel(
-    const uint32_t* __restrict__ tile_base, int64_t tiles, const uint32_t* __restrict__ tile_bits,
-    int64_t* __restrict__ num_candidates, uint32_t* __restrict__ count_bits,
+    const uint32_t* __restrict__ tile_base, const WaveCounts* __restrict__ tile_waves, int64_t tiles,
+    const uint32_t* __restrict__ tile_bits, int64_t* __restrict__ num_candidates, uint32_t* __restrict__ count_bits,
     const SortPair* __restrict__ stage, SortPair* __restrict__ pairs)
 {
     const int64_t tile = blockIdx.x;
-    const int64_t from = tile * kSelTile;
-    uint32_t first, next;
+    const WaveCounts each = tile_waves[tile];
+    uint32_t first;
     if constexpr (SUM) {
         __shared__ uint32_t wave_sums[16];
         __shared__ uint32_t wave_bits[16];
@@ -463,16 +489,19 @@ __global__ __launch_bounds__(kBlock) void plan_move_kernel(
         uint32_t sum;
         block_exclusive_scan(before, wave_sums, &sum);
         first = tile == 0 ? 0u : sum;
-        next = first + tile_base[tile];
         if (tile == 0) {                                         // block-uniform
             bits = block_or(bits, wave_bits);
             if (threadIdx.x == 0) { *num_candidates = (int64_t)sum; *count_bits = bits; }
         }
     } else {
         first = tile_base[tile];
-        next = tile + 1 < tiles ? tile_base[tile + 1] : (uint32_t)*num_candidates;
     }
-    for (uint32_t i = threadIdx.x; i < next - first; i += kBlock) pairs[first + i] = stage[from + i];
+    // a wave moves the candidates of the wave that packed them
+    const int w = wave_id();
+    for (int k = 0; k < w; ++k) first += (uint32_t)(each >> (16 * k)) & 0xFFFFu;
+    const uint32_t n = (uint32_t)(each >> (16 * w)) & 0xFFFFu;
+    const SortPair* from = stage + tile * kSelTile + w * kMarkSpan;
+    for (uint32_t i = lane_id(); i < n; i += kWave) pairs[first + i] = from[i];
 }
 
 // Compaction and sort of the candidates, shared by the two planners: rows in (count desc, row asc) order behind their
@@ -486,6 +515,7 @@ struct PlanScratch {
     uint32_t* count_bits;
     uint32_t* tile_count;
     uint32_t* tile_bits;
+    WaveCounts* tile_waves;
     SortPair* pairs_a;
     SortPair* pairs_b;
     char* sort_scratch;
@@ -511,6 +541,7 @@ static PlanScratch take_plan_scratch(Carver& ws, int64_t R)
     p.count_bits = ws.take<uint32_t>(1);
     p.tile_count = ws.take<uint32_t>(tiles);
     p.tile_bits = ws.take<uint32_t>(tiles);
+    p.tile_waves = ws.take<WaveCounts>(tiles);
     p.pairs_a = ws.take<SortPair>((size_t)R);
     p.pairs_b = ws.take<SortPair>((size_t)R);
     p.sort_scratch = ws.take<char>(R > 0 ? radix_sort_scratch_bytes(R) : 0);
@@ -521,13 +552,15 @@ static PlanScratch take_plan_scratch(Carver& ws, int64_t R)
 static fs_status sort_candidates(const uint32_t* counts, int64_t R, int allow_zero, const PlanScratch& p, hipStream_t s)
 {
     const int64_t tiles = (R + kSelTile - 1) / kSelTile;
-    if (fs_status rc = launch_mark(counts, R, allow_zero, tiles, p.tile_count, p.tile_bits, p.pairs_b, s); rc != FS_OK) return rc;
+    if (fs_status rc = launch_mark(counts, R, allow_zero, tiles, p.tile_count, p.tile_waves, p.tile_bits, p.pairs_b, s); rc != FS_OK) return rc;
     if (tiles <= kMoveSumTiles) {
-        FS_LAUNCH("plan_move", plan_move_kernel<true>, dim3((unsigned)tiles), dim3(kBlock), s, p.tile_count, tiles,
+        FS_LAUNCH("plan_move", plan_move_kernel<true>, dim3((unsigned)tiles), dim3(kBlock), s, p.tile_count, p.tile_waves, tiles,
                   p.tile_bits, p.num_cand, p.count_bits, p.pairs_b, p.pairs_a);
     } else {
-        FS_LAUNCH("plan_scan", plan_scan_kernel, dim3(1), dim3(kScanBlock), s, p.tile_count, tiles, p.tile_bits, p.num_cand, p.count_bits);
-        FS_LAUNCH("plan_move", plan_move_kernel<false>, dim3((unsigned)tiles), dim3(kBlock), s, p.tile_count, tiles,
+        const size_t lds = tiles <= kScanLdsTiles ? (size_t)kScanBlock * (size_t)scan_run(tiles) * sizeof(uint32_t) : 0;
+        FS_LAUNCH_SMEM("plan_scan", plan_scan_kernel, dim3(1), dim3(kScanBlock), lds, s, p.tile_count, tiles, p.tile_bits, p.num_cand,
+                       p.count_bits);
+        FS_LAUNCH("plan_move", plan_move_kernel<false>, dim3((unsigned)tiles), dim3(kBlock), s, p.tile_count, p.tile_waves, tiles,
                   p.tile_bits, p.num_cand, p.count_bits, p.pairs_b, p.pairs_a);
     }
     SortJob job;
@@ -655,19 +688,31 @@ __device__ __forceinline__ int64_t wave_partition_point(int64_t lo, int64_t hi, 
     return lo;
 }
 
-// Sum of the first k sorted counts: the scanned tile sums plus a partial tile, summed by the wave.
-__device__ __forceinline__ uint64_t prefix_count(const SortPair* __restrict__ pairs,
-                                                 const uint64_t* __restrict__ tile_sum, int64_t k)
+// Sum of the first k sorted counts: the scanned tile sums plus a partial tile, summed by the block with every load in flight
+// at once.  `waves` is LDS scratch; every thread of the block must call it.
+__device__ __forceinline__ uint64_t prefix_count(const SortPair* __restrict__ pairs, const uint64_t* __restrict__ tile_sum,
+                                                 int64_t k, uint64_t* waves)
 {
     const int64_t t = k / kSumTile;
-    uint64_t part = 0;
-#pragma unroll 16
-    for (int j = 0; j < kSumTile / kWave; ++j) {
-        const int64_t i = t * kSumTile + j * kWave + lane_id();
-        part += i < k ? (uint32_t)~pairs[i][0] : 0u;
+    const int rest = (int)(k - t * kSumTile);
+    constexpr int kPer = kSumTile / kBlock;
+    const uint64_t before = tile_sum[t];
+    uint32_t v[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int i = j * kBlock + (int)threadIdx.x;
+        v[j] = ~pairs[i < rest ? t * kSumTile + i : 0][0];
     }
+    uint64_t part = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) part += j * kBlock + (int)threadIdx.x < rest ? v[j] : 0u;
     for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
-    return tile_sum[t] + part;
+    __syncthreads();                                                 // `waves` may still be read from a previous call
+    if (lane_id() == 0) waves[wave_id()] = part;
+    __syncthreads();
+    uint64_t sum = before;
+    for (int q = 0; q < kWavesPerBlock; ++q) sum += waves[q];
+    return sum;
 }
 
 // Summed DP memory terms of the first k rows, times U * S:  k (dp U - 1) S - U B P(k).
@@ -677,8 +722,9 @@ __device__ __forceinline__ i128 cum_memory(const TierConsts& c, int64_t k, uint6
 }
 
 // The searches are chains of dependent loads, so each has a wave of its own: breakpoints A, C and FLEX and point B.
-// The budget and the sums of the two tiers follow in the first wave, the sums' partial tiles with 16 loads in flight:
-// 39 -> 27 us with 1.5 M candidates (one wave doing all of it, and every row of point B's tile tested on its own).
+// The budget and the sums of the two tiers follow, the sums' partial tiles read by the whole block at once.  1.5 M candidates:
+// one wave doing all of it, and every row of point B's tile tested on its own, 39 us; the sums by the first wave, 16 loads
+// in flight, the first tier's three times over, 29; so 12.
 __global__ __launch_bounds__(kBlock) void tiers_cuts_kernel(
     const SortPair* __restrict__ pairs_a, const SortPair* __restrict__ pairs_b, const uint32_t* __restrict__ count_bits, int first_bits,
     const int64_t* __restrict__ num_candidates,
@@ -719,11 +765,14 @@ __global__ __launch_bounds__(kBlock) void tiers_cuts_kernel(
                 return v;
             };
             uint64_t mine = 0;
-#pragma unroll 16
+            uint32_t v[kPer];
+#pragma unroll
             for (int q = 0; q < kPer; ++q) {
                 const int64_t i = first + (int64_t)lane * kPer + q;
-                mine += i < K ? (uint32_t)~pairs[i][0] : 0u;
+                v[q] = ~pairs[i < K ? i : K - 1][0];
             }
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) mine += first + (int64_t)lane * kPer + q < K ? v[q] : 0u;
             const uint64_t upto = tile_sum[t0] + wave_inclusive(mine);
             const int64_t piece_end = first + (int64_t)(lane + 1) * kPer;
             const int whole = __popcll(ballot(cum_memory(c, piece_end < K ? piece_end : K, upto) <= 0));   // < 64
@@ -735,16 +784,15 @@ __global__ __launch_bounds__(kBlock) void tiers_cuts_kernel(
         if (lane == 0) found[3] = kB;
     }
     __syncthreads();
-    if (w != 0) return;
     const int64_t kA = found[0], kC = found[1], kF = found[2], kB = found[3];
 
     const int64_t gran = c.granule;
-    int64_t n_dp, n_flex = 0;
-    if (c.tiers == 2) {
-        n_dp = kB / gran * gran;
-    } else {
-        n_dp = kA / gran * gran;
-        const i128 saved = -cum_memory(c, n_dp, prefix_count(pairs, tile_sum, n_dp));     // >= 0
+    __shared__ uint64_t wave_part[kWavesPerBlock];
+    const int64_t n_dp = (c.tiers == 2 ? kB : kA) / gran * gran;
+    int64_t n_flex = 0;
+    const uint64_t sum_dp = prefix_count(pairs, tile_sum, n_dp, wave_part);
+    if (c.tiers != 2) {
+        const i128 saved = -cum_memory(c, n_dp, sum_dp);                 // >= 0
         int64_t room = K - n_dp;
         if (kF - n_dp < room) room = kF > n_dp ? kF - n_dp : 0;
         int64_t lo = 0, hi = room;                                       // most rows j with j * flex_cost <= saved
@@ -758,9 +806,8 @@ __global__ __launch_bounds__(kBlock) void tiers_cuts_kernel(
         }
         n_flex = lo / gran * gran;
     }
-    const uint64_t sum_dp = prefix_count(pairs, tile_sum, n_dp);
-    const uint64_t sum_both = prefix_count(pairs, tile_sum, n_dp + n_flex);
-    if (lane == 0) {
+    const uint64_t sum_both = n_flex == 0 ? sum_dp : prefix_count(pairs, tile_sum, n_dp + n_flex, wave_part);      // block-uniform
+    if (threadIdx.x == 0) {
         cuts[0] = K; cuts[1] = kA; cuts[2] = kB; cuts[3] = kC; cuts[4] = kF;
         cuts[5] = n_dp; cuts[6] = n_flex;
         cuts[7] = (int64_t)tile_sum[tiles]; cuts[8] = (int64_t)sum_dp; cuts[9] = (int64_t)(sum_both - sum_dp);

@@ -405,7 +405,10 @@ constexpr int kSmallBlock = 256, kSmallItems = 4;
 constexpr int kSortStripe = 16;              // tiles per XCD stripe in the scatter
 constexpr int64_t kSortSmallTiles = 256;
 constexpr int64_t kSortSumTiles = 64;
-constexpr int64_t kSortScatterGrid = 8192;   // blocks of the scatter at most; they walk the tiles with a grid stride
+// Blocks of the scatter at most; they walk the tiles with a grid stride.  Where the count is on the device it is usually a
+// few per cent of what the buffers hold, and a pass may be idle: fewer blocks, four rounds of the three that a CU takes.
+constexpr int64_t kSortScatterGrid = 8192;
+constexpr int64_t kSortScatterGridDev = 3072;
 // From this many pairs on they lie apart between passes too.  Side by side the scatter's stores are half as many and its
 // runs twice as long, but the count reads 8 bytes for a key of 4, which costs more where a pass no longer fits the 256 MB
 // memory-side cache.  Side by side : apart, us, rows of 27 bits: 8.4 M 170 : 175, 15.7 M 278 : 286, 30 M 534 : 532,
@@ -497,7 +500,8 @@ static fs_status launch_sort_pass(const Reader& in, const SortPass& p)
     }
     if (!p.shape.small) {
         const int64_t padded = xcd_striped_grid(p.shape.tiles, kSortStripe);       // a multiple of 8, as the largest grid is
-        FS_SCATTER(kLargeBlock, kLargeItems, kSortStripe, false, padded < kSortScatterGrid ? padded : kSortScatterGrid);
+        const int64_t most = p.m_dev != nullptr ? kSortScatterGridDev : kSortScatterGrid;
+        FS_SCATTER(kLargeBlock, kLargeItems, kSortStripe, false, padded < most ? padded : most);
     }
 #undef FS_COUNT
 #undef FS_SCATTER

@@ -136,6 +136,33 @@ def test_selection_at_every_number_of_passes(G, R):
         assert np.array_equal(sel[:n].cpu().numpy(), order[:n]), bits
 
 
+@pytest.mark.parametrize("tiles", [1025, 2048, 2049, 15 * 1024, 15 * 1024 + 1])
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("zero", [False, True])
+def test_compaction_tiles(G, tiles, off, zero):
+    """Numbers of compaction tiles around the runs of the scan in LDS (odd lengths, at most 15) and beyond it, the last
+    tile ragged; counters 16-byte aligned or not; dense stretches, full waves and empty ones."""
+    import paper_2301_02959_amd as fs
+    R = tiles * TILE - (777 if off else 0)
+    if zero and tiles > 1025:
+        pytest.skip("every row a candidate: the smallest size is enough")
+    torch.manual_seed(tiles + off)
+    buf = torch.zeros(R + off, dtype=torch.int32, device=G.DEV)
+    counts = buf[off:]
+    some = torch.randint(0, R, (30_000,), device=G.DEV)
+    counts[some] = torch.randint(1, 300, (30_000,), dtype=torch.int32, device=G.DEV)
+    for lo in (0, 3 * TILE, 5 * TILE + 2048, R - 5000):                         # whole waves of candidates, the ragged end
+        counts[lo:lo + 2048] = 1
+    counts[-1] = 70_000
+    K = R if zero else int((counts > 0).sum())
+    sel = torch.full((K,), -7, dtype=torch.int64, device=G.DEV)
+    num = torch.zeros(1, dtype=torch.int64, device=G.DEV)
+    fs.fs_plan_replication(None, None, 1, 1, None, 0, R, counts, S | (Z if zero else 0), K, 1, sel, num)
+    rows = torch.arange(R, device=G.DEV) if zero else torch.nonzero(counts > 0).flatten()
+    order = torch.sort(counts[rows], descending=True, stable=True)[1]
+    assert int(num.item()) == K and torch.equal(sel, rows[order])
+
+
 def test_a_workspace_for_more_rows_serves_fewer():
     """The scratch size does not shrink as the rows grow, also where the sort goes over to larger tiles."""
     import ctypes
