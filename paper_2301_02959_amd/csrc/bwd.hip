@@ -48,6 +48,12 @@ __device__ __forceinline__ uint32_t from_lane_below(uint32_t v, uint32_t first)
     return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
 }
 
+// `v` of the lane above; lane 63 gets `last`.
+__device__ __forceinline__ uint32_t from_lane_above(uint32_t v, uint32_t last)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)v, 0x130 /* wave_shl:1 */, 0xf, 0xf, false);
+}
+
 // TOTAL: one block is all there is, and the scan over the blocks no launch of its own.
 template <bool TOTAL>
 __global__ __launch_bounds__(kHeadsBlock) void bwd_count_heads_kernel(
@@ -614,39 +620,56 @@ __device__ __forceinline__ void singles_batch(
 __device__ __forceinline__ bool list_singletons(
     const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals, int64_t m, int64_t chunks, uint32_t n,
     const uint32_t* __restrict__ block_base, const uint32_t* __restrict__ chunk_local,
-    uint32_t* s_pos, uint32_t* s_run, uint32_t* s_key, uint32_t* singles_out, uint32_t* runs_end)
+    uint32_t* s_pos, uint32_t* s_run, uint32_t* s_key, uint32_t* singles_out, uint32_t* runs_end, int spread = 0)
 {
     const int lane = lane_id();
     const int64_t wave_global = (int64_t)blockIdx.x * kWavesPerBlock + wave_id();
-    const int64_t chunk = wave_global / kSinglesSplit;
-    const int part = (int)(wave_global % kSinglesSplit);
+    const int64_t part_global = wave_global >> spread;
+    const int64_t chunk = part_global / kSinglesSplit;
+    const int part = (int)(part_global % kSinglesSplit);
+    const bool mine = (lane >> (6 - spread)) == (int)(wave_global & ((1 << spread) - 1));
     if (chunk >= chunks) return false;
     const int64_t k0 = chunk * kChunk;
     const int64_t k1 = k0 + kChunk < m ? k0 + kChunk : m;
+    // One round of loads, none behind a predicate: the chunk's keys, the ones before and after it, the positions of the
+    // part.  A lookup's neighbours are its lane's; the ends of the list are known by index (no key can stand for "none",
+    // a caller's list may hold any 32-bit word).
+    constexpr int Q = kChunk / kWave;
+    static_assert(kSinglesSplit == Q, "a part is one round of 64 lookups");
+    uint32_t key[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int64_t k = k0 + q * kWave + lane;
+        key[q] = keys[k < k1 ? k : k1 - 1];
+    }
+    const uint32_t before = keys[k0 > 0 ? k0 - 1 : 0];
+    const uint32_t after = keys[k1 < m ? k1 : k1 - 1];
+    const int64_t my_k = k0 + part * kWave + lane;
+    const uint32_t my_pos = vals[my_k < k1 ? my_k : k1 - 1];
     const uint32_t first_run = runs_before(block_base, chunk_local, chunk, chunks);
 
-    uint32_t heads_before = 0, singles = 0;
+    uint32_t heads_before = 0, singles = 0, last = before;
 #pragma unroll
-    for (int q = 0; q < kChunk / kWave; ++q) {
+    for (int q = 0; q < Q; ++q) {
         const int64_t k = k0 + q * kWave + lane;
         const bool valid = k < k1;
-        const uint32_t key = valid ? keys[k] : 0u;
-        const uint32_t prev = (valid && k > 0) ? keys[k - 1] : 0u;
-        const uint32_t next = (valid && k + 1 < m) ? keys[k + 1] : 0u;
-        // the ends of the list by index: no key can stand for "none", a caller's list may hold any 32-bit word
-        const bool head = valid && (k == 0 || key != prev);
-        const bool single = head && (k + 1 >= m || key != next) && q * kSinglesSplit / (kChunk / kWave) == part;
+        const uint32_t prev = from_lane_below(key[q], last);
+        const uint32_t next = from_lane_above(key[q], q + 1 < Q ? (uint32_t)__builtin_amdgcn_readlane((int)key[q + 1 < Q ? q + 1 : q], 0) : after);
+        const bool head = valid && (k == 0 || key[q] != prev);
         const uint64_t hb = ballot(head);
-        const uint64_t sb = ballot(single);
-        if (single) {
-            const uint32_t at = singles + (uint32_t)popc_below(sb);
-            const uint32_t p = vals[k];
-            s_pos[at] = p < n ? p : 0u;                          // a position outside the batch reads row 0
-            s_run[at] = first_run + heads_before + (uint32_t)popc_below(hb);
-            s_key[at] = key;
+        if (q == part) {                                         // wave-uniform
+            const bool single = mine && head && (k + 1 >= m || key[q] != (k + 1 < k1 ? next : after));
+            const uint64_t sb = ballot(single);
+            if (single) {
+                const uint32_t at = (uint32_t)popc_below(sb);
+                s_pos[at] = my_pos < n ? my_pos : 0u;            // a position outside the batch reads row 0
+                s_run[at] = first_run + heads_before + (uint32_t)popc_below(hb);
+                s_key[at] = key[q];
+            }
+            singles = (uint32_t)__popcll(sb);
         }
         heads_before += (uint32_t)__popcll(hb);
-        singles += (uint32_t)__popcll(sb);
+        last = (uint32_t)__builtin_amdgcn_readlane((int)key[q], kWave - 1);
     }
     *singles_out = singles;
     *runs_end = first_run + heads_before;
@@ -755,12 +778,19 @@ __device__ __forceinline__ void singles_update_batch(
     }
 }
 
+// 2^spread waves share a part where there are few chunks: a wave's time is its chain of rows, each with a division and a
+// square root to an element, and 640 waves leave most SIMDs idle.  The backward with the step, spread 0 / 1 / 2 / 3, us
+// (with 16 entries to a wave of the step that follows): 10 k lookups of 512-byte rows 59 / 50 / 43 / 39 (36), of f16 rows with
+// element-wise state 43 / 38 / 35 / 34 (33); 50 k 74 / 64 / 56 / 52 (49) and 54 / 51 / 47 / 46 (43); 260 k 111 / 105 / 100 / 101
+// and 84 / 78 / 76 / 76; 1 M 228 / 221 / 221 / 234 and 180 / 176 / 174 / 188; 2 M of 256-byte rows 205 / 207 / 220 / 247.
+static int update_spread(int64_t chunks) { return chunks <= 256 ? 3 : chunks <= 2048 ? 2 : chunks <= 4608 ? 1 : 0; }
+
 template <int LG, int DT, int OPT, bool EXACT>
 __global__ __launch_bounds__(kBlock) void bwd_singletons_update_kernel(
     const u32x4* __restrict__ grad, const UpdateArgs a,
     const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals, int64_t m, int64_t chunks, uint32_t n,
     const uint32_t* __restrict__ block_base, const uint32_t* __restrict__ chunk_local,
-    int64_t* __restrict__ uniq_rows, int64_t cap, uint8_t* __restrict__ applied)
+    int64_t* __restrict__ uniq_rows, int64_t cap, uint8_t* __restrict__ applied, int spread)
 {
     constexpr int RPI = kWave / LG;
     constexpr int CNT = 2;                                           // rows a group keeps in flight (each brings a gradient row, a table
@@ -773,7 +803,7 @@ __global__ __launch_bounds__(kBlock) void bwd_singletons_update_kernel(
     const int w = wave_id();
     uint32_t singles, runs_end;
     if (!list_singletons(keys, vals, m, chunks, n, block_base, chunk_local, s_pos[w], s_run[w], s_key[w], &singles,
-                         &runs_end))
+                         &runs_end, spread))
         return;                                                      // wave-uniform; no block barrier below
     for (uint32_t s = 0; s < singles; s += CNT * RPI)
         singles_update_batch<CNT, LG, DT, OPT, EXACT>(grad, a, s_pos[w], s_run[w], s_key[w], s_stage[w], s, singles, cap,
@@ -1100,13 +1130,14 @@ static fs_status launch_singletons_update_opt(int optimizer, const void* grad, c
                                               const uint32_t* block_base, const uint32_t* chunk_local, int64_t* uniq_rows,
                                               int64_t cap, uint8_t* applied, hipStream_t stream)
 {
-    const int64_t waves = chunks * kSinglesSplit;
+    const int spread = update_spread(chunks);
+    const int64_t waves = (chunks * kSinglesSplit) << spread;
     if ((waves + kWavesPerBlock - 1) / kWavesPerBlock > 0x7FFFFFFF) return FS_ERR_SIZE;
     const dim3 grid((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock));
     const u32x4* g = static_cast<const u32x4*>(grad);
 #define FS_SU_LAUNCH(OPT, EX)                                                                                      \
     FS_LAUNCH("bwd_singletons_update", (bwd_singletons_update_kernel<LG, DT, OPT, EX>), grid, dim3(kBlock), stream, g, a, \
-              keys, vals, m, chunks, n, block_base, chunk_local, uniq_rows, cap, applied)
+              keys, vals, m, chunks, n, block_base, chunk_local, uniq_rows, cap, applied, spread)
     const bool exact = a.units == LG;
     if (optimizer == FS_OPT_SGD) { if (exact) FS_SU_LAUNCH(FS_OPT_SGD, true); else FS_SU_LAUNCH(FS_OPT_SGD, false); }
     else if (optimizer == FS_OPT_ADAGRAD) { if (exact) FS_SU_LAUNCH(FS_OPT_ADAGRAD, true); else FS_SU_LAUNCH(FS_OPT_ADAGRAD, false); }

@@ -139,6 +139,7 @@ struct UpdateArgs {
     const int32_t* slot_of_row;
     int64_t k;
     int32_t* status;
+    int per_wave;                    // entries to a wave, at most 64: set by the launch
     const uint8_t* skip;             // if set: entries u with skip[u] != 0 are left alone (another kernel updated them)
 };
 

@@ -157,3 +157,43 @@ def test_bwd_update_host_faults_and_empty(G):
     assert call(m=0) == 0
     torch.cuda.synchronize()
     assert int(nu.item()) == 0
+
+
+@pytest.mark.parametrize("m", [1, 63, 256 * 256, 256 * 256 + 1, 2048 * 256, 2048 * 256 + 1, 4608 * 256, 4608 * 256 + 77])
+@pytest.mark.parametrize("dt,D", [("f32", 8), ("bf16", 24)])
+def test_bwd_update_batch_sizes(G, m, dt, D):
+    """The sizes at which a part of a chunk goes to 8, 4, 2 waves or one.  Gradients are small whole numbers and the
+    learning rate a power of two, so every row is exact in any order."""
+    import paper_2301_02959_amd as fs
+    R = m + 100
+    gen = torch.Generator(device=G.DEV).manual_seed(m)
+    rows = torch.sort(torch.randint(0, R, (m,), device=G.DEV, generator=gen))[0]          # about half of them looked up once
+    pos = torch.arange(m, dtype=torch.int32, device=G.DEV)
+    grad = torch.randint(-2, 3, (m, D), device=G.DEV, generator=gen).to(TDT[dt])
+    W = torch.randint(-3, 4, (R, D), device=G.DEV, generator=gen).to(TDT[dt])
+    want = W.double().index_add_(0, rows, grad.double(), alpha=-0.25)
+    cap = int(torch.unique(rows).numel())
+    uniq = torch.full((cap,), -7, dtype=torch.int64, device=G.DEV)
+    rg = torch.zeros(cap, D, device=G.DEV)
+    nu = torch.zeros(1, dtype=torch.int64, device=G.DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    fs.fs_seq_grad_bwd_update(grad, rows.to(torch.int32), pos, m, R, W, fs.FS_OPT_SGD, 0.25, 1e-8, None, None, None, 0, uniq, rg, cap, nu, st)
+    assert int(st.item()) == 0 and int(nu.item()) == cap and torch.equal(uniq, torch.unique(rows))
+    assert torch.equal(W.double(), want)
+
+
+@pytest.mark.parametrize("cap", [1, 7, 8, 9, 8192, 8193, 1 << 19, (1 << 19) + 1])
+@pytest.mark.parametrize("share", [0.4, 1.0])
+def test_update_entries_to_a_wave(G, cap, share):
+    """The optimizer step with 8, 16 and 64 entries to a wave; the device's count at the capacity or below it."""
+    import paper_2301_02959_amd as fs
+    R, D = cap + 50, 12
+    gen = torch.Generator(device=G.DEV).manual_seed(cap)
+    n = max(1, int(cap * share))
+    uniq = torch.sort(torch.randperm(R, device=G.DEV, generator=gen)[:cap])[0]
+    rg = torch.randint(-2, 3, (cap, D), device=G.DEV, generator=gen).float()
+    W = torch.randint(-3, 4, (R, D), device=G.DEV, generator=gen).float()
+    want = W.clone()
+    want[uniq[:n]] -= 0.25 * rg[:n]
+    fs.fs_sparse_update(W, uniq, rg, cap, torch.tensor([n], device=G.DEV), fs.FS_OPT_SGD, 0.25, 1e-8, None)
+    assert torch.equal(W, want)
