@@ -862,11 +862,12 @@ struct LongRun {
     uint32_t first, last;                        // chunks
 };
 // Runs with more carries than this are left to it, where the batch is large enough (chunks times columns) for the launch
-// to be worth its 2 us.  The backward without and with it, Zipf(1.3) and Zipf(1.05) over 50 M rows: 300 k lookups (1172 chunks)
-// of 128 columns 52 : 54 and 62 : 66 us, of 256 80 : 75 and 93 : 96, 1 M (4102) of 64 93 : 97 and 107 : 107, of 128 111 : 105
-// and 125 : 125, of 256 197 : 167 and 224 : 219, 4.2 M of 64 293 : 287 and 313 : 314, of 256 657 : 519 and 729 : 691.
+// to be worth its 3 to 5 us.  The backward without and with it, Zipf(1.3) and Zipf(1.05) over 50 M rows: 300 k lookups (1172
+// chunks) of 128 columns 52 : 54 and 62 : 66 us, of 256 80 : 75 and 93 : 96, 1 M (4102) of 64 93 : 97 and 107 : 107, of 128
+// 111 : 105 and 125 : 125 (Zipf(1.1) over 8 tables: the folds alone 8 : 12), of 256 197 : 167 and 224 : 219, 4.2 M of 64
+// 293 : 287 and 313 : 314, of 256 657 : 519 and 729 : 691.
 constexpr int64_t kFoldLong = 64;
-constexpr int64_t kFoldLongWork = 500000;
+constexpr int64_t kFoldLongWork = 1000000;
 
 // One wave per chunk; a wave whose chunk starts a spilling run (one that goes on into the next
 // chunk) adds the carries of the chunks the run goes on into, left to right.

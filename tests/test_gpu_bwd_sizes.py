@@ -155,15 +155,15 @@ def test_runs_over_many_chunks(G, D, first):
 @pytest.mark.parametrize("D", [36, 60, 128, 132, 260])
 @pytest.mark.parametrize("first", [0, 100])
 def test_runs_left_to_the_long_fold(G, D, first):
-    """Batches of more than 500 k chunks times columns: runs of up to 64 further chunks are folded by their own wave, longer
+    """Batches of more than a million chunks times columns: runs of up to 64 further chunks are folded by their own wave, longer
     ones by a block 256 carries at a time, 32 of them at once, for 32 columns each."""
     rng = np.random.default_rng(D + first)
     more = [1, 63, 64, 65, 66, 96, 97, 98, 255, 256, 257, 289, 512, 513, 514, 769, 1025]
-    more.append(max(600, 500_000 // D + 2 - sum(more)))
+    more.append(max(600, 1_000_000 // D + 2 - sum(more)))
     rows = np.repeat(np.arange(len(more) + 1), [first] + [k * CHUNK for k in more])
     rows = rows[rows > 0] if first == 0 else rows
     m = len(rows)
-    assert -(-m // CHUNK) * D > 500_000
+    assert -(-m // CHUNK) * D > 1_000_000
     pos = (np.arange(m) % 1021).astype(np.int32)
     pos = pos[np.lexsort((pos, rows))]
     gnp, gt = _np_grad(rng.standard_normal((1021, D)).astype(np.float32), "f32")
