@@ -2,7 +2,7 @@
 //
 // A stable counting sort of the n lookups by destination bucket, in three steps
 // that touch each lookup twice:
-//   route_remap     one 2048-lookup tile per block: table of each lookup, global
+//   route_remap     one tile of 2048 lookups (small batches: 512 or 1024) per block: table of each lookup, global
 //                   row g, placement entry, destination; per-tile bucket
 //                   histogram (the own bucket and one other by ballots, the rest by LDS adds) plus the tile's three tier
 //                   counts; dest (u16) and g (u32) go to the workspace; each block also
@@ -10,7 +10,7 @@
 //   route_scan      one block per bucket (and per tier): exclusive scan of its per-tile
 //                   counts over the tiles, and its total (skipped when the counts are few
 //                   enough for every scatter block to sum them itself)
-//   route_scatter   same tiles: each wave ranks its 512 consecutive lookups by
+//   route_scatter   same tiles: each wave ranks its consecutive lookups by
 //                   ballot matching against a wave-private running histogram in
 //                   LDS, adds the tile's and the bucket's base, writes
 //                   out_rows / out_pos
@@ -25,14 +25,21 @@
 namespace fs {
 
 constexpr int kRouteItems = 8;                        // lookups per thread
-constexpr int kRouteTile = kBlock * kRouteItems;      // lookups per block
-constexpr int kRouteWaveSpan = kWave * kRouteItems;   // consecutive lookups per wave
 constexpr int kRouteStripe = 32;                      // tiles per XCD stripe in the scatter
 // Up to this many tile counts (tiles x (buckets + 3)) every scatter block sums them itself, the threads of a block
 // sharing a bucket's tiles, and route_scan is not launched: 8192 lookups over 8 buckets take 5.5 us of GPU time
 // after the remap instead of 9, 80 k over 64 (2747 counts) 6 instead of 8, and the host saves a launch (2.3 us).
 // At 6499 counts the two are even on the GPU, at 14 k the sums are 12 us slower.
 constexpr int64_t kRouteSumMax = 6144;
+// Small batches take tiles of 512 and 1024 lookups instead of 2048, whose counts every scatter block sums too: a block's
+// time is its chain of rounds, its share of random placement reads and the memory's latency.  Both kernels, 2048 / 1024 / 512
+// lookups to a tile, us: 8192 lookups over 8 buckets 11.9 / 10.0 / 9.9, 50 k over 64 13.1 / 10.1 / 9.4, 83 k (10.9 k counts of
+// 512) 13.2 / 10.8 / 10.2, 130 k (17 k) 13.1 / 10.8 / 11.1, 260 k over 8 (5.6 k) 13.7 / 10.7 / 10.4, 520 k (11.2 k) 15.6 / 13.1 /
+// 14.2; 260 k over 64 (17 k counts of 1024) 16.9 / 12.7, over 128 (33 k) 17.2 / 15.2, 520 k over 64 (34 k) 18.1 / 18.2.  Up to 128
+// buckets: there the threads that share a bucket bring its counts in one round.
+constexpr int64_t kRouteSmallCounts[2] = {11000, 33500};         // of tiles of 512 and 1024 lookups
+constexpr int64_t kRouteSmallTiles = 512;
+constexpr int kRouteSmallBuckets = 128;
 // Beyond one tile for every CU the remap counts the first foreign bucket by ballots too (LEAD).  16 M lookups, every row
 // on one other GPU: 76 us with a full match of the buckets, 83 with plain adds, 73 so; rows dealt over 8 buckets 82, 73.5,
 // 73.5.  2.4 M: plain 20.7 and 16.4, so 16.9 and 16.8.  Up to one tile the waves' own chains are the time, and the ballots
@@ -58,7 +65,7 @@ __global__ __launch_bounds__(kBlock) void route_prepare_kernel(
 // A tile's tables and their rows, staged in LDS when there are at most this many of them.
 constexpr int kRouteTileTables = 64;
 
-template <bool LEAD>
+template <bool LEAD, int ITEMS>
 __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     const int64_t* __restrict__ ids, const int64_t* __restrict__ offsets, int T, int64_t B,
     const int64_t* __restrict__ row_base, const uint32_t* __restrict__ placement,
@@ -67,6 +74,7 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     uint32_t* __restrict__ tile_hist /* buckets, then the three tiers */, int64_t tiles,
     int by_tile /* tile_hist is [tiles][U + 3], else [U + 3][tiles] */, int32_t* status)
 {
+    constexpr int kTile = kBlock * ITEMS;
     extern __shared__ uint32_t lds_hist[];            // [U]
     __shared__ int tile_tables[2];
     __shared__ int64_t table_end[kRouteTileTables];   // tables t_lo .. t_hi of the tile: first lookup after table t,
@@ -74,14 +82,14 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     __shared__ int64_t table_rows[kRouteTileTables];  // and how many it has
     __shared__ unsigned int wave_counts[kWavesPerBlock][3];   // tiers 1 and 2, lookups of the own bucket
     const int64_t tile = blockIdx.x;
-    const int64_t base = tile * kRouteTile;
+    const int64_t base = tile * kTile;
     const int w = wave_id();
 
     // Every load that waits for nothing goes out first: the ids, this block's share of the offsets (checked at
-    // the very end), the table bounds.
-    int64_t id[kRouteItems];
+    // the very end), the table bounds: of all tables if they fit, so that no load waits for the search of the tile's.
+    int64_t id[ITEMS];
 #pragma unroll
-    for (int it = 0; it < kRouteItems; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         const int64_t i = base + (int64_t)it * kBlock + threadIdx.x;
         id[it] = load_stream(ids + (i < n ? i : n - 1));             // past the end: the last id again, unused
     }
@@ -92,42 +100,65 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     const bool has_segment = s_lo + threadIdx.x < s_hi;
     int64_t seg0 = 0, seg1 = 0;
     if (has_segment) { seg0 = offsets[s_lo + threadIdx.x]; seg1 = offsets[s_lo + threadIdx.x + 1]; }
-
-    for (int b = threadIdx.x; b < U; b += kBlock) lds_hist[b] = 0;
-    if (w < 2) {                                                     // two waves find the tile's first and last table
-        const int64_t last = (base + kRouteTile < n ? base + kRouteTile : n) - 1;
-        const int t = wave_table_of(offsets, T, B, w == 0 ? base : last);
-        if (lane_id() == 0) tile_tables[w] = t;
-    }
-    __syncthreads();
-    const int t_lo = __builtin_amdgcn_readfirstlane(tile_tables[0]);
-    const int t_hi = __builtin_amdgcn_readfirstlane(tile_tables[1]);
-    const bool staged = t_hi - t_lo < kRouteTileTables;              // block-uniform
-    if (t_lo != t_hi && staged) {
-        const int k = threadIdx.x;
-        if (k <= t_hi - t_lo) {
-            table_end[k] = offsets[(int64_t)(t_lo + k + 1) * B];
-            table_first[k] = row_base[t_lo + k];
-            table_rows[k] = row_base[t_lo + k + 1] - row_base[t_lo + k];
+    const int64_t last = (base + kTile < n ? base + kTile : n) - 1;
+    const int64_t R_all = row_base[T];                // rows of all tables; g must stay below it (and below 2^32 - 1)
+    const bool all_staged = T <= kRouteTileTables;    // uniform
+    int t_lo, t_hi;
+    int staged_from;                                  // the table that table_end[0] is of
+    bool staged = true;                               // block-uniform
+    if (all_staged) {
+        // every wave finds the tile's first and last table itself: a lane for each
+        const int k = lane_id() < T ? lane_id() : T - 1;
+        const int64_t starts = offsets[(int64_t)k * B];
+        t_lo = __popcll(ballot(lane_id() > 0 && lane_id() < T && starts <= base));
+        t_hi = __popcll(ballot(lane_id() > 0 && lane_id() < T && starts <= last));
+        staged_from = 0;
+        if (w == 0 && lane_id() < T) {
+            const int64_t first = row_base[k];
+            table_end[k] = offsets[(int64_t)(k + 1) * B];
+            table_first[k] = first;
+            table_rows[k] = row_base[k + 1] - first;
+        }
+        for (int b = threadIdx.x; b < U; b += kBlock) lds_hist[b] = 0;
+        __syncthreads();
+    } else {
+        for (int b = threadIdx.x; b < U; b += kBlock) lds_hist[b] = 0;
+        if (w < 2) {                                                 // two waves find the tile's first and last table
+            const int t = wave_table_of(offsets, T, B, w == 0 ? base : last);
+            if (lane_id() == 0) tile_tables[w] = t;
         }
         __syncthreads();
+        t_lo = tile_tables[0];
+        t_hi = tile_tables[1];
+        staged_from = t_lo;
+        staged = t_hi - t_lo < kRouteTileTables;
+        if (staged) {
+            const int k = threadIdx.x;
+            if (k <= t_hi - t_lo) {
+                table_end[k] = offsets[(int64_t)(t_lo + k + 1) * B];
+                table_first[k] = row_base[t_lo + k];
+                table_rows[k] = row_base[t_lo + k + 1] - row_base[t_lo + k];
+            }
+            __syncthreads();
+        }
     }
+    t_lo = __builtin_amdgcn_readfirstlane(t_lo);
+    t_hi = __builtin_amdgcn_readfirstlane(t_hi);
     const int group_base = (self / W) * W;
-    const int64_t R_all = row_base[T];                // rows of all tables; g must stay below it (and below 2^32 - 1)
     const bool rows_ok = R_all >= 1 && R_all < 4294967295LL;
     int32_t faults = rows_ok ? 0 : FS_DEV_BAD_ID;
 
-    const int64_t first_lo = row_base[t_lo];
-    const int64_t rows_lo = row_base[t_lo + 1] - first_lo;
-    int64_t g[kRouteItems];
+    const int64_t first_lo = staged ? table_first[t_lo - staged_from] : row_base[t_lo];
+    const int64_t rows_lo = staged ? table_rows[t_lo - staged_from] : row_base[t_lo + 1] - first_lo;
+    int64_t g[ITEMS];
 #pragma unroll
-    for (int it = 0; it < kRouteItems; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         const int64_t i = base + (int64_t)it * kBlock + threadIdx.x;
         int64_t first = first_lo, rows_t = rows_lo;
         if (t_lo != t_hi) {                                          // block-uniform
             if (staged) {
-                int k = 0;
-                while (k < t_hi - t_lo && table_end[k] <= i) ++k;
+                int k = t_lo - staged_from;
+                while (k < t_hi - staged_from && table_end[k] <= i) ++k;
                 first = table_first[k];
                 rows_t = table_rows[k];
             } else {
@@ -144,16 +175,16 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
         if ((uint64_t)row >= (uint64_t)R_all) { if (valid) faults |= FS_DEV_BAD_ID; row = 0; }   // row_base not ascending
         g[it] = row;
     }
-    uint32_t e[kRouteItems];
+    uint32_t e[ITEMS];
 #pragma unroll
-    for (int it = 0; it < kRouteItems; ++it) e[it] = rows_ok ? placement[g[it]] : 0u;
+    for (int it = 0; it < ITEMS; ++it) e[it] = rows_ok ? placement[g[it]] : 0u;
     // Counts of the wave: the tiers and the own bucket with one ballot each, and (LEAD) one more for the bucket of the
     // wave's first lookup that goes elsewhere: a bucket that most of the rest go to (few buckets, whole tables or a hot row
     // on one other GPU) is nearly always that one.  What is left are plain LDS adds, of which few meet in one word.
     uint32_t in_tier1 = 0, in_tier2 = 0, own = 0;                    // tier 0: the tile's other lookups
     uint32_t led = 0, in_led = 0;                                    // led: any bucket if the first item has none
 #pragma unroll
-    for (int it = 0; it < kRouteItems; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         const int64_t i = base + (int64_t)it * kBlock + threadIdx.x;
         const bool valid = i < n;
         const uint32_t tier = e[it] >> FS_TIER_SHIFT;
@@ -198,7 +229,7 @@ __global__ __launch_bounds__(kBlock) void route_remap_kernel(
     // tier counts travel as three more histogram rows (no global atomics: 3 hot addresses
     // shared by every wave of the grid serialise in L2)
     if (threadIdx.x < 3) {
-        const uint32_t in_tile = (uint32_t)(n - base < kRouteTile ? n - base : kRouteTile);
+        const uint32_t in_tile = (uint32_t)(n - base < kTile ? n - base : kTile);
         const uint32_t in_tier = threadIdx.x == 0 ? in_tile - waves_sum(0) - waves_sum(1) : waves_sum(threadIdx.x - 1);
         my_hist[(U + threadIdx.x) * step] = in_tier;
     }
@@ -233,7 +264,7 @@ __global__ __launch_bounds__(kRouteScanBlock) void route_scan_kernel(uint32_t* _
 }
 
 // SUM: the counts are few, route_scan has not run: tile_hist holds plain counts and every block adds up what it needs.
-template <int NBITS, bool SUM>
+template <int NBITS, bool SUM, int ITEMS>
 __global__ __launch_bounds__(kBlock) void route_scatter_kernel(
     const uint16_t* __restrict__ dest_in, const uint32_t* __restrict__ g_in, int64_t n, int U,
     const uint32_t* __restrict__ tile_hist /* scanned, unless SUM */, int64_t tiles, const uint32_t* __restrict__ totals,
@@ -253,17 +284,17 @@ __global__ __launch_bounds__(kBlock) void route_scatter_kernel(
     // which one XCD's L2 merges into whole lines (0.082 -> 0.073 ms on 15.7 M lookups)
     const int64_t tile = SUM ? (int64_t)blockIdx.x : xcd_striped_tile(blockIdx.x, kRouteStripe);
     if (tile >= tiles) return;                                          // block-uniform, before any barrier
-    const int64_t base = tile * kRouteTile;
+    const int64_t base = tile * (kBlock * ITEMS);
     const int w = wave_id();
     const int lane = lane_id();
 
-    uint32_t dest[kRouteItems];
-    uint32_t rank[kRouteItems];
-    uint32_t g[kRouteItems];
-    int32_t slot[kRouteItems];
+    uint32_t dest[ITEMS];
+    uint32_t rank[ITEMS];
+    uint32_t g[ITEMS];
+    int32_t slot[ITEMS];
 #pragma unroll
-    for (int it = 0; it < kRouteItems; ++it) {
-        const int64_t i = base + (int64_t)w * kRouteWaveSpan + it * kWave + lane;
+    for (int it = 0; it < ITEMS; ++it) {
+        const int64_t i = base + (int64_t)w * (kWave * ITEMS) + it * kWave + lane;
         const bool valid = i < n;
         dest[it] = valid ? dest_in[i] : 0;
         g[it] = valid ? g_in[i] : 0;
@@ -283,12 +314,20 @@ __global__ __launch_bounds__(kBlock) void route_scatter_kernel(
             const int b = threadIdx.x & (kBins - 1);
             const int part = threadIdx.x >> NBITS;
             uint32_t all = 0, before = 0;
-            if (b < U) {
-#pragma unroll 8
-                for (int k = part; k < (int)tiles; k += kParts) {
-                    const uint32_t v = tile_hist[k * stride + b];
-                    all += v;
-                    before += k < (int)tile ? v : 0u;
+            const int bc = b < U ? b : 0;
+            constexpr int kAhead = 16;                                  // loads in flight, none behind a predicate
+            for (int k0 = part; k0 < (int)tiles; k0 += kAhead * kParts) {
+                uint32_t v[kAhead];
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) {
+                    const int k = k0 + q * kParts;
+                    v[q] = tile_hist[(k < (int)tiles ? k : (int)tiles - 1) * stride + bc];
+                }
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) {
+                    const int k = k0 + q * kParts;
+                    all += k < (int)tiles ? v[q] : 0u;
+                    before += k < (int)tile ? v[q] : 0u;
                 }
             }
             part_all[threadIdx.x] = all;
@@ -366,8 +405,8 @@ __global__ __launch_bounds__(kBlock) void route_scatter_kernel(
 
     uint16_t* my_hist = wave_hist + w * U;
 #pragma unroll
-    for (int it = 0; it < kRouteItems; ++it) {
-        const int64_t i = base + (int64_t)w * kRouteWaveSpan + it * kWave + lane;
+    for (int it = 0; it < ITEMS; ++it) {
+        const int64_t i = base + (int64_t)w * (kWave * ITEMS) + it * kWave + lane;
         const bool valid = i < n;
         const uint64_t same = match_bits_n<NBITS>(dest[it], valid);
         const uint32_t before = popc_below(same);
@@ -391,8 +430,8 @@ __global__ __launch_bounds__(kBlock) void route_scatter_kernel(
     }
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < kRouteItems; ++it) {
-        const int64_t i = base + (int64_t)w * kRouteWaveSpan + it * kWave + lane;
+    for (int it = 0; it < ITEMS; ++it) {
+        const int64_t i = base + (int64_t)w * (kWave * ITEMS) + it * kWave + lane;
         if (i < n) {
             const uint32_t j = bucket_base[dest[it]] + my_hist[dest[it]] + rank[it];
             out_rows[j] = (int64_t)g[it];
@@ -415,6 +454,32 @@ __global__ __launch_bounds__(kBlock) void route_finalize_kernel(
     }
 }
 
+static int64_t route_tiles(int64_t n, int items) { return (n + kBlock * items - 1) / (kBlock * items); }
+
+static int route_items(int64_t n, int64_t U)
+{
+    for (int k = 0; k < 2 && U <= kRouteSmallBuckets; ++k) {
+        const int items = 2 << k;
+        const int64_t tiles = route_tiles(n, items);
+        if (tiles <= kRouteSmallTiles && tiles * (U + 3) <= kRouteSmallCounts[k]) return items;
+    }
+    return kRouteItems;
+}
+
+// Room for the tile counts, never less than a smaller batch asks for: a workspace sized for a caller's largest batch
+// serves the smaller ones.
+static int64_t route_counts(int64_t n, int64_t U)
+{
+    int64_t counts = route_tiles(n, kRouteItems) * (U + 3);
+    for (int k = 0; k < 2 && U <= kRouteSmallBuckets; ++k) {
+        const int64_t tiles = route_tiles(n, 2 << k);
+        int64_t small = (tiles < kRouteSmallTiles ? tiles : kRouteSmallTiles) * (U + 3);
+        if (small > kRouteSmallCounts[k]) small = kRouteSmallCounts[k];
+        if (counts < small) counts = small;
+    }
+    return counts;
+}
+
 // All three entry points: host checks, workspace carving, and the launches (remap, scan unless the counts are few, scatter).
 static fs_status route_run(
     const int64_t* ids, const int64_t* offsets, int32_t T, int32_t B,
@@ -429,10 +494,11 @@ static fs_status route_run(
     if (n < 0 || n >= (1LL << 31) || T < 1 || B < 1 || (int64_t)T * B >= (1LL << 31)) return FS_ERR_SIZE;
     if (U < 1 || U > FS_MAX_BUCKETS || W < 1 || U % W != 0 || self < 0 || self >= U) return FS_ERR_CONFIG;
 
-    const int64_t tiles = (n + kRouteTile - 1) / kRouteTile;
+    const int items = route_items(n, U);
+    const int64_t tiles = route_tiles(n, items);
     Carver ws(workspace);
     uint32_t* totals = ws.take<uint32_t>((size_t)U + 3);
-    uint32_t* tile_hist = ws.take<uint32_t>(((size_t)U + 3) * (size_t)tiles);
+    uint32_t* tile_hist = ws.take<uint32_t>((size_t)route_counts(n, U));
     uint32_t* g_tmp = ws.take<uint32_t>((size_t)n);
     uint16_t* dest_tmp = ws.take<uint16_t>((size_t)n);
     int32_t* slot_tmp = with_slots ? ws.take<int32_t>((size_t)n) : nullptr;
@@ -453,35 +519,41 @@ static fs_status route_run(
         return FS_OK;
     }
     {
-        const bool sum = tiles * ((int64_t)U + 3) <= kRouteSumMax;
-#define FS_REMAP(LEAD)                                                                                             \
-    FS_LAUNCH_SMEM("route_remap", route_remap_kernel<LEAD>, dim3((unsigned)tiles), dim3(kBlock), (size_t)U * sizeof(uint32_t), s, \
+        const bool sum = items < kRouteItems || tiles * ((int64_t)U + 3) <= kRouteSumMax;
+#define FS_REMAP(LEAD, ITEMS)                                                                                      \
+    FS_LAUNCH_SMEM("route_remap", (route_remap_kernel<LEAD, ITEMS>), dim3((unsigned)tiles), dim3(kBlock), (size_t)U * sizeof(uint32_t), s, \
                    ids, offsets, (int)T, (int64_t)B, row_base, placement, n, (int)U, (int)W, (int)self,             \
                    dest_tmp, g_tmp, slot_tmp, tile_hist, tiles, sum ? 1 : 0, dev_status)
-        if (tiles > kRouteLeadTiles && U > 1) FS_REMAP(true);
-        else FS_REMAP(false);
+        if (items == 2) FS_REMAP(false, 2);
+        else if (items == 4) FS_REMAP(false, 4);
+        else if (tiles > kRouteLeadTiles && U > 1) FS_REMAP(true, kRouteItems);
+        else FS_REMAP(false, kRouteItems);
 #undef FS_REMAP
         if (!sum)
             FS_LAUNCH("route_scan", route_scan_kernel, dim3((unsigned)U + 3), dim3(kRouteScanBlock), s, tile_hist, tiles, totals);
         const unsigned scatter_grid = (unsigned)(sum ? tiles : xcd_striped_grid(tiles, kRouteStripe));
         const size_t scatter_lds = (size_t)U * sizeof(uint32_t) + (size_t)kWavesPerBlock * U * sizeof(uint16_t);
+#define FS_SCATTER_AS(NB, SUM, ITEMS)                                                                              \
+    FS_LAUNCH_SMEM("route_scatter", (route_scatter_kernel<NB, SUM, ITEMS>), dim3(scatter_grid), dim3(kBlock), scatter_lds, s, \
+                   dest_tmp, g_tmp, n, (int)U, tile_hist, tiles, totals, out_rows, out_pos, bucket_offsets,        \
+                   tier_counts, (const int32_t*)slot_tmp, out_slots)
 #define FS_SCATTER(NB)                                                                                             \
-    if (sum)                                                                                                       \
-        FS_LAUNCH_SMEM("route_scatter", (route_scatter_kernel<NB, true>), dim3(scatter_grid), dim3(kBlock), scatter_lds, s, \
-                       dest_tmp, g_tmp, n, (int)U, tile_hist, tiles, totals, out_rows, out_pos, bucket_offsets,    \
-                       tier_counts, (const int32_t*)slot_tmp, out_slots);                                          \
-    else                                                                                                           \
-        FS_LAUNCH_SMEM("route_scatter", (route_scatter_kernel<NB, false>), dim3(scatter_grid), dim3(kBlock), scatter_lds, s, \
-                       dest_tmp, g_tmp, n, (int)U, tile_hist, tiles, totals, out_rows, out_pos, bucket_offsets,    \
-                       tier_counts, (const int32_t*)slot_tmp, out_slots)
+    if (sum) FS_SCATTER_AS(NB, true, kRouteItems);                                                                 \
+    else FS_SCATTER_AS(NB, false, kRouteItems)
+#define FS_SCATTER_SMALL(NB)                                                                                       \
+    if (items == 2) FS_SCATTER_AS(NB, true, 2);                                                                    \
+    else if (items == 4) FS_SCATTER_AS(NB, true, 4);                                                               \
+    else FS_SCATTER(NB)
         switch (dest_bits) {                            // U <= FS_MAX_BUCKETS = 2^12
-            case 1: FS_SCATTER(1); break;  case 2: FS_SCATTER(2); break;  case 3: FS_SCATTER(3); break;
-            case 4: FS_SCATTER(4); break;  case 5: FS_SCATTER(5); break;  case 6: FS_SCATTER(6); break;
-            case 7: FS_SCATTER(7); break;  case 8: FS_SCATTER(8); break;  case 9: FS_SCATTER(9); break;
+            case 1: FS_SCATTER_SMALL(1); break;  case 2: FS_SCATTER_SMALL(2); break;  case 3: FS_SCATTER_SMALL(3); break;
+            case 4: FS_SCATTER_SMALL(4); break;  case 5: FS_SCATTER_SMALL(5); break;  case 6: FS_SCATTER_SMALL(6); break;
+            case 7: FS_SCATTER_SMALL(7); break;  case 8: FS_SCATTER(8); break;  case 9: FS_SCATTER(9); break;
             case 10: FS_SCATTER(10); break;  case 11: FS_SCATTER(11); break;
             default: FS_SCATTER(12); break;
         }
+#undef FS_SCATTER_SMALL
 #undef FS_SCATTER
+#undef FS_SCATTER_AS
     }
     return FS_OK;
 }

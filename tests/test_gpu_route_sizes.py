@@ -45,6 +45,49 @@ def test_route_shapes(G, T, B, n, U, W):
     assert np.array_equal(rows.cpu().numpy(), orows) and np.array_equal(pos.cpu().numpy(), opos)
 
 
+@pytest.mark.parametrize("T,B,n,U,W,slots", [
+    (1, 1, 512, 2, 1, True), (2, 3, 513, 3, 3, False), (64, 2, 164 * 512, 64, 8, True), (5, 9, 164 * 512 + 1, 64, 8, False),
+    (65, 3, 84 * 512 - 1, 128, 8, False), (4, 2, 84 * 512 + 511, 128, 8, True),          # 83 x 131 = 10873 counts of 512 lookups
+    (3, 5, 512 * 512, 8, 8, False), (3, 5, 512 * 512 + 1, 8, 8, True), (2, 7, 512 * 1024, 8, 2, False), (1, 8, 512 * 1024 + 1, 8, 2, False),
+    (4, 4, 500 * 1024, 64, 8, True), (4, 4, 500 * 1024 + 1, 64, 8, False),               # 500 x 67 = 33500 counts of 1024 lookups
+    (2, 2, 255 * 1024, 128, 64, False), (2, 2, 255 * 1024 + 1, 128, 64, False), (64, 1, 3000, 129, 129, False),
+])
+def test_small_tiles(G, T, B, n, U, W, slots):
+    """Tiles of 512 lookups up to 11000 counts, of 1024 up to 33500, at most 512 of them and up to 128 buckets; empty tables
+    among 64 and more; with and without the replica slots."""
+    import paper_2301_02959_amd as fs
+    rng = np.random.default_rng(T + n + U)
+    cuts = np.sort(rng.choice(rng.integers(0, n + 1, 5), T * B - 1)) if T * B > 1 else np.zeros(0, np.int64)   # most segments empty
+    offsets = np.concatenate([[0], cuts, [n]]).astype(np.int64)
+    E = 41
+    ids = rng.integers(0, E, n).astype(np.int64)
+    row_base = (np.arange(T + 1) * E).astype(np.int64)
+    placement = random_placement(rng, T * E, U, W)
+    self_ = int(rng.integers(0, U))
+    args = (G.to_dev(ids), G.to_dev(offsets), T, B, G.to_dev(row_base), G.placement_dev(placement))
+    rc, st, bo, rows, pos, tc = G.hip_route(*args, U, W, self_, n=n)
+    orc, ost, obo, orows, opos, otc = oracle.route_bucketize(ids, offsets, T, B, row_base, placement, U, W, self_, n=n)
+    assert (rc, st) == (orc, ost) == (0, 0)
+    assert np.array_equal(bo.cpu().numpy(), obo) and np.array_equal(tc.cpu().numpy(), otc)
+    assert np.array_equal(rows.cpu().numpy(), orows) and np.array_equal(pos.cpu().numpy(), opos)
+    if slots:
+        bo2, rows2, pos2 = torch.zeros_like(bo), torch.zeros_like(rows), torch.zeros_like(pos)
+        out = torch.full((n,), -7, dtype=torch.int32, device=G.DEV)
+        fs.fs_route_bucketize_slots(*args, n, U, W, self_, bo2, rows2, pos2, out)
+        assert torch.equal(bo2, bo) and torch.equal(rows2, rows) and torch.equal(pos2, pos)
+        entries = placement[orows]
+        owner = (entries & 0x3FFFFFFF).astype(np.int64)
+        assert np.array_equal(out.cpu().numpy(), np.where((entries >> 30 == 0) & (owner != 0x3FFFFFFF), owner, -1))
+
+
+@pytest.mark.parametrize("U", [1, 8, 24, 64, 128, 129, 4096])
+def test_a_workspace_for_more_lookups_serves_fewer(U):
+    import paper_2301_02959_amd as fs
+    edges = [k * step + d for step in (512, 1024, 2048) for k in (1, 64, 83, 84, 164, 165, 255, 256, 500, 501, 512) for d in (-1, 0, 1)]
+    sizes = [fs.route_workspace_bytes(2, 3, n, U, 1, 0) for n in sorted(edges)]
+    assert sizes == sorted(sizes)
+
+
 @pytest.mark.parametrize("n", [256 * TILE, 256 * TILE + 1, 256 * TILE + 777])
 @pytest.mark.parametrize("U,self_", [(1, 0), (2, 0), (2, 1), (3, 1), (64, 5)])
 @pytest.mark.parametrize("owners", ["one", "tables", "hot"])
