@@ -1,4 +1,4 @@
-"""Builds libflexshard_hip.so for gfx950 with hipcc (cross-compiles without a GPU)."""
+"""Builds libflexshard_hip.so for gfx950 with hipcc (cross-compiles without a GPU), and the binding's native helper."""
 from __future__ import annotations
 
 import glob
@@ -10,6 +10,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libflexshard_hip.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -24,11 +25,22 @@ def sources():
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
         return True
     t = os.path.getmtime(LIB)
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
+    deps = sources() + glob.glob(os.path.join(CSRC, "*.[hc]*")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
     return any(os.path.getmtime(p) > t for p in deps)
+
+
+def marshal_command():
+    """The binding's native helper (no device code): against the installed torch's own headers and libraries."""
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", os.path.join(CSRC, "marshal.cpp"),
+            "-I", os.path.join(base, "include"), "-I", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+            "-I", sysconfig.get_paths()["include"], f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", MARSHAL]
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
@@ -47,6 +59,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    procs.append(("marshal.cpp", subprocess.Popen(marshal_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, p in procs:
         out, _ = p.communicate()
@@ -55,9 +68,9 @@ def build(force: bool = True, verbose: bool = False) -> str:
             print(out, file=sys.stderr)
         if p.returncode != 0:
             failed = True
-            print(f"hipcc failed on {src}", file=sys.stderr)
+            print(f"the compiler failed on {src}", file=sys.stderr)
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("a source did not compile")
     subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], check=True)
     return LIB
 

@@ -61,3 +61,63 @@ def test_binding_refuses_host_tensors_and_wrong_element_types():
     w = torch.zeros(4, 8)
     with pytest.raises(TypeError):
         fs.fs_seq_gather_fwd(w, torch.zeros(1, dtype=torch.int64), torch.zeros(1, dtype=torch.int32), 0, 1, w.clone())
+
+
+def test_pointers_in_native_code_and_in_python():
+    """The binding's native helper is built and hands everything that is no plain CUDA tensor to the Python check: host
+    tensors, subclasses, other objects raise as they do there."""
+    import torch
+    import paper_2301_02959_amd as fs
+    from paper_2301_02959_amd import _marshal
+    assert fs._ptr is _marshal.device_pointer
+
+    class Sub(torch.Tensor):
+        pass
+
+    assert fs._ptr(None) is None and fs._ptr(None, (torch.int64,)) is None
+    for bad in (torch.zeros(3), torch.zeros(3).as_subclass(Sub), torch.zeros(2, 2).t(), "text", 7):
+        for dtypes in (None, (torch.float32,), (torch.int64,), [torch.float32]):
+            seen = []
+            for check in (fs._ptr, fs._ptr_checked):
+                with pytest.raises((TypeError, AttributeError)) as e:
+                    check(bad, dtypes)
+                seen.append((type(e.value), str(e.value)))
+            assert seen[0] == seen[1]
+    with pytest.raises(TypeError):
+        fs._ptr()
+
+
+@pytest.mark.gpu
+def test_native_pointers_on_the_gpu():
+    import torch
+    import paper_2301_02959_amd as fs
+    t = torch.zeros(8, 4, device="cuda")
+
+    class Sub(torch.Tensor):
+        pass
+
+    for good in (t, t[3:], t.view(-1)[5:], torch.nn.Parameter(t), t.as_subclass(Sub), t[8:], t.int(), torch.zeros(0, device="cuda")):
+        for dtypes in (None, (good.dtype,), (torch.uint8, good.dtype)):
+            assert fs._ptr(good, dtypes) == fs._ptr_checked(good, dtypes) == good.data_ptr()
+    for bad, dtypes in ((t.t(), None), (t[:, 1:], None), (t, (torch.int32,)), (t, ()), (t.cpu(), None)):
+        seen = []
+        for check in (fs._ptr, fs._ptr_checked):
+            with pytest.raises(TypeError) as e:
+                check(bad, dtypes)
+            seen.append(str(e.value))
+        assert seen[0] == seen[1]
+    errors = []
+    for check in (fs._ptr, fs._ptr_checked):                # no storage to point to: the same answer from both
+
+        def call(x):
+            check(x)
+            return x
+
+        with pytest.raises(Exception) as e:
+            torch.func.vmap(call)(t)
+        errors.append(type(e.value))
+    assert errors[0] is errors[1]
+    assert fs._stream() == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert fs._stream() == side.cuda_stream
