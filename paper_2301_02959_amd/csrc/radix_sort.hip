@@ -96,7 +96,9 @@ __host__ __device__ __forceinline__ int64_t sort_group_tiles(int64_t used) { ret
 template <typename Reader, int NBITS, int BLOCK, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void sort_count_kernel(
     Reader in, int64_t m_max, const int64_t* __restrict__ m_dev, const uint32_t* __restrict__ varying, int shift,
-    uint32_t* __restrict__ tile_hist /* [tiles][bins], if a group has several */, uint32_t* __restrict__ group_sums /* [groups][bins] */)
+    uint32_t* __restrict__ tile_hist /* [tiles][bins], if a group has several */,
+    uint32_t* __restrict__ group_sums /* [groups][bins], rows of kSortMaxBins without a scan */,
+    uint32_t* __restrict__ later_sums /* or null: the later passes' tables, [passes][tiles][kSortMaxBins] */, int later, int64_t later_tiles)
 {
     constexpr int bins = 1 << NBITS;
     constexpr int kTile = BLOCK * ITEMS;
@@ -157,7 +159,13 @@ __global__ __launch_bounds__(BLOCK) void sort_count_kernel(
         }
         __syncthreads();
     }
-    for (int b = threadIdx.x; b < bins; b += BLOCK) group_sums[(int64_t)blockIdx.x * bins + b] = copies_sum(b);
+    const int64_t stride = later_sums != nullptr ? kSortMaxBins : bins;
+    for (int b = threadIdx.x; b < bins; b += BLOCK) group_sums[(int64_t)blockIdx.x * stride + b] = copies_sum(b);
+    // the later passes' counts of this tile, which the scatters add to, start at zero
+    for (int k = 0; k < later; ++k) {
+        u32x4* row = reinterpret_cast<u32x4*>(later_sums + ((int64_t)k * later_tiles + blockIdx.x) * kSortMaxBins);
+        for (int q = threadIdx.x; q < kSortMaxBins / 4; q += BLOCK) row[q] = u32x4{0u, 0u, 0u, 0u};
+    }
 }
 
 // group_sums[group][digit] -> exclusive prefix over the groups, in place, and totals[digit].  A block takes 32 digits, its
@@ -221,13 +229,15 @@ __global__ __launch_bounds__(kScanBins * kScanSlices) void sort_scan_kernel(
 
 // SUM: few groups (of one tile each); no scan has run, group_sums holds plain counts, and every block adds up the
 // digits' totals and what stands before its tile itself, one vector load per group and thread, 16 in flight, while its
-// pairs are on the way.
+// pairs are on the way.  It also counts the next pass's digits, by the tile that its pairs go to, with an add to memory for
+// every stretch of neighbours with one counter: only the first pass has a count launch.
 template <typename Reader, int NBITS, int BLOCK, int ITEMS, int STRIPE, bool SUM>
 __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(
     Reader in, int64_t m_max, const int64_t* __restrict__ m_dev, const uint32_t* __restrict__ varying, int shift,
     const uint32_t* __restrict__ tile_hist, const uint32_t* __restrict__ group_sums /* scanned, unless SUM */,
     const uint32_t* __restrict__ totals, SortPair* __restrict__ pairs_out /* or null */,
-    uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int32_t* status)
+    uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
+    uint32_t* __restrict__ next_sums /* SUM, or null */, int next_bits, int32_t* status)
 {
     constexpr int bins = 1 << NBITS;
     constexpr int kTile = BLOCK * ITEMS;
@@ -281,7 +291,7 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(
             for (int t0 = 0; t0 < (int)used; t0 += kAhead) {
                 Bins x[kAhead];
 #pragma unroll
-                for (int a = 0; a < kAhead; ++a) x[a] = mine[(t0 + a < (int)used ? t0 + a : (int)used - 1) * (bins / kBinsPerThread)];
+                for (int a = 0; a < kAhead; ++a) x[a] = mine[(t0 + a < (int)used ? t0 + a : (int)used - 1) * (kSortMaxBins / kBinsPerThread)];
 #pragma unroll
                 for (int a = 0; a < kAhead; ++a) {
 #pragma unroll
@@ -362,6 +372,25 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(
             }
         }
         __syncthreads();
+        if constexpr (SUM) {
+            if (next_sums != nullptr && !sort_pass_idle(varying, shift + NBITS)) {          // block-uniform
+                const uint32_t next_mask = (1u << next_bits) - 1u;
+#pragma unroll
+                for (int it = 0; it < ITEMS; ++it) {
+                    const uint32_t at = it * BLOCK + threadIdx.x;
+                    const uint32_t k = s_pair[at < left ? at : left - 1u][0];
+                    const uint32_t j = out_base[(k >> shift) & mask] + at;
+                    const uint32_t counter = (j / kTile) * (uint32_t)kSortMaxBins + ((k >> (shift + NBITS)) & next_mask);
+                    // a popular row's pairs stand side by side: one add for a stretch of lanes with one counter
+                    const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)counter, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
+                    const bool starts = at < left && counter != below;               // lane 0: -1 is no counter
+                    const uint64_t later_starts = ballot(starts) >> lane >> 1;
+                    const uint32_t valid_lanes = (uint32_t)__popcll(ballot(at < left));
+                    if (starts)
+                        atomicAdd(next_sums + counter, later_starts != 0 ? (uint32_t)__builtin_ctzll(later_starts) + 1u : valid_lanes - (uint32_t)lane);
+                }
+            }
+        }
         if (pairs_out != nullptr) {                              // block-uniform
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
@@ -405,6 +434,8 @@ constexpr int kSmallBlock = 256, kSmallItems = 4;
 constexpr int kSortStripe = 16;              // tiles per XCD stripe in the scatter
 constexpr int64_t kSortSmallTiles = 256;
 constexpr int64_t kSortSumTiles = 64;
+constexpr int kSortMaxPasses = 4;
+static_assert(kSortMaxPasses * 2 * kSortSumTiles >= kSortSmallTiles);
 // Blocks of the scatter at most; they walk the tiles with a grid stride.  Where the count is on the device it is usually a
 // few per cent of what the buffers hold, and a pass may be idle: fewer blocks, four rounds of the three that a CU takes.
 constexpr int64_t kSortScatterGrid = 8192;
@@ -445,7 +476,8 @@ static SortTables take_tables(Carver& c, int64_t m_max)
     // never less than a smaller m_max asks for: a workspace sized for a caller's largest batch serves the smaller ones
     const int64_t small = (m_max + kSmallBlock * kSmallItems - 1) / (kSmallBlock * kSmallItems);
     int64_t groups = tiles < kSortMaxGroups ? tiles : kSortMaxGroups;
-    if (groups < kSortSmallTiles) groups = small < kSortSmallTiles ? small : kSortSmallTiles;
+    const int64_t small_rows = kSortMaxPasses * (small < 2 * kSortSumTiles ? small : 2 * kSortSumTiles);     // a table for every pass
+    if (groups < small_rows) groups = small_rows;
     SortTables t;
     t.totals = c.take<uint32_t>((size_t)kSortMaxBins);
     t.group_sums = c.take<uint32_t>((size_t)kSortMaxBins * (size_t)groups);
@@ -470,6 +502,8 @@ struct SortPass {
     SortPair* pairs_out;
     uint32_t* keys_out;
     uint32_t* vals_out;
+    int number, passes;                      // this pass's number
+    int next_bits;                           // the next one's digit, if there is one
     int32_t* status;
     hipStream_t stream;
 };
@@ -479,16 +513,21 @@ static fs_status launch_sort_pass(const Reader& in, const SortPass& p)
 {
     constexpr int bins = 1 << NBITS;
     const int64_t groups = p.shape.tiles < kSortMaxGroups ? p.shape.tiles : kSortMaxGroups;
+    // without a scan every pass has a table of its own
+    const int64_t table = p.shape.tiles * kSortMaxBins;
+    uint32_t* sums = p.shape.sum ? p.t.group_sums + p.number * table : p.t.group_sums;
+    uint32_t* next_sums = p.shape.sum && p.number + 1 < p.passes ? sums + table : nullptr;
 #define FS_COUNT(BLOCK, ITEMS)                                                                                        \
     FS_LAUNCH("sort_count", (sort_count_kernel<Reader, NBITS, BLOCK, ITEMS>), dim3((unsigned)groups), dim3(BLOCK), p.stream, \
-              in, p.m_max, p.m_dev, p.varying, p.shift, p.t.tile_hist, p.t.group_sums)
+              in, p.m_max, p.m_dev, p.varying, p.shift, p.t.tile_hist, sums, p.shape.sum ? sums + table : (uint32_t*)nullptr, \
+              p.shape.sum ? p.passes - 1 : 0, p.shape.tiles)
 #define FS_SCATTER(BLOCK, ITEMS, STRIPE, SUM, GRID)                                                                   \
     FS_LAUNCH("sort_scatter", (sort_scatter_kernel<Reader, NBITS, BLOCK, ITEMS, STRIPE, SUM>), dim3((unsigned)(GRID)), dim3(BLOCK), \
-              p.stream, in, p.m_max, p.m_dev, p.varying, p.shift, p.t.tile_hist, p.t.group_sums, p.t.totals, p.pairs_out, \
-              p.keys_out, p.vals_out, p.status)
+              p.stream, in, p.m_max, p.m_dev, p.varying, p.shift, p.t.tile_hist, sums, p.t.totals, p.pairs_out, \
+              p.keys_out, p.vals_out, next_sums, p.next_bits, p.status)
     constexpr bool kMaySmall = !std::is_same<Reader, SplitReader>::value;
     if constexpr (kMaySmall) {
-        if (p.shape.small) FS_COUNT(kSmallBlock, kSmallItems);
+        if (p.shape.small && (p.number == 0 || !p.shape.sum)) FS_COUNT(kSmallBlock, kSmallItems);
     }
     if (!p.shape.small) FS_COUNT(kLargeBlock, kLargeItems);
     if (!p.shape.sum)
@@ -523,12 +562,18 @@ fs_status radix_sort(const SortJob& job)
     const SortPair* src = job.pairs_a;
     SortPair* dst = job.rows != nullptr ? job.pairs_a : job.pairs_b;
     const bool split = job.m_dev == nullptr && job.m_max >= kSortSplitFrom;
-    for (int k = 0; k < passes; ++k) {
-        // spread the bits evenly over the passes: 27 bits -> 9, 9, 9; where passes can turn out idle the digits are fixed:
-        // 32 bits -> 10, 10, 6, 6 or 8, 8, 8, 8
-        const int left = key_bits - p.shift;
+    // spread the bits evenly over the passes: 27 bits -> 9, 9, 9; where passes can turn out idle the digits are fixed:
+    // 32 bits -> 10, 10, 6, 6 or 8, 8, 8, 8
+    auto digit = [&](int k, int shift) {
+        const int left = key_bits - shift;
         const int even = (left + (passes - k) - 1) / (passes - k);
-        const int nbits = job.varying != nullptr && k < 2 ? job.first_bits : even;
+        return job.varying != nullptr && k < 2 ? job.first_bits : even;
+    };
+    p.passes = passes;
+    for (int k = 0; k < passes; ++k) {
+        const int nbits = digit(k, p.shift);
+        p.number = k;
+        p.next_bits = k + 1 < passes ? digit(k + 1, p.shift + nbits) : 0;
         const bool apart = k == passes - 1 && job.keys_out != nullptr;
         p.pairs_out = apart || split ? nullptr : dst;
         p.keys_out = apart ? job.keys_out : reinterpret_cast<uint32_t*>(dst);
