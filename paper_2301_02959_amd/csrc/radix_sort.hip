@@ -19,6 +19,7 @@
 namespace fs {
 
 constexpr int kSortMaxBins = 1 << kSortMaxDigitBits;
+constexpr int kLargeBlock = 512, kLargeItems = 8;
 
 __device__ __forceinline__ int64_t sort_count_of(const int64_t* m_dev, int64_t m_max)
 {
@@ -82,6 +83,23 @@ __device__ __forceinline__ bool sort_pass_idle(const uint32_t* varying, int shif
     return varying != nullptr && shift > 0 && (*varying >> shift) == 0;
 }
 
+// What the kernels of a pass are given, as one argument: the runtime spends 0.5 us more on a launch of 16.
+struct SortArgs {
+    int64_t m_max;
+    const int64_t* m_dev;
+    const uint32_t* varying;
+    uint32_t* tile_hist;             // [tiles][bins], if a group has several
+    uint32_t* group_sums;            // [groups][bins], rows of kSortMaxBins without a scan; the scan's prefixes after it
+    uint32_t* later_sums;            // without a scan: the later passes' tables, [passes][tiles][kSortMaxBins]; else null
+    int64_t later_tiles;
+    const uint32_t* totals;
+    SortPair* pairs_out;             // or null
+    uint32_t* keys_out;
+    uint32_t* vals_out;
+    int32_t* status;
+    int shift, later, next_bits;     // later: passes after this one; the next one's digit
+};
+
 // The tiles are dealt to at most this many groups, consecutive ones to a group.
 constexpr int kSortMaxGroups = 1024;
 
@@ -94,19 +112,16 @@ __host__ __device__ __forceinline__ int64_t sort_group_tiles(int64_t used) { ret
 // per distinct digit by ballot matching 28 whatever they are: with these guards memory is what bounds it (5 TB/s).  Small
 // tiles: the adds alone, the rest costs more than it saves.
 template <typename Reader, int NBITS, int BLOCK, int ITEMS>
-__global__ __launch_bounds__(BLOCK) void sort_count_kernel(
-    Reader in, int64_t m_max, const int64_t* __restrict__ m_dev, const uint32_t* __restrict__ varying, int shift,
-    uint32_t* __restrict__ tile_hist /* [tiles][bins], if a group has several */,
-    uint32_t* __restrict__ group_sums /* [groups][bins], rows of kSortMaxBins without a scan */,
-    uint32_t* __restrict__ later_sums /* or null: the later passes' tables, [passes][tiles][kSortMaxBins] */, int later, int64_t later_tiles)
+__global__ __launch_bounds__(BLOCK) void sort_count_kernel(const Reader in, const SortArgs a)
 {
+    const int shift = a.shift;
     constexpr int bins = 1 << NBITS;
     constexpr int kTile = BLOCK * ITEMS;
     constexpr int kCopies = ITEMS > 4 ? 4 : 1;         // small tiles: clearing and adding up four cost more than they save
     typedef uint32_t Copies __attribute__((ext_vector_type(kCopies)));
     __shared__ __attribute__((aligned(16))) uint32_t hist[bins * kCopies];
-    if (sort_pass_idle(varying, shift)) return;
-    const int64_t m = sort_count_of(m_dev, m_max);
+    if (sort_pass_idle(a.varying, shift)) return;
+    const int64_t m = sort_count_of(a.m_dev, a.m_max);
     const int64_t used = (m + kTile - 1) / kTile;      // tiles that hold pairs (m may live on the device)
     const int64_t per = sort_group_tiles(used);
     const int64_t t0 = (int64_t)blockIdx.x * per;
@@ -141,7 +156,7 @@ __global__ __launch_bounds__(BLOCK) void sort_count_kernel(
         for (int it = 0; it < ITEMS; ++it) digit[it] = (key[it] >> shift) & mask;
         if (t + 1 < t1) load(t + 1);
         if (per > 1) {                                           // block-uniform
-            for (int b = threadIdx.x; b < bins; b += BLOCK) tile_hist[t * bins + b] = copies_sum(b);
+            for (int b = threadIdx.x; b < bins; b += BLOCK) a.tile_hist[t * bins + b] = copies_sum(b);
             __syncthreads();
         }
 #pragma unroll
@@ -159,11 +174,12 @@ __global__ __launch_bounds__(BLOCK) void sort_count_kernel(
         }
         __syncthreads();
     }
-    const int64_t stride = later_sums != nullptr ? kSortMaxBins : bins;
-    for (int b = threadIdx.x; b < bins; b += BLOCK) group_sums[(int64_t)blockIdx.x * stride + b] = copies_sum(b);
+    const int64_t stride = a.later_sums != nullptr ? kSortMaxBins : bins;
+    for (int b = threadIdx.x; b < bins; b += BLOCK) a.group_sums[(int64_t)blockIdx.x * stride + b] = copies_sum(b);
+    if (a.later_sums == nullptr) return;
     // the later passes' counts of this tile, which the scatters add to, start at zero
-    for (int k = 0; k < later; ++k) {
-        u32x4* row = reinterpret_cast<u32x4*>(later_sums + ((int64_t)k * later_tiles + blockIdx.x) * kSortMaxBins);
+    for (int k = 0; k < a.later; ++k) {
+        u32x4* row = reinterpret_cast<u32x4*>(a.later_sums + ((int64_t)k * a.later_tiles + blockIdx.x) * kSortMaxBins);
         for (int q = threadIdx.x; q < kSortMaxBins / 4; q += BLOCK) row[q] = u32x4{0u, 0u, 0u, 0u};
     }
 }
@@ -232,13 +248,10 @@ __global__ __launch_bounds__(kScanBins * kScanSlices) void sort_scan_kernel(
 // pairs are on the way.  It also counts the next pass's digits, by the tile that its pairs go to, with an add to memory for
 // every stretch of neighbours with one counter: only the first pass has a count launch.
 template <typename Reader, int NBITS, int BLOCK, int ITEMS, int STRIPE, bool SUM>
-__global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(
-    Reader in, int64_t m_max, const int64_t* __restrict__ m_dev, const uint32_t* __restrict__ varying, int shift,
-    const uint32_t* __restrict__ tile_hist, const uint32_t* __restrict__ group_sums /* scanned, unless SUM */,
-    const uint32_t* __restrict__ totals, SortPair* __restrict__ pairs_out /* or null */,
-    uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
-    uint32_t* __restrict__ next_sums /* SUM, or null */, int next_bits, int32_t* status)
+__global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(const Reader in, const SortArgs a)
 {
+    const int shift = a.shift;
+    const uint32_t* const group_sums = a.group_sums;             // scanned, unless SUM
     constexpr int bins = 1 << NBITS;
     constexpr int kTile = BLOCK * ITEMS;
     constexpr int kWaves = BLOCK / kWave;
@@ -249,8 +262,8 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(
     __shared__ uint16_t wave_hist[kWaves][bins];
     __shared__ SortPair s_pair[kTile];
     __shared__ uint32_t wave_sums[16];
-    if (sort_pass_idle(varying, shift)) return;
-    const int64_t m = sort_count_of(m_dev, m_max);
+    if (sort_pass_idle(a.varying, shift)) return;
+    const int64_t m = sort_count_of(a.m_dev, a.m_max);
     const int64_t used = (m + kTile - 1) / kTile;
     const int64_t per_group = sort_group_tiles(used);
     constexpr uint32_t mask = (uint32_t)bins - 1u;
@@ -291,13 +304,13 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(
             for (int t0 = 0; t0 < (int)used; t0 += kAhead) {
                 Bins x[kAhead];
 #pragma unroll
-                for (int a = 0; a < kAhead; ++a) x[a] = mine[(t0 + a < (int)used ? t0 + a : (int)used - 1) * (kSortMaxBins / kBinsPerThread)];
+                for (int e = 0; e < kAhead; ++e) x[e] = mine[(t0 + e < (int)used ? t0 + e : (int)used - 1) * (kSortMaxBins / kBinsPerThread)];
 #pragma unroll
-                for (int a = 0; a < kAhead; ++a) {
+                for (int e = 0; e < kAhead; ++e) {
 #pragma unroll
                     for (int q = 0; q < kBinsPerThread; ++q) {
-                        tot[q] += t0 + a < (int)used ? x[a][q] : 0u;
-                        before_tile[q] += t0 + a < (int)tile ? x[a][q] : 0u;
+                        tot[q] += t0 + e < (int)used ? x[e][q] : 0u;
+                        before_tile[q] += t0 + e < (int)tile ? x[e][q] : 0u;
                     }
                 }
             }
@@ -320,9 +333,9 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(
         }
         if constexpr (!SUM) {
             const uint32_t group = (uint32_t)tile / (uint32_t)per_group;        // tiles < 2^31
-            const Bins t = reinterpret_cast<const Bins*>(totals)[my_bins];
+            const Bins t = reinterpret_cast<const Bins*>(a.totals)[my_bins];
             Bins g = reinterpret_cast<const Bins*>(group_sums + (int64_t)group * bins)[my_bins];
-            if (per_group > 1) g += reinterpret_cast<const Bins*>(tile_hist + tile * bins)[my_bins];
+            if (per_group > 1) g += reinterpret_cast<const Bins*>(a.tile_hist + tile * bins)[my_bins];
 #pragma unroll
             for (int q = 0; q < kBinsPerThread; ++q) { tot[q] = t[q]; before_tile[q] = g[q]; }
         }
@@ -373,8 +386,9 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(
         }
         __syncthreads();
         if constexpr (SUM) {
-            if (next_sums != nullptr && !sort_pass_idle(varying, shift + NBITS)) {          // block-uniform
-                const uint32_t next_mask = (1u << next_bits) - 1u;
+            uint32_t* const next_sums = a.later != 0 ? a.later_sums : nullptr;
+            if (next_sums != nullptr && !sort_pass_idle(a.varying, shift + NBITS)) {          // block-uniform
+                const uint32_t next_mask = (1u << a.next_bits) - 1u;
 #pragma unroll
                 for (int it = 0; it < ITEMS; ++it) {
                     const uint32_t at = it * BLOCK + threadIdx.x;
@@ -391,13 +405,13 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(
                 }
             }
         }
-        if (pairs_out != nullptr) {                              // block-uniform
+        if (a.pairs_out != nullptr) {                              // block-uniform
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
                 const uint32_t at = it * BLOCK + threadIdx.x;
                 if (at < left) {
                     const SortPair p = s_pair[at];
-                    pairs_out[out_base[(p[0] >> shift) & mask] + at] = p;
+                    a.pairs_out[out_base[(p[0] >> shift) & mask] + at] = p;
                 }
             }
         } else {
@@ -407,8 +421,8 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(
                 if (at < left) {
                     const SortPair p = s_pair[at];
                     const uint32_t j = out_base[(p[0] >> shift) & mask] + at;
-                    keys_out[j] = p[0];
-                    vals_out[j] = p[1];
+                    a.keys_out[j] = p[0];
+                    a.vals_out[j] = p[1];
                 }
             }
         }
@@ -416,12 +430,13 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(
     }
     if (ballot(faults != 0) != 0) {
         for (int off = 32; off > 0; off >>= 1) faults |= __shfl_down(faults, off);
-        if (lane == 0) report(status, faults);
+        if (lane == 0) report(a.status, faults);
     }
 }
 
-// Large sorts: 8 waves to a tile of 4096 pairs, 8 ranking rounds each, 24 waves to a CU.  What bounds them is the memory's
-// rate for a stream that reads and writes at once (a 4-bit scatter of 15.7 M pairs, nearly a copy, takes 49 us, this one
+// Large sorts: 8 waves to a tile of 4096 pairs, 8 ranking rounds each, two tiles to a CU by their registers (held to 80 of
+// them, three: the L2s then merge fewer of the runs' pieces, 15.7 M pairs 279 -> 289 us, 72 M uniform ones 1469 -> 1646).  What
+// bounds them is the memory's rate for a stream that reads and writes at once (a 4-bit scatter of 15.7 M pairs, nearly a copy, takes 49 us, this one
 // with 9 bits 59; 4 waves of 16 rounds 62 to 72, tiles of 8192 61, 16 waves 80).  Small ones, up to 256 tiles of 1024
 // pairs: a block's time is its chain of ranking rounds and of the memory's latency, and the smaller tiles have four
 // rounds.  Up to 64 of them (128 where the count is on the device: the plan's candidates, usually a few per cent of the
@@ -429,7 +444,6 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(
 // fs_sort_lookups as a whole against 4 waves of 16 rounds, keys and values apart, two scan launches and a count by
 // ballots, Zipf(1.1) over 80 M rows, us: 8192 pairs 30 -> 25, 65 k 52 -> 32, 262 k 51 -> 39, 1 M 84 -> 54, 4.2 M 145 -> 116,
 // 15.7 M 304 -> 278, 72 M 1406 -> 1310.
-constexpr int kLargeBlock = 512, kLargeItems = 8;
 constexpr int kSmallBlock = 256, kSmallItems = 4;
 constexpr int kSortStripe = 16;              // tiles per XCD stripe in the scatter
 constexpr int64_t kSortSmallTiles = 256;
@@ -515,16 +529,20 @@ static fs_status launch_sort_pass(const Reader& in, const SortPass& p)
     const int64_t groups = p.shape.tiles < kSortMaxGroups ? p.shape.tiles : kSortMaxGroups;
     // without a scan every pass has a table of its own
     const int64_t table = p.shape.tiles * kSortMaxBins;
-    uint32_t* sums = p.shape.sum ? p.t.group_sums + p.number * table : p.t.group_sums;
-    uint32_t* next_sums = p.shape.sum && p.number + 1 < p.passes ? sums + table : nullptr;
+    SortArgs a;
+    a.m_max = p.m_max; a.m_dev = p.m_dev; a.varying = p.varying;
+    a.tile_hist = p.t.tile_hist;
+    a.group_sums = p.shape.sum ? p.t.group_sums + p.number * table : p.t.group_sums;
+    a.later_sums = p.shape.sum ? a.group_sums + table : nullptr;
+    a.later_tiles = p.shape.tiles;
+    a.totals = p.t.totals;
+    a.pairs_out = p.pairs_out; a.keys_out = p.keys_out; a.vals_out = p.vals_out; a.status = p.status;
+    a.shift = p.shift; a.later = p.passes - 1 - p.number; a.next_bits = p.next_bits;
 #define FS_COUNT(BLOCK, ITEMS)                                                                                        \
-    FS_LAUNCH("sort_count", (sort_count_kernel<Reader, NBITS, BLOCK, ITEMS>), dim3((unsigned)groups), dim3(BLOCK), p.stream, \
-              in, p.m_max, p.m_dev, p.varying, p.shift, p.t.tile_hist, sums, p.shape.sum ? sums + table : (uint32_t*)nullptr, \
-              p.shape.sum ? p.passes - 1 : 0, p.shape.tiles)
+    FS_LAUNCH("sort_count", (sort_count_kernel<Reader, NBITS, BLOCK, ITEMS>), dim3((unsigned)groups), dim3(BLOCK), p.stream, in, a)
 #define FS_SCATTER(BLOCK, ITEMS, STRIPE, SUM, GRID)                                                                   \
     FS_LAUNCH("sort_scatter", (sort_scatter_kernel<Reader, NBITS, BLOCK, ITEMS, STRIPE, SUM>), dim3((unsigned)(GRID)), dim3(BLOCK), \
-              p.stream, in, p.m_max, p.m_dev, p.varying, p.shift, p.t.tile_hist, sums, p.t.totals, p.pairs_out, \
-              p.keys_out, p.vals_out, next_sums, p.next_bits, p.status)
+              p.stream, in, a)
     constexpr bool kMaySmall = !std::is_same<Reader, SplitReader>::value;
     if constexpr (kMaySmall) {
         if (p.shape.small && (p.number == 0 || !p.shape.sum)) FS_COUNT(kSmallBlock, kSmallItems);
