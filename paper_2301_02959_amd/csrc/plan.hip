@@ -54,17 +54,20 @@ __global__ __launch_bounds__(kBlock) void plan_check_offsets_kernel(
 }
 
 constexpr int kHistSlotBits = 14;
+// Spans of up to 2048 ids (half as many as the slots) take 2^12 entries: a quarter of the slots to clear and to look through
+// at the end.  8192 ids 7.3 -> 5.0 us (Zipf(1.3)), 7.6 -> 6.6 (Zipf(1.05)), 300 k 10.5 -> 8.4 and 14.6 -> 13.3.
+constexpr int kHistSmallSlotBits = 12;
 constexpr uint32_t kHistMul1 = 2654435761u, kHistMul1Inv = 0x0e8b2f51u;    // odd multipliers: bijections of 32-bit words,
 constexpr uint32_t kHistMul2 = 2246822519u, kHistMul2Inv = 0xb6c92f47u;    // undone by their inverses mod 2^32
 constexpr int kHistBlock = 1024;          // 16 waves per span: a span per 256 threads leaves the chip idle
 
-// One block counts the ids of [blockIdx.x * span, + span) into an LDS table of 2^14 entries of 32 bits
+// One block counts the ids of [blockIdx.x * span, + span) into an LDS table of 2^14 (short spans: 2^12) entries of 32 bits
 // (64 KB: two blocks per CU, so that one block's flush, a stretch of nothing but global adds, runs beside
 // the other's counting).  A row takes the first of its two slots (two hashes of the row) that is free or
 // already its own; a row that finds both taken by other rows is added to the global counter at once.  An
-// entry does not hold the row: the slot is the top 14 bits of a hash that is a bijection of 32-bit words,
-// so the other 18 bits (plus one, so that a used entry is never zero, and one bit for which hash it was)
-// name the row, and the 12 bits above them count it; a count that wraps sends its 4096 to the global
+// entry does not hold the row: the slot is the top 14 (12) bits of a hash that is a bijection of 32-bit words,
+// so the other 18 (20) bits (plus one, so that a used entry is never zero, and one bit for which hash it was)
+// name the row, and the 12 (10) bits above them count it; a count that wraps sends its 4096 (1024) to the global
 // counter at once.  At the end the table is flushed with one saturating add per used slot.  The first row
 // to claim a slot keeps it, so the counts stay exact.
 // What the kernel costs is its global adds: the chip retires about 27 G of them a second wherever they land
@@ -76,14 +79,14 @@ constexpr int kHistBlock = 1024;          // 16 waves per span: a span per 256 t
 // those 67 M ids; counting the most popular rows in registers changed nothing (the LDS is not the limit).
 typedef int64_t Id2 __attribute__((ext_vector_type(2)));
 
-template <bool SELF>
+template <bool SELF, int SLOT_BITS>
 __global__ __launch_bounds__(kHistBlock) void plan_histogram_kernel(
     const int64_t* __restrict__ ids, const int64_t* __restrict__ offsets, int T, int64_t B,
     const int64_t* __restrict__ row_base, int64_t n, int64_t R, int64_t span, uint32_t* __restrict__ counts,
     const int32_t* __restrict__ verdicts, int num_verdicts, int32_t* status)
 {
-    constexpr int kSlots = 1 << kHistSlotBits;
-    constexpr int kRestBits = 32 - kHistSlotBits;                   // bits of a row's hash that its slot does not give
+    constexpr int kSlots = 1 << SLOT_BITS;
+    constexpr int kRestBits = 32 - SLOT_BITS;                   // bits of a row's hash that its slot does not give
     constexpr int kCountShift = kRestBits + 2;                      // entry: [count | which hash | rest + 1]
     constexpr uint32_t kTagMask = (1u << kCountShift) - 1u;
     constexpr uint32_t kCountMax = (1u << (32 - kCountShift)) - 1u;
@@ -885,18 +888,24 @@ extern "C" fs_status fs_plan_replication(
         const int64_t S = (int64_t)T * B;
         const int64_t span = hist_span(n);
         const int64_t blocks = (n + span - 1) / span;
+#define FS_HISTOGRAM(SELF, BITS, VERDICTS)                                                                           \
+    FS_LAUNCH("plan_histogram", (plan_histogram_kernel<SELF, BITS>), dim3((unsigned)blocks), dim3(kHistBlock), s,     \
+              ids, offsets, (int)T, (int64_t)B, row_base, n, R, span, counts, verdicts, VERDICTS, dev_status)
+        const bool small = span <= (1 << (kHistSmallSlotBits - 1));
         if (n > 0 && S <= kCheckSelfSegments && blocks <= kCheckSelfBlocks) {
-            FS_LAUNCH("plan_histogram", plan_histogram_kernel<true>, dim3((unsigned)blocks), dim3(kHistBlock), s,
-                      ids, offsets, (int)T, (int64_t)B, row_base, n, R, span, counts, verdicts, 0, dev_status);
+            if (small) FS_HISTOGRAM(true, kHistSmallSlotBits, 0);
+            else FS_HISTOGRAM(true, kHistSlotBits, 0);
         } else {
             const int64_t wanted = (S + kBlock * kCheckPerThread - 1) / (kBlock * kCheckPerThread);
             const int grid = (int)(wanted < kCheckBlocksMax ? wanted : kCheckBlocksMax);
             FS_LAUNCH("plan_check_offsets", plan_check_offsets_kernel, dim3((unsigned)grid), dim3(kBlock), s,
                       offsets, S, n, verdicts, dev_status);
-            if (n > 0)
-                FS_LAUNCH("plan_histogram", plan_histogram_kernel<false>, dim3((unsigned)blocks), dim3(kHistBlock), s,
-                          ids, offsets, (int)T, (int64_t)B, row_base, n, R, span, counts, verdicts, grid, dev_status);
+            if (n > 0) {
+                if (small) FS_HISTOGRAM(false, kHistSmallSlotBits, grid);
+                else FS_HISTOGRAM(false, kHistSlotBits, grid);
+            }
         }
+#undef FS_HISTOGRAM
     }
     if (sel) {
         const int allow_zero = (flags & FS_PLAN_ALLOW_ZERO) ? 1 : 0;

@@ -202,6 +202,24 @@ def test_histogram_sizes(G, T, B, n, bad):
     assert np.array_equal(dev.cpu().numpy().view(np.uint32), oc)
 
 
+@pytest.mark.parametrize("n", [2048, 256 * 2048, 256 * 2048 + 1])
+@pytest.mark.parametrize("law", ["one row", "all different", "64 rows"])
+def test_histogram_tables(G, n, law):
+    """The small table of spans of 2048 ids and the large one: counts that wrap their entry's 10 bits, every id another
+    row, few rows that share slots."""
+    import paper_2301_02959_amd as fs
+    R = 300_000_000
+    row = {"one row": torch.full((n,), R - 1, device=G.DEV), "all different": (torch.arange(n, device=G.DEV) * 571 + 5) % R,
+           "64 rows": (torch.arange(n, device=G.DEV) % 64) * 4_194_301}[law]
+    offsets, row_base = (torch.tensor([0, end], device=G.DEV) for end in (n, R))
+    counts = torch.zeros(R, dtype=torch.int32, device=G.DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    fs.fs_plan_replication(row, offsets, 1, 1, row_base, n, R, counts, fs.FS_PLAN_ACCUMULATE, dev_status=st)
+    want_rows, want = torch.unique(row, return_counts=True)
+    assert int(st.item()) == 0 and torch.equal(counts[want_rows].long(), want)
+    assert int(counts.sum(dtype=torch.int64)) == n
+
+
 @pytest.mark.parametrize("n", [2048, 256 * 2048, 256 * 2048 + 1, 256 * 2048 + 255, 256 * 2048 + 256, 700_001, 256 * 30_720 + 1, 256 * 32_768])
 def test_batches_are_counted_in_one_launch(G, n):
     """Up to 256 spans the counting blocks check the offsets themselves, and shorter spans never make more of them."""
