@@ -170,6 +170,31 @@ def test_runs_left_to_the_long_fold(G, D, first):
     _check(G, gnp, gt, rows, pos, 0, m, len(more) + 2, "f32", atomic_too=False)
 
 
+@pytest.mark.parametrize("blocks", [1, 2, 3, 31, 32, 33])
+@pytest.mark.parametrize("more", [-1, 0, 1])
+@pytest.mark.parametrize("R", [50, 400_000])
+def test_counting_blocks(G, blocks, more, R):
+    """Up to 32 blocks of 64 chunks every wave adds up the blocks' run counts itself, beyond them a launch scans them; the
+    number of runs with room for all of them and for fewer."""
+    import paper_2301_02959_amd as fs
+    m = blocks * 64 * CHUNK + more
+    rows = torch.sort(torch.randint(0, R, (m,), device=G.DEV, generator=torch.Generator(device=G.DEV).manual_seed(m)))[0]
+    pos = torch.arange(m, dtype=torch.int32, device=G.DEV) % 977                # ascending within a row is not needed for whole numbers
+    grad = torch.randint(-2, 3, (977, 8), device=G.DEV).float()
+    want_rows, inverse = torch.unique(rows, return_inverse=True)
+    want = torch.zeros(len(want_rows), 8, device=G.DEV, dtype=torch.float64).index_add_(0, inverse, grad[pos.long()].double())
+    for cap in (len(want_rows), len(want_rows) // 2):
+        uniq = torch.full((cap + 1,), -7, dtype=torch.int64, device=G.DEV)
+        rg = torch.full((cap + 1, 8), 7.0, device=G.DEV)
+        nu = torch.zeros(1, dtype=torch.int64, device=G.DEV)
+        st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+        fs.fs_seq_grad_bwd_sorted(grad, rows.to(torch.int32), pos, m, R, 0, uniq, rg, cap, nu, st)
+        assert int(nu.item()) == len(want_rows)
+        assert bool(int(st.item()) & fs.FS_DEV_UNIQUE_OVERFLOW) == (cap < len(want_rows))
+        assert torch.equal(uniq[:cap], want_rows[:cap]) and int(uniq[cap]) == -7
+        assert torch.equal(rg[:cap].double(), want[:cap]) and bool((rg[cap] == 7.0).all())
+
+
 @pytest.mark.parametrize("tail", [1, 2, 700])
 @pytest.mark.parametrize("m", [1, 2, 300, 700, 1024 * CHUNK, 1024 * CHUNK + 1, 1024 * CHUNK + 300])
 def test_last_row_of_all_ones(G, m, tail):
