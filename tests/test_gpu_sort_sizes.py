@@ -220,6 +220,35 @@ def test_histogram_tables(G, n, law):
     assert int(counts.sum(dtype=torch.int64)) == n
 
 
+@pytest.mark.parametrize("first", [16383, 16384, 16385, 20001, 32767])
+def test_table_ends_inside_a_span(G, first):
+    """A first table of rows that are all different fills a span's slots (32 k ids a span), then the rows are another table's:
+    few popular ones, and, after as many ids again, a third table's."""
+    import paper_2301_02959_amd as fs
+    n, E = 8_400_000, 10_000_000
+    ends = [first, first + (32768 - first) // 2, n]
+    ids = torch.arange(n, device=G.DEV) * 7 % E
+    ids[ends[0]:ends[1]] = 3
+    ids[ends[1]:32768 * 2] %= 5
+    offsets = torch.tensor([0, *ends], device=G.DEV)
+    row_base = torch.tensor([0, E, 2 * E, 3 * E], device=G.DEV)
+    counts = torch.zeros(3 * E, dtype=torch.int32, device=G.DEV)
+    counts[E + 3] = -2                                     # 2^32 - 2: pinned at the maximum
+    st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    fs.fs_plan_replication(ids, offsets, 3, 1, row_base, n, 3 * E, counts, fs.FS_PLAN_ACCUMULATE, dev_status=st)
+    rows = ids.clone()
+    rows[ends[0]:ends[1]] += E
+    rows[ends[1]:] += 2 * E
+    want = torch.bincount(rows, minlength=3 * E)
+    if ends[1] - ends[0] > 1:
+        want[E + 3] = 0xFFFFFFFF
+        assert int(st.item()) == fs.FS_DEV_COUNT_OVERFLOW
+    else:
+        want[E + 3] += 0xFFFFFFFE
+        assert int(st.item()) == 0
+    assert torch.equal(counts.long() & 0xFFFFFFFF, want)
+
+
 @pytest.mark.parametrize("n", [2048, 256 * 2048, 256 * 2048 + 1, 256 * 2048 + 255, 256 * 2048 + 256, 700_001, 256 * 30_720 + 1, 256 * 32_768])
 def test_batches_are_counted_in_one_launch(G, n):
     """Up to 256 spans the counting blocks check the offsets themselves, and shorter spans never make more of them."""
