@@ -1,6 +1,6 @@
 // fs_plan_replication: row-frequency histogram and top-k rows under a byte budget.
 //
-// ACCUMULATE  plan_histogram: each block counts a span of the sampled ids (2048 to 512 k of them, see hist_span).  Zipf
+// ACCUMULATE  plan_histogram: each block counts a span of the sampled ids (2048 to 2 M of them, see hist_span).  Zipf
 //             samples hit a few rows most of the time, so a block counts in a table of 2^14 entries in LDS, two slots
 //             to choose from for a row (the first row to claim a slot keeps it); only rows that find both taken and
 //             the final flush reach the global counters, as saturating 32-bit atomic adds.  The offsets are checked by
@@ -276,14 +276,14 @@ __global__ __launch_bounds__(kHistBlock) void plan_histogram_kernel(
 // CU gain nothing (540 k ids in 235 spans of 2304 23.6 us, in 132 of 4096 22.5).  From one 64 k span for each of the two
 // blocks a CU holds, spans of up to 128 k ids, shortened so that their number is a multiple of the CU count
 // where that is possible.  A popular row is flushed once per span, so a planning pass over very many ids
-// (from 2^27) takes spans of up to 512 k ids, all of one length and a whole number of rounds over the chip's
-// 512 resident blocks: 10^9 ids of Zipf(1.3) in one call take 4.7 ms with 128 k spans, 4.1 ms with 512 k,
-// 10 ms with 2 M.  A training batch of a flatter law (72 M ids of Zipf(1.1) over 16 tables) does better with
-// the shorter spans (1.13 ms at 96 k, 1.25 ms at 144 k): the first rows to arrive keep the slots, and a fresh
+// (from 2^27) takes spans of up to 2 M ids, all of one length and a whole number of rounds over the chip's
+// 512 resident blocks: 10^9 ids of Zipf(1.3) over 4 tables 3.47 ms with spans of up to 512 k, 3.15 with 1 M, 2.89 with 2 M, 400 M
+// 1.52 and 1.32, 600 M of Zipf(1.05) 8.73 and 8.72.  A training batch of a flatter law (72 M ids of Zipf(1.1) over 16 tables)
+// did better with the shorter spans (1.13 ms at 96 k, 1.25 ms at 144 k): the first rows to arrive keep the slots, and a fresh
 // table serves the rows that repeat within a stretch.
 constexpr int64_t kHistSpanSmall = 32768;
 constexpr int64_t kHistSpanLarge = 131072;
-constexpr int64_t kHistSpanHuge = 524288;
+constexpr int64_t kHistSpanHuge = 2097152;
 constexpr int64_t kHistHugeFrom = (int64_t)1 << 27;
 constexpr int64_t kHistCus = 256;
 
