@@ -135,7 +135,7 @@ def _ptr_checked(t: Optional[torch.Tensor], dtypes: Optional[tuple] = None) -> O
 # The same in native code, for plain tensors that pass; for the others it calls the function above, which raises.
 try:
     from . import _marshal
-    _marshal.set_checker(_ptr_checked)
+    _marshal.set_fallback(_ptr_checked)
     _ptr = _marshal.device_pointer
 except (ImportError, AttributeError):        # not built, or for another torch: the same answers, 0.2 us a tensor slower
     _ptr = _ptr_checked

@@ -1,21 +1,21 @@
 // The binding's per-tensor check and pointer, in native code: device_pointer(tensor, dtypes=None) returns the data pointer
 // of a contiguous CUDA tensor whose dtype is in the tuple `dtypes` (None: any), None for None, and hands whatever else,
-// a tensor subclass or wrapper included, to the function given to set_checker, which looks at it in Python and raises.
+// a tensor subclass or wrapper included, to the function given to set_fallback, which looks at it in Python and raises.
 // A call of the router passes nine tensors; four attribute reads and a call each in Python are 0.31 us a tensor, this is 0.07.
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
 
-static PyObject* checker = nullptr;
+static PyObject* fallback = nullptr;
 
-static PyObject* set_checker(PyObject*, PyObject* fn)
+static PyObject* set_fallback(PyObject*, PyObject* fn)
 {
     Py_INCREF(fn);
-    Py_XDECREF(checker);
-    checker = fn;
+    Py_XDECREF(fallback);
+    fallback = fn;
     Py_RETURN_NONE;
 }
 
-// The pointer as a Python integer, or null (and no Python error) where the checker has to look.
+// The pointer as a Python integer, or null (and no Python error) where the fallback has to look.
 static PyObject* plain_pointer(PyObject* obj, PyObject* dtypes)
 {
     if (!THPVariable_CheckExact(obj) || (dtypes != Py_None && !PyTuple_CheckExact(dtypes))) return nullptr;
@@ -40,20 +40,20 @@ static PyObject* plain_pointer(PyObject* obj, PyObject* dtypes)
 
 static PyObject* device_pointer(PyObject*, PyObject* const* args, Py_ssize_t nargs)
 {
-    if (nargs < 1 || nargs > 2 || checker == nullptr) {
-        PyErr_SetString(PyExc_TypeError, "device_pointer(tensor, dtypes=None), after set_checker");
+    if (nargs < 1 || nargs > 2 || fallback == nullptr) {
+        PyErr_SetString(PyExc_TypeError, "device_pointer(tensor, dtypes=None), after set_fallback");
         return nullptr;
     }
     if (args[0] == Py_None) Py_RETURN_NONE;
     PyObject* const pointer = plain_pointer(args[0], nargs == 2 ? args[1] : Py_None);
     if (pointer != nullptr || PyErr_Occurred()) return pointer;
-    return PyObject_Vectorcall(checker, args, (size_t)nargs, nullptr);
+    return PyObject_Vectorcall(fallback, args, (size_t)nargs, nullptr);
 }
 
 static PyMethodDef methods[] = {
     {"device_pointer", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(device_pointer)), METH_FASTCALL,
      "device_pointer(tensor, dtypes=None): data pointer of a contiguous CUDA tensor"},
-    {"set_checker", set_checker, METH_O, "set_checker(function): what device_pointer calls for anything but such a tensor"},
+    {"set_fallback", set_fallback, METH_O, "set_fallback(function): what device_pointer calls for anything but such a tensor"},
     {nullptr, nullptr, 0, nullptr}};
 static PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
