@@ -22,6 +22,7 @@
 // (fs_seq_grad_bwd's variant 1 still reads and writes row_grads with atomics in L2.)
 #include "fs_common.h"
 #include "radix_sort.h"
+#include "run_end.h"
 #include "update_rules.h"
 
 namespace fs {
@@ -163,8 +164,8 @@ constexpr int64_t kSumBlocks = 32;
 
 __host__ __device__ __forceinline__ int64_t heads_blocks(int64_t chunks) { return (chunks + kChunksPerBlock - 1) / kChunksPerBlock; }
 
-// `v` added up over the wave, in every lane.
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
+// `v` added up over the wave's lanes up to each, itself included.
+__device__ __forceinline__ uint32_t wave_sums_upto(uint32_t v)
 {
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111 /* row_shr:1 */, 0xf, 0xf, true);
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112 /* row_shr:2 */, 0xf, 0xf, true);
@@ -172,7 +173,13 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118 /* row_shr:8 */, 0xf, 0xf, true);
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142 /* row_bcast:15 */, 0xa, 0xf, false);
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143 /* row_bcast:31 */, 0xc, 0xf, false);
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+    return v;
+}
+
+// `v` added up over the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_sums_upto(v), kWave - 1);
 }
 
 // Runs that start in the chunks before `chunk` (at most `chunks`); the same in every lane of the wave, all of which call it.
@@ -942,26 +949,28 @@ __global__ __launch_bounds__(kBlock) void bwd_fold_kernel(
     const uint32_t before = keys[k0 > 0 ? k0 - 1 : 0];
     const bool has_far = chunk + 2 < chunks;                         // then (chunk + 2) * kChunk < m
     const uint32_t far = keys[has_far ? k1 + kChunk : k1];
-    const int64_t u = (int64_t)runs_before(block_base, chunk_local, chunk + 1, chunks) - 1;
+    // Runs before a chunk from what stands in chunk_local for it.  Few blocks: their sums added up once, a lane for each.
+    const int64_t blocks = heads_blocks(chunks);
+    uint32_t upto = 0;
+    if (blocks > 1 && blocks <= kSumBlocks) upto = wave_sums_upto(lane_id() < (int)blocks ? block_base[lane_id()] : 0u);
+    auto runs_at = [&](int64_t c, uint32_t local) {                  // c < chunks, the same in the whole wave
+        const int block = __builtin_amdgcn_readfirstlane((int)(c / kChunksPerBlock));
+        if (blocks > kSumBlocks) return block_base[block] + local;
+        return (block == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)upto, block - 1)) + local;
+    };
+    const uint32_t local_here = chunk_local[chunk], local_next = chunk_local[chunk + 1];
+    const uint32_t local_far = chunk_local[has_far ? chunk + 2 : chunk];
+    const uint32_t runs = runs_at(chunk + 1, local_next);
+    const int64_t u = (int64_t)runs - 1;
     if (next != key) return;                                         // the chunk's last run ends with it
-    if (k0 > 0 && head == key && before == key) return;              // the run started in an earlier chunk
+    // The run goes on into a chunk that starts with its row and has no other run before it.  In an ascending list the row
+    // alone says so; in a list that a caller brings in another order a row may come again in a later run, and the count keeps
+    // any two runs from going on into one chunk.
+    auto goes_on_into = [&](int64_t c, uint32_t first, uint32_t local) { return (first == key) & (runs_at(c, local) == runs); };
+    if (k0 > 0 && before == key && goes_on_into(chunk, head, local_here)) return;          // it started in an earlier chunk
     if (u >= cap) return;
-    // The last chunk whose first lookup still belongs to the run.  Most spilling runs end in the
-    // very next chunk, so the search gallops from there (1, 2, 4 .. chunks ahead) and then bisects:
-    // no further load for a short run instead of log2(m) dependent ones.
-    int64_t lo = chunk + 1, step = 1;                                // chunk lo starts inside the run
-    bool go_on = has_far && far == key;
-    while (go_on) {
-        lo += step;
-        step <<= 1;
-        go_on = lo + step < chunks && keys[(lo + step) * kChunk] == key;
-    }
-    int64_t hi = lo + step < chunks ? lo + step : chunks;            // chunk hi does not (or does not exist)
-    while (hi - lo > 1) {
-        const int64_t mid = lo + ((hi - lo) >> 1);
-        if (keys[mid * kChunk] == key) lo = mid; else hi = mid;
-    }
-    const int64_t last_chunk = lo;
+    const int64_t last_chunk = last_chunk_of_run(chunk, chunks, has_far && goes_on_into(chunk + 2, far, local_far),
+                                                 [&](int64_t c) { return goes_on_into(c, keys[c * kChunk], chunk_local[c]); });
     if (long_runs != nullptr && last_chunk - chunk > kFoldLong) {
         if (lane_id() == 0) long_runs[atomicAdd(num_long, 1u)] = {(uint32_t)u, (uint32_t)(chunk + 1), (uint32_t)last_chunk};
         return;
@@ -1320,7 +1329,7 @@ static BwdScratch take_bwd_scratch(Carver& ws, int64_t m, int D, int variant)
     w.block_base = ws.take<uint32_t>((size_t)blocks + 1);
     w.carry = ws.take<float>(variant == 0 ? (size_t)chunks * (size_t)D : 0);
     const bool may_long = variant == 0 && chunks * D > kFoldLongWork;
-    w.long_runs = ws.take<LongRun>(may_long ? (size_t)(chunks / kFoldLong) + 1 : 0);      // each has more than kFoldLong chunks of its own
+    w.long_runs = ws.take<LongRun>(may_long ? (size_t)(chunks / kFoldLong) + 1 : 0);      // each goes on into more than kFoldLong chunks, no two into one
     w.num_long = ws.take<uint32_t>(may_long ? 1 : 0);
     if (!may_long) { w.long_runs = nullptr; w.num_long = nullptr; }
     return w;

@@ -170,6 +170,47 @@ def test_runs_left_to_the_long_fold(G, D, first):
     _check(G, gnp, gt, rows, pos, 0, m, len(more) + 2, "f32", atomic_too=False)
 
 
+@pytest.mark.parametrize("D,chunks", [(8, 9), (128, 70), (128, 7900), (256, 4100)])
+@pytest.mark.parametrize("order", ["alternating", "long and short", "random"])
+def test_rows_that_come_again(G, D, chunks, order):
+    """Lists that are not ascending: every stretch of equal rows is a row of its own, wherever else its row stands, also
+    where runs go on over many chunks; the workspace is not written past its end.  Gradients are small whole numbers."""
+    import ctypes
+    import paper_2301_02959_amd as fs
+    m = chunks * CHUNK - 3
+    k = torch.arange(m, device=G.DEV)
+    if order == "alternating":                             # every chunk starts with row 7, every other one is nothing else
+        rows = torch.where(k % (2 * CHUNK) <= CHUNK, 7, 9)
+    elif order == "long and short":                        # 65 chunks of row 7 and a bit, then 65 that only start with it
+        rows = torch.where((k % (130 * CHUNK) <= 65 * CHUNK) | (k % CHUNK == 0), 7, 9)
+    else:
+        gen = torch.Generator(device=G.DEV).manual_seed(chunks)
+        rows = torch.randint(0, 3, (m // 200 + 1,), device=G.DEV, generator=gen).repeat_interleave(200)[:m]
+    heads = torch.ones(m, dtype=torch.bool, device=G.DEV)
+    heads[1:] = rows[1:] != rows[:-1]
+    run = torch.cumsum(heads, 0) - 1
+    runs = int(run[-1]) + 1
+    pos = torch.arange(m, dtype=torch.int32, device=G.DEV) % 977
+    grad = torch.randint(-2, 3, (977, D), device=G.DEV).float()
+    want = torch.zeros(runs, D, device=G.DEV, dtype=torch.float64)
+    for k0 in range(0, m, 1 << 20):
+        want.index_add_(0, run[k0:k0 + (1 << 20)], grad[pos[k0:k0 + (1 << 20)].long()].double())
+    uniq = torch.full((runs,), -7, dtype=torch.int64, device=G.DEV)
+    rg = torch.full((runs, D), 7.0, device=G.DEV)
+    nu = torch.zeros(1, dtype=torch.int64, device=G.DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    args = (m, 100, 0, uniq, rg, runs, nu, st)
+    need = ctypes.c_size_t(0)
+    assert fs._typed().fs_seq_grad_bwd_sorted(None, 977, D, fs.FS_F32, None, None, m, 100, 0, None, None, runs, None, None,
+                                              ctypes.byref(need), None, None) == 0
+    guarded = torch.full((need.value + (1 << 20),), 85, dtype=torch.uint8, device=G.DEV)
+    fs.fs_seq_grad_bwd_sorted(grad, rows.to(torch.int32), pos, *args, workspace=guarded[:need.value])
+    assert int(nu.item()) == runs
+    assert bool(int(st.item()) & fs.FS_DEV_NOT_SORTED) == bool((rows[1:] < rows[:-1]).any())
+    assert torch.equal(uniq, rows[heads]) and torch.equal(rg.double(), want)
+    assert bool((guarded[need.value:] == 85).all())
+
+
 @pytest.mark.parametrize("blocks", [1, 2, 3, 31, 32, 33])
 @pytest.mark.parametrize("more", [-1, 0, 1])
 @pytest.mark.parametrize("R", [50, 400_000])
