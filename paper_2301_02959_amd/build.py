@@ -25,14 +25,18 @@ def sources():
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
+    if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.[hc]*")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
+    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
     return any(os.path.getmtime(p) > t for p in deps)
 
 
-def marshal_command():
+def helper_stale() -> bool:
+    return not os.path.exists(MARSHAL) or os.path.getmtime(os.path.join(CSRC, "marshal.cpp")) > os.path.getmtime(MARSHAL)
+
+
+def helper_command(out):
     """The binding's native helper (no device code): against the installed torch's own headers and libraries."""
     import sysconfig
     import torch
@@ -40,12 +44,35 @@ def marshal_command():
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", os.path.join(CSRC, "marshal.cpp"),
             "-I", os.path.join(base, "include"), "-I", os.path.join(base, "include", "torch", "csrc", "api", "include"),
             "-I", sysconfig.get_paths()["include"], f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-            "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", MARSHAL]
+            "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", out]
 
 
-def build(force: bool = True, verbose: bool = False) -> str:
-    if not force and not stale():
-        return LIB
+def build_helper(verbose: bool = False) -> bool:
+    """The library and the package do without the helper (the binding then checks its pointers in Python), so a machine
+    without a host compiler or torch's headers is told so and goes on; no helper of another source stays behind."""
+    out = MARSHAL + ".new"
+    try:
+        cmd = helper_command(out)
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        done = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        said = done.stdout.strip()
+        built = done.returncode == 0 and os.path.exists(out)
+    except OSError as e:
+        said, built = str(e), False
+    if said:
+        print(said, file=sys.stderr)
+    if built:
+        os.replace(out, MARSHAL)
+        return True
+    for path in (out, MARSHAL):
+        if os.path.exists(path):
+            os.remove(path)
+    print("marshal.cpp did not compile: the binding will check its pointers in Python", file=sys.stderr)
+    return False
+
+
+def build_library(verbose: bool = False) -> None:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = []
     obj_dir = os.path.join(PKG, "_build")
@@ -59,7 +86,6 @@ def build(force: bool = True, verbose: bool = False) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-    procs.append(("marshal.cpp", subprocess.Popen(marshal_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, p in procs:
         out, _ = p.communicate()
@@ -68,10 +94,17 @@ def build(force: bool = True, verbose: bool = False) -> str:
             print(out, file=sys.stderr)
         if p.returncode != 0:
             failed = True
-            print(f"the compiler failed on {src}", file=sys.stderr)
+            print(f"hipcc failed on {src}", file=sys.stderr)
     if failed:
-        raise RuntimeError("a source did not compile")
+        raise RuntimeError("hipcc failed")
     subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], check=True)
+
+
+def build(force: bool = True, verbose: bool = False) -> str:
+    if force or stale():
+        build_library(verbose)
+    if force or helper_stale():
+        build_helper(verbose)
     return LIB
 
 

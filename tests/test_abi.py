@@ -87,6 +87,30 @@ def test_pointers_in_native_code_and_in_python():
         fs._ptr()
 
 
+@pytest.mark.parametrize("cxx", ["false", "/no/such/compiler"])
+def test_the_build_does_without_the_native_helper(tmp_path, monkeypatch, capsys, cxx):
+    """Only the HIP library has to build: without a host compiler the helper is left out, and an old one removed."""
+    from paper_2301_02959_amd import build
+    hipcc = tmp_path / "hipcc"                             # writes its output file, as a compiler does
+    hipcc.write_text('#!/bin/sh\nwhile [ "$1" != -o ]; do shift; done\necho built > "$2"\n')
+    hipcc.chmod(0o755)
+    monkeypatch.setattr(build, "PKG", str(tmp_path))
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "lib.so"))
+    monkeypatch.setattr(build, "MARSHAL", str(tmp_path / "_marshal.so"))
+    (tmp_path / "_marshal.so").write_text("of another source")
+    monkeypatch.setenv("HIPCC", str(hipcc))
+    monkeypatch.setenv("CXX", cxx)
+    assert build.build(force=True) == build.LIB
+    assert (tmp_path / "lib.so").read_text() == "built\n" and not (tmp_path / "_marshal.so").exists()
+    assert "check its pointers in Python" in capsys.readouterr().err
+    assert not build.stale() and build.helper_stale()
+    monkeypatch.setenv("HIPCC", "/no/such/compiler")
+    assert build.build(force=False) == build.LIB           # the library is current, whatever the helper is
+    monkeypatch.setenv("HIPCC", "false")
+    with pytest.raises(RuntimeError):
+        build.build(force=True)
+
+
 @pytest.mark.gpu
 def test_native_pointers_on_the_gpu():
     import torch
