@@ -132,13 +132,21 @@ def _ptr_checked(t: Optional[torch.Tensor], dtypes: Optional[tuple] = None) -> O
     return t.data_ptr()
 
 
-# The same in native code, for plain tensors that pass; for the others it calls the function above, which raises.
-try:
-    from . import _marshal
-    _marshal.set_fallback(_ptr_checked)
-    _ptr = _marshal.device_pointer
-except (ImportError, AttributeError):        # not built, or for another torch: the same answers, 0.2 us a tensor slower
-    _ptr = _ptr_checked
+def _native_ptr():
+    """The same in native code, for plain tensors that pass; for the others it calls the function above, which raises.  The
+    function above itself (0.2 us a tensor slower) where the native one is not built, or not for the torch that runs: it has
+    the layout of torch's objects compiled in, and a library of another one may well load."""
+    try:
+        from . import _marshal
+        if _marshal.built_for != f"{torch.__version__} {torch.version.git_version}":
+            return _ptr_checked
+        _marshal.set_fallback(_ptr_checked)
+        return _marshal.device_pointer
+    except (ImportError, AttributeError):
+        return _ptr_checked
+
+
+_ptr = _native_ptr()
 
 
 # torch's current stream as a handle.  torch.cuda.current_stream() builds a Stream object for it (2.9 us of the

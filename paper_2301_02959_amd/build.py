@@ -5,12 +5,15 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libflexshard_hip.so")
-MARSHAL = os.path.join(PKG, "_marshal.so")
+# named for the interpreter, so that no other one loads it
+MARSHAL = os.path.join(PKG, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+UNTAGGED = os.path.join(PKG, "_marshal.so")                # what any interpreter would load in its place
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -38,12 +41,13 @@ def helper_stale() -> bool:
 
 def helper_command(out):
     """The binding's native helper (no device code): against the installed torch's own headers and libraries."""
-    import sysconfig
     import torch
     base = os.path.dirname(torch.__file__)
+    built_for = f"{torch.__version__} {torch.version.git_version}"
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", os.path.join(CSRC, "marshal.cpp"),
             "-I", os.path.join(base, "include"), "-I", os.path.join(base, "include", "torch", "csrc", "api", "include"),
             "-I", sysconfig.get_paths()["include"], f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f'-DFS_BUILT_FOR="{built_for}"',
             "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", out]
 
 
@@ -64,8 +68,10 @@ def build_helper(verbose: bool = False) -> bool:
         print(said, file=sys.stderr)
     if built:
         os.replace(out, MARSHAL)
+        if os.path.exists(UNTAGGED):
+            os.remove(UNTAGGED)
         return True
-    for path in (out, MARSHAL):
+    for path in (out, MARSHAL, UNTAGGED):
         if os.path.exists(path):
             os.remove(path)
     print("marshal.cpp did not compile: the binding will check its pointers in Python", file=sys.stderr)

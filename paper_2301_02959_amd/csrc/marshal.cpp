@@ -57,4 +57,14 @@ static PyMethodDef methods[] = {
     {nullptr, nullptr, 0, nullptr}};
 static PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+// built_for: the torch whose headers this was compiled with.  Its objects' layouts are compiled in, so the binding takes no
+// other's.
+PyMODINIT_FUNC PyInit__marshal()
+{
+    PyObject* const m = PyModule_Create(&module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "built_for", FS_BUILT_FOR) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -87,6 +87,24 @@ def test_pointers_in_native_code_and_in_python():
         fs._ptr()
 
 
+def test_a_native_helper_for_another_torch_is_not_used(monkeypatch):
+    import torch
+    import paper_2301_02959_amd as fs
+    from paper_2301_02959_amd import _marshal, build
+    assert _marshal.__file__ == build.MARSHAL and not os.path.exists(build.UNTAGGED)
+    assert fs._native_ptr() is _marshal.device_pointer
+    with monkeypatch.context() as m:
+        m.setattr(torch, "__version__", "1.0.0")
+        assert fs._native_ptr() is fs._ptr_checked
+    with monkeypatch.context() as m:
+        m.setattr(torch.version, "git_version", "of another build")
+        assert fs._native_ptr() is fs._ptr_checked
+    with monkeypatch.context() as m:
+        m.delattr(_marshal, "built_for")                   # a helper that does not say
+        assert fs._native_ptr() is fs._ptr_checked
+    assert fs._native_ptr() is _marshal.device_pointer
+
+
 @pytest.mark.parametrize("cxx", ["false", "/no/such/compiler"])
 def test_the_build_does_without_the_native_helper(tmp_path, monkeypatch, capsys, cxx):
     """Only the HIP library has to build: without a host compiler the helper is left out, and an old one removed."""
@@ -97,6 +115,7 @@ def test_the_build_does_without_the_native_helper(tmp_path, monkeypatch, capsys,
     monkeypatch.setattr(build, "PKG", str(tmp_path))
     monkeypatch.setattr(build, "LIB", str(tmp_path / "lib.so"))
     monkeypatch.setattr(build, "MARSHAL", str(tmp_path / "_marshal.so"))
+    monkeypatch.setattr(build, "UNTAGGED", str(tmp_path / "_marshal.so"))
     (tmp_path / "_marshal.so").write_text("of another source")
     monkeypatch.setenv("HIPCC", str(hipcc))
     monkeypatch.setenv("CXX", cxx)
