@@ -46,6 +46,30 @@ struct SortJob {
     hipStream_t stream = nullptr;
 };
 
+// From this many pairs on they lie apart between passes too.  Side by side the scatter's stores are half as many and its
+// runs twice as long, but the count reads 8 bytes for a key of 4, which costs more where a pass no longer fits the 256 MB
+// memory-side cache.  Side by side : apart, us, rows of 27 bits: 8.4 M 170 : 175, 15.7 M 278 : 286, 30 M 534 : 532,
+// 72 M 1367 : 1310; of 29 bits 182 : 190, 300 : 317, 572 : 587, 1464 : 1443; of 22 bits 162 : 161, 261 : 263, 494 : 480, 1236 : 1137.
+constexpr int64_t kSortSplitFrom = (int64_t)1 << 25;
+
+// Where pairs lie before or after a pass: side by side, or (pairs == nullptr) apart.
+struct SortPlace {
+    SortPair* pairs;
+    uint32_t* keys;
+    uint32_t* vals;
+};
+
+// Where pass k (of `passes`) leaves its pairs; k = -1: where those lie that do not come from `rows`.
+inline SortPlace sort_place_after(const SortJob& job, int passes, int k)
+{
+    if (k < 0) return {job.pairs_a, nullptr, nullptr};
+    if (k == passes - 1 && job.keys_out != nullptr) return {nullptr, job.keys_out, job.vals_out};
+    SortPair* const buffer = (k % 2 == 0) == (job.rows != nullptr) ? job.pairs_a : job.pairs_b;
+    if (job.m_dev != nullptr || job.m_max < kSortSplitFrom) return {buffer, nullptr, nullptr};
+    uint32_t* const words = reinterpret_cast<uint32_t*>(buffer);
+    return {nullptr, words, words + job.m_max};
+}
+
 // Number of passes over keys of key_bits bits.
 inline int radix_sort_passes(int key_bits)
 {

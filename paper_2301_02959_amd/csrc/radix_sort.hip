@@ -454,12 +454,6 @@ static_assert(kSortMaxPasses * 2 * kSortSumTiles >= kSortSmallTiles);
 // few per cent of what the buffers hold, and a pass may be idle: fewer blocks, four rounds of the three that a CU takes.
 constexpr int64_t kSortScatterGrid = 8192;
 constexpr int64_t kSortScatterGridDev = 3072;
-// From this many pairs on they lie apart between passes too.  Side by side the scatter's stores are half as many and its
-// runs twice as long, but the count reads 8 bytes for a key of 4, which costs more where a pass no longer fits the 256 MB
-// memory-side cache.  Side by side : apart, us, rows of 27 bits: 8.4 M 170 : 175, 15.7 M 278 : 286, 30 M 534 : 532,
-// 72 M 1367 : 1310; of 29 bits 182 : 190, 300 : 317, 572 : 587, 1464 : 1443; of 22 bits 162 : 161, 261 : 263, 494 : 480, 1236 : 1137.
-constexpr int64_t kSortSplitFrom = (int64_t)1 << 25;
-
 struct SortShape {
     bool small;
     bool sum;                                // no scan launch
@@ -513,9 +507,7 @@ struct SortPass {
     const int64_t* m_dev;
     const uint32_t* varying;
     int shift;
-    SortPair* pairs_out;
-    uint32_t* keys_out;
-    uint32_t* vals_out;
+    SortPlace to;
     int number, passes;                      // this pass's number
     int next_bits;                           // the next one's digit, if there is one
     int32_t* status;
@@ -536,7 +528,7 @@ static fs_status launch_sort_pass(const Reader& in, const SortPass& p)
     a.later_sums = p.shape.sum ? a.group_sums + table : nullptr;
     a.later_tiles = p.shape.tiles;
     a.totals = p.t.totals;
-    a.pairs_out = p.pairs_out; a.keys_out = p.keys_out; a.vals_out = p.vals_out; a.status = p.status;
+    a.pairs_out = p.to.pairs; a.keys_out = p.to.keys; a.vals_out = p.to.vals; a.status = p.status;
     a.shift = p.shift; a.later = p.passes - 1 - p.number; a.next_bits = p.next_bits;
 #define FS_COUNT(BLOCK, ITEMS)                                                                                        \
     FS_LAUNCH("sort_count", (sort_count_kernel<Reader, NBITS, BLOCK, ITEMS>), dim3((unsigned)groups), dim3(BLOCK), p.stream, in, a)
@@ -577,9 +569,6 @@ fs_status radix_sort(const SortJob& job)
     p.m_max = job.m_max; p.m_dev = job.m_dev; p.varying = job.varying; p.stream = job.stream;
     p.shift = 0;
     const int passes = job.varying == nullptr ? radix_sort_passes(key_bits) : 4;          // with `varying`: 32 bits
-    const SortPair* src = job.pairs_a;
-    SortPair* dst = job.rows != nullptr ? job.pairs_a : job.pairs_b;
-    const bool split = job.m_dev == nullptr && job.m_max >= kSortSplitFrom;
     // spread the bits evenly over the passes: 27 bits -> 9, 9, 9; where passes can turn out idle the digits are fixed:
     // 32 bits -> 10, 10, 6, 6 or 8, 8, 8, 8
     auto digit = [&](int k, int shift) {
@@ -592,10 +581,8 @@ fs_status radix_sort(const SortJob& job)
         const int nbits = digit(k, p.shift);
         p.number = k;
         p.next_bits = k + 1 < passes ? digit(k + 1, p.shift + nbits) : 0;
-        const bool apart = k == passes - 1 && job.keys_out != nullptr;
-        p.pairs_out = apart || split ? nullptr : dst;
-        p.keys_out = apart ? job.keys_out : reinterpret_cast<uint32_t*>(dst);
-        p.vals_out = apart ? job.vals_out : reinterpret_cast<uint32_t*>(dst) + job.m_max;
+        const SortPlace from = sort_place_after(job, passes, k - 1);
+        p.to = sort_place_after(job, passes, k);
         fs_status rc = FS_OK;
         if (k == 0 && job.rows != nullptr) {
             const RowPosReader in{job.rows, job.pos, job.R, job.n};
@@ -603,14 +590,14 @@ fs_status radix_sort(const SortJob& job)
 #define FS_SORT_ROWS(NB) rc = launch_sort_pass<NB>(in, p)
             FS_DISPATCH_BITS(nbits, FS_SORT_ROWS)
 #undef FS_SORT_ROWS
-        } else if (split) {
-            const SplitReader in{reinterpret_cast<const uint32_t*>(src), reinterpret_cast<const uint32_t*>(src) + job.m_max};
+        } else if (from.pairs == nullptr) {
+            const SplitReader in{from.keys, from.vals};
             p.status = nullptr;
 #define FS_SORT_SPLIT(NB) rc = launch_sort_pass<NB>(in, p)
             FS_DISPATCH_BITS(nbits, FS_SORT_SPLIT)
 #undef FS_SORT_SPLIT
         } else {
-            const PairReader in{src};
+            const PairReader in{from.pairs};
             p.status = nullptr;
 #define FS_SORT_PAIRS(NB) rc = launch_sort_pass<NB>(in, p)
             FS_DISPATCH_BITS(nbits, FS_SORT_PAIRS)
@@ -618,8 +605,6 @@ fs_status radix_sort(const SortJob& job)
         }
         if (rc != FS_OK) return rc;
         p.shift += nbits;
-        src = dst;
-        dst = src == job.pairs_a ? job.pairs_b : job.pairs_a;
     }
     return FS_OK;
 }
