@@ -23,8 +23,8 @@ struct SortJob {
     int64_t R = 0;
     int64_t n = 0;
     int32_t* status = nullptr;
-    // Buffers of m_max pairs; the passes go from one to the other, the first pass of `rows` into pairs_a (pairs_b is
-    // not touched by sorts of up to two passes from `rows`).
+    // Buffers of m_max pairs; the passes go from one to the other, the first pass of `rows` into pairs_a.  Without pairs_b
+    // (sorts of `rows` only) keys_out and vals_out serve as the other one, from the first pass on if their number is odd.
     SortPair* pairs_a = nullptr;
     SortPair* pairs_b = nullptr;
     // Where the last pass writes keys and values apart; null: as pairs, into the buffer whose turn it is.  They may
@@ -63,8 +63,9 @@ struct SortPlace {
 inline SortPlace sort_place_after(const SortJob& job, int passes, int k)
 {
     if (k < 0) return {job.pairs_a, nullptr, nullptr};
-    if (k == passes - 1 && job.keys_out != nullptr) return {nullptr, job.keys_out, job.vals_out};
-    SortPair* const buffer = (k % 2 == 0) == (job.rows != nullptr) ? job.pairs_a : job.pairs_b;
+    const bool out = k == passes - 1 || (job.pairs_b == nullptr && (passes - 1 - k) % 2 == 0);
+    if (out && job.keys_out != nullptr) return {nullptr, job.keys_out, job.vals_out};
+    SortPair* const buffer = job.pairs_b == nullptr || (k % 2 == 0) == (job.rows != nullptr) ? job.pairs_a : job.pairs_b;
     if (job.m_dev != nullptr || job.m_max < kSortSplitFrom) return {buffer, nullptr, nullptr};
     uint32_t* const words = reinterpret_cast<uint32_t*>(buffer);
     return {nullptr, words, words + job.m_max};

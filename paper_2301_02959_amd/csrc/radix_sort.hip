@@ -12,8 +12,6 @@
 // Stability comes from wave -> tile -> digit prefix order; no block ever waits for another.
 // The first pass can read (int64 row, int32 position) directly, validating them on the way.  Between passes key and
 // value lie side by side (apart in very large sorts); the last pass can write them apart.
-#include <type_traits>
-
 #include "radix_sort.h"
 
 namespace fs {
@@ -535,18 +533,13 @@ static fs_status launch_sort_pass(const Reader& in, const SortPass& p)
 #define FS_SCATTER(BLOCK, ITEMS, STRIPE, SUM, GRID)                                                                   \
     FS_LAUNCH("sort_scatter", (sort_scatter_kernel<Reader, NBITS, BLOCK, ITEMS, STRIPE, SUM>), dim3((unsigned)(GRID)), dim3(BLOCK), \
               p.stream, in, a)
-    constexpr bool kMaySmall = !std::is_same<Reader, SplitReader>::value;
-    if constexpr (kMaySmall) {
-        if (p.shape.small && (p.number == 0 || !p.shape.sum)) FS_COUNT(kSmallBlock, kSmallItems);
-    }
+    if (p.shape.small && (p.number == 0 || !p.shape.sum)) FS_COUNT(kSmallBlock, kSmallItems);
     if (!p.shape.small) FS_COUNT(kLargeBlock, kLargeItems);
     if (!p.shape.sum)
         FS_LAUNCH("sort_scan", sort_scan_kernel, dim3((bins + kScanBins - 1) / kScanBins), dim3(kScanBins * kScanSlices), p.stream,
                   p.t.group_sums, bins, p.shape.tile_pairs, p.m_max, p.m_dev, p.varying, p.shift, p.t.totals);
-    if constexpr (kMaySmall) {
-        if (p.shape.small && p.shape.sum) FS_SCATTER(kSmallBlock, kSmallItems, 1, true, p.shape.tiles);
-        if (p.shape.small && !p.shape.sum) FS_SCATTER(kSmallBlock, kSmallItems, 1, false, p.shape.tiles);
-    }
+    if (p.shape.small && p.shape.sum) FS_SCATTER(kSmallBlock, kSmallItems, 1, true, p.shape.tiles);
+    if (p.shape.small && !p.shape.sum) FS_SCATTER(kSmallBlock, kSmallItems, 1, false, p.shape.tiles);
     if (!p.shape.small) {
         const int64_t padded = xcd_striped_grid(p.shape.tiles, kSortStripe);       // a multiple of 8, as the largest grid is
         const int64_t most = p.m_dev != nullptr ? kSortScatterGridDev : kSortScatterGrid;

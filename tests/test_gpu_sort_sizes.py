@@ -163,6 +163,51 @@ def test_compaction_tiles(G, tiles, off, zero):
     assert int(num.item()) == K and torch.equal(sel, rows[order])
 
 
+def sort_workspace_bytes(m, R):
+    import ctypes
+    import paper_2301_02959_amd as fs
+    size = ctypes.c_size_t(0)
+    assert fs._typed().fs_sort_lookups(None, None, 0, m, R, max(m, 1), None, None, None, ctypes.byref(size), None, None) == 0
+    return size.value
+
+
+def test_the_sorts_workspace():
+    """What two passes ask for serves any number of rows and any smaller batch: a buffer for the pairs, 1024 counts of 4 bytes
+    for 4096 of them, up to 5 MB; never more than a second buffer beyond it is asked for."""
+    before = 0
+    for m in (0, 1, 1000, 65_536, 65_537, 262_144, 262_145, 1_000_000, 4_194_304, 4_194_305, (1 << 25) - 1, 1 << 25, (1 << 31) - 1):
+        need = sort_workspace_bytes(m, 200)
+        assert before <= need <= 8 * m + m + (5 << 20)
+        for R in (1, 1 << 10, 1 << 20, (1 << 20) + 1, 1 << 30, (1 << 32) - 2):
+            second = R > 1 << 20 and m < 1 << 25
+            assert need <= sort_workspace_bytes(m, R) <= need + (8 * m + 256 if second else 0)
+        before = need
+
+
+@pytest.mark.parametrize("R", [1000, 1 << 20, 80_000_000, (1 << 32) - 2])
+@pytest.mark.parametrize("m", [1, 1025, 65_536, 65_537, 262_145, 1_100_000, 1 << 25])
+def test_one_to_four_passes_in_that_workspace(G, R, m):
+    """In what every R is served with, in what this one asks for and in one byte less than that; nothing is written past the
+    end of the workspace or of the outputs."""
+    import paper_2301_02959_amd as fs
+    gen = torch.Generator(device=G.DEV).manual_seed(m)
+    rows = torch.randint(0, R, (m,), device=G.DEV, generator=gen)
+    rows[torch.rand(m, device=G.DEV, generator=gen) < 0.2] = R // 2
+    pos = torch.arange(m, dtype=torch.int32, device=G.DEV)
+    want, order = torch.sort(rows, stable=True)
+    need, asked = sort_workspace_bytes(m, 200), sort_workspace_bytes(m, R)
+    for size in sorted({need, max(need, asked - 1), asked}):
+        guarded = torch.full((size + 4096,), 85, dtype=torch.uint8, device=G.DEV)
+        out = torch.full((2 * m + 128,), -7, dtype=torch.int32, device=G.DEV)
+        srows, spos = out[1:m + 1], out[m + 65:2 * m + 65]
+        st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+        fs.fs_sort_lookups(rows, pos, 0, m, R, m, srows, spos, st, workspace=guarded[:size])
+        assert int(st.item()) == 0 and torch.equal(srows.long() & 0xFFFFFFFF, want) and torch.equal(spos.long(), order)
+        assert bool((guarded[size:] == 85).all())
+        assert all(bool((part == -7).all()) for part in (out[:1], out[m + 1:m + 65], out[2 * m + 65:]))
+    assert fs.fs_sort_lookups(rows, pos, 0, m, R, m, srows, spos, st, workspace=guarded[:need - 1], raise_on_error=False) == 5
+
+
 def test_a_workspace_for_more_rows_serves_fewer():
     """The scratch size does not shrink as the rows grow, also where the sort goes over to larger tiles."""
     import ctypes

@@ -47,14 +47,17 @@ int main()
         for (int passes = 1; passes <= 4; ++passes)
             for (int from_rows = 0; from_rows < 2; ++from_rows)
                 for (int on_device = 0; on_device < 2; ++on_device)
-                    for (int out = 0; out < 3; ++out) {              // as pairs, to arrays, to the buffer that the last pass does not read
+                    for (int out = 0; out < 4; ++out) {              // as pairs, to arrays, to the buffer that the last pass does not read,
+                                                                     // to arrays that stand in for the second buffer
+                        if (out == 3 && !from_rows) continue;
                         fs::SortJob job;
                         job.rows = from_rows ? &row : nullptr;
                         job.m_max = m;
                         job.m_dev = on_device ? &count : nullptr;
                         job.pairs_a = reinterpret_cast<fs::SortPair*>(base);
                         job.pairs_b = reinterpret_cast<fs::SortPair*>(base + 8 * m);
-                        if (out == 1) { job.keys_out = reinterpret_cast<uint32_t*>(base + 16 * m); job.vals_out = job.keys_out + m; }
+                        if (out == 3) job.pairs_b = nullptr;
+                        if (out == 1 || out == 3) { job.keys_out = reinterpret_cast<uint32_t*>(base + 16 * m); job.vals_out = job.keys_out + m; }
                         if (out == 2) {
                             job.keys_out = reinterpret_cast<uint32_t*>((passes % 2 == 1) == (from_rows == 1) ? job.pairs_a : job.pairs_b);
                             job.vals_out = job.keys_out + m;
