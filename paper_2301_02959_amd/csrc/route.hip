@@ -492,14 +492,15 @@ static int route_items(int64_t n, int64_t U)
     return kRouteItems;
 }
 
-// Room for the tile counts, never less than a smaller batch asks for: a workspace sized for a caller's largest batch
-// serves the smaller ones.
+// Room for the tile counts, never less than a smaller batch or fewer buckets ask for: a workspace sized for a caller's
+// largest batch serves the smaller ones.
 static int64_t route_counts(int64_t n, int64_t U)
 {
     int64_t counts = route_tiles(n, kRouteItems) * (U + 3);
-    for (int k = 0; k < 2 && U <= kRouteSmallBuckets; ++k) {
+    const int64_t small_buckets = U < kRouteSmallBuckets ? U : kRouteSmallBuckets;
+    for (int k = 0; k < 2; ++k) {
         const int64_t tiles = route_tiles(n, 2 << k);
-        int64_t small = (tiles < kRouteSmallTiles ? tiles : kRouteSmallTiles) * (U + 3);
+        int64_t small = (tiles < kRouteSmallTiles ? tiles : kRouteSmallTiles) * (small_buckets + 3);
         if (small > kRouteSmallCounts[k]) small = kRouteSmallCounts[k];
         if (counts < small) counts = small;
     }

@@ -88,6 +88,13 @@ def test_a_workspace_for_more_lookups_serves_fewer(U):
     assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("n", [1, 512, 513, 2048, 40_000, 128 * 512, 255 * 1024, 512 * 512, 512 * 1024 + 1, 4_000_000])
+def test_a_workspace_for_more_buckets_serves_fewer(n):
+    import paper_2301_02959_amd as fs
+    sizes = [fs.route_workspace_bytes(2, 3, n, U, 1, 0) for U in (1, 2, 8, 63, 64, 65, 82, 83, 127, 128, 129, 130, 200, 512, 4096)]
+    assert sizes == sorted(sizes)
+
+
 @pytest.mark.parametrize("n", [256 * TILE, 256 * TILE + 1, 256 * TILE + 777])
 @pytest.mark.parametrize("U,self_", [(1, 0), (2, 0), (2, 1), (3, 1), (64, 5)])
 @pytest.mark.parametrize("owners", ["one", "tables", "hot"])
