@@ -21,15 +21,6 @@ namespace fs {
 constexpr int kSelTile = kBlock * 32;     // rows per block in the compaction (fewer, larger tiles: the one-block
                                           // scan of the tile counts is what they cost)
 
-__device__ __forceinline__ void add_saturating(uint32_t* p, uint32_t v, int32_t* faults)
-{
-    const uint32_t old = atomicAdd(p, v);
-    if (old > 0xFFFFFFFFu - v) {          // wrapped: pin the counter at the maximum
-        atomicExch(p, 0xFFFFFFFFu);
-        *faults |= FS_DEV_COUNT_OVERFLOW;
-    }
-}
-
 // Bad offsets count nothing, so all of them are checked before the first count.  Few segments and blocks: every
 // block of the histogram checks them all itself (SELF).  Otherwise the blocks of this kernel check a share each and leave
 // their verdicts, which every block of the histogram reads: no flag to set beforehand.

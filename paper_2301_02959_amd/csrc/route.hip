@@ -468,16 +468,10 @@ __global__ __launch_bounds__(kBlock) void route_scatter_kernel(const RouteArgs a
 }
 
 __global__ __launch_bounds__(kBlock) void route_finalize_kernel(
-    const uint32_t* __restrict__ totals /* [U + 3] */, int U, int64_t n,
-    int64_t* __restrict__ bucket_offsets, int64_t* __restrict__ tier_counts)
+    int U, int64_t* __restrict__ bucket_offsets, int64_t* __restrict__ tier_counts)
 {
-    if (threadIdx.x == 0) {
-        int64_t run = 0;
-        for (int b = 0; b < U; ++b) { bucket_offsets[b] = run; run += (n > 0 ? totals[b] : 0u); }
-        bucket_offsets[U] = run;
-        if (tier_counts != nullptr)
-            for (int k = 0; k < 3; ++k) tier_counts[k] = n > 0 ? (int64_t)totals[U + k] : 0;
-    }
+    for (int b = threadIdx.x; b <= U; b += kBlock) bucket_offsets[b] = 0;
+    if (tier_counts != nullptr && threadIdx.x < 3) tier_counts[threadIdx.x] = 0;
 }
 
 static int64_t route_tiles(int64_t n, int items) { return (n + kBlock * items - 1) / (kBlock * items); }
@@ -542,7 +536,7 @@ static fs_status route_run(
         FS_LAUNCH("route_prepare", route_prepare_kernel, dim3(prep_grid), dim3(kBlock), s,
                   offsets, S, n, dev_status);
         FS_LAUNCH("route_finalize", route_finalize_kernel, dim3(1), dim3(kBlock), s,
-                  totals, (int)U, n, bucket_offsets, tier_counts);
+                  (int)U, bucket_offsets, tier_counts);
         return FS_OK;
     }
     {
