@@ -156,6 +156,12 @@ __device__ __forceinline__ uint64_t match_bits_n(uint32_t key, bool valid)
         case 7: CALL(7); break;  case 8: CALL(8); break;  case 9: CALL(9); break;       \
         default: CALL(10); break;                                                       \
     }
+// The same for a digit of at least 5 bits.
+#define FS_DISPATCH_BITS_FROM_5(nbits, CALL)                                            \
+    switch (nbits) {                                                                    \
+        case 5: CALL(5); break;  case 6: CALL(6); break;  case 7: CALL(7); break;       \
+        case 8: CALL(8); break;  case 9: CALL(9); break;  default: CALL(10); break;     \
+    }
 
 template <typename T>
 __device__ __forceinline__ T load_stream(const T* p) { return __builtin_nontemporal_load(p); }

@@ -8,6 +8,8 @@
 namespace fs {
 
 constexpr int kSortMaxDigitBits = 10;
+constexpr int kSortPairsBits = 5;            // the shortest digit by which pairs are sorted
+static_assert(kSortPairsBits <= (kSortMaxDigitBits + 1) / 2);
 
 // A pair between two passes: [0] the key, [1] the value.  Side by side they leave the scatter as one store and a
 // digit's run is twice as long as in an array of its own (very large sorts from `rows` keep them apart, in the same buffers).
@@ -34,7 +36,7 @@ struct SortJob {
     // Number of pairs: *m_dev if m_dev != nullptr (device memory, read by the kernels; at most m_max) else m_max.
     int64_t m_max = 0;
     const int64_t* m_dev = nullptr;
-    int key_bits = 32;               // the sort is by the low key_bits bits of the key
+    int key_bits = 32;               // the sort is by the low key_bits bits of the key; of pairs, by at least kSortPairsBits
     // A device word with every bit set in which two keys differ (or null).  Passes above its highest set bit copy
     // nothing and return at once; the result is then where the last pass that ran left it, which only the device knows:
     // sort_result_in_b below.  For 32-bit keys that came in pairs_a; keys_out must be null.
@@ -77,6 +79,15 @@ inline int radix_sort_passes(int key_bits)
     if (key_bits < 1) key_bits = 1;
     if (key_bits > 32) key_bits = 32;
     return (key_bits + kSortMaxDigitBits - 1) / kSortMaxDigitBits;
+}
+
+// Bits of pass k's digit, the bits below `shift` done.  They are spread evenly over the passes: 27 bits -> 9, 9, 9; where
+// passes can turn out idle the digits are fixed: 32 bits -> 10, 10, 6, 6 or 8, 8, 8, 8.  A pass after the first has at least
+// kSortPairsBits (11 bits -> 6, 5).
+inline int sort_digit_bits(const SortJob& job, int key_bits, int passes, int k, int shift)
+{
+    const int even = (key_bits - shift + (passes - k) - 1) / (passes - k);
+    return job.varying != nullptr && k < 2 ? job.first_bits : even;
 }
 
 // Scratch the sort needs for up to m_max pairs (beyond the two buffers).

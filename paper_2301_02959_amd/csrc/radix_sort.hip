@@ -553,7 +553,8 @@ static fs_status launch_sort_pass(const Reader& in, const SortPass& p)
 fs_status radix_sort(const SortJob& job)
 {
     if (job.m_max <= 0) return FS_OK;
-    const int key_bits = job.key_bits < 1 ? 1 : job.key_bits > 32 ? 32 : job.key_bits;
+    const int least = job.rows != nullptr ? 1 : kSortPairsBits;
+    const int key_bits = job.key_bits < least ? least : job.key_bits > 32 ? 32 : job.key_bits;
     SortPass p;
     p.shape = sort_shape(job.m_max, job.m_dev != nullptr);
     if (p.shape.tiles > 0x7FFFFFFF) return FS_ERR_SIZE;
@@ -562,18 +563,11 @@ fs_status radix_sort(const SortJob& job)
     p.m_max = job.m_max; p.m_dev = job.m_dev; p.varying = job.varying; p.stream = job.stream;
     p.shift = 0;
     const int passes = job.varying == nullptr ? radix_sort_passes(key_bits) : 4;          // with `varying`: 32 bits
-    // spread the bits evenly over the passes: 27 bits -> 9, 9, 9; where passes can turn out idle the digits are fixed:
-    // 32 bits -> 10, 10, 6, 6 or 8, 8, 8, 8
-    auto digit = [&](int k, int shift) {
-        const int left = key_bits - shift;
-        const int even = (left + (passes - k) - 1) / (passes - k);
-        return job.varying != nullptr && k < 2 ? job.first_bits : even;
-    };
     p.passes = passes;
     for (int k = 0; k < passes; ++k) {
-        const int nbits = digit(k, p.shift);
+        const int nbits = sort_digit_bits(job, key_bits, passes, k, p.shift);
         p.number = k;
-        p.next_bits = k + 1 < passes ? digit(k + 1, p.shift + nbits) : 0;
+        p.next_bits = k + 1 < passes ? sort_digit_bits(job, key_bits, passes, k + 1, p.shift + nbits) : 0;
         const SortPlace from = sort_place_after(job, passes, k - 1);
         p.to = sort_place_after(job, passes, k);
         fs_status rc = FS_OK;
@@ -587,13 +581,13 @@ fs_status radix_sort(const SortJob& job)
             const SplitReader in{from.keys, from.vals};
             p.status = nullptr;
 #define FS_SORT_SPLIT(NB) rc = launch_sort_pass<NB>(in, p)
-            FS_DISPATCH_BITS(nbits, FS_SORT_SPLIT)
+            FS_DISPATCH_BITS_FROM_5(nbits, FS_SORT_SPLIT)
 #undef FS_SORT_SPLIT
         } else {
             const PairReader in{from.pairs};
             p.status = nullptr;
 #define FS_SORT_PAIRS(NB) rc = launch_sort_pass<NB>(in, p)
-            FS_DISPATCH_BITS(nbits, FS_SORT_PAIRS)
+            FS_DISPATCH_BITS_FROM_5(nbits, FS_SORT_PAIRS)
 #undef FS_SORT_PAIRS
         }
         if (rc != FS_OK) return rc;

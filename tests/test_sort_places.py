@@ -73,6 +73,22 @@ int main()
                                 check(to.pairs == ((passes % 2 == 1) == (from_rows == 1) ? job.pairs_a : job.pairs_b), "result", passes, k);
                         }
                     }
+    const uint32_t varying = 0;
+    for (int bits = 1; bits <= 32; ++bits)                              // the digits cover the key and have a kernel each
+        for (int first_bits : {0, 8, 10}) {
+            if (first_bits != 0 && bits != 32) continue;
+            fs::SortJob job;
+            job.varying = first_bits != 0 ? &varying : nullptr;
+            job.first_bits = first_bits;
+            const int passes = first_bits != 0 ? 4 : fs::radix_sort_passes(bits);
+            int shift = 0;
+            for (int k = 0; k < passes; ++k) {
+                const int digit = fs::sort_digit_bits(job, bits, passes, k, shift);
+                check(digit >= (k > 0 ? fs::kSortPairsBits : 1) && digit <= fs::kSortMaxDigitBits, "digit", passes, k);
+                shift += digit;
+            }
+            check(shift == bits, "bits", passes, bits);
+        }
     std::printf("sort places ok\n");
     return 0;
 }
