@@ -144,7 +144,8 @@ fs_status fs_route_bucketize(
  * faults and kernels; the workspace is a static device array inside the
  * library, FS_ROUTE_NOALLOC_SCRATCH_BYTES per GPU (held until the process ends).
  * A batch whose workspace would be larger (about 6 bytes per lookup plus
- * 4 * (U + 3) bytes per 2048 lookups: roughly 5 million lookups at U = 64)
+ * 4 * (U + 3) bytes per 2048 lookups, per 512 or 1024 of them in batches of up
+ * to half a million: roughly 5 million lookups at U = 64)
  * returns FS_ERR_WORKSPACE and launches nothing.  The call allocates and
  * frees nothing.  The first call on a GPU looks up that GPU's address of the
  * array (a host-side query, no allocation); make that call outside a capture.

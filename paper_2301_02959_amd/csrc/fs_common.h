@@ -128,8 +128,8 @@ __device__ __forceinline__ int wave_table_of(const int64_t* __restrict__ offsets
 
 // Lanes of the wave whose `key` has the same low NBITS bits as this lane's, restricted to lanes with `valid`:
 // NBITS ballots, no LDS.  Written on 32-bit halves with the lane's bit spread to a whole word: per bit one bit-field
-// extract, one compare (the ballot) and one three-input operation per half, as the router's and the sort's kernels are
-// bound by these instructions before anything else.
+// extract, one compare (the ballot) and one three-input operation per half: the router's and the sort's scatter run it for
+// every lookup, beside memory streams that bound them where the batch is large.
 constexpr uint32_t kAndXnor = 0x90;                     // a & ~(b ^ c): set for a = 1 and b = c
 
 template <int NBITS>

@@ -449,9 +449,10 @@ constexpr int64_t kSortSumTiles = 64;
 constexpr int kSortMaxPasses = 4;
 static_assert(kSortMaxPasses * 2 * kSortSumTiles >= kSortSmallTiles);
 // Blocks of the scatter at most; they walk the tiles with a grid stride.  Where the count is on the device it is usually a
-// few per cent of what the buffers hold, and a pass may be idle: fewer blocks, four rounds of the three that a CU takes.
+// few per cent of what the buffers hold, and a pass may be idle: fewer blocks, six rounds of the 512 that the chip holds.
 constexpr int64_t kSortScatterGrid = 8192;
 constexpr int64_t kSortScatterGridDev = 3072;
+
 struct SortShape {
     bool small;
     bool sum;                                // no scan launch

@@ -322,7 +322,7 @@ def test_c5_plan_one_billion_ids(G):
     assert int(st.item()) == 0 and seen == 4 * per_table
     assert np.array_equal(counts.cpu().numpy().view(np.uint32), ocounts)
     assert int(ocounts.astype(np.int64).sum()) == seen
-    # the same sample in ONE call (as bench.py runs the pass: spans of half a million ids, some across two tables)
+    # the same sample in ONE call (as bench.py runs the pass: spans of up to two million ids, some across two tables)
     all_ids = torch.cat(parts)
     del parts
     one = torch.zeros(R, dtype=torch.int32, device=dev)
