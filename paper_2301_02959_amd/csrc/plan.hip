@@ -146,11 +146,14 @@ __global__ __launch_bounds__(kHistBlock) void plan_histogram_kernel(
     // address allows it.
     // Where the rows change to another table's late in a span they find the slots taken by rows that don't come any more, the
     // new table's most popular ones too, and a quarter of the block's remaining ids go one by one to one global counter.  So
-    // the slots are emptied first, from as many ids on as there are slots (earlier it costs more than it saves: 4.2 M ids of 8
-    // tables, spans of 18 k, 76 us, emptied from half as many on 79).  Without and with it, us: 50 M ids of 8 tables,
-    // Zipf(1.2), 446 and 363, 72 M of 16, Zipf(1.1), 945 and 853, 150 M of 8 2016 and 1666, 400 M of 4, Zipf(1.3), 1863 and
-    // 1521, 10^9 3896 and 3470, 40 M of 8, Zipf(1.2), 308 and 319: a block that crosses a table's end was the last to finish
-    // by up to a millisecond.
+    // the slots are emptied first where that saves more than it costs, up to an add for every slot: from as many ids on as
+    // there are slots with an eighth as many still to come, and from half as many on with twice as many still to come.
+    // Never / from as many on, however few come / so, Zipf(1.2), 40 M rows in all, us: 34 M ids of 8 tables 363, 275 and 279,
+    // 40 M 454, 459 and 307, 50 M 474, 361 and 361, 40 M of 26 382, 300 and 291, 60 M of 200 654, 526 and 350, 20 M of 1000
+    // 250, 215 and 215, 72 M of 16, Zipf(1.1), 893, 815 and 817, 10^9 of 4, Zipf(1.3), 3.82, 3.19 and 3.19 ms; with only twice as
+    // many still to come, however many came, 40 M of 26 364.  Up to 8 M ids, where every block is on the chip at once, the
+    // block that empties its slots late is the last: 6 M of 16 67.6, 70.4 and 69.6, 7 M 76, 80 and 79, but 7 M of 1000 120,
+    // 101 and 100.
     int64_t held = 0;                                                // ids counted since the slots were last empty
     for (int t = t_lo;; ++t) {
         const bool done = t > t_hi;
@@ -162,7 +165,8 @@ __global__ __launch_bounds__(kHistBlock) void plan_histogram_kernel(
             hi = hi < end ? hi : end;
             if (lo >= hi) continue;
         }
-        if (done || held >= kSlots) {                                // block-uniform
+        const bool empty = held >= kSlots / 2 && end - lo >= (held >= kSlots ? kSlots / 8 : 2 * kSlots);
+        if (done || empty) {                                         // block-uniform
             __syncthreads();
             // The flush: one saturating add per used slot.  A thread's adds are all issued before the first old
             // value is looked at: one after the other, each waiting for its answer, they are the longest stretch

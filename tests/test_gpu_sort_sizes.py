@@ -294,6 +294,26 @@ def test_table_ends_inside_a_span(G, first):
     assert torch.equal(counts.long() & 0xFFFFFFFF, want)
 
 
+@pytest.mark.parametrize("held", [8191, 8192, 16383, 16384, 81920 - 32769, 81920 - 32768, 81920 - 2049, 81920 - 2048, 81920 - 2047])
+def test_what_is_left_of_a_span_where_a_table_ends(G, held):
+    """Spans of 80 k ids: after so many of them every other span goes on in another table, over an empty one between; ids of
+    popular rows among ids that are all different."""
+    import paper_2301_02959_amd as fs
+    n, E, span = 40_000_000, 1_000_000, 81920
+    ends = torch.arange(40, device=G.DEV) * 2 * span + held
+    offsets = torch.cat([ends.new_zeros(1), ends.repeat_interleave(2), ends.new_tensor([n])])
+    T = offsets.numel() - 1
+    at = torch.arange(n, device=G.DEV)
+    ids = at * 7919 % E
+    ids[::3] %= 50
+    row_base = torch.arange(T + 1, device=G.DEV) * E
+    counts = torch.zeros(T * E, dtype=torch.int32, device=G.DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    fs.fs_plan_replication(ids, offsets, T, 1, row_base, n, T * E, counts, fs.FS_PLAN_ACCUMULATE, dev_status=st)
+    tables = torch.searchsorted(offsets[1:].contiguous(), at, right=True)
+    assert int(st.item()) == 0 and torch.equal(counts.long(), torch.bincount(tables * E + ids, minlength=T * E))
+
+
 @pytest.mark.parametrize("n", [2048, 256 * 2048, 256 * 2048 + 1, 256 * 2048 + 255, 256 * 2048 + 256, 700_001, 256 * 30_720 + 1, 256 * 32_768])
 def test_batches_are_counted_in_one_launch(G, n):
     """Up to 256 spans the counting blocks check the offsets themselves, and shorter spans never make more of them."""
