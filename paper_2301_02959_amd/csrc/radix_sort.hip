@@ -440,8 +440,8 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(const Reader in, co
 // rounds.  Up to 64 of them (128 where the count is on the device: the plan's candidates, usually a few per cent of the
 // rows that the buffers are sized for) there is no scan launch.
 // fs_sort_lookups as a whole against 4 waves of 16 rounds, keys and values apart, two scan launches and a count by
-// ballots, Zipf(1.1) over 80 M rows, us: 8192 pairs 30 -> 25, 65 k 52 -> 32, 262 k 51 -> 39, 1 M 84 -> 54, 4.2 M 145 -> 116,
-// 15.7 M 304 -> 278, 72 M 1406 -> 1310.
+// ballots, Zipf(1.1) over 80 M rows, us: 8192 pairs 27 -> 20.5, 65 k 52 -> 31.5, 262 k 51 -> 39.5, 1 M 67 -> 52.5, 4.2 M 146 ->
+// 115, 15.7 M 308 -> 280, 72 M 1391 -> 1288.
 constexpr int kSmallBlock = 256, kSmallItems = 4;
 constexpr int kSortStripe = 16;              // tiles per XCD stripe in the scatter
 constexpr int64_t kSortSmallTiles = 256;
