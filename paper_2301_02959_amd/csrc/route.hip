@@ -35,7 +35,9 @@ constexpr int64_t kRouteSumMax = 6144;
 // time is its chain of rounds, its share of random placement reads and the memory's latency.  Both kernels, 2048 / 1024 / 512
 // lookups to a tile, us: 8192 lookups over 8 buckets 11.9 / 10.0 / 9.9, 50 k over 64 13.1 / 10.1 / 9.4, 83 k (10.9 k counts of
 // 512) 13.2 / 10.8 / 10.2, 130 k (17 k) 13.1 / 10.8 / 11.1, 260 k over 8 (5.6 k) 13.7 / 10.7 / 10.4, 520 k (11.2 k) 15.6 / 13.1 /
-// 14.2; 260 k over 64 (17 k counts of 1024) 16.9 / 12.7, over 128 (33 k) 17.2 / 15.2, 520 k over 64 (34 k) 18.1 / 18.2.  Up to 128
+// 14.2; 260 k over 64 (17 k counts of 1024) 16.9 / 12.7, over 128 (33 k) 17.2 / 15.2, 520 k over 64 (34 k) 18.1 / 18.2.  Around the
+// first line (11 k counts of 512), 1024 / 512, in a graph: 24 buckets 12 k 11.0 / 11.7, 13 k 11.1 / 12.0; 64 buckets 12 k
+// 10.5 / 9.9, 13 k 10.3 / 10.4, 17 k 10.7 / 10.8; 128 buckets 12 k 10.5 / 9.6, 15 k 10.5 / 10.1, 19 k 11.0 / 10.9.  Up to 128
 // buckets: there the threads that share a bucket bring its counts in one round.
 constexpr int64_t kRouteSmallCounts[2] = {11000, 33500};         // of tiles of 512 and 1024 lookups
 constexpr int64_t kRouteSmallTiles = 512;
