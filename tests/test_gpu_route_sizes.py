@@ -88,6 +88,21 @@ def test_a_workspace_for_more_lookups_serves_fewer(U):
     assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("U", [1, 254, 255, 256, 257, 4096])
+@pytest.mark.parametrize("tiers", [True, False])
+def test_an_empty_batch_of_many_buckets(G, U, tiers):
+    import paper_2301_02959_amd as fs
+    offsets, row_base = torch.zeros(7, dtype=torch.int64, device=G.DEV), torch.tensor([0, 4, 8], device=G.DEV)
+    none64, none32 = torch.zeros(1, dtype=torch.int64, device=G.DEV), torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    buckets = torch.full((U + 3,), 77, dtype=torch.int64, device=G.DEV)
+    counts = torch.full((4,), 77, dtype=torch.int64, device=G.DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    fs.fs_route_bucketize(none64, offsets, 2, 3, row_base, torch.zeros(8, dtype=torch.int32, device=G.DEV), 0, U, 1, 0,
+                          buckets[1:U + 2], none64, none32, counts[:3] if tiers else None, st)
+    assert buckets.tolist() == [77] + [0] * (U + 1) + [77] and int(st.item()) == 0
+    assert counts.tolist() == ([0, 0, 0, 77] if tiers else [77] * 4)
+
+
 @pytest.mark.parametrize("n", [1, 512, 513, 2048, 40_000, 128 * 512, 255 * 1024, 512 * 512, 512 * 1024 + 1, 4_000_000])
 def test_a_workspace_for_more_buckets_serves_fewer(n):
     import paper_2301_02959_amd as fs
